@@ -65,13 +65,25 @@ uint32_t ceil_log2(uint64_t v)
   return l;
 }
 
+// The constants of fast_div for the divisor d >= 1.
+FastDiv make_fast_div(uint32_t d)
+{
+  if (d == 0) d = 1;
+  uint32_t L = 0;
+  while (L < 32 && (1ull << L) < d) ++L;
+  const unsigned __int128 num = ((unsigned __int128)((1ull << L) - d)) << 64;
+  return FastDiv{(uint64_t)(num / d) + 1, L < 1 ? L : 1, L > 0 ? L - 1 : 0};
+}
+
 uint64_t qmax_for(uint64_t max_slots) { return max_slots ? 1ull << (62 - ceil_log2(max_slots)) : 1ull << 62; }
 
 constexpr uint32_t kStepSets = 64;  // buffer sets a sequence of fused steps can cycle through
 
 struct Geometry {
   uint64_t obs_off, act_off, ret_off, gacc_off, storage_bytes;
-  uint32_t nlev;
+  uint32_t nlev;            // levels in the tree, ...
+  uint32_t exported_nlev;   // ... of which apex_replay_layout shows these (a summit is not shown)
+  uint32_t top_log2;        // fan-out of the last level over the one below it
   uint64_t level_off[kMaxLevels], level_size[kMaxLevels], tree_words;
   // scratch: DeviceState | mass | claim | new masses of the batches of fused steps
   uint64_t state_off, mass_off, claim_off, stepq_off, scratch_bytes;
@@ -98,15 +110,24 @@ int geometry(const apex_replay_config_t *c, Geometry *g)
   uint64_t n = P, off = 0;
   uint32_t l = 0;
   for (;;) {
-    if (l >= kMaxLevels) return APEX_ERR_INVALID_ARG;
+    if (l + 1 >= kMaxLevels) return APEX_ERR_INVALID_ARG;  // one place is kept for the summit
     g->level_off[l] = off;
     g->level_size[l] = n;
     off += round_up(n, kFanout);
     ++l;
-    if (n <= kTopMax) break;
+    if (n <= kExportedTopMax) break;
     n = (n + kFanout - 1) / kFanout;
   }
-  g->nlev = l;
+  g->exported_nlev = g->nlev = l;
+  g->top_log2 = kFanoutLog2;
+  if (n > kTopMax) {  // the summit
+    g->top_log2 = 0;
+    while (((n - 1) >> g->top_log2) + 1 > kTopMax) ++g->top_log2;
+    g->level_off[l] = off;
+    g->level_size[l] = ((n - 1) >> g->top_log2) + 1;
+    off += round_up(g->level_size[l], kFanout);
+    ++g->nlev;
+  }
   g->tree_words = off;
 
   g->state_off = 0;
@@ -133,6 +154,15 @@ struct apex_replay {
   // changes the first copy moves tree_version on.
   TreeView tv2;
   uint64_t tree_version = 1, second_version = 0;
+
+  // Words from the first copy to the second while the two are equal, else 0 (see AddLeavesArgs).
+  uint64_t second_words() const { return second_version == tree_version ? geo.tree_words : 0; }
+  // What a launch that has written to both copies (or, second == 0, to the first alone) leaves behind.
+  void tree_changed(uint64_t second)
+  {
+    ++tree_version;
+    if (second) second_version = tree_version;
+  }
 
   DeviceState *state() const { return reinterpret_cast<DeviceState *>(scratch + geo.state_off); }
   uint64_t *mass() const { return reinterpret_cast<uint64_t *>(scratch + geo.mass_off); }
@@ -242,48 +272,27 @@ int launch_copy(const void *src, const RowMap &smap, void *dst, const RowMap &dm
   return launch_copy_t<uint8_t>(s, smap, d, dmap, nrows, row_bytes, stream, jobs);
 }
 
-
-// The constants of fast_div for the divisor d >= 1.
-FastDiv make_fast_div(uint32_t d)
-{
-  if (d == 0) d = 1;
-  uint32_t L = 0;
-  while (L < 32 && (1ull << L) < d) ++L;
-  const unsigned __int128 num = ((unsigned __int128)((1ull << L) - d)) << 64;
-  return FastDiv{(uint64_t)(num / d) + 1, L < 1 ? L : 1, L > 0 ? L - 1 : 0};
-}
-
 // One launch of the fused learner step (see learner_step_kernel) for vectors of sizeof(Vec) bytes.
 // Steps whose rows are decoded on their way out (16-byte vectors; riders: none, or the masses of an add round).
-void launch_step_codec(const StepArgs &a, uint32_t n_top, uint32_t wgs, uint32_t threads, size_t lds, int rider,
-                       hipStream_t stream)
+void launch_step_codec(const StepArgs &a, uint32_t wgs, uint32_t threads, int rider, hipStream_t stream)
 {
   const dim3 grid(wgs), block(threads);
   if (rider == kLeavesRide)
-    learner_step_kernel<u32x4, kStepThreads, kStepUnroll, 1, kLeavesRide, true><<<grid, block, lds, stream>>>(a);
-  else if (n_top <= 8 * kWave)
-    learner_step_kernel<u32x4, kStepThreads, kStepUnroll, 1, kNoRider, true><<<grid, block, lds, stream>>>(a);
-  else if (n_top <= 16 * kWave)
-    learner_step_kernel<u32x4, kStepThreads, kStepUnroll, 2, kNoRider, true><<<grid, block, lds, stream>>>(a);
+    learner_step_kernel<u32x4, kStepThreads, kStepUnroll, kLeavesRide, true><<<grid, block, 0, stream>>>(a);
   else
-    learner_step_kernel<u32x4, kStepThreads, kStepUnroll, 4, kNoRider, true><<<grid, block, lds, stream>>>(a);
+    learner_step_kernel<u32x4, kStepThreads, kStepUnroll, kNoRider, true><<<grid, block, 0, stream>>>(a);
 }
 
 template <typename Vec>
-void launch_step_t(const StepArgs &a, uint32_t n_top, uint32_t wgs, uint32_t threads, size_t lds, int rider,
-                   hipStream_t stream)
+void launch_step_t(const StepArgs &a, uint32_t wgs, uint32_t threads, int rider, hipStream_t stream)
 {
   const dim3 grid(wgs), block(threads);
   if (rider == kRoundRides)  // further workgroups carry part of an add round (such a launch draws nothing)
-    learner_step_kernel<Vec, kStepThreads, kStepUnroll, 1, kRoundRides><<<grid, block, lds, stream>>>(a);
+    learner_step_kernel<Vec, kStepThreads, kStepUnroll, kRoundRides><<<grid, block, 0, stream>>>(a);
   else if (rider == kLeavesRide)
-    learner_step_kernel<Vec, kStepThreads, kStepUnroll, 1, kLeavesRide><<<grid, block, lds, stream>>>(a);
-  else if (n_top <= 8 * kWave)
-    learner_step_kernel<Vec, kStepThreads, kStepUnroll, 1, kNoRider><<<grid, block, lds, stream>>>(a);
-  else if (n_top <= 16 * kWave)
-    learner_step_kernel<Vec, kStepThreads, kStepUnroll, 2, kNoRider><<<grid, block, lds, stream>>>(a);
+    learner_step_kernel<Vec, kStepThreads, kStepUnroll, kLeavesRide><<<grid, block, 0, stream>>>(a);
   else
-    learner_step_kernel<Vec, kStepThreads, kStepUnroll, 4, kNoRider><<<grid, block, lds, stream>>>(a);
+    learner_step_kernel<Vec, kStepThreads, kStepUnroll, kNoRider><<<grid, block, 0, stream>>>(a);
 }
 
 // A small add round (observations of at most 1 KB per row) as one launch: n-step priorities, payload,
@@ -292,7 +301,7 @@ void launch_step_t(const StepArgs &a, uint32_t n_top, uint32_t wgs, uint32_t thr
 // Arguments of such a round for workgroups of `threads` lanes and vectors of vector_bytes bytes;
 // *blocks: the workgroups it takes.
 int add_round_args(const apex_replay *r, const NstepArgs &ns, const void *obs, const void *act, uint32_t vector_bytes,
-                   uint32_t threads, bool both, AddRoundArgs *out, uint32_t *blocks)
+                   uint32_t threads, AddRoundArgs *out, uint32_t *blocks)
 {
   const uint64_t count = (uint64_t)ns.S * ns.T;
   const uint32_t vpr = r->cfg.obs_bytes / vector_bytes;
@@ -302,7 +311,7 @@ int add_round_args(const apex_replay *r, const NstepArgs &ns, const void *obs, c
   const uint64_t nb = (count + rows_per_block - 1) / rows_per_block;
   if (nb > 0x7ffffff0ull) return APEX_ERR_TOO_LARGE;
   *blocks = (uint32_t)nb;
-  *out = AddRoundArgs{ns, r->tv, r->tv2, both, r->state(), r->qp, static_cast<const uint8_t *>(obs),
+  *out = AddRoundArgs{ns, r->tv, r->second_words(), r->state(), r->qp, static_cast<const uint8_t *>(obs),
                       static_cast<const uint8_t *>(act), r->obs(), r->act(), r->ret(), r->gacc(), vpr, lanes_log2,
                       r->cfg.obs_bytes, r->cfg.act_bytes};
   return APEX_OK;
@@ -318,10 +327,9 @@ bool add_round_small_fits(const apex_replay *r, const NstepArgs &ns, const void 
 }
 
 // Host-side bookkeeping of a round that has been enqueued.
-void add_round_published(apex_replay *r, uint64_t count, bool both, uint64_t *first_key_out)
+void add_round_published(apex_replay *r, uint64_t count, uint64_t second, uint64_t *first_key_out)
 {
-  ++r->tree_version;
-  if (both) r->second_version = r->tree_version;
+  r->tree_changed(second);
   if (first_key_out) *first_key_out = r->tail;
   r->tail += count;
 }
@@ -334,16 +342,16 @@ int add_round_small(apex_replay *r, const NstepArgs &ns, const void *obs, const 
   uint32_t vb = 0, blocks = 0;
   if (!add_round_small_fits(r, ns, obs, &vb)) return APEX_ERR_NOT_READY;
   if ((r->tail - r->head) + count > r->cfg.max_slots) return APEX_ERR_FULL;
-  const bool both = r->second_version == r->tree_version;
+  const uint64_t second = r->second_words();
   AddRoundArgs a;
-  const int rc = add_round_args(r, ns, obs, act, vb, kAddRoundThreads, both, &a, &blocks);
+  const int rc = add_round_args(r, ns, obs, act, vb, kAddRoundThreads, &a, &blocks);
   if (rc != APEX_OK) return rc;
   const dim3 grid(blocks), block(kAddRoundThreads);
   if (vb == 16) add_round_small_kernel<u32x4><<<grid, block, 0, stream>>>(a);
   else if (vb == 4) add_round_small_kernel<uint32_t><<<grid, block, 0, stream>>>(a);
   else add_round_small_kernel<uint8_t><<<grid, block, 0, stream>>>(a);
   APEX_HIP(hipGetLastError());
-  add_round_published(r, count, both, first_key_out);
+  add_round_published(r, count, second, first_key_out);
   return APEX_OK;
 }
 
@@ -402,7 +410,7 @@ int add_small_columns(const PayloadRing &pr, uint64_t count, const void *act, co
 int add_payload_rows(const PayloadRing &pr, uint64_t count, const void *obs, const void *act, const float *ret,
                      const float *gacc, const RowMap &to, hipStream_t stream)
 {
-  const RowMap ident{nullptr, nullptr, 0};
+  const RowMap ident{nullptr, nullptr, 0, {}};
   int rc;
   if (obs && (rc = add_payload_short(pr, count, obs, act, ret, gacc, to, stream)) != APEX_ERR_NOT_READY) return rc;
   if (obs && (rc = launch_copy(obs, ident, pr.obs, to, count, pr.obs_bytes, stream)) != APEX_OK) return rc;
@@ -452,7 +460,9 @@ int apex_replay_create(const apex_replay_config_t *cfg, void *d_storage, void *d
   r->qp = QuantParams{cfg->alpha, cfg->eps, cfg->frac_bits, qmax_for(cfg->max_slots)};
   r->tv.nlev = r->geo.nlev;
   r->tv.n_top = (uint32_t)r->geo.level_size[r->geo.nlev - 1];
+  r->tv.top_log2 = r->geo.top_log2;
   r->tv.P = cfg->max_slots;
+  r->tv.p_div = make_fast_div((uint32_t)cfg->max_slots);
   for (uint32_t l = 0; l < kMaxLevels; ++l) r->tv.level[l] = l < r->geo.nlev ? r->tree + r->geo.level_off[l] : nullptr;
   r->tv2 = r->tv;
   for (uint32_t l = 0; l < r->geo.nlev; ++l) r->tv2.level[l] = r->tv.level[l] + r->geo.tree_words;
@@ -487,11 +497,11 @@ int apex_replay_layout(const apex_replay_t *r, apex_replay_layout_t *out)
   out->act_offset = r->geo.act_off;
   out->ret_offset = r->geo.ret_off;
   out->gacc_offset = r->geo.gacc_off;
-  out->tree_levels = r->geo.nlev;
+  out->tree_levels = r->geo.exported_nlev;
   out->tree_fanout = kFanout;
   for (uint32_t l = 0; l < APEX_TREE_MAX_LEVELS; ++l) {
-    out->level_offset[l] = l < r->geo.nlev ? r->geo.level_off[l] : 0;
-    out->level_size[l] = l < r->geo.nlev ? r->geo.level_size[l] : 0;
+    out->level_offset[l] = l < r->geo.exported_nlev ? r->geo.level_off[l] : 0;
+    out->level_size[l] = l < r->geo.exported_nlev ? r->geo.level_size[l] : 0;
   }
   return APEX_OK;
 }
@@ -523,7 +533,7 @@ int apex_replay_add_payload(apex_replay_t *r, uint64_t count, const void *obs, c
   if ((r->tail - r->head) + count > r->cfg.max_slots) return APEX_ERR_FULL;
   if (count == 0) return APEX_OK;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-  const RowMap ring{nullptr, &r->state()->tail, r->cfg.max_slots};
+  const RowMap ring{nullptr, &r->state()->tail, r->cfg.max_slots, r->tv.p_div};
   const PayloadRing pr{r->obs(), r->act(), r->ret(), r->gacc(), r->cfg.obs_bytes, r->cfg.act_bytes};
   return add_payload_rows(pr, count, obs, act, ret, gacc, ring, stream);
 }
@@ -535,11 +545,10 @@ int apex_replay_add_publish(apex_replay_t *r, uint64_t count, const float *prio,
   if ((r->tail - r->head) + count > r->cfg.max_slots) return APEX_ERR_FULL;
   if (count) {
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    const bool both = r->second_version == r->tree_version;
-    ++r->tree_version;
-    if (both) r->second_version = r->tree_version;
-    add_leaves_kernel<<<dim3(blocks_for(count, 256)), dim3(256), 0, stream>>>(
-        AddLeavesArgs{r->tv, r->tv2, both, r->state(), count, prio, r->qp});
+    const uint64_t second = r->second_words();
+    r->tree_changed(second);
+    add_leaves_kernel<<<dim3(blocks_for(count, kLeavesThreads)), dim3(kLeavesThreads), 0, stream>>>(
+        AddLeavesArgs{r->tv, second, r->state(), count, prio, r->qp});
     APEX_HIP(hipGetLastError());
   }
   if (first_key_out) *first_key_out = r->tail;
@@ -557,6 +566,14 @@ int apex_replay_add(apex_replay_t *r, uint64_t count, const void *obs, const voi
 }
 
 namespace {
+
+// a.k samples of each of num_batches batches (with a.k_dev: at most a.k).
+int launch_draw(SampleArgs &a, uint32_t num_batches, hipStream_t stream)
+{
+  a.k_div = make_fast_div(a.k);
+  sample_draw_kernel<<<dim3(blocks_for(a.k, 16), num_batches), dim3(256), 0, stream>>>(a);
+  return hip_failed(hipGetLastError()) ? APEX_ERR_HIP : APEX_OK;
+}
 
 int sample_begin_impl(apex_replay *r, uint32_t num_batches, uint32_t k, const uint64_t *rnd, uint64_t *key_out,
                       uint32_t *slot_out, uint64_t *mass_out, void *act_out, float *ret_out, float *gacc_out,
@@ -583,13 +600,7 @@ int sample_begin_impl(apex_replay *r, uint32_t num_batches, uint32_t k, const ui
   a.act_out = static_cast<uint8_t *>(act_out);
   a.ret_out = ret_out;
   a.gacc_out = gacc_out;
-  // every workgroup stages the whole top level: with a large top and many samples, larger workgroups
-  // (16 samples each) stage it fewer times
-  const uint32_t waves = (r->tv.n_top > 1024 && (uint64_t)num_batches * k >= 1024) ? 16 : 4;
-  const size_t lds = ((size_t)r->tv.n_top + waves) * sizeof(uint64_t);
-  sample_descent_kernel<<<dim3(blocks_for(k, waves), num_batches), dim3(waves * kWave), lds, stream>>>(a);
-  APEX_HIP(hipGetLastError());
-  return APEX_OK;
+  return launch_draw(a, num_batches, stream);
 }
 
 }  // namespace
@@ -615,7 +626,7 @@ int launch_update(apex_replay *r, uint64_t m, const uint64_t *key, const float *
   } else {
     const dim3 grid(blocks_for(m, 256)), block(256);
     if (!claimed)
-      update_claim_kernel<<<grid, block, 0, stream>>>(ClaimArgs{r->cfg.max_slots, r->state(), (uint32_t)m, key, r->claim()});
+      update_claim_kernel<<<grid, block, 0, stream>>>(ClaimArgs{r->cfg.max_slots, r->tv.p_div, r->state(), (uint32_t)m, key, r->claim()});
     update_apply_kernel<<<grid, block, 0, stream>>>(r->tv, r->state(), (uint32_t)m, key, prio, r->qp, r->claim(), qs);
   }
   return hip_failed(hipGetLastError()) ? APEX_ERR_HIP : APEX_OK;
@@ -636,10 +647,10 @@ int finish_impl(apex_replay *r, uint32_t num_batches, uint32_t k, float beta, co
     jobs.ua = UpdateArgs{r->tv, r->state(), (uint32_t)m, key, prio, r->qp, hint ? slot : nullptr, hint ? mass : nullptr,
                          QSource{}};
   }
-  if (m > 1024) jobs.claim = ClaimArgs{r->cfg.max_slots, r->state(), (uint32_t)m, key, r->claim()};
+  if (m > 1024) jobs.claim = ClaimArgs{r->cfg.max_slots, r->tv.p_div, r->state(), (uint32_t)m, key, r->claim()};
   if (obs_out) {
-    const RowMap by_slot{slot, nullptr, 0};
-    const RowMap ident{nullptr, nullptr, 0};
+    const RowMap by_slot{slot, nullptr, 0, {}};
+    const RowMap ident{nullptr, nullptr, 0, {}};
     const int rc = launch_copy(r->obs(), by_slot, obs_out, ident, (uint64_t)num_batches * k, r->cfg.obs_bytes, stream, &jobs);
     if (rc != APEX_OK) return rc;
   }
@@ -675,16 +686,16 @@ bool fused_steps_fit(const apex_replay *r, uint32_t num_batches, uint32_t k, uin
   return true;
 }
 
-void launch_step(const StepArgs &args, uint32_t vector_bytes, uint32_t n_top, uint32_t wgs, uint32_t threads,
-                 size_t lds, hipStream_t stream, int rider = kNoRider)
+void launch_step(const StepArgs &args, uint32_t vector_bytes, uint32_t wgs, uint32_t threads, hipStream_t stream,
+                 int rider = kNoRider)
 {
   StepArgs a = args;
   a.next_top = a.next.tv.level[a.next.tv.nlev - 1];
   a.next_k_div = make_fast_div(a.next.k);
-  if (a.codec.raw_bytes && a.slot) return launch_step_codec(a, n_top, wgs, threads, lds, rider, stream);
-  if (vector_bytes == 16) launch_step_t<u32x4>(a, n_top, wgs, threads, lds, rider, stream);
-  else if (vector_bytes == 4) launch_step_t<uint32_t>(a, n_top, wgs, threads, lds, rider, stream);
-  else launch_step_t<uint8_t>(a, n_top, wgs, threads, lds, rider, stream);
+  if (a.codec.raw_bytes && a.slot) return launch_step_codec(a, wgs, threads, rider, stream);
+  if (vector_bytes == 16) launch_step_t<u32x4>(a, wgs, threads, rider, stream);
+  else if (vector_bytes == 4) launch_step_t<uint32_t>(a, wgs, threads, rider, stream);
+  else launch_step_t<uint8_t>(a, wgs, threads, rider, stream);
 }
 
 // A step launch that has been prepared but not issued: the last one of a call, held back while a small
@@ -692,15 +703,14 @@ void launch_step(const StepArgs &args, uint32_t vector_bytes, uint32_t n_top, ui
 struct HeldStep {
   bool valid = false;
   StepArgs a;
-  uint32_t vector_bytes, n_top;
-  size_t lds;
+  uint32_t vector_bytes;
 };
 
 int issue_held_step(HeldStep *h, hipStream_t stream)
 {
   if (!h->valid) return APEX_OK;
   h->valid = false;
-  launch_step(h->a, h->vector_bytes, h->n_top, h->a.k, kStepThreads, h->lds, stream);
+  launch_step(h->a, h->vector_bytes, h->a.k, kStepThreads, stream);
   APEX_HIP(hipGetLastError());
   return APEX_OK;
 }
@@ -715,13 +725,13 @@ int issue_held_step_with_round(apex_replay *r, HeldStep *h, const NstepArgs &ns,
   if (!h->valid || h->a.codec.raw_bytes || !add_round_small_fits(r, ns, obs, &vb) || vb < h->vector_bytes)
     return APEX_ERR_NOT_READY;
   if ((r->tail - r->head) + count > r->cfg.max_slots) return APEX_ERR_FULL;
-  const bool both = r->second_version == r->tree_version;
-  const int rc = add_round_args(r, ns, obs, act, h->vector_bytes, kStepThreads, both, &h->a.add, &blocks);
+  const uint64_t second = r->second_words();
+  const int rc = add_round_args(r, ns, obs, act, h->vector_bytes, kStepThreads, &h->a.add, &blocks);
   if (rc != APEX_OK) return rc;
   h->valid = false;
-  launch_step(h->a, h->vector_bytes, h->n_top, h->a.k + blocks, kStepThreads, h->lds, stream, kRoundRides);
+  launch_step(h->a, h->vector_bytes, h->a.k + blocks, kStepThreads, stream, kRoundRides);
   APEX_HIP(hipGetLastError());
-  add_round_published(r, count, both, first_key_out);
+  add_round_published(r, count, second, first_key_out);
   return APEX_OK;
 }
 
@@ -732,13 +742,12 @@ int issue_held_step_with_leaves(apex_replay *r, HeldStep *h, uint64_t count, con
 {
   if (!h->valid || !count || !prio) return APEX_ERR_NOT_READY;
   if ((r->tail - r->head) + count > r->cfg.max_slots) return APEX_ERR_FULL;
-  const bool both = r->second_version == r->tree_version;
-  h->a.leaves = AddLeavesArgs{r->tv, r->tv2, both, r->state(), count, prio, r->qp};
+  const uint64_t second = r->second_words();
+  h->a.leaves = AddLeavesArgs{r->tv, second, r->state(), count, prio, r->qp};
   h->valid = false;
-  launch_step(h->a, h->vector_bytes, h->n_top, h->a.k + blocks_for(count, kStepThreads), kStepThreads, h->lds, stream,
-              kLeavesRide);
+  launch_step(h->a, h->vector_bytes, h->a.k + blocks_for(count, kStepThreads), kStepThreads, stream, kLeavesRide);
   APEX_HIP(hipGetLastError());
-  add_round_published(r, count, both, first_key_out);
+  add_round_published(r, count, second, first_key_out);
   return APEX_OK;
 }
 
@@ -754,7 +763,6 @@ int fused_steps(apex_replay *r, uint32_t n, uint32_t k, float beta, const uint64
   const auto idx = [&](uint32_t i) { return (first_set + i) % depth; };
   const auto set = [&](uint32_t i) -> const apex_batch_buffers_t & { return sets[idx(i)]; };
   const apex_batch_buffers_t &b0 = set(0);
-  const size_t lds = round_up(r->tv.n_top, kFanout) * 8;
   const uint32_t vb = step_vector_bytes(r, depth, sets);
   if (new_prio) {
     // Launch i reads one copy of the tree and writes the other; the first draw is launch "-1" of that
@@ -776,7 +784,7 @@ int fused_steps(apex_replay *r, uint32_t n, uint32_t k, float beta, const uint64
     a.next.mass = b0.mass;
     a.next_prio = new_prio;
     a.next_dq = r->stepq(idx(0));
-    launch_step(a, vb, r->tv.n_top, k, kWave, lds, stream);
+    launch_step(a, vb, k, kWave, stream);
     APEX_HIP(hipGetLastError());
   } else {
     const int rc = sample_begin_impl(r, 1, k, rnd, b0.key, b0.slot, b0.mass, nullptr, nullptr, nullptr, stream);
@@ -828,10 +836,8 @@ int fused_steps(apex_replay *r, uint32_t n, uint32_t k, float beta, const uint64
       hold->valid = true;
       hold->a = a;
       hold->vector_bytes = vb;
-      hold->n_top = r->tv.n_top;
-      hold->lds = lds;
     } else {
-      launch_step(a, vb, r->tv.n_top, k, kStepThreads, lds, stream);
+      launch_step(a, vb, k, kStepThreads, stream);
     }
   }
   // (every change has now been applied to both copies)
@@ -918,8 +924,8 @@ int apex_replay_gather(apex_replay_t *r, uint64_t count, const uint32_t *slot, v
   if (!r || (count && !slot)) return APEX_ERR_INVALID_ARG;
   if (count > APEX_MAX_SAMPLES_PER_CALL) return APEX_ERR_TOO_LARGE;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-  const RowMap by_slot{slot, nullptr, 0};
-  const RowMap ident{nullptr, nullptr, 0};
+  const RowMap by_slot{slot, nullptr, 0, {}};
+  const RowMap ident{nullptr, nullptr, 0, {}};
   int rc;
   if (obs_out && (rc = launch_copy(r->obs(), by_slot, obs_out, ident, count, r->cfg.obs_bytes, stream)) != APEX_OK) return rc;
   if (act_out && (rc = launch_copy(r->act(), by_slot, act_out, ident, count, r->cfg.act_bytes, stream)) != APEX_OK) return rc;
@@ -956,10 +962,9 @@ int apex_replay_evict(apex_replay_t *r, uint64_t *evicted_out, void *hip_stream)
   if (evicted_out) *evicted_out = e;
   if (e == 0) return APEX_OK;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-  const bool both = r->second_version == r->tree_version;
-  ++r->tree_version;
-  if (both) r->second_version = r->tree_version;
-  evict_leaves_kernel<<<dim3(blocks_for(e, 256)), dim3(256), 0, stream>>>(r->tv, r->tv2, both, r->state(), e);
+  const uint64_t second = r->second_words();
+  r->tree_changed(second);
+  evict_leaves_kernel<<<dim3(blocks_for(e, kLeavesThreads)), dim3(kLeavesThreads), 0, stream>>>(EvictLeavesArgs{r->tv, second, r->state(), e});
   APEX_HIP(hipGetLastError());
   r->head += e;
   return APEX_OK;

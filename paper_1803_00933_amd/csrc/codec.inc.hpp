@@ -128,7 +128,7 @@ int apex_replay_add_payload_encoded(apex_replay_t *r, uint64_t count, const void
   if (count == 0) return APEX_OK;
   if (count > 0x7ffffff0ull) return APEX_ERR_TOO_LARGE;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-  const RowMap ring{nullptr, &r->state()->tail, r->cfg.max_slots};
+  const RowMap ring{nullptr, &r->state()->tail, r->cfg.max_slots, r->tv.p_div};
   codec_encode_rows_kernel<<<dim3((uint32_t)count), dim3(kCodecThreads), 0, stream>>>(
       static_cast<const uint8_t *>(raw_obs), r->obs(), ring, r->cfg.obs_bytes, codec_shape(raw_bytes));
   APEX_HIP(hipGetLastError());

@@ -40,7 +40,7 @@ __global__ __launch_bounds__(256) void pe_add_kernel(PeView v, PeState *__restri
   uint32_t nclamp = 0, slot = 0;
   uint64_t q1 = 0, q2 = 0;
   if (i < count) {
-    slot = v.free_ring[(st->free_head + i) % v.ts.P];
+    slot = v.free_ring[ring_slot(v.ts, st->free_head + i)];
     v.gen[slot] += 1;
     bool c1, c2;
     const float p = prio[i];
@@ -94,7 +94,7 @@ __global__ __launch_bounds__(kPeAddThreads) void pe_add_rows_kernel(PeView v, Pe
   const uint64_t i = (uint64_t)blockIdx.x * rows_per_block + r;
   const uint32_t vv = threadIdx.x & (lanes - 1);
   if (i < count) {
-    const uint64_t slot = v.free_ring[(st->free_head + i) % v.ts.P];
+    const uint64_t slot = v.free_ring[ring_slot(v.ts, st->free_head + i)];
     if (vv < vecs_per_row)
       reinterpret_cast<Vec *>(obs_ring + slot * obs_bytes)[vv] = reinterpret_cast<const Vec *>(obs + i * obs_bytes)[vv];
     if (act)
@@ -366,7 +366,7 @@ __global__ __launch_bounds__(kPeScanThreads) void pe_remove_kernel(PeView v, PeS
     o1 = v.ts.level[0][slot], o2 = v.te.level[0][slot];
     v.ts.level[0][slot] = 0;
     v.te.level[0][slot] = 0;
-    v.free_ring[(st->free_tail + offset + p) % v.ts.P] = slot;
+    v.free_ring[ring_slot(v.ts, st->free_tail + offset + p)] = slot;
   }
   add_runs_to_ancestors(v.ts, counts, slot, 0 - o1);  // the candidates ascend: neighbours share their ancestors
   add_runs_to_ancestors(v.te, counts, slot, 0 - o2);
@@ -399,7 +399,7 @@ namespace {
 
 struct PeGeometry {
   uint64_t obs_off, act_off, ret_off, gacc_off, storage_bytes;
-  uint32_t nlev;
+  uint32_t nlev, exported_nlev, top_log2;  // as in Geometry
   uint64_t level_off[kMaxLevels], level_size[kMaxLevels], tree_words;  // of one tree; the second follows it
   uint64_t state_off, mass_off, cand_off, pos_off, sums_off, gen_off, ring_off, claim_off, scratch_bytes;
 };
@@ -431,6 +431,8 @@ int pe_geometry(const apex_pe_config_t *c, PeGeometry *g)
   g->gacc_off = base.gacc_off;
   g->storage_bytes = base.storage_bytes;
   g->nlev = base.nlev;
+  g->exported_nlev = base.exported_nlev;
+  g->top_log2 = base.top_log2;
   for (uint32_t l = 0; l < kMaxLevels; ++l) {
     g->level_off[l] = base.level_off[l];
     g->level_size[l] = base.level_size[l];
@@ -522,7 +524,7 @@ int pe_enqueue_eviction(apex_pe_replay *r, uint64_t e, uint32_t rounds, const ui
   SampleArgs a{};
   a.tv = r->v.te;
   a.st = &st->base;
-  a.k = 0;
+  a.k = (uint32_t)e;
   a.k_dev = &st->remaining;
   a.gen = nullptr;
   a.key_out = nullptr;
@@ -533,12 +535,10 @@ int pe_enqueue_eviction(apex_pe_replay *r, uint64_t e, uint32_t rounds, const ui
   a.ret = a.gacc = nullptr;
   a.act_out = nullptr;
   a.ret_out = a.gacc_out = nullptr;
-  const uint32_t waves = 4;  // (16 waves per workgroup, which stage the top level fewer times, measured 20 % slower)
-  const size_t lds = ((size_t)a.tv.n_top + waves) * sizeof(uint64_t);
   const uint32_t scan_blocks = blocks_for(e, kPeScanThreads);  // <= 1024 since e <= 2^20
   for (uint32_t rd = 0; rd < rounds; ++rd) {
     a.rnd = rnd + (uint64_t)rd * e;
-    sample_descent_kernel<<<dim3(blocks_for(e, waves), 1), dim3(waves * kWave), lds, stream>>>(a);
+    APEX_TRY(launch_draw(a, 1, stream));
     pe_flag_scan_kernel<<<dim3(scan_blocks), dim3(kPeScanThreads), 0, stream>>>(r->cand(), st, r->pos(), r->sums());
     pe_remove_kernel<<<dim3(scan_blocks), dim3(kPeScanThreads), 0, stream>>>(r->v, st, r->cand(), r->pos(), r->sums());
   }
@@ -595,7 +595,9 @@ int apex_pe_create(const apex_pe_config_t *cfg, void *d_storage, void *d_tree, v
   for (TreeView *tv : {&r->v.ts, &r->v.te}) {
     tv->nlev = r->geo.nlev;
     tv->n_top = (uint32_t)r->geo.level_size[r->geo.nlev - 1];
+    tv->top_log2 = r->geo.top_log2;
     tv->P = cfg->max_slots;
+    tv->p_div = make_fast_div((uint32_t)cfg->max_slots);
     uint64_t *base = r->tree + (tv == &r->v.te ? r->geo.tree_words : 0);
     for (uint32_t l = 0; l < kMaxLevels; ++l) tv->level[l] = l < r->geo.nlev ? base + r->geo.level_off[l] : nullptr;
   }
@@ -635,11 +637,11 @@ int apex_pe_layout(const apex_pe_replay_t *r, apex_pe_layout_t *out)
   out->act_offset = r->geo.act_off;
   out->ret_offset = r->geo.ret_off;
   out->gacc_offset = r->geo.gacc_off;
-  out->tree_levels = r->geo.nlev;
+  out->tree_levels = r->geo.exported_nlev;
   out->tree_fanout = kFanout;
   for (uint32_t l = 0; l < APEX_TREE_MAX_LEVELS; ++l) {
-    out->level_offset[l] = l < r->geo.nlev ? r->geo.level_off[l] : 0;
-    out->level_size[l] = l < r->geo.nlev ? r->geo.level_size[l] : 0;
+    out->level_offset[l] = l < r->geo.exported_nlev ? r->geo.level_off[l] : 0;
+    out->level_size[l] = l < r->geo.exported_nlev ? r->geo.level_size[l] : 0;
   }
   out->evict_tree_offset = r->geo.tree_words;
   out->gen_offset = r->geo.gen_off;
@@ -654,7 +656,7 @@ int apex_pe_add(apex_pe_replay_t *r, uint64_t count, const void *obs, const void
   APEX_TRY(pe_check_room(r, count));
   if (count == 0) return APEX_OK;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-  const RowMap freed{r->v.free_ring, &r->state()->free_head, r->cfg.max_slots};  // the next free slots, in order
+  const RowMap freed{r->v.free_ring, &r->state()->free_head, r->cfg.max_slots, r->v.ts.p_div};  // the next free slots, in order
   const PayloadRing pr{r->obs(), r->act(), r->ret(), r->gacc(), r->cfg.obs_bytes, r->cfg.act_bytes};
   const uintptr_t mis = (uintptr_t)obs | (uintptr_t)r->obs() | (uintptr_t)r->cfg.obs_bytes;
   const uint32_t vb = (mis & 15) == 0 ? 16 : (mis & 3) == 0 ? 4 : 1;
@@ -711,15 +713,12 @@ int apex_pe_sample(apex_pe_replay_t *r, uint32_t num_batches, uint32_t k, float 
   a.act_out = static_cast<uint8_t *>(act_out);
   a.ret_out = ret_out;
   a.gacc_out = gacc_out;
-  const uint32_t waves = 4;
-  const size_t lds = ((size_t)a.tv.n_top + waves) * sizeof(uint64_t);
-  sample_descent_kernel<<<dim3(blocks_for(k, waves), num_batches), dim3(waves * kWave), lds, stream>>>(a);
-  APEX_HIP(hipGetLastError());
+  APEX_TRY(launch_draw(a, num_batches, stream));
   SideJobs jobs;
   jobs.wa = WeightArgs{r->mass(), weight_out, k, beta};
   if (obs_out) {
-    const RowMap by_slot{slot_out, nullptr, 0};
-    const RowMap ident{nullptr, nullptr, 0};
+    const RowMap by_slot{slot_out, nullptr, 0, {}};
+    const RowMap ident{nullptr, nullptr, 0, {}};
     const int rc = launch_copy(r->obs(), by_slot, obs_out, ident, (uint64_t)num_batches * k, r->cfg.obs_bytes, stream, &jobs);
     if (rc != APEX_OK) return rc;
   }
@@ -854,15 +853,13 @@ int apex_pe_sample_update(apex_pe_replay_t *r, uint32_t k, float beta, const uin
   a.act_out = static_cast<uint8_t *>(act_out);
   a.ret_out = ret_out;
   a.gacc_out = gacc_out;
-  const uint32_t waves = 4;
-  const size_t lds = ((size_t)a.tv.n_top + waves) * sizeof(uint64_t);
-  sample_descent_kernel<<<dim3(blocks_for(k, waves), 1), dim3(waves * kWave), lds, stream>>>(a);
+  APEX_TRY(launch_draw(a, 1, stream));
   // gather, weights and the write-back of the batch just drawn: one launch
   uint32_t lanes_log2 = 0;
   while ((1u << lanes_log2) < vpr) ++lanes_log2;
   const uint64_t rows_per_block = 1024u >> lanes_log2;
   const uint32_t copy_blocks = obs_out ? (uint32_t)((k + rows_per_block - 1) / rows_per_block) : 0;
-  const ShortCopyArgs c{r->obs(), RowMap{slot_out, nullptr, 0}, static_cast<uint8_t *>(obs_out), RowMap{nullptr, nullptr, 0},
+  const ShortCopyArgs c{r->obs(), RowMap{slot_out, nullptr, 0, {}}, static_cast<uint8_t *>(obs_out), RowMap{nullptr, nullptr, 0, {}},
                         k, vpr, lanes_log2, r->cfg.obs_bytes};
   const WeightArgs wa{r->mass(), weight_out, k, beta};
   const dim3 grid(copy_blocks + 2), block(1024);

@@ -3,9 +3,16 @@
 // Data layout in HBM
 //   payload ring   obs[P][obs_bytes], act[P][act_bytes], ret[P], gacc[P]   (structure of arrays)
 //   sum tree       level 0 = one uint64 mass per slot; node i of level l+1 = sum of nodes
-//                  [64 i, 64 i + 64) of level l; levels are added until one has at most kTopMax
-//                  nodes.  A wavefront reads the 64 children of a node as one coalesced 512-byte
-//                  row; the top level is staged and prefix-summed in LDS by every workgroup.
+//                  [64 i, 64 i + 64) of level l; levels are added until one has at most kExportedTopMax
+//                  nodes.  A wavefront reads the 64 children of a node as one coalesced 512-byte row.
+//                  If the last of these levels has more than kTopMax nodes, a summit stands above it:
+//                  node i = sum of 2^top_log2 of its nodes, the smallest power of two that leaves at
+//                  most kTopMax.  So the level a walk starts from always fits the registers of one wave
+//                  (8 nodes per lane).  Where every workgroup staged the whole top in LDS instead, a
+//                  draw of 4096 from 2^24 slots (4352 nodes) took 11.5 us, now 7.2; the learner steps on
+//                  2^18 slots (4096 nodes) 10.6 us per launch, now 9.4.  Not fewer nodes than that:
+//                  every change of a mass is an atomic on every level, and atomics of different waves
+//                  on one address take about 10 ns one after the other.
 //   device state   head, tail, counters: read by the kernels, so the same launches can be replayed.
 // The set of transitions and the sampled indices do not depend on this shape: a sample is
 // defined by the cumulative mass in slot order, whatever tree sums it up.
@@ -20,7 +27,8 @@ namespace apex {
 
 constexpr uint32_t kFanoutLog2 = 6;
 constexpr uint32_t kFanout = 1u << kFanoutLog2;
-constexpr uint32_t kTopMax = 4608;  // 36 KB of LDS; covers 2^24 + 2^20 slots with three levels
+constexpr uint32_t kExportedTopMax = 4608;  // covers 2^24 + 2^20 slots with three levels
+constexpr uint32_t kTopMax = 512;           // nodes of the level that walks start from
 constexpr uint32_t kMaxLevels = 8;
 
 struct DeviceState {
@@ -30,86 +38,152 @@ struct DeviceState {
   uint32_t ticket_evict;    // ... and of the running evict launch that are done with head (the two may overlap)
 };
 
-// Called by every thread of every workgroup of a launch once it has read what it needs of head or
-// tail: the workgroup that arrives last moves that counter on, so that the launch needs no
-// follow-up launch for it (the ticket is back at 0 afterwards).  Contains a barrier.
-// n_wgs: the workgroups that take part (all of the launch unless stated).
-__device__ __forceinline__ void advance_state_when_all_done(uint32_t *ticket, uint64_t *counter, uint64_t inc,
-                                                            uint32_t n_wgs = gridDim.x)
+// The launches that move head or tail on read them first: every workgroup takes a ticket once all its threads
+// have what they read of the counter (the caller puts a barrier in between), and the one with the last ticket
+// writes the counter, so that the launch needs no follow-up launch for it (the ticket is back at 0 afterwards).
+// The last lane of the workgroup does it: the ticket's round trip (1.5 - 2 us, like that of every atomic that the
+// eight L2 caches have to agree on) then runs beside those of the first wave's atomics on the tree.
+// n_wgs: the workgroups that take part.
+__device__ __forceinline__ void advance_state(uint32_t *ticket, uint64_t *counter, uint64_t now, uint32_t n_wgs)
 {
-  __syncthreads();
-  if (threadIdx.x == 0) {
+  if (threadIdx.x == blockDim.x - 1) {
     const uint32_t t = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (t == n_wgs - 1) {
       *ticket = 0;
-      *counter += inc;
+      *counter = now;
     }
   }
 }
 
+// Exact floor(n / d) for any n by a multiplication, for a divisor that the host knows at launch time
+// (a 64-bit quotient is otherwise a long software division).  Granlund and Montgomery's unsigned division by an
+// invariant integer: L = ceil(log2 d), mul = floor(2^64 (2^L - d) / d) + 1, sh1 = min(L, 1), sh2 = max(L - 1, 0).
+struct FastDiv {
+  uint64_t mul;
+  uint32_t sh1, sh2;
+};
+
+__device__ __forceinline__ uint64_t fast_div(uint64_t n, const FastDiv &d)
+{
+  const uint64_t t = __umul64hi(d.mul, n);
+  return (t + ((n - t) >> d.sh1)) >> d.sh2;
+}
+
 struct TreeView {
   uint64_t *level[kMaxLevels];
-  uint32_t nlev;   // level nlev-1 is the top
-  uint32_t n_top;  // nodes of the top level
-  uint64_t P;      // ring size
+  uint32_t nlev;      // level nlev-1 is the top
+  uint32_t n_top;     // nodes of the top level: at most kTopMax
+  uint32_t top_log2;  // log2 of the top level's fan-out (kFanoutLog2, or less where the top is a summit)
+  uint32_t pad;
+  uint64_t P;         // ring size
+  FastDiv p_div;      // division by P
 };
+
+// key mod P
+__device__ __forceinline__ uint64_t ring_slot(const TreeView &tv, uint64_t key) { return key - fast_div(key, tv.p_div) * tv.P; }
+
+// log2 of the fan-out of level l (l >= 1) over the level below it.
+__device__ __forceinline__ uint32_t fanout_log2(const TreeView &tv, uint32_t l)
+{
+  return l + 1 == tv.nlev ? tv.top_log2 : kFanoutLog2;
+}
 
 // Adds delta (mod 2^64) to every ancestor of `slot` above level 0.
 __device__ __forceinline__ void add_to_ancestors(const TreeView &tv, uint64_t slot, uint64_t delta)
 {
   uint64_t idx = slot;
   for (uint32_t l = 1; l < tv.nlev; ++l) {
-    idx >>= kFanoutLog2;
+    idx >>= fanout_log2(tv, l);
     atomic_add_u64(tv.level[l] + idx, delta);
   }
 }
 
-// Same, for a wave whose active lanes hold neighbouring slots (adds, evictions): lanes under one
-// level-1 node are summed first, so each node receives one atomic per wave instead of up to 64.
-// Must be called by all 64 lanes; `active` marks the lanes that carry a delta.
-// second: another copy of the same tree that receives the same sums, or null.
-__device__ __forceinline__ void add_to_ancestors_grouped(const TreeView &tv, bool active, uint64_t slot, uint64_t delta,
-                                                         const TreeView *second = nullptr)
+// Where the runs of neighbouring lanes with equal `node` lie that a prefix sum of the lanes' values is cut into.
+struct LaneRuns {
+  bool ends;        // this lane is the last of its run
+  int first;        // the first lane of this lane's run
+};
+
+__device__ __forceinline__ LaneRuns lane_runs(uint64_t node)
 {
   const int lane = lane_id();
-  const uint64_t node1 = slot >> kFanoutLog2;
-  uint64_t todo = __ballot(active);
-  while (todo) {
-    const int leader = __ffsll((unsigned long long)todo) - 1;
-    const uint64_t node = __shfl(node1, leader, kWave);
-    const bool mine = active && node1 == node;
-    const uint64_t sum = wave_sum(mine ? delta : 0);
-    if (lane == leader) {
-      uint64_t idx = node;
-      for (uint32_t l = 1; l < tv.nlev; ++l) {
-        atomic_add_u64(tv.level[l] + idx, sum);
-        if (second) atomic_add_u64(second->level[l] + idx, sum);
-        idx >>= kFanoutLog2;
-      }
-    }
-    todo &= ~__ballot(mine);
+  const uint64_t prev = __shfl_up(node, 1, kWave);
+  const uint64_t starts = __ballot(lane == 0 || prev != node);
+  LaneRuns r;
+  r.ends = lane == kWave - 1 || ((starts >> (lane + 1)) & 1);
+  r.first = 63 - __builtin_clzll(starts & (~0ull >> (63 - lane)));  // bit 0 is set
+  return r;
+}
+
+// Adds to a node of the tree and, if second != 0, to the same node of the copy that lies `second` words behind it.
+__device__ __forceinline__ void atomic_add_both(uint64_t *p, uint64_t second, uint64_t v)
+{
+  atomic_add_u64(p, v);
+  if (second) atomic_add_u64(p + second, v);
+}
+
+// Same, for a wave whose lanes hold slots in mostly ascending order (the consecutive slots of an add or a FIFO
+// eviction, free slots handed out again, drawn keys): on every level each run of neighbouring lanes under one node
+// is summed with one prefix sum over the wave and sends one atomic instead of one per lane.  A node that appears
+// in several runs receives several atomics.  Sums are modulo 2^64, so a removal passes 0 - mass.  Must be called
+// by all 64 lanes; `active` marks the lanes that carry a delta.
+// idx: the node of level `from` - 1 that the delta belongs to (a slot, from = 1).
+__device__ __forceinline__ void add_runs_to_ancestors(const TreeView &tv, bool active, uint64_t idx, uint64_t delta,
+                                                      uint64_t second = 0, uint32_t from = 1)
+{
+  const uint64_t incl = wave_inclusive_scan(active ? delta : 0);
+  for (uint32_t l = from; l < tv.nlev; ++l) {
+    idx >>= fanout_log2(tv, l);
+    const LaneRuns run = lane_runs(active ? idx : ~0ull);  // lanes without a delta form runs of their own, which send nothing
+    const uint64_t before = __shfl(incl, run.first > 0 ? run.first - 1 : 0, kWave);
+    if (active && run.ends) atomic_add_both(tv.level[l] + idx, second, incl - (run.first > 0 ? before : 0));
   }
 }
 
-// Same, for a wave whose lanes hold slots in any order (the free slots that a memory with prioritized
-// eviction hands out, the candidates of an eviction round - both mostly ascending, so that neighbouring lanes
-// mostly share their ancestors): on every level each run of neighbouring lanes under one node is summed with
-// one prefix sum over the wave and sends one atomic.  A node that appears in several runs receives several
-// atomics.  Sums are modulo 2^64, so a removal passes 0 - mass.  Must be called by all 64 lanes.
-__device__ __forceinline__ void add_runs_to_ancestors(const TreeView &tv, bool active, uint64_t slot, uint64_t delta)
+// Same, for a workgroup of at most 1024 threads that holds consecutive slots of the ring, one per thread: the waves'
+// sums on level 1 (at most three runs a wave: 64 slots that cross one node's border and the ring's end) are
+// collected in LDS, and one wave enters them into the levels above, which so receive one atomic per workgroup and
+// node instead of one per wave: all waves of a round meet on one or two nodes there (51,200 transitions of 2^24:
+// 800 atomics on one address, about 10 ns each; the launch took 8.6 us, now 3.9).  Contains a barrier.  Called by
+// every thread.
+struct DenseSums {
+  uint64_t sum[64];
+  uint32_t node[64];
+};
+
+__device__ __forceinline__ void add_dense_to_ancestors(const TreeView &tv, bool active, uint64_t slot, uint64_t delta,
+                                                       uint64_t second, DenseSums &sh)
 {
-  const int lane = lane_id();
+  if (tv.nlev < 2) {
+    __syncthreads();
+    return;
+  }
+  const uint32_t lane = lane_id(), wave = threadIdx.x / kWave;
   const uint64_t incl = wave_inclusive_scan(active ? delta : 0);
-  uint64_t idx = slot;
-  for (uint32_t l = 1; l < tv.nlev; ++l) {
-    idx >>= kFanoutLog2;
-    const uint64_t node = active ? idx : ~0ull;  // lanes without a delta form runs of their own, which send nothing
-    const uint64_t prev = __shfl_up(node, 1, kWave);
-    const uint64_t starts = __ballot(lane == 0 || prev != node);
-    const bool ends = lane == kWave - 1 || ((starts >> (lane + 1)) & 1);
-    const int first = 63 - __builtin_clzll(starts & (~0ull >> (63 - lane)));  // where this lane's run starts (bit 0 is set)
-    const uint64_t before = __shfl(incl, first > 0 ? first - 1 : 0, kWave);
-    if (active && ends) atomic_add_u64(tv.level[l] + idx, incl - (first > 0 ? before : 0));
+  const uint64_t node = slot >> fanout_log2(tv, 1);
+  const LaneRuns run = lane_runs(active ? node : ~0ull);
+  const uint64_t before = __shfl(incl, run.first > 0 ? run.first - 1 : 0, kWave);
+  const uint64_t sum = incl - (run.first > 0 ? before : 0);
+  const bool sends = active && run.ends;
+  const uint64_t senders = __ballot(sends);
+  if (sends) atomic_add_both(tv.level[1] + node, second, sum);
+  const bool more = tv.nlev > 2;  // levels above (level 1 then has the full fan-out: at most three runs)
+  const uint32_t e = 4 * wave + (more ? __popcll(senders & ((1ull << lane) - 1)) : 0);
+  if (sends && more) {
+    sh.sum[e] = sum;
+    sh.node[e] = (uint32_t)node;
+  }
+  // places a wave does not use: zero on its last node (a gap would cut the runs of the second stage), none if idle
+  const uint32_t n_sent = __popcll(senders);
+  const uint32_t filler = n_sent ? (uint32_t)__shfl(node, 63 - __builtin_clzll(senders | 1), kWave) : ~0u;
+  if (lane < 4 && lane >= n_sent) {
+    sh.sum[4 * wave + lane] = 0;
+    sh.node[4 * wave + lane] = filler;
+  }
+  __syncthreads();
+  if (wave == 0 && more) {
+    const uint32_t nd = lane < 4 * (blockDim.x / kWave) ? sh.node[lane] : ~0u;
+    add_runs_to_ancestors(tv, nd != ~0u, nd, sh.sum[lane], second, 2);
   }
 }
 
@@ -184,13 +258,16 @@ struct RowMap {
   const uint32_t *index;     // row = index[i]
   const uint64_t *ring_key;  // row = (*ring_key + i) mod ring; with index: row = index[(*ring_key + i) mod ring]
   uint64_t ring;
+  FastDiv ring_div;          // division by ring
 };
 
 __device__ __forceinline__ uint64_t map_row(const RowMap &m, uint64_t i)
 {
-  if (m.index) return m.ring_key ? m.index[(*m.ring_key + i) % m.ring] : m.index[i];
-  if (m.ring_key) return (*m.ring_key + i) % m.ring;
-  return i;
+  if (m.ring_key) {
+    const uint64_t key = *m.ring_key + i;
+    i = key - fast_div(key, m.ring_div) * m.ring;
+  }
+  return m.index ? m.index[i] : i;
 }
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -377,7 +454,7 @@ __device__ __forceinline__ void update_batch_apply(const UpdateArgs &ua, UpdateL
   uint64_t q = 0, old = u.old;
   if (valid) {
     if (!ua.slot_hint) {
-      slot = (uint32_t)(u.key % tv.P);
+      slot = (uint32_t)ring_slot(tv, u.key);
       old = tv.level[0][slot];  // in flight during the dedupe
     }
     h = (slot * 2654435761u) >> 21;  // top 11 bits
@@ -669,10 +746,11 @@ __global__ __launch_bounds__(256) void add_payload_short_kernel(const uint8_t *_
 // --------------------------------------------------------------------------------------------
 // add: masses of the new keys, and their sums into the upper levels
 // --------------------------------------------------------------------------------------------
-// both: the second copy of the tree (tv2) is in step with the first and is kept so.
+// second: the second copy of the tree is in step with the first, lies that many words behind it and is kept so;
+// 0: the first copy alone is written.
 struct AddLeavesArgs {
-  TreeView tv, tv2;
-  bool both;
+  TreeView tv;
+  uint64_t second;
   DeviceState *st;
   uint64_t count;
   const float *prio;  // [count]
@@ -680,25 +758,32 @@ struct AddLeavesArgs {
 };
 
 // Workgroup blk of n_wgs.
-__device__ __forceinline__ void add_leaves_block(const AddLeavesArgs &a, uint32_t blk, uint32_t n_wgs)
+__device__ __forceinline__ void add_leaves_block(const AddLeavesArgs &a, uint32_t blk, uint32_t n_wgs, DenseSums &sh)
 {
   const uint64_t i = (uint64_t)blk * blockDim.x + threadIdx.x;
   const bool active = i < a.count;
-  uint64_t slot = 0, q = 0;
+  const uint64_t tail = a.st->tail;
+  const float prio = a.prio[active ? i : 0];
+  const uint64_t slot = ring_slot(a.tv, tail + (active ? i : 0));
   bool clamped = false;
+  const uint64_t q = quantise_priority(prio, a.qp, &clamped);
   if (active) {
-    slot = (a.st->tail + i) % a.tv.P;
-    q = quantise_priority(a.prio[i], a.qp, &clamped);
     a.tv.level[0][slot] = q;  // the slot was empty (mass 0): the ring is never over-filled
-    if (a.both) a.tv2.level[0][slot] = q;
+    if (a.second) a.tv.level[0][slot + a.second] = q;
   }
-  add_to_ancestors_grouped(a.tv, active, slot, q, a.both ? &a.tv2 : nullptr);
-  const uint64_t nc = __popcll(__ballot(clamped));
+  add_dense_to_ancestors(a.tv, active, slot, q, a.second, sh);
+  advance_state(&a.st->ticket_add, &a.st->tail, tail + a.count, n_wgs);
+  const uint64_t nc = __popcll(__ballot(active && clamped));
   if (nc && lane_id() == 0) atomic_add_u64(&a.st->n_clamped, nc);
-  advance_state_when_all_done(&a.st->ticket_add, &a.st->tail, a.count, n_wgs);
 }
 
-__global__ __launch_bounds__(256) void add_leaves_kernel(AddLeavesArgs a) { add_leaves_block(a, blockIdx.x, gridDim.x); }
+constexpr int kLeavesThreads = 1024;  // workgroups of add_leaves_kernel and evict_leaves_kernel
+
+__global__ __launch_bounds__(kLeavesThreads) void add_leaves_kernel(AddLeavesArgs a)
+{
+  __shared__ DenseSums sh;
+  add_leaves_block(a, blockIdx.x, gridDim.x, sh);
+}
 
 // A small add round in one launch (Algorithm 1: ComputePriorities, replay.Add): 2^lanes_log2 lanes
 // per transition copy its payload row into the ring; the first of them computes the n-step
@@ -710,8 +795,8 @@ constexpr int kAddRoundThreads = 1024;
 
 struct AddRoundArgs {
   NstepArgs ns;
-  TreeView tv, tv2;
-  bool both;  // tv2 receives the same masses
+  TreeView tv;
+  uint64_t second;  // as in AddLeavesArgs
   DeviceState *st;
   QuantParams qp;
   const uint8_t *obs, *act;  // [S*T, obs_bytes], [S*T, act_bytes] (act may be null)
@@ -734,8 +819,9 @@ __device__ __forceinline__ void add_round_small_block(const AddRoundArgs &a, uin
   const uint64_t count = (uint64_t)a.ns.S * a.ns.T;
   const bool in_range = i < count;
   bool clamped = false;
+  const uint64_t tail = a.st->tail;
   if (in_range) {
-    const uint64_t slot = (a.st->tail + i) % a.tv.P;
+    const uint64_t slot = ring_slot(a.tv, tail + i);
     for (uint32_t vv = v; vv < a.vecs_per_row; vv += lanes)
       reinterpret_cast<Vec *>(a.obs_ring + slot * a.obs_bytes)[vv] =
           reinterpret_cast<const Vec *>(a.obs + i * a.obs_bytes)[vv];
@@ -748,7 +834,7 @@ __device__ __forceinline__ void add_round_small_block(const AddRoundArgs &a, uin
       a.gacc_ring[slot] = o.G;
       const uint64_t q = quantise_priority(o.p, a.qp, &clamped);
       a.tv.level[0][slot] = q;  // the slot was empty (mass 0): the ring is never over-filled
-      if (a.both) a.tv2.level[0][slot] = q;
+      if (a.second) a.tv.level[0][slot + a.second] = q;
       sh_slot[r] = slot;
       sh_q[r] = q;
     }
@@ -759,9 +845,9 @@ __device__ __forceinline__ void add_round_small_block(const AddRoundArgs &a, uin
   if (threadIdx.x < ((rows_per_block + kWave - 1) & ~(uint32_t)(kWave - 1))) {  // whole waves
     const uint32_t e = threadIdx.x;
     const bool active = e < rows_per_block && (uint64_t)blk * rows_per_block + e < count;
-    add_to_ancestors_grouped(a.tv, active, active ? sh_slot[e] : 0, active ? sh_q[e] : 0, a.both ? &a.tv2 : nullptr);
+    add_runs_to_ancestors(a.tv, active, active ? sh_slot[e] : 0, active ? sh_q[e] : 0, a.second);
   }
-  advance_state_when_all_done(&a.st->ticket_add, &a.st->tail, count, n_wgs);
+  advance_state(&a.st->ticket_add, &a.st->tail, tail + count, n_wgs);
 }
 
 template <typename Vec>
@@ -772,20 +858,27 @@ __global__ __launch_bounds__(kAddRoundThreads) void add_round_small_kernel(AddRo
 }
 
 // evict: zero the masses of the e oldest keys and take them out of the upper levels
-__global__ __launch_bounds__(256) void evict_leaves_kernel(TreeView tv, TreeView tv2, bool both,
-                                                           DeviceState *__restrict__ st, uint64_t e)
+struct EvictLeavesArgs {
+  TreeView tv;
+  uint64_t second;  // as in AddLeavesArgs
+  DeviceState *st;
+  uint64_t e;
+};
+
+__global__ __launch_bounds__(kLeavesThreads) void evict_leaves_kernel(EvictLeavesArgs a)
 {
+  __shared__ DenseSums sh;
   const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const bool active = i < e;
-  uint64_t slot = 0, old = 0;
+  const bool active = i < a.e;
+  const uint64_t head = a.st->head;
+  const uint64_t slot = ring_slot(a.tv, head + (active ? i : 0));
+  const uint64_t old = a.tv.level[0][slot];
   if (active) {
-    slot = (st->head + i) % tv.P;
-    old = tv.level[0][slot];
-    tv.level[0][slot] = 0;
-    if (both) tv2.level[0][slot] = 0;
+    a.tv.level[0][slot] = 0;
+    if (a.second) a.tv.level[0][slot + a.second] = 0;
   }
-  add_to_ancestors_grouped(tv, active, slot, 0 - old, both ? &tv2 : nullptr);
-  advance_state_when_all_done(&st->ticket_evict, &st->head, e);
+  add_dense_to_ancestors(a.tv, active, slot, 0 - old, a.second, sh);
+  advance_state(&a.st->ticket_evict, &a.st->head, head + a.e, gridDim.x);
 }
 
 // --------------------------------------------------------------------------------------------
@@ -794,6 +887,7 @@ __global__ __launch_bounds__(256) void evict_leaves_kernel(TreeView tv, TreeView
 // pass 1: every valid pair bids its position for the slot (highest position wins)
 struct ClaimArgs {
   uint64_t P;
+  FastDiv p_div;
   DeviceState *st;
   uint32_t m;           // 0: nothing to claim
   const uint64_t *key;
@@ -807,7 +901,7 @@ __device__ __forceinline__ void update_claim_block(const ClaimArgs &c, uint32_t 
   if (i < c.m) {
     const uint64_t k = c.key[i];
     if (k >= c.st->head && k < c.st->tail)
-      __hip_atomic_fetch_max(c.claim + (k % c.P), i + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_fetch_max(c.claim + (k - fast_div(k, c.p_div) * c.P), i + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     else
       stale = true;
   }
@@ -842,24 +936,26 @@ __global__ __launch_bounds__(256) void update_apply_kernel(TreeView tv, DeviceSt
                                                            uint32_t *__restrict__ claim, QSource qs)
 {
   const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-  bool clamped = false;
+  bool clamped = false, wins = false;
+  uint64_t slot = 0, delta = 0;
   if (i < m) {
     const uint64_t k = key[i];
     if (k >= st->head && k < st->tail) {
-      const uint64_t slot = k % tv.P;
+      slot = ring_slot(tv, k);
       const float p = qs.q_taken ? td_priority(qs, i, slot) : prio[i];
       if (qs.q_taken && qs.prio_out) qs.prio_out[i] = p;
       const uint64_t q = quantise_priority(p, qp, &clamped);
       if (claim[slot] == i + 1) {
-        const uint64_t old = tv.level[0][slot];
+        wins = true;
+        delta = q - tv.level[0][slot];
         tv.level[0][slot] = q;
-        add_to_ancestors(tv, slot, q - old);
         claim[slot] = 0;
       }
     } else if (qs.q_taken && qs.prio_out) {
       qs.prio_out[i] = 0.0f;
     }
   }
+  add_runs_to_ancestors(tv, wins, slot, delta);  // the keys of a drawn batch ascend: neighbours share their upper nodes
   const uint64_t nc = __popcll(__ballot(clamped));
   if (nc && lane_id() == 0) atomic_add_u64(&st->n_clamped, nc);
 }
@@ -874,68 +970,24 @@ struct SampleArgs {
   const DeviceState *st;
   uint32_t k;                // samples per batch
   const uint64_t *k_dev;     // not null: the number of samples is read here, on the device (waves beyond it idle)
+  FastDiv k_div;             // division by k (unused with k_dev)
   const uint32_t *gen;       // not null: keys are (generation of the slot << 32) | slot instead of ring keys
   const uint64_t *rnd;       // [nb,k]
   uint64_t *key_out;         // [nb,k] or null
   uint32_t *slot_out;        // [nb,k]
   uint64_t *mass;            // [nb,k]: mass of each drawn transition, for the weights
-  // small payload columns, gathered here; the observation rows are copied by copy_rows_*
+  // payload columns and their outputs (each output may be null); obs only where the draw gathers the rows itself
   const uint8_t *act;
   uint32_t act_bytes;
   const float *ret, *gacc;
   uint8_t *act_out;
   float *ret_out, *gacc_out;
-  // not null (one batch only): the new priorities of the batch being drawn; their mass differences
 };
-
-// Turns pre[0, n_top) (LDS, the top level's masses, complete and visible) into exclusive prefix sums in
-// place and returns their total.  wave_total: blockDim/64 words of LDS.  Called by every thread
-// of the workgroup; ends with a barrier.
-__device__ __forceinline__ uint64_t top_prefix_sums(uint64_t *pre, uint64_t *wave_total, uint32_t n_top)
-{
-  const uint32_t tid = threadIdx.x, nthr = blockDim.x, nwave = nthr / kWave, wave = tid / kWave;
-  const uint32_t per = (n_top + nthr - 1) / nthr;
-  const uint32_t lo = min(tid * per, n_top), hi = min(lo + per, n_top);
-  uint64_t mine = 0;
-  for (uint32_t i = lo; i < hi; ++i) mine += pre[i];
-  const uint64_t incl = wave_inclusive_scan(mine);
-  if (lane_id() == kWave - 1) wave_total[wave] = incl;
-  __syncthreads();
-  uint64_t before = 0, total = 0;
-  for (uint32_t w = 0; w < nwave; ++w) {
-    const uint64_t t = wave_total[w];
-    if (w < wave) before += t;
-    total += t;
-  }
-  uint64_t run = before + incl - mine;
-  for (uint32_t i = lo; i < hi; ++i) {
-    const uint64_t v = pre[i];
-    pre[i] = run;
-    run += v;
-  }
-  __syncthreads();
-  return total;
-}
 
 struct Drawn {
   uint64_t slot, mass;
   uint64_t x;  // where in the slot's interval of cumulative mass the point fell: 0 <= x < mass
 };
-
-// Exact floor(n / d) for any n by a multiplication, for a divisor that the host knows at launch time
-// (the 64-bit quotient of a sum of masses by the batch size is otherwise a long software division on the
-// drawing wave's critical path).  Granlund and Montgomery's unsigned division by an invariant integer:
-// L = ceil(log2 d), mul = floor(2^64 (2^L - d) / d) + 1, sh1 = min(L, 1), sh2 = max(L - 1, 0).
-struct FastDiv {
-  uint64_t mul;
-  uint32_t sh1, sh2;
-};
-
-__device__ __forceinline__ uint64_t fast_div(uint64_t n, const FastDiv &d)
-{
-  const uint64_t t = __umul64hi(d.mul, n);
-  return (t + ((n - t) >> d.sh1)) >> d.sh2;
-}
 
 // Where a walk stands after the top level: node idx of that level, whose interval of cumulative mass
 // holds the point; x is the point's offset inside the interval, mass the node's mass.
@@ -943,30 +995,6 @@ struct TopHit {
   uint64_t idx, x, mass;
 };
 
-// Top level from LDS: `pre` holds its exclusive prefix sums; largest i with pre[i] <= x, by two rounds of
-// 64-way comparison.  Called by all 64 lanes.
-__device__ __forceinline__ TopHit top_search_lds(const uint64_t *pre, uint32_t n_top, uint64_t total, uint64_t x)
-{
-  const int lane = lane_id();
-  const uint32_t stride = (n_top + kWave - 1) / kWave;
-  const uint32_t p0 = lane * stride;
-  uint32_t cnt = __popcll(__ballot(p0 < n_top && pre[p0] <= x));
-  const uint32_t base = (cnt - 1) * stride;  // pre[0] = 0 <= x, so cnt >= 1
-  cnt = 0;
-  for (uint32_t off = 0; off < stride; off += kWave) {
-    const uint32_t p1 = base + off + lane;
-    cnt += __popcll(__ballot(off + lane < stride && p1 < n_top && pre[p1] <= x));
-  }
-  const uint64_t idx = base + cnt - 1;
-  const uint64_t mass = ((idx + 1 < n_top) ? pre[idx + 1] : total) - pre[idx];
-  return TopHit{idx, x - pre[idx], mass};
-}
-
-// Top level of at most 512 nodes from registers: lane l holds the masses v[0..8) of nodes 8l .. 8l+7 (zero
-// beyond the level) and lane_before, the sum of all nodes before them.  The same node as top_search_lds
-// finds (the last one whose prefix sum is <= x), without a round trip through LDS: the lane by one
-// ballot, the node inside the lane by eight comparisons that every lane makes for itself, the winner's
-// values by lane reads.  Called by all 64 lanes.
 __device__ __forceinline__ uint32_t read_lane_u32(uint32_t v, uint32_t l)
 {
   return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)l);
@@ -975,21 +1003,59 @@ __device__ __forceinline__ uint64_t read_lane_u64(uint64_t v, uint32_t l)
 {
   return ((uint64_t)read_lane_u32((uint32_t)(v >> 32), l) << 32) | read_lane_u32((uint32_t)v, l);
 }
-__device__ __forceinline__ TopHit top_search_regs(const uint64_t (&v)[8], uint64_t lane_before, uint64_t x)
-{
-  const uint32_t l = __popcll(__ballot(lane_before <= x)) - 1;  // lane 0 has lane_before = 0 <= x
-  uint64_t p = lane_before, p_hit = lane_before, v_hit = v[0];
-  uint32_t t_hit = 0;
+
+typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
+
+// The top level in the registers of one wave: lane l holds the masses v[0..8) of nodes 8l .. 8l+7 (zero beyond
+// the level).  load() only issues the loads (16 bytes wide), scan() waits for them.
+struct TopLevel {
+  uint64_t v[8];
+  uint64_t before;  // sum of all nodes before this lane's
+
+  __device__ __forceinline__ void load(const uint64_t *top, uint32_t n_top)
+  {
+    const uint32_t i0 = 8 * (uint32_t)lane_id();
+    const uint32_t n_pad = (n_top + kFanout - 1) & ~(kFanout - 1);  // the level is zero-padded to this in memory
 #pragma unroll
-  for (int t = 1; t < 8; ++t) {
-    p += v[t - 1];
-    const bool le = p <= x;  // true for the first few t only: the prefix sums do not decrease
-    t_hit = le ? t : t_hit;
-    p_hit = le ? p : p_hit;
-    v_hit = le ? v[t] : v_hit;
+    for (int t = 0; t < 8; ++t) v[t] = 0;
+    if (i0 < n_pad) {
+#pragma unroll
+      for (int t = 0; t < 8; t += 2) {
+        const u64x2 v2 = *reinterpret_cast<const u64x2 *>(top + i0 + t);
+        v[t] = v2.x, v[t + 1] = v2.y;
+      }
+    }
   }
-  return TopHit{8ull * l + read_lane_u32(t_hit, l), x - read_lane_u64(p_hit, l), read_lane_u64(v_hit, l)};
-}
+
+  // Returns the sum of the whole level.
+  __device__ __forceinline__ uint64_t scan()
+  {
+    uint64_t mine = 0;
+#pragma unroll
+    for (int t = 0; t < 8; ++t) mine += v[t];
+    const uint64_t incl = wave_inclusive_scan(mine);
+    before = incl - mine;
+    return read_lane_u64(incl, kWave - 1);
+  }
+
+  // The last node whose prefix sum is <= x: the lane by one ballot, the node inside the lane by eight comparisons
+  // that every lane makes for itself, the winner's values by lane reads.
+  __device__ __forceinline__ TopHit find(uint64_t x) const
+  {
+    const uint32_t l = __popcll(__ballot(before <= x)) - 1;  // lane 0 has before = 0 <= x
+    uint64_t p = before, p_hit = before, v_hit = v[0];
+    uint32_t t_hit = 0;
+#pragma unroll
+    for (int t = 1; t < 8; ++t) {
+      p += v[t - 1];
+      const bool le = p <= x;  // true for the first few t only: the prefix sums do not decrease
+      t_hit = le ? t : t_hit;
+      p_hit = le ? p : p_hit;
+      v_hit = le ? v[t] : v_hit;
+    }
+    return TopHit{8ull * l + read_lane_u32(t_hit, l), x - read_lane_u64(p_hit, l), read_lane_u64(v_hit, l)};
+  }
+};
 
 // One wavefront walks from its places in the top level down to the slots whose cumulative-mass intervals
 // hold the points: the loads of all samples go out together on every level, so that several draws take
@@ -1000,121 +1066,169 @@ template <int kSamples, typename Between>
 __device__ __forceinline__ void walk_down(const TreeView &tv, const TopHit (&top)[kSamples], Drawn (&out)[kSamples],
                                           Between between)
 {
-  const int lane = lane_id();
+  const uint32_t lane = lane_id();
   // the two lowest levels' addresses are at fixed places of the arguments: fetched with them, not on the way down
   const uint64_t *const low0 = tv.level[0], *const low1 = tv.level[1];
   uint64_t x[kSamples], idx[kSamples], mass[kSamples];
 #pragma unroll
   for (int s = 0; s < kSamples; ++s) x[s] = top[s].x, idx[s] = top[s].idx, mass[s] = top[s].mass;
-  // 64 children per step, prefix sum across the wave, first child whose running sum exceeds the remainder
+  // up to 64 children per step, prefix sum across the wave, first child whose running sum exceeds the remainder
   bool called = false;
+  uint32_t fl = tv.top_log2;  // of the node the walk stands on
   for (int l = (int)tv.nlev - 2; l >= 0; --l) {
     const uint64_t *const lv = l == 0 ? low0 : l == 1 ? low1 : tv.level[l];
     uint64_t c[kSamples];
 #pragma unroll
-    for (int s = 0; s < kSamples; ++s) c[s] = lv[idx[s] * kFanout + lane];
+    for (int s = 0; s < kSamples; ++s) c[s] = lv[(idx[s] << fl) + (lane & ((1u << fl) - 1))];
     if (!called) {
       between();
       called = true;
     }
 #pragma unroll
     for (int s = 0; s < kSamples; ++s) {
+      if (lane >> fl) c[s] = 0;  // a summit's node has fewer children than the wave has lanes
       const uint64_t sc = wave_inclusive_scan(c[s]);
       const uint64_t hit = __ballot(sc > x[s]);
-      const int sel = hit ? __ffsll((unsigned long long)hit) - 1 : kWave - 1;
-      const uint64_t c_sel = __shfl(c[s], sel, kWave);
-      const uint64_t s_sel = __shfl(sc, sel, kWave);
-      x[s] -= s_sel - c_sel;
-      idx[s] = idx[s] * kFanout + sel;
+      const uint32_t sel = hit ? __ffsll((unsigned long long)hit) - 1 : (1u << fl) - 1;
+      const uint64_t c_sel = read_lane_u64(c[s], sel);
+      x[s] -= read_lane_u64(sc, sel) - c_sel;
+      idx[s] = (idx[s] << fl) + sel;
       mass[s] = c_sel;
     }
+    fl = kFanoutLog2;
   }
   if (!called) between();
 #pragma unroll
   for (int s = 0; s < kSamples; ++s) out[s] = Drawn{idx[s], mass[s], x[s]};
 }
 
-// The whole descent with the top level in LDS (exclusive prefix sums `pre`).
-template <int kSamples, typename Between>
-__device__ __forceinline__ void wave_descend(const TreeView &tv, const uint64_t *pre, uint64_t total,
-                                             const uint64_t (&x_in)[kSamples], Drawn (&out)[kSamples],
-                                             Between between)
-{
-  TopHit top[kSamples];
-#pragma unroll
-  for (int s = 0; s < kSamples; ++s) top[s] = top_search_lds(pre, tv.n_top, total, x_in[s]);
-  walk_down<kSamples>(tv, top, out, between);
-}
-
-template <int kSamples>
-__device__ __forceinline__ void wave_descend(const TreeView &tv, const uint64_t *pre, uint64_t total,
-                                             const uint64_t (&x_in)[kSamples], Drawn (&out)[kSamples])
-{
-  wave_descend<kSamples>(tv, pre, total, x_in, out, [] {});
-}
-
 // The ring key of a drawn slot: head + its distance from the head's slot around the ring.
-// head_slot = head % P.
+// head_slot = head mod P.
 __device__ __forceinline__ uint64_t ring_key(uint64_t slot, uint64_t head, uint64_t head_slot, uint64_t P)
 {
   return head + (slot >= head_slot ? slot - head_slot : slot + P - head_slot);
 }
 
-// What a draw writes for sample o (called by all 64 lanes of the wave that drew it).
-__device__ __forceinline__ void write_drawn(const SampleArgs &a, uint64_t o, Drawn d, uint64_t head,
-                                            uint64_t head_slot)
+// One of the four 16-lane rows of a wave: inclusive prefix sum.
+__device__ __forceinline__ uint64_t row_inclusive_scan(uint64_t v)
 {
-  const TreeView &tv = a.tv;
-  const int lane = lane_id();
-  const uint64_t slot = d.slot;
-  if (lane == 0) {
-    a.slot_out[o] = (uint32_t)slot;
-    if (a.key_out)
-      a.key_out[o] = a.gen ? ((uint64_t)a.gen[slot] << 32) | slot : ring_key(slot, head, head_slot, tv.P);
-    a.mass[o] = d.mass;
-    if (a.ret_out) a.ret_out[o] = a.ret[slot];
-    if (a.gacc_out) a.gacc_out[o] = a.gacc[slot];
-  }
-  if (a.act_out)
-    for (uint32_t by = lane; by < a.act_bytes; by += kWave)
-      a.act_out[o * a.act_bytes + by] = a.act[slot * a.act_bytes + by];
+  v = dpp_add_step<0x111, 0xf>(v);  // row_shr:1
+  v = dpp_add_step<0x112, 0xf>(v);  // row_shr:2
+  v = dpp_add_step<0x114, 0xf>(v);  // row_shr:4
+  v = dpp_add_step<0x118, 0xf>(v);  // row_shr:8
+  return v;
 }
 
-// Dynamic LDS: n_top uint64 (exclusive prefix sums of the top level) + blockDim/64 words.
-__global__ __launch_bounds__(1024) void sample_descent_kernel(SampleArgs a)
+// The walk of four samples at once, one per 16-lane row of the wave (every lane of a row holds its sample's values):
+// a lane takes four neighbouring children, so that a level costs four steps of a prefix sum for four samples
+// instead of six for one.  With a whole wave per sample the arithmetic of the scans, not memory, was what a call
+// of many samples took (8192 samples from 2^21 slots: 11.0 us, now 6.2; the 32,000 of an eviction round: 14.9, now
+// 5.6); a call of few is bound by its chain of round trips (256 from 2^20 slots: 7.0 us, now 6.0).
+struct RowWalk {
+  uint64_t idx, x, mass;
+};
+
+// The lane of the row that holds the first running sum above x has found the child: its values go to the whole row.
+__device__ __forceinline__ void row_descend(RowWalk &w, const uint64_t *lv, uint32_t fl)
 {
-  extern __shared__ uint64_t lds[];
-  const TreeView &tv = a.tv;
-  const uint32_t n_top = tv.n_top;
-  uint64_t *pre = lds;
-  uint64_t *wave_total = lds + n_top;
-  const uint32_t tid = threadIdx.x, nthr = blockDim.x, nwave = nthr / kWave;
-  const uint32_t wave = tid / kWave;
-  const uint32_t b = blockIdx.y;
-  const uint32_t j = blockIdx.x * nwave + wave;
-  const uint32_t k = a.k_dev ? (uint32_t)*a.k_dev : a.k;
-  const uint64_t o = (uint64_t)b * k + j;
-  // issued ahead of the LDS work below, which does not depend on them
-  const uint64_t u = j < k ? a.rnd[o] : 0;
-  const uint64_t head = a.st->head;
+  const uint32_t lane = lane_id(), gl = lane & 15, child0 = 4 * gl;
+  const uint32_t f = 1u << fl;
+  const uint64_t base = w.idx << fl;
+  // lanes beyond the node's children read its first ones again and count as empty; a node of two children (16-byte
+  // aligned all the same) is read together with its neighbour, or with what follows the level in the tree region
+  const uint64_t *c = lv + base + (child0 < f ? child0 : 0);
+  const u64x2 lo = *reinterpret_cast<const u64x2 *>(c), hi = *reinterpret_cast<const u64x2 *>(c + 2);
+  const bool in = child0 < f, in2 = child0 + 2 < f;
+  const uint64_t c0 = in ? lo.x : 0, c1 = in ? lo.y : 0, c2 = in2 ? hi.x : 0, c3 = in2 ? hi.y : 0;
+  const uint64_t p1 = c0 + c1, p2 = p1 + c2, sum = p2 + c3;
+  const uint64_t incl = row_inclusive_scan(sum);
+  const uint32_t hits = (uint32_t)(__ballot(incl > w.x) >> (lane & 48)) & 0xffffu;
+  const uint32_t src = (lane & 48) + (hits ? __ffs(hits) - 1 : 15);
+  const uint64_t r = w.x - (incl - sum);  // of use in the lane that has the hit
+  const uint32_t t = (r >= c0) + (r >= p1) + (r >= p2);
+  const uint64_t below = t == 0 ? 0 : t == 1 ? c0 : t == 2 ? p1 : p2;
+  const uint64_t m = t == 0 ? c0 : t == 1 ? c1 : t == 2 ? c2 : c3;
+  w.idx = base + __shfl(child0 + t, src, kWave);
+  w.x = __shfl(r - below, src, kWave);
+  w.mass = __shfl(m, src, kWave);
+}
 
-  // ---- top level -> LDS, exclusive prefix sums in place
-  const uint64_t *top = tv.level[tv.nlev - 1];
-  for (uint32_t i = tid; i < n_top; i += nthr) pre[i] = top[i];
-  __syncthreads();
-  const uint64_t total = top_prefix_sums(pre, wave_total, n_top);
+// A few bytes by one 16-lane row: pieces of four bytes at any alignment, the last one overlapping the one before;
+// the first 256 bytes' loads go out together.
+typedef uint32_t u32_any __attribute__((aligned(1)));
 
-  // ---- one sample per wavefront
-  if (j < k) {
-    const uint64_t w = total / k;                           // stratum width
-    const uint64_t x = (uint64_t)j * w + __umul64hi(u, w);  // point inside stratum j
-    const uint64_t xs[1] = {x};
-    Drawn drs[1];
-    uint64_t head_slot = 0;
-    wave_descend<1>(tv, pre, total, xs, drs, [&] { head_slot = head % tv.P; });
-    const Drawn dr = drs[0];
-    write_drawn(a, o, dr, head, head_slot);
+__device__ __forceinline__ void copy_bytes_by_row(uint8_t *__restrict__ d, const uint8_t *__restrict__ s, uint32_t bytes)
+{
+  const uint32_t gl = lane_id() & 15;
+  if (bytes < 4) {
+    if (gl < bytes) d[gl] = s[gl];
+    return;
   }
+  const uint32_t n = (bytes + 3) / 4, last = bytes - 4;
+  for (uint32_t v0 = 0; v0 < n; v0 += 64) {
+    uint32_t t[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) t[u] = *reinterpret_cast<const u32_any *>(s + min(4 * (v0 + 16 * u + gl), last));
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (v0 + 16 * u < n) *reinterpret_cast<u32_any *>(d + min(4 * (v0 + 16 * u + gl), last)) = t[u];
+  }
+}
+
+// Four consecutive samples of a batch per wave, no LDS and no barrier.
+__global__ __launch_bounds__(256) void sample_draw_kernel(SampleArgs a)
+{
+  const TreeView &tv = a.tv;
+  const uint32_t lane = lane_id(), gl = lane & 15, b = blockIdx.y;
+  const uint32_t j0 = (blockIdx.x * (256 / kWave) + threadIdx.x / kWave) * 4;
+  const uint32_t k = a.k_dev ? (uint32_t)*a.k_dev : a.k;
+  if (j0 >= k) return;
+  const uint32_t j = j0 + lane / 16;
+  const bool valid = j < k;  // a row without a sample repeats the batch's last one and writes nothing
+  const uint64_t o = (uint64_t)b * k + min(j, k - 1);
+  TopLevel top;
+  const uint64_t *const top_level = tv.level[tv.nlev - 1];
+  top.load(top_level, tv.n_top);
+  const uint64_t u = a.rnd[o];
+  const uint64_t head = a.st->head;
+  const uint64_t total = top.scan();
+  const uint64_t w = a.k_dev ? total / k : fast_div(total, a.k_div);  // stratum width
+  RowWalk walk;
+  walk.x = (uint64_t)min(j, k - 1) * w + __umul64hi(u, w);  // point inside stratum j
+
+  // top level: the lane that holds the node by a ballot per sample, then its eight nodes anew (they are in the
+  // first cache), as if they were the children of a node
+  uint32_t l = 0;
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    const uint32_t ls = __popcll(__ballot(top.before <= read_lane_u64(walk.x, 16 * s))) - 1;
+    l = lane / 16 == (uint32_t)s ? ls : l;
+  }
+  walk.x -= __shfl(top.before, l, kWave);
+  walk.idx = l;
+  row_descend(walk, top_level, 3);
+  const uint64_t head_slot = ring_slot(tv, head);
+  uint32_t fl = tv.top_log2;
+  for (int lv = (int)tv.nlev - 2; lv >= 0; --lv) {
+    row_descend(walk, tv.level[lv], fl);
+    fl = kFanoutLog2;
+  }
+  if (!valid) return;
+  const uint64_t slot = walk.idx;
+  float col = 0.f;
+  uint32_t gen = 0;
+  const bool ret_lane = gl == 1 && a.ret_out, gacc_lane = gl == 2 && a.gacc_out;
+  if (ret_lane) col = a.ret[slot];
+  if (gacc_lane) col = a.gacc[slot];
+  if (gl == 0 && a.gen) gen = a.gen[slot];
+  if (a.act_out) copy_bytes_by_row(a.act_out + o * a.act_bytes, a.act + slot * a.act_bytes, a.act_bytes);
+  if (gl == 0) {
+    a.slot_out[o] = (uint32_t)slot;
+    a.mass[o] = walk.mass;
+    if (a.key_out) a.key_out[o] = a.gen ? ((uint64_t)gen << 32) | slot : ring_key(slot, head, head_slot, tv.P);
+  }
+  if (ret_lane) a.ret_out[o] = col;
+  if (gacc_lane) a.gacc_out[o] = col;
 }
 
 // --------------------------------------------------------------------------------------------
@@ -1142,14 +1256,6 @@ __device__ __forceinline__ void add_delta(const TreeView &tv, uint32_t slot, uin
   if (!delta) return;
   atomic_add_u64(tv.level[0] + slot, delta);
   add_to_ancestors(tv, slot, delta);
-}
-
-// Orders the LDS accesses of one wavefront among its lanes (the hardware runs them in order; this
-// keeps the compiler from moving them).
-__device__ __forceinline__ void wave_lds_sync()
-{
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
 }
 
 // Workgroups of 8 waves, 4 vectors per lane: as fast as 16 waves x 2 when the kernel runs alone, and the
@@ -1196,8 +1302,6 @@ struct StepArgs {
 
 enum StepRider { kNoRider = 0, kRoundRides = 1, kLeavesRide = 2 };
 
-typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
-
 // Waits until every load (and store) that this wave has issued is through.
 __device__ __forceinline__ void wait_for_all_loads()
 {
@@ -1212,46 +1316,23 @@ __device__ __forceinline__ void fetch_now(T *p)
   asm volatile("" ::"s"(p));
 }
 
-// The draw of sample `row` of the next batch by the first wave of a workgroup, with no barrier: the
-// top level (eight consecutive nodes per lane and pass of 512, 16-byte loads) into registers, the walk
-// down, outputs, and the change that the sample's new priority brings.
+// The draw of sample `row` of the next batch by the first wave of a workgroup, with no barrier and no LDS: the
+// top level in registers, the walk down, outputs, and the change that the sample's new priority brings.
 // The wave's path through memory is the launch's critical path, so it holds exactly one round trip per
 // tree level and as little else as can be:
 //  - the top-level loads are the first instructions to go out, the sample's random number, new priority
 //    and the ring's head follow them and are used after them (a wave's loads return in the order of issue);
-//  - a top level of one pass (kTopChunk == 1: at most 512 nodes) is searched in the registers it was
-//    loaded into; larger ones go through LDS as exclusive prefix sums (round_up(n_top, 64) words of 8 bytes);
 //  - the stratum width is an exact division by multiplication (StepArgs::next_k_div);
 //  - what does not depend on the walk (priority -> mass, head % P, the addresses of everything written at
 //    the end) is computed or fetched while the first row of children is on its way.
-template <int kTopChunk>
-__device__ __forceinline__ void draw_in_first_wave(const StepArgs &a, uint32_t row, uint64_t *pre)
+__device__ __forceinline__ void draw_in_first_wave(const StepArgs &a, uint32_t row)
 {
   const TreeView &rd = a.next.tv;
-  const uint32_t n_top = rd.n_top, lane = lane_id();
-  const uint32_t n_top_pad = (n_top + kFanout - 1) & ~(kFanout - 1);  // the level is zero-padded to this in memory
+  const uint32_t lane = lane_id();
   const bool second = a.next_prio && row + 1 < a.next.k;              // a next sample to compare slots with
   __builtin_amdgcn_s_setprio(2);
-  const uint64_t *top = a.next_top;
-  constexpr uint32_t kChunkNodes = kTopChunk * 8 * kWave;
-
-  uint64_t v[kTopChunk][8];
-  auto issue = [&](uint32_t c0) {
-#pragma unroll
-    for (int p = 0; p < kTopChunk; ++p) {
-      const uint32_t i0 = c0 + p * 8 * kWave + 8 * lane;
-#pragma unroll
-      for (int t = 0; t < 8; ++t) v[p][t] = 0;
-      if (i0 < n_top_pad) {
-#pragma unroll
-        for (int t = 0; t < 8; t += 2) {
-          const u64x2 v2 = *reinterpret_cast<const u64x2 *>(top + i0 + t);
-          v[p][t] = v2.x, v[p][t + 1] = v2.y;
-        }
-      }
-    }
-  };
-  issue(0);
+  TopLevel top;
+  top.load(a.next_top, rd.n_top);
   // no load below is conditional: a branch around a load would make the wave wait for it there
   const uint64_t un0 = a.next.rnd[row], un1 = a.next.rnd[second ? row + 1 : row];
   const float prio_next = *(a.next_prio ? a.next_prio + row : reinterpret_cast<const float *>(a.next.rnd + row));
@@ -1261,51 +1342,10 @@ __device__ __forceinline__ void draw_in_first_wave(const StepArgs &a, uint32_t r
   // them is the one that counts: pair `row` loses to pair row + 1 exactly if the next point still lies in the
   // interval of cumulative mass of the slot drawn here, which needs no second walk: both points are known
   // from the start, and the walk ends with the place of its point inside the slot's interval.
-  uint64_t point = 0, next_point = 0;
-  TopHit hit[1];
-  if constexpr (kTopChunk == 1) {
-    // ---- one pass: the level stays in the registers it was loaded into
-    uint64_t mine = 0;
-#pragma unroll
-    for (int t = 0; t < 8; ++t) mine += v[0][t];
-    const uint64_t incl = wave_inclusive_scan(mine);
-    const uint64_t total = read_lane_u64(incl, kWave - 1);
-    const uint64_t w = fast_div(total, a.next_k_div);
-    point = (uint64_t)row * w + __umul64hi(un0, w), next_point = (uint64_t)(row + 1) * w + __umul64hi(un1, w);
-    hit[0] = top_search_regs(v[0], incl - mine, point);
-  } else {
-    // ---- exclusive prefix sums -> LDS; the loads of kTopChunk passes go out together
-    uint64_t carry = 0;
-    auto consume = [&](uint32_t c0) {
-#pragma unroll
-      for (int p = 0; p < kTopChunk; ++p) {
-        const uint32_t i0 = c0 + p * 8 * kWave + 8 * lane;
-        uint64_t mine = 0;
-#pragma unroll
-        for (int t = 0; t < 8; ++t) mine += v[p][t];
-        const uint64_t incl = wave_inclusive_scan(mine);
-        uint64_t run = carry + incl - mine;
-        if (i0 < n_top_pad) {
-#pragma unroll
-          for (int t = 0; t < 8; ++t) {
-            pre[i0 + t] = run;
-            run += v[p][t];
-          }
-        }
-        carry += __shfl(incl, kWave - 1, kWave);
-      }
-    };
-    consume(0);
-    for (uint32_t c0 = kChunkNodes; c0 < n_top_pad; c0 += kChunkNodes) {
-      issue(c0);
-      consume(c0);
-    }
-    const uint64_t total = carry;
-    wave_lds_sync();
-    const uint64_t w = fast_div(total, a.next_k_div);
-    point = (uint64_t)row * w + __umul64hi(un0, w), next_point = (uint64_t)(row + 1) * w + __umul64hi(un1, w);
-    hit[0] = top_search_lds(pre, n_top, total, point);
-  }
+  const uint64_t total = top.scan();
+  const uint64_t w = fast_div(total, a.next_k_div);
+  const uint64_t point = (uint64_t)row * w + __umul64hi(un0, w), next_point = (uint64_t)(row + 1) * w + __umul64hi(un1, w);
+  const TopHit hit[1] = {top.find(point)};
 
   bool clamped = false;
   uint64_t q_next = 0, head_slot = 0;
@@ -1316,11 +1356,11 @@ __device__ __forceinline__ void draw_in_first_wave(const StepArgs &a, uint32_t r
   auto add_to_written_copy = [&](uint64_t slot, uint64_t delta) {  // one lane
     if (!delta) return;
     atomic_add_u64(wr0 + slot, delta);
-    if (wr_nlev > 1) atomic_add_u64(wr1 + (slot >> kFanoutLog2), delta);
-    if (wr_nlev > 2) atomic_add_u64(wr2 + (slot >> (2 * kFanoutLog2)), delta);
-    uint64_t idx = slot >> (2 * kFanoutLog2);
+    uint64_t idx = slot;
+    if (wr_nlev > 1) atomic_add_u64(wr1 + (idx >>= fanout_log2(a.wr, 1)), delta);
+    if (wr_nlev > 2) atomic_add_u64(wr2 + (idx >>= fanout_log2(a.wr, 2)), delta);
     for (uint32_t l = 3; l < wr_nlev; ++l) {
-      idx >>= kFanoutLog2;
+      idx >>= fanout_log2(a.wr, l);
       atomic_add_u64(a.wr.level[l] + idx, delta);
     }
   };
@@ -1328,7 +1368,7 @@ __device__ __forceinline__ void draw_in_first_wave(const StepArgs &a, uint32_t r
     fetch_now(slot_out), fetch_now(key_out), fetch_now(mass_out), fetch_now(dq_out);
     fetch_now(wr0), fetch_now(wr1), fetch_now(wr2);
     if (a.next_prio) q_next = quantise_priority(prio_next, a.qp, &clamped);
-    head_slot = head % rd.P;
+    head_slot = ring_slot(rd, head);
   };
   Drawn dr[1];
   walk_down<1>(rd, hit, dr, between);
@@ -1359,15 +1399,11 @@ __device__ __forceinline__ void draw_in_first_wave(const StepArgs &a, uint32_t r
 //                lanes 1, 2 gather ret and gacc of the row
 //   wave 2       gathers the action bytes of the row
 //   wave 3       in the first ceil(k / 64) workgroups: importance weights of 64 samples
-// Dynamic LDS: see draw_in_first_wave.
-// kTopChunk: passes of 512 top-level nodes whose loads the drawing wave issues together (1 for tops of at
-// most 512 nodes, 2 up to 1024, 4 beyond: more registers, fewer memory round trips).
 // kRider: what the workgroups beyond the first k carry (StepArgs::add or ::leaves).
 // kCodec: the rows are decoded on their way out (StepArgs::codec; Vec is 16 bytes wide).
-template <typename Vec, int kThreads, int kUnroll, int kTopChunk, int kRider, bool kCodec = false>
+template <typename Vec, int kThreads, int kUnroll, int kRider, bool kCodec = false>
 __global__ __launch_bounds__(kThreads) void learner_step_kernel(StepArgs a)
 {
-  extern __shared__ uint64_t lds[];
   const uint32_t row = blockIdx.x, tid = threadIdx.x, nthr = blockDim.x;
   if constexpr (kRider == kRoundRides) {
     if (row >= a.k) {
@@ -1378,19 +1414,20 @@ __global__ __launch_bounds__(kThreads) void learner_step_kernel(StepArgs a)
   }
   if constexpr (kRider == kLeavesRide) {
     if (row >= a.k) {
-      add_leaves_block(a.leaves, row - a.k, gridDim.x - a.k);
+      __shared__ DenseSums sh;
+      add_leaves_block(a.leaves, row - a.k, gridDim.x - a.k, sh);
       return;
     }
   }
   const uint32_t wave = tid / kWave, lane = lane_id();
   const bool write_back = a.dq != nullptr, draw = a.next.rnd != nullptr;
   if (!a.slot) {  // the first draw of a sequence (one wave per workgroup): no batch to gather yet
-    if (draw && wave == 0) draw_in_first_wave<kTopChunk>(a, row, lds);
+    if (draw && wave == 0) draw_in_first_wave(a, row);
     return;
   }
   const uint32_t first = (draw && a.vecs_per_row <= (nthr - kWave) * kUnroll) ? kWave : 0;
   if (draw && wave == 0) {
-    draw_in_first_wave<kTopChunk>(a, row, lds);
+    draw_in_first_wave(a, row);
     if (first) return;
   }
   // The compiler places its waits for memory by counting loads in flight; it can count them only along

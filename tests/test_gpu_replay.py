@@ -77,6 +77,31 @@ def test_random_operation_sequences(P, C, ob, ab):
         sample_both(g, o, rng, 2, 64)
 
 
+@pytest.mark.parametrize("P", [512, 513, 1025, 4608, 4609, 32_768, 32_769, 294_912, 294_913])
+def test_tree_shapes_around_the_summit(P):
+    """Sizes on both sides of every border of the tree's shape: the level that walks start from is the leaves themselves
+    (512), a summit of 2, 4 and 16 children per node (513, 1025, 4608; 32,769 and 294,912 above more levels), or an
+    ordinary level.  Rounds that wrap around the ring and cross several workgroups, draws at the very ends of the
+    cumulative mass, updates and evictions, bit for bit against the oracle."""
+    rng = np.random.default_rng(P)
+    C = P * 3 // 4
+    g, o = make_pair(C, P, 16, 4)
+    assert add_both(g, o, rng, C) == 0
+    for it in range(5):
+        cnt = min(P - o.size, (1, 700, 2100, 63, 5000)[it])
+        assert add_both(g, o, rng, cnt) == 0
+        check_gpu_tree(g, o)
+        edges = np.array([0, U64 - 1] * 8, np.uint64)
+        sample_both(g, o, rng, 1, 16, rnd=edges)
+        for nb, k in ((1, 1), (2, 17), (5, 450)):     # batches that leave a wave's four samples incomplete
+            oo = sample_both(g, o, rng, nb, k)
+        pr = rng.lognormal(0, 2, len(oo["key"])).astype(F32)
+        assert g.update_priorities(dev(oo["key"]), dev(pr)) == o.update_priorities(oo["key"], pr) == 0
+        assert g.evict() == o.evict()
+        check_gpu_tree(g, o)
+        sample_both(g, o, rng, 3, 64)
+
+
 @pytest.mark.parametrize("P,C,ob,ab", [(5000, 4000, 48, 8), (3000, 2500, 4112, 4)])
 def test_add_with_payload_written_in_place(P, C, ob, ab):
     """A producer writes observations and actions of the coming keys straight into the ring (row
