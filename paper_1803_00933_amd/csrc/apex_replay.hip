@@ -77,6 +77,7 @@ FastDiv make_fast_div(uint32_t d)
 
 uint64_t qmax_for(uint64_t max_slots) { return max_slots ? 1ull << (62 - ceil_log2(max_slots)) : 1ull << 62; }
 
+constexpr uint64_t kTicketBytes = (uint64_t)APEX_MAX_BATCHES_PER_CALL * kTicketStride * 4;
 constexpr uint32_t kStepSets = 64;  // buffer sets a sequence of fused steps can cycle through
 
 struct Geometry {
@@ -85,8 +86,8 @@ struct Geometry {
   uint32_t exported_nlev;   // ... of which apex_replay_layout shows these (a summit is not shown)
   uint32_t top_log2;        // fan-out of the last level over the one below it
   uint64_t level_off[kMaxLevels], level_size[kMaxLevels], tree_words;
-  // scratch: DeviceState | mass | claim | new masses of the batches of fused steps
-  uint64_t state_off, mass_off, claim_off, stepq_off, scratch_bytes;
+  // scratch: DeviceState | tickets of sample calls | mass | claim | new masses of the batches of fused steps
+  uint64_t state_off, ticket_off, mass_off, claim_off, stepq_off, scratch_bytes;
 };
 
 int validate(const apex_replay_config_t *c)
@@ -131,7 +132,8 @@ int geometry(const apex_replay_config_t *c, Geometry *g)
   g->tree_words = off;
 
   g->state_off = 0;
-  g->mass_off = 256;
+  g->ticket_off = 256;
+  g->mass_off = g->ticket_off + kTicketBytes;
   g->claim_off = g->mass_off + (uint64_t)APEX_MAX_SAMPLES_PER_CALL * 8;
   g->stepq_off = g->claim_off + round_up(P * 4, 256);
   g->scratch_bytes = g->stepq_off + (uint64_t)kStepSets * kStepMaxK * 8;
@@ -165,6 +167,7 @@ struct apex_replay {
   }
 
   DeviceState *state() const { return reinterpret_cast<DeviceState *>(scratch + geo.state_off); }
+  uint32_t *tickets() const { return reinterpret_cast<uint32_t *>(scratch + geo.ticket_off); }
   uint64_t *mass() const { return reinterpret_cast<uint64_t *>(scratch + geo.mass_off); }
   uint32_t *claim() const { return reinterpret_cast<uint32_t *>(scratch + geo.claim_off); }
   uint64_t *stepq(uint32_t set) const { return reinterpret_cast<uint64_t *>(scratch + geo.stepq_off) + (uint64_t)set * kStepMaxK; }
@@ -567,17 +570,25 @@ int apex_replay_add(apex_replay_t *r, uint64_t count, const void *obs, const voi
 
 namespace {
 
-// a.k samples of each of num_batches batches (with a.k_dev: at most a.k).
-int launch_draw(SampleArgs &a, uint32_t num_batches, hipStream_t stream)
+// Importance weights in a launch of their own.
+int launch_weights(const WeightArgs &wa, uint32_t num_batches, hipStream_t stream)
 {
-  a.k_div = make_fast_div(a.k);
-  sample_draw_kernel<<<dim3(blocks_for(a.k, 16), num_batches), dim3(256), 0, stream>>>(a);
+  batch_weights_kernel<<<dim3(num_batches, blocks_for(wa.k, 512)), dim3(256), 0, stream>>>(wa);
   return hip_failed(hipGetLastError()) ? APEX_ERR_HIP : APEX_OK;
 }
 
-int sample_begin_impl(apex_replay *r, uint32_t num_batches, uint32_t k, const uint64_t *rnd, uint64_t *key_out,
-                      uint32_t *slot_out, uint64_t *mass_out, void *act_out, float *ret_out, float *gacc_out,
-                      hipStream_t stream)
+// a.k samples of each of num_batches batches (with a.k_dev: at most a.k).
+int launch_sample(SampleArgs &a, uint32_t num_batches, hipStream_t stream)
+{
+  a.k_div = make_fast_div(a.k);
+  const uint32_t threads = sample_threads(a.k, a.weight_out != nullptr);
+  sample_kernel<<<dim3(blocks_for(a.k, threads / 16), num_batches), dim3(threads), 0, stream>>>(a);
+  return hip_failed(hipGetLastError()) ? APEX_ERR_HIP : APEX_OK;
+}
+
+// Checks, and the arguments of a draw with the small payload columns (no weights, no observation rows).
+int sample_args(apex_replay *r, uint32_t num_batches, uint32_t k, const uint64_t *rnd, uint64_t *key_out,
+                uint32_t *slot_out, uint64_t *mass_out, void *act_out, float *ret_out, float *gacc_out, SampleArgs *out)
 {
   if (!r || !num_batches || !k || !rnd || !slot_out || !mass_out) return APEX_ERR_INVALID_ARG;
   if (num_batches > APEX_MAX_BATCHES_PER_CALL || (uint64_t)num_batches * k > APEX_MAX_SAMPLES_PER_CALL)
@@ -585,7 +596,8 @@ int sample_begin_impl(apex_replay *r, uint32_t num_batches, uint32_t k, const ui
   const uint64_t size = r->tail - r->head;
   if (size < r->cfg.min_size_to_sample) return APEX_ERR_NOT_READY;
   if (size == 0) return APEX_ERR_EMPTY;
-  SampleArgs a{};
+  SampleArgs &a = *out;
+  a = SampleArgs{};
   a.tv = r->tv;
   a.st = r->state();
   a.k = k;
@@ -600,7 +612,41 @@ int sample_begin_impl(apex_replay *r, uint32_t num_batches, uint32_t k, const ui
   a.act_out = static_cast<uint8_t *>(act_out);
   a.ret_out = ret_out;
   a.gacc_out = gacc_out;
-  return launch_draw(a, num_batches, stream);
+  return APEX_OK;
+}
+
+int sample_begin_impl(apex_replay *r, uint32_t num_batches, uint32_t k, const uint64_t *rnd, uint64_t *key_out,
+                      uint32_t *slot_out, uint64_t *mass_out, void *act_out, float *ret_out, float *gacc_out,
+                      hipStream_t stream)
+{
+  SampleArgs a;
+  const int rc = sample_args(r, num_batches, k, rnd, key_out, slot_out, mass_out, act_out, ret_out, gacc_out, &a);
+  return rc != APEX_OK ? rc : launch_sample(a, num_batches, stream);
+}
+
+// Whether the rows' gather rides in the draw's launch: short rows do (the wave that has drawn a sample copies its row);
+// of long ones a workgroup per row moves more bytes per second (copy_rows_long_kernel).
+bool gather_in_draw(const apex_replay *r) { return r->cfg.obs_bytes <= kGatherInDrawBytes; }
+
+// apex_replay_sample for rows that gather_in_draw: one launch (two for the weights of very large batches).  claim: the
+// first pass of an update of all drawn keys rides along.
+int sample_in_one(apex_replay *r, uint32_t num_batches, uint32_t k, float beta, const uint64_t *rnd, uint64_t *key_out,
+                  uint32_t *slot_out, uint64_t *mass_out, float *weight_out, void *obs_out, void *act_out,
+                  float *ret_out, float *gacc_out, bool claim, hipStream_t stream)
+{
+  SampleArgs a;
+  const int rc = sample_args(r, num_batches, k, rnd, key_out, slot_out, mass_out, act_out, ret_out, gacc_out, &a);
+  if (rc != APEX_OK) return rc;
+  a.obs = r->obs();
+  a.obs_bytes = r->cfg.obs_bytes;
+  a.obs_out = static_cast<uint8_t *>(obs_out);
+  a.weight_out = k <= kWeightsInDrawMaxK ? weight_out : nullptr;
+  a.beta = beta;
+  a.ticket = r->tickets();
+  a.claim = claim ? r->claim() : nullptr;
+  const int rl = launch_sample(a, num_batches, stream);
+  return rl != APEX_OK || a.weight_out == weight_out ? rl
+                                                     : launch_weights(WeightArgs{mass_out, weight_out, k, beta}, num_batches, stream);
 }
 
 }  // namespace
@@ -655,8 +701,8 @@ int finish_impl(apex_replay *r, uint32_t num_batches, uint32_t k, float beta, co
     if (rc != APEX_OK) return rc;
   }
   if (jobs.wa.weight_out) {  // no gather, or short rows: the weights get a small launch of their own
-    batch_weights_kernel<<<dim3(num_batches, blocks_for(k, 512)), dim3(256), 0, stream>>>(jobs.wa);
-    APEX_HIP(hipGetLastError());
+    const int rc = launch_weights(jobs.wa, num_batches, stream);
+    if (rc != APEX_OK) return rc;
   }
   // whatever of the update no launch above has taken (a claim pass that has run leaves the second pass)
   if (m && (jobs.ua.m || !(m <= 1024 || hint)))
@@ -896,6 +942,9 @@ int apex_replay_sample(apex_replay_t *r, uint32_t num_batches, uint32_t k, float
                        float *ret_out, float *gacc_out, void *hip_stream)
 {
   if (!r || !(beta >= 0.0f) || !(beta <= 1.0f)) return APEX_ERR_INVALID_ARG;
+  if (!obs_out || gather_in_draw(r))
+    return sample_in_one(r, num_batches, k, beta, rnd, key_out, slot_out, r->mass(), weight_out, obs_out, act_out, ret_out,
+                         gacc_out, /*claim=*/false, static_cast<hipStream_t>(hip_stream));
   const int rc = apex_replay_sample_begin(r, num_batches, k, rnd, key_out, slot_out, r->mass(), act_out, ret_out,
                                           gacc_out, hip_stream);
   if (rc != APEX_OK) return rc;

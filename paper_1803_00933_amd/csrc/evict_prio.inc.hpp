@@ -236,23 +236,17 @@ __device__ __forceinline__ void pe_writeback_block(const PeView &v, PeState *__r
   if (nc && lane_id() == 0) atomic_add_u64(&st->base.n_clamped, nc);
 }
 
-// Everything that follows the draw of one batch of short rows whose new priorities are known, in one launch of
-// workgroups of 1024 lanes: workgroups [0, copy_blocks) gather the rows, the next one writes the importance
-// weights, the last one writes the batch's new priorities back (m = k <= 1024 pairs).
-template <typename Vec>
-__global__ __launch_bounds__(1024) void pe_finish_update_kernel(ShortCopyArgs c, uint32_t copy_blocks, WeightArgs wa,
-                                                                PeView v, PeState *__restrict__ st, uint32_t m,
-                                                                const uint32_t *__restrict__ slot,
+// What follows the draw and gather of one batch whose new priorities are known: one workgroup writes the importance
+// weights, another writes the batch's new priorities back (m = k <= 1024 pairs).
+__global__ __launch_bounds__(1024) void pe_finish_update_kernel(WeightArgs wa, PeView v, PeState *__restrict__ st,
+                                                                uint32_t m, const uint32_t *__restrict__ slot,
                                                                 const float *__restrict__ prio)
 {
   __shared__ uint64_t red[1024 / kWave];
-  const uint32_t blk = blockIdx.x;
-  if (blk < copy_blocks) {
-    copy_rows_short_block<Vec>(c, blk);
-  } else if (blk == copy_blocks && wa.weight_out) {
-    batch_weights(wa, 0, red);
-  } else if (blk == copy_blocks + 1) {
+  if (blockIdx.x == 0) {
     pe_writeback_block(v, st, m, slot, wa.mass, prio);
+  } else if (wa.weight_out) {
+    batch_weights(wa, 0, red);
   }
 }
 
@@ -401,7 +395,7 @@ struct PeGeometry {
   uint64_t obs_off, act_off, ret_off, gacc_off, storage_bytes;
   uint32_t nlev, exported_nlev, top_log2;  // as in Geometry
   uint64_t level_off[kMaxLevels], level_size[kMaxLevels], tree_words;  // of one tree; the second follows it
-  uint64_t state_off, mass_off, cand_off, pos_off, sums_off, gen_off, ring_off, claim_off, scratch_bytes;
+  uint64_t state_off, ticket_off, mass_off, cand_off, pos_off, sums_off, gen_off, ring_off, claim_off, scratch_bytes;
 };
 
 int pe_validate(const apex_pe_config_t *c)
@@ -440,7 +434,8 @@ int pe_geometry(const apex_pe_config_t *c, PeGeometry *g)
   g->tree_words = base.tree_words;
   const uint64_t P = c->max_slots;
   g->state_off = 0;
-  g->mass_off = 256;
+  g->ticket_off = 256;
+  g->mass_off = g->ticket_off + kTicketBytes;
   g->cand_off = g->mass_off + (uint64_t)APEX_PE_MAX_EVICT_PER_CALL * 8;  // also holds the masses of a sample call
   g->pos_off = g->cand_off + (uint64_t)APEX_PE_MAX_EVICT_PER_CALL * 4;
   g->sums_off = g->pos_off + (uint64_t)APEX_PE_MAX_EVICT_PER_CALL * 4;
@@ -471,6 +466,7 @@ struct apex_pe_replay {
   PeView v;
 
   PeState *state() const { return reinterpret_cast<PeState *>(scratch + geo.state_off); }
+  uint32_t *tickets() const { return reinterpret_cast<uint32_t *>(scratch + geo.ticket_off); }
   uint64_t *mass() const { return reinterpret_cast<uint64_t *>(scratch + geo.mass_off); }
   uint32_t *cand() const { return reinterpret_cast<uint32_t *>(scratch + geo.cand_off); }
   uint32_t *pos() const { return reinterpret_cast<uint32_t *>(scratch + geo.pos_off); }
@@ -538,12 +534,38 @@ int pe_enqueue_eviction(apex_pe_replay *r, uint64_t e, uint32_t rounds, const ui
   const uint32_t scan_blocks = blocks_for(e, kPeScanThreads);  // <= 1024 since e <= 2^20
   for (uint32_t rd = 0; rd < rounds; ++rd) {
     a.rnd = rnd + (uint64_t)rd * e;
-    APEX_TRY(launch_draw(a, 1, stream));
+    APEX_TRY(launch_sample(a, 1, stream));
     pe_flag_scan_kernel<<<dim3(scan_blocks), dim3(kPeScanThreads), 0, stream>>>(r->cand(), st, r->pos(), r->sums());
     pe_remove_kernel<<<dim3(scan_blocks), dim3(kPeScanThreads), 0, stream>>>(r->v, st, r->cand(), r->pos(), r->sums());
   }
   APEX_HIP(hipGetLastError());
   return APEX_OK;
+}
+
+// The arguments of a draw with the small payload columns.
+SampleArgs pe_sample_args(apex_pe_replay *r, uint32_t k, const uint64_t *rnd, uint64_t *key_out, uint32_t *slot_out,
+                          void *act_out, float *ret_out, float *gacc_out)
+{
+  SampleArgs a{};
+  a.tv = r->v.ts;
+  a.st = &r->state()->base;
+  a.k = k;
+  a.gen = r->v.gen;
+  a.rnd = rnd;
+  a.key_out = key_out;
+  a.slot_out = slot_out;
+  a.mass = r->mass();
+  a.act = r->act();
+  a.act_bytes = r->cfg.act_bytes;
+  a.ret = r->ret();
+  a.gacc = r->gacc();
+  a.act_out = static_cast<uint8_t *>(act_out);
+  a.ret_out = ret_out;
+  a.gacc_out = gacc_out;
+  a.obs = r->obs();
+  a.obs_bytes = r->cfg.obs_bytes;
+  a.ticket = r->tickets();
+  return a;
 }
 
 void pe_free(apex_pe_replay *r)
@@ -696,37 +718,23 @@ int apex_pe_sample(apex_pe_replay_t *r, uint32_t num_batches, uint32_t k, float 
     return APEX_ERR_TOO_LARGE;
   if (r->size() == 0) return APEX_ERR_EMPTY;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-  SampleArgs a{};
-  a.tv = r->v.ts;
-  a.st = &r->state()->base;
-  a.k = k;
-  a.k_dev = nullptr;
-  a.gen = r->v.gen;
-  a.rnd = rnd;
-  a.key_out = key_out;
-  a.slot_out = slot_out;
-  a.mass = r->mass();
-  a.act = r->act();
-  a.act_bytes = r->cfg.act_bytes;
-  a.ret = r->ret();
-  a.gacc = r->gacc();
-  a.act_out = static_cast<uint8_t *>(act_out);
-  a.ret_out = ret_out;
-  a.gacc_out = gacc_out;
-  APEX_TRY(launch_draw(a, num_batches, stream));
+  SampleArgs a = pe_sample_args(r, k, rnd, key_out, slot_out, act_out, ret_out, gacc_out);
   SideJobs jobs;
   jobs.wa = WeightArgs{r->mass(), weight_out, k, beta};
-  if (obs_out) {
+  const bool gather = obs_out && r->cfg.obs_bytes <= kGatherInDrawBytes;
+  if (gather) a.obs_out = static_cast<uint8_t *>(obs_out);
+  if ((gather || !obs_out) && k <= kWeightsInDrawMaxK) {
+    a.weight_out = weight_out;
+    a.beta = beta;
+    jobs.wa.weight_out = nullptr;
+  }
+  APEX_TRY(launch_sample(a, num_batches, stream));
+  if (obs_out && !gather) {
     const RowMap by_slot{slot_out, nullptr, 0, {}};
     const RowMap ident{nullptr, nullptr, 0, {}};
-    const int rc = launch_copy(r->obs(), by_slot, obs_out, ident, (uint64_t)num_batches * k, r->cfg.obs_bytes, stream, &jobs);
-    if (rc != APEX_OK) return rc;
+    APEX_TRY(launch_copy(r->obs(), by_slot, obs_out, ident, (uint64_t)num_batches * k, r->cfg.obs_bytes, stream, &jobs));
   }
-  if (jobs.wa.weight_out) {
-    batch_weights_kernel<<<dim3(num_batches, blocks_for(k, 512)), dim3(256), 0, stream>>>(jobs.wa);
-    APEX_HIP(hipGetLastError());
-  }
-  return APEX_OK;
+  return jobs.wa.weight_out ? launch_weights(jobs.wa, num_batches, stream) : APEX_OK;
 }
 
 int apex_pe_update_priorities(apex_pe_replay_t *r, uint64_t m, const uint64_t *key, const float *prio,
@@ -837,38 +845,12 @@ int apex_pe_sample_update(apex_pe_replay_t *r, uint32_t k, float beta, const uin
   if (obs_out && vpr > 256) return APEX_ERR_TOO_LARGE;  // long rows: apex_pe_sample + apex_pe_update_priorities
   if (r->size() == 0) return APEX_ERR_EMPTY;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-  SampleArgs a{};
-  a.tv = r->v.ts;
-  a.st = &r->state()->base;
-  a.k = k;
-  a.gen = r->v.gen;
-  a.rnd = rnd;
-  a.key_out = key_out;
-  a.slot_out = slot_out;
-  a.mass = r->mass();
-  a.act = r->act();
-  a.act_bytes = r->cfg.act_bytes;
-  a.ret = r->ret();
-  a.gacc = r->gacc();
-  a.act_out = static_cast<uint8_t *>(act_out);
-  a.ret_out = ret_out;
-  a.gacc_out = gacc_out;
-  APEX_TRY(launch_draw(a, 1, stream));
-  // gather, weights and the write-back of the batch just drawn: one launch
-  uint32_t lanes_log2 = 0;
-  while ((1u << lanes_log2) < vpr) ++lanes_log2;
-  const uint64_t rows_per_block = 1024u >> lanes_log2;
-  const uint32_t copy_blocks = obs_out ? (uint32_t)((k + rows_per_block - 1) / rows_per_block) : 0;
-  const ShortCopyArgs c{r->obs(), RowMap{slot_out, nullptr, 0, {}}, static_cast<uint8_t *>(obs_out), RowMap{nullptr, nullptr, 0, {}},
-                        k, vpr, lanes_log2, r->cfg.obs_bytes};
+  SampleArgs a = pe_sample_args(r, k, rnd, key_out, slot_out, act_out, ret_out, gacc_out);
+  a.obs_out = static_cast<uint8_t *>(obs_out);
+  APEX_TRY(launch_sample(a, 1, stream));
+  // weights and the write-back of the batch just drawn: one launch of two workgroups
   const WeightArgs wa{r->mass(), weight_out, k, beta};
-  const dim3 grid(copy_blocks + 2), block(1024);
-#define APEX_PE_FINISH(Vec) \
-  pe_finish_update_kernel<Vec><<<grid, block, 0, stream>>>(c, copy_blocks, wa, r->v, r->state(), k, slot_out, new_prio)
-  if (vb == 16) APEX_PE_FINISH(u32x4);
-  else if (vb == 4) APEX_PE_FINISH(uint32_t);
-  else APEX_PE_FINISH(uint8_t);
-#undef APEX_PE_FINISH
+  pe_finish_update_kernel<<<dim3(2), dim3(1024), 0, stream>>>(wa, r->v, r->state(), k, slot_out, new_prio);
   APEX_HIP(hipGetLastError());
   return APEX_OK;
 }

@@ -10,7 +10,7 @@
 //                  most kTopMax.  So the level a walk starts from always fits the registers of one wave
 //                  (8 nodes per lane).  Where every workgroup staged the whole top in LDS instead, a
 //                  draw of 4096 from 2^24 slots (4352 nodes) took 11.5 us, now 7.2; the learner steps on
-//                  2^18 slots (4096 nodes) 10.6 us per launch, now 9.4.  Not fewer nodes than that:
+//                  2^18 slots (4096 nodes) 10.6 us per launch, now 8.6.  Not fewer nodes than that:
 //                  every change of a mass is an atomic on every level, and atomics of different waves
 //                  on one address take about 10 ns one after the other.
 //   device state   head, tail, counters: read by the kernels, so the same launches can be replayed.
@@ -503,6 +503,13 @@ struct WeightArgs {
   float beta;
 };
 
+// fp32 with the library's own power routine (relative error below 1e-6 here): a double-precision pow would cost 70
+// registers per lane.
+__device__ __forceinline__ float batch_weight(uint64_t mass_min, uint64_t mass, float beta)
+{
+  return pow_fixed_sequence((float)mass_min / (float)mass, beta);
+}
+
 // part, nparts: the workgroup writes the weights of samples [part * k / nparts ...) of batch b only
 // (every part still finds the minimum over the whole batch).
 __device__ __forceinline__ void batch_weights(const WeightArgs &wa, uint32_t b, uint64_t *red, uint32_t part = 0,
@@ -511,18 +518,23 @@ __device__ __forceinline__ void batch_weights(const WeightArgs &wa, uint32_t b, 
   const uint32_t tid = threadIdx.x, nthr = blockDim.x, nwave = nthr / kWave;
   const uint64_t *bm = wa.mass + (uint64_t)b * wa.k;
   uint64_t mn = ~0ull;
-  for (uint32_t i = tid; i < wa.k; i += nthr) mn = bm[i] < mn ? bm[i] : mn;
+  for (uint32_t i0 = 0; i0 < wa.k; i0 += 8 * nthr) {  // eight loads in flight (one by one, 16,384 masses took 20 us)
+    uint64_t m[8];
+#pragma unroll
+    for (int t = 0; t < 8; ++t)
+      if (i0 + t * nthr < wa.k) m[t] = bm[min(i0 + t * nthr + tid, wa.k - 1)];
+#pragma unroll
+    for (int t = 0; t < 8; ++t)
+      if (i0 + t * nthr < wa.k) mn = m[t] < mn ? m[t] : mn;
+  }
   mn = wave_min(mn);
   if (lane_id() == 0) red[tid / kWave] = mn;
   __syncthreads();
   for (uint32_t w = 0; w < nwave; ++w) mn = red[w] < mn ? red[w] : mn;
-  // fp32 with the library's own power routine (relative error below 1e-6 here): a double-precision
-  // pow would cost this kernel 70 registers per lane and half of its occupancy
-  const float fmn = (float)mn;
   const uint32_t per = (wa.k + nparts - 1) / nparts;
   const uint32_t lo = min(part * per, wa.k), hi = min(lo + per, wa.k);
   for (uint32_t i = lo + tid; i < hi; i += nthr)
-    wa.weight_out[(uint64_t)b * wa.k + i] = pow_fixed_sequence(fmn / (float)bm[i], wa.beta);
+    wa.weight_out[(uint64_t)b * wa.k + i] = batch_weight(mn, bm[i], wa.beta);
 }
 
 constexpr int kLongCopyThreads = 1024;  // one workgroup of 16 waves per 28 KB frame stack
@@ -976,13 +988,28 @@ struct SampleArgs {
   uint64_t *key_out;         // [nb,k] or null
   uint32_t *slot_out;        // [nb,k]
   uint64_t *mass;            // [nb,k]: mass of each drawn transition, for the weights
-  // payload columns and their outputs (each output may be null); obs only where the draw gathers the rows itself
+  // payload columns and their outputs (each output may be null)
   const uint8_t *act;
   uint32_t act_bytes;
   const float *ret, *gacc;
   uint8_t *act_out;
   float *ret_out, *gacc_out;
+  const uint8_t *obs;
+  uint64_t obs_bytes;
+  uint8_t *obs_out;          // null: the rows are gathered by another launch (copy_rows_*)
+  float *weight_out;         // null: no weights, or written by another launch (batch_weights)
+  float beta;
+  uint32_t *ticket;          // with weight_out: one word per batch, kTicketStride words apart, 0 between launches
+  uint32_t *claim;           // not null: the first pass of an update of the drawn keys (update_claim_block) as well
 };
+
+constexpr uint32_t kTicketStride = 16;
+
+// Waits until every load (and store) that this wave has issued is through.
+__device__ __forceinline__ void wait_for_all_loads()
+{
+  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0); the other counters at their maxima (not waited for)
+}
 
 struct Drawn {
   uint64_t slot, mass;
@@ -1153,82 +1180,189 @@ __device__ __forceinline__ void row_descend(RowWalk &w, const uint64_t *lv, uint
   w.mass = __shfl(m, src, kWave);
 }
 
-// A few bytes by one 16-lane row: pieces of four bytes at any alignment, the last one overlapping the one before;
-// the first 256 bytes' loads go out together.
+// Rows at any alignment and of any length are copied in pieces of 16 bytes, the last one overlapping the one before it
+// (the hardware takes unaligned vector accesses; in units that the row length divides by, 5003-byte rows went byte by
+// byte).
 typedef uint32_t u32_any __attribute__((aligned(1)));
+typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(1)));
 
-__device__ __forceinline__ void copy_bytes_by_row(uint8_t *__restrict__ d, const uint8_t *__restrict__ s, uint32_t bytes)
+// An observation row by one 16-lane row of a wave.  Everything that the wave has issued before is through when the
+// first piece is stored.
+__device__ __forceinline__ void copy_row_by_16(uint8_t *__restrict__ d, const uint8_t *__restrict__ s, uint32_t bytes)
 {
+  constexpr int kUnroll = 8;  // pieces per lane in flight: 2 KB of the row
   const uint32_t gl = lane_id() & 15;
-  if (bytes < 4) {
-    if (gl < bytes) d[gl] = s[gl];
+  if (bytes < 16) {
+    const uint8_t t = s[min(gl, bytes - 1)];
+    wait_for_all_loads();
+    if (gl < bytes) d[gl] = t;
     return;
   }
-  const uint32_t n = (bytes + 3) / 4, last = bytes - 4;
-  for (uint32_t v0 = 0; v0 < n; v0 += 64) {
-    uint32_t t[4];
+  const uint32_t n = (bytes + 15) / 16, last = bytes - 16;
+  for (uint32_t v0 = 0; v0 < n; v0 += 16 * kUnroll) {
+    u32x4_any t[kUnroll];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) t[u] = *reinterpret_cast<const u32_any *>(s + min(4 * (v0 + 16 * u + gl), last));
+    for (int u = 0; u < kUnroll; ++u)
+      if (v0 + 16 * u < n) t[u] = *reinterpret_cast<const u32x4_any *>(s + min(16 * (v0 + 16 * u + gl), last));
+    wait_for_all_loads();
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
-      if (v0 + 16 * u < n) *reinterpret_cast<u32_any *>(d + min(4 * (v0 + 16 * u + gl), last)) = t[u];
+    for (int u = 0; u < kUnroll; ++u)
+      if (v0 + 16 * u < n) *reinterpret_cast<u32x4_any *>(d + min(16 * (v0 + 16 * u + gl), last)) = t[u];
   }
 }
 
-// Four consecutive samples of a batch per wave, no LDS and no barrier.
-__global__ __launch_bounds__(256) void sample_draw_kernel(SampleArgs a)
+constexpr uint32_t kGatherInDrawBytes = 4096;  // observation rows up to here can ride in the draw's launch
+
+// Most samples of a batch whose weights the draw's launch can write: its last workgroup writes them all (16,384 of them
+// took that launch 21.6 us instead of 8.2 without, where a launch of its own takes 5).
+constexpr uint32_t kWeightsInDrawMaxK = 4096;
+
+// Threads per workgroup.  16 samples (256 threads) spread the draws best over the chip; a batch of at most 32 goes into
+// one workgroup, whose waves agree on the smallest mass through LDS (32 samples: 5.7 instead of 6.5 us through tickets
+// and memory; with 64 the sixteen waves of the workgroup slow one another down, 8.8 us); a large one has fewer tickets to take and more threads for its weights with 32 (4096 samples: 10.9 us,
+// with 16 and with 64 samples per workgroup 17.6 and 13.0).
+__host__ __device__ inline uint32_t sample_threads(uint32_t k, bool weights)
 {
+  if (!weights) return 256;
+  return k <= 32 ? (k + 3) / 4 * kWave : k > 2048 ? 512 : 256;
+}
+
+// Four consecutive samples of a batch per wave: the walks, and with them whatever of replay.Sample the caller wants in
+// the same launch: the gather of short observation rows, the importance weights, the first pass of an update.
+// The weights need the smallest mass of the whole batch: every workgroup writes its masses through to memory (agent
+// scope), takes the batch's ticket, and the one with the last ticket reads all of them back and writes the batch's
+// weights.  Only these words cross between workgroups, so no cache has to be written back or invalidated for it.
+// Bound by a chain of round trips (top level, its eight nodes again, a row of children per level, the payload row, with
+// weights the ticket and the masses).  In one launch instead of two (draw; gather and weights): 16 x 512 rows of 64
+// bytes from 2^21 slots 6.2 + 3.8 -> 9.2 us, 4096 of 128 bytes from 2^24 7.2 + 7.4 -> 10.9, 256 of 268 bytes from 2^20
+// 6.0 + 3.1 -> 8.0, each with one launch (3 us on the host, 1 between two kernels) less.
+__global__ __launch_bounds__(1024) void sample_kernel(SampleArgs a)
+{
+  __shared__ uint64_t red[1024 / kWave];
+  __shared__ uint32_t sh_ticket;
   const TreeView &tv = a.tv;
   const uint32_t lane = lane_id(), gl = lane & 15, b = blockIdx.y;
-  const uint32_t j0 = (blockIdx.x * (256 / kWave) + threadIdx.x / kWave) * 4;
+  const uint32_t nthr = blockDim.x;
+  const uint32_t j0 = (blockIdx.x * (nthr / kWave) + threadIdx.x / kWave) * 4;
   const uint32_t k = a.k_dev ? (uint32_t)*a.k_dev : a.k;
-  if (j0 >= k) return;
   const uint32_t j = j0 + lane / 16;
-  const bool valid = j < k;  // a row without a sample repeats the batch's last one and writes nothing
-  const uint64_t o = (uint64_t)b * k + min(j, k - 1);
-  TopLevel top;
-  const uint64_t *const top_level = tv.level[tv.nlev - 1];
-  top.load(top_level, tv.n_top);
-  const uint64_t u = a.rnd[o];
-  const uint64_t head = a.st->head;
-  const uint64_t total = top.scan();
-  const uint64_t w = a.k_dev ? total / k : fast_div(total, a.k_div);  // stratum width
-  RowWalk walk;
-  walk.x = (uint64_t)min(j, k - 1) * w + __umul64hi(u, w);  // point inside stratum j
+  uint64_t my_mass = ~0ull;
+  if (j0 < k) {
+    const uint64_t o = (uint64_t)b * k + min(j, k - 1);  // a row without a sample repeats the last one and writes nothing
+    TopLevel top;
+    const uint64_t *const top_level = tv.level[tv.nlev - 1];
+    top.load(top_level, tv.n_top);
+    const uint64_t u = a.rnd[o];
+    const uint64_t head = a.st->head;
+    const uint64_t total = top.scan();
+    const uint64_t w = a.k_dev ? total / k : fast_div(total, a.k_div);  // stratum width
+    RowWalk walk;
+    walk.x = (uint64_t)min(j, k - 1) * w + __umul64hi(u, w);  // point inside stratum j
 
-  // top level: the lane that holds the node by a ballot per sample, then its eight nodes anew (they are in the
-  // first cache), as if they were the children of a node
-  uint32_t l = 0;
+    // top level: the lane that holds the node by a ballot per sample, then its eight nodes anew (they are in the
+    // first cache), as if they were the children of a node
+    uint32_t l = 0;
 #pragma unroll
-  for (int s = 0; s < 4; ++s) {
-    const uint32_t ls = __popcll(__ballot(top.before <= read_lane_u64(walk.x, 16 * s))) - 1;
-    l = lane / 16 == (uint32_t)s ? ls : l;
+    for (int s = 0; s < 4; ++s) {
+      const uint32_t ls = __popcll(__ballot(top.before <= read_lane_u64(walk.x, 16 * s))) - 1;
+      l = lane / 16 == (uint32_t)s ? ls : l;
+    }
+    walk.x -= __shfl(top.before, l, kWave);
+    walk.idx = l;
+    row_descend(walk, top_level, 3);
+    const uint64_t head_slot = ring_slot(tv, head);
+    uint32_t fl = tv.top_log2;
+    for (int lv = (int)tv.nlev - 2; lv >= 0; --lv) {
+      row_descend(walk, tv.level[lv], fl);
+      fl = kFanoutLog2;
+    }
+    if (j < k) {
+      const uint64_t slot = walk.idx;
+      my_mass = walk.mass;
+      if (gl == 0) {
+        __hip_atomic_store(a.mass + o, walk.mass, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        a.slot_out[o] = (uint32_t)slot;
+        if (a.claim) __hip_atomic_fetch_max(a.claim + slot, (uint32_t)o + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+      // the small columns' loads go out with those of the observation row: partial return, accumulated discount,
+      // generation, and the first 64 action bytes (four per lane; fewer than four in all: one per lane)
+      const uint8_t *const act = a.act + slot * a.act_bytes;
+      uint8_t *const act_out = a.act_out + o * a.act_bytes;
+      const bool whole_words = a.act_bytes >= 4;
+      const uint32_t act_last = a.act_bytes - (whole_words ? 4 : 1), act_at = min(whole_words ? 4 * gl : gl, act_last);
+      float col = 0.f;
+      uint32_t gen = 0, act_piece = 0;
+      const bool ret_lane = gl == 1 && a.ret_out, gacc_lane = gl == 2 && a.gacc_out;
+      if (ret_lane) col = a.ret[slot];
+      if (gacc_lane) col = a.gacc[slot];
+      if (gl == 0 && a.gen) gen = a.gen[slot];
+      if (a.act_out) {
+        if (whole_words) act_piece = *reinterpret_cast<const u32_any *>(act + act_at);
+        else act_piece = act[act_at];
+      }
+      if (a.obs_out) copy_row_by_16(a.obs_out + o * a.obs_bytes, a.obs + slot * a.obs_bytes, (uint32_t)a.obs_bytes);
+      else wait_for_all_loads();  // (either way: this wave's masses are in memory from here on)
+      if (a.act_out) {
+        if (whole_words) *reinterpret_cast<u32_any *>(act_out + act_at) = act_piece;
+        else act_out[act_at] = (uint8_t)act_piece;
+        for (uint32_t at = 64 + 4 * gl; at < a.act_bytes; at += 64) {
+          const uint32_t p = min(at, act_last);
+          *reinterpret_cast<u32_any *>(act_out + p) = *reinterpret_cast<const u32_any *>(act + p);
+        }
+      }
+      if (gl == 0 && a.key_out)
+        a.key_out[o] = a.gen ? ((uint64_t)gen << 32) | slot : ring_key(slot, head, head_slot, tv.P);
+      if (ret_lane) a.ret_out[o] = col;
+      if (gacc_lane) a.gacc_out[o] = col;
+    }
   }
-  walk.x -= __shfl(top.before, l, kWave);
-  walk.idx = l;
-  row_descend(walk, top_level, 3);
-  const uint64_t head_slot = ring_slot(tv, head);
-  uint32_t fl = tv.top_log2;
-  for (int lv = (int)tv.nlev - 2; lv >= 0; --lv) {
-    row_descend(walk, tv.level[lv], fl);
-    fl = kFanoutLog2;
+  if (!a.weight_out) return;
+
+  if (gridDim.x == 1) {  // the whole batch is here
+    const uint64_t wave_mn = wave_min(my_mass);
+    if (lane == 0) red[threadIdx.x / kWave] = wave_mn;
+    __syncthreads();
+    uint64_t mn = red[0];
+    for (uint32_t v = 1; v < nthr / kWave; ++v) mn = red[v] < mn ? red[v] : mn;
+    if (gl == 0 && j < k) a.weight_out[(uint64_t)b * k + j] = batch_weight(mn, my_mass, a.beta);
+    return;
   }
-  if (!valid) return;
-  const uint64_t slot = walk.idx;
-  float col = 0.f;
-  uint32_t gen = 0;
-  const bool ret_lane = gl == 1 && a.ret_out, gacc_lane = gl == 2 && a.gacc_out;
-  if (ret_lane) col = a.ret[slot];
-  if (gacc_lane) col = a.gacc[slot];
-  if (gl == 0 && a.gen) gen = a.gen[slot];
-  if (a.act_out) copy_bytes_by_row(a.act_out + o * a.act_bytes, a.act + slot * a.act_bytes, a.act_bytes);
-  if (gl == 0) {
-    a.slot_out[o] = (uint32_t)slot;
-    a.mass[o] = walk.mass;
-    if (a.key_out) a.key_out[o] = a.gen ? ((uint64_t)gen << 32) | slot : ring_key(slot, head, head_slot, tv.P);
+  __syncthreads();
+  uint32_t *const ticket = a.ticket + (uint64_t)b * kTicketStride;
+  if (threadIdx.x == 0) sh_ticket = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __syncthreads();
+  if (sh_ticket != gridDim.x - 1) return;
+  if (threadIdx.x == 0) *ticket = 0;
+  const uint64_t *const bm = a.mass + (uint64_t)b * k;
+  float *const bw = a.weight_out + (uint64_t)b * k;
+  constexpr int kHeld = 8;  // enough for kWeightsInDrawMaxK / 512
+  // kHeld masses per thread are on their way at a time; the first of them stay in registers between the two passes
+  uint64_t first[kHeld], mn = ~0ull;
+  for (uint32_t i0 = threadIdx.x; i0 < k; i0 += kHeld * nthr) {
+    uint64_t m[kHeld];
+#pragma unroll
+    for (int t = 0; t < kHeld; ++t)
+      m[t] = __hip_atomic_load(bm + min(i0 + t * nthr, k - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+    for (int t = 0; t < kHeld; ++t) {
+      mn = m[t] < mn ? m[t] : mn;
+      if (i0 == threadIdx.x) first[t] = m[t];
+    }
   }
-  if (ret_lane) a.ret_out[o] = col;
-  if (gacc_lane) a.gacc_out[o] = col;
+  mn = wave_min(mn);
+  if (lane == 0) red[threadIdx.x / kWave] = mn;
+  __syncthreads();
+  for (uint32_t v = 0; v < nthr / kWave; ++v) mn = red[v] < mn ? red[v] : mn;
+  for (uint32_t i0 = threadIdx.x; i0 < k; i0 += kHeld * nthr) {
+    uint64_t m[kHeld];
+#pragma unroll
+    for (int t = 0; t < kHeld; ++t)
+      m[t] = i0 == threadIdx.x ? first[t]
+                               : __hip_atomic_load(bm + min(i0 + t * nthr, k - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+    for (int t = 0; t < kHeld; ++t)
+      if (i0 + t * nthr < k) bw[i0 + t * nthr] = batch_weight(mn, m[t], a.beta);
+  }
 }
 
 // --------------------------------------------------------------------------------------------
@@ -1301,12 +1435,6 @@ struct StepArgs {
 };
 
 enum StepRider { kNoRider = 0, kRoundRides = 1, kLeavesRide = 2 };
-
-// Waits until every load (and store) that this wave has issued is through.
-__device__ __forceinline__ void wait_for_all_loads()
-{
-  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0); the other counters at their maxima (not waited for)
-}
 
 // Keeps a wave-uniform value in scalar registers from here on: the compiler would otherwise fetch a
 // kernel argument only where it is first used, behind a wait of its own.
@@ -1542,7 +1670,7 @@ __global__ __launch_bounds__(kThreads) void learner_step_kernel(StepArgs a)
     }
   }
   if (weigher) {
-    const float weight = pow_fixed_sequence((float)wave_min(mass_min) / (float)mass_mine, a.wa.beta);
+    const float weight = batch_weight(wave_min(mass_min), mass_mine, a.wa.beta);
     if (row * kWave + lane < a.k) a.wa.weight_out[row * kWave + lane] = weight;
   }
 

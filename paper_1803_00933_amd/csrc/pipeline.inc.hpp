@@ -272,6 +272,15 @@ int apex_pipeline_steps(apex_pipeline_t *p, uint32_t n, float beta, const uint64
       ++p->step;
       continue;
     }
+    if (gather_in_draw(p->r)) {
+      // short rows: draw, gather, weights (and the first pass of a large update) in one launch, then the update
+      const bool claim = new_prio && per > 1024;
+      APEX_TRY(sample_in_one(p->r, p->nb, p->k, beta, rnd + i * per, b.key, b.slot, b.mass, b.weight, b.obs, b.act,
+                             b.ret, b.gacc, claim, p->tree));
+      if (new_prio) APEX_TRY(launch_update(p->r, per, b.key, new_prio + i * per, p->tree, QSource{}, claim));
+      ++p->step;
+      continue;
+    }
     APEX_TRY(apex_replay_sample_begin(p->r, p->nb, p->k, rnd + i * per, b.key, b.slot, b.mass, b.act, b.ret, b.gacc,
                                       p->tree));
     // the gather of this batch, its weights, and the write-back of its priorities: one launch

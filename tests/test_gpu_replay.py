@@ -102,6 +102,33 @@ def test_tree_shapes_around_the_summit(P):
         sample_both(g, o, rng, 3, 64)
 
 
+@pytest.mark.parametrize("ob,ab,nb,k", [
+    (1, 1, 1, 32), (15, 3, 1, 33), (16, 4, 2, 31), (17, 5, 3, 64), (67 * 4, 21 * 4, 1, 256), (2048, 64, 1, 100),
+    (2049, 65, 2, 65), (4095, 130, 1, 200), (4096, 2, 1, 32), (4097, 7, 1, 40),       # row lengths and action bytes
+    (24, 4, 1, 2048), (24, 4, 1, 2049), (20, 4, 1, 4096), (20, 4, 2, 4097), (12, 8, 700, 3),  # batch sizes and counts
+])
+def test_sample_in_one_launch(ob, ab, nb, k):
+    """replay.Sample of short rows as one launch, at the edges of what its lanes and workgroups hold: rows and action
+    bytes around every width they are copied in, batches around the borders between one workgroup, several (tickets)
+    and a launch of their own for the weights.  Called twice in a row (the tickets are back at 0) and on the memory
+    with prioritized eviction too."""
+    from paper_1803_00933_amd import apex
+    rng = np.random.default_rng(ob * 7 + k)
+    g, o = make_pair(3000, 4000, ob, ab)
+    assert add_both(g, o, rng, 3000) == 0
+    for _ in range(2):
+        sample_both(g, o, rng, nb, k)
+    gp = apex.PeReplay(3000, 4000, ob, ab)
+    op = oracle.PrioritizedEvictionReplay(3000, 4000, ob, ab)
+    obs = rng.integers(0, 256, (2000, ob), dtype=np.uint8)
+    act = rng.integers(0, 256, (2000, ab), dtype=np.uint8)
+    ret, gacc, prio = (rng.random(2000).astype(F32) for _ in range(3))
+    assert op.add(prio, obs, act, ret, gacc)[0] == 0
+    assert gp.add(dev(prio), dev(obs), dev(act), dev(ret), dev(gacc)) == 0
+    for _ in range(2):
+        sample_both(gp, op, rng, nb, k)
+
+
 @pytest.mark.parametrize("P,C,ob,ab", [(5000, 4000, 48, 8), (3000, 2500, 4112, 4)])
 def test_add_with_payload_written_in_place(P, C, ob, ab):
     """A producer writes observations and actions of the coming keys straight into the ring (row
