@@ -143,8 +143,11 @@ def _ptr(t):
 
 
 def _stream(stream=None):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return s.cuda_stream
+    """Raw handle of `stream`, or of the current device's current stream (asked for without making the
+    torch.cuda.Stream object that current_stream() returns: 0.2 instead of 2.8 us, where a whole call takes 6)."""
+    if stream is not None:
+        return stream.cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def workspace_bytes(cfg: Config):
