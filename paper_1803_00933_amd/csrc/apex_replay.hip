@@ -179,8 +179,35 @@ struct apex_replay {
 
 namespace {
 
-// Copies nrows rows of row_bytes bytes; picks the widest vector the row size and the base
-// addresses allow and the long- or short-row kernel.
+// How rows of row_bytes bytes at addresses whose bits are or-ed into mis are moved (see Piece): in aligned 16-byte
+// pieces, in 16-byte pieces at any alignment, or, rows shorter than that, in aligned words or bytes.
+enum RowPieces { kPieces16, kPiecesAny, kPieces4, kPieces1 };
+
+RowPieces row_pieces(uintptr_t mis, uint64_t row_bytes)
+{
+  mis |= (uintptr_t)row_bytes;
+  if (row_bytes >= 16) return (mis & 15) == 0 ? kPieces16 : kPiecesAny;
+  return (mis & 3) == 0 ? kPieces4 : kPieces1;
+}
+
+uint64_t pieces_per_row(RowPieces rp, uint64_t row_bytes)
+{
+  return rp == kPieces1 ? row_bytes : rp == kPieces4 ? row_bytes / 4 : (row_bytes + 15) / 16;
+}
+
+// Calls f with the piece type that rp names.
+template <typename F>
+auto with_pieces(RowPieces rp, F f)
+{
+  switch (rp) {
+    case kPieces16: return f(Piece16{});
+    case kPiecesAny: return f(PieceAny{});
+    case kPieces4: return f(Piece4{});
+    default: return f(Piece1{});
+  }
+}
+
+// Copies nrows rows of row_bytes bytes with the long- or short-row kernel.
 // Side jobs a long-row copy can take along in leading workgroups (see copy_rows_long_kernel).
 // A field is cleared once a kernel has taken the job on; what is left needs launches of its own.
 struct SideJobs {
@@ -191,10 +218,9 @@ struct SideJobs {
 
 template <typename Vec>
 int launch_copy_t(const uint8_t *src, const RowMap &smap, uint8_t *dst, const RowMap &dmap, uint64_t nrows,
-                  uint64_t row_bytes, hipStream_t stream, SideJobs *jobs)
+                  uint64_t row_bytes, uint32_t vpr, hipStream_t stream, SideJobs *jobs)
 {
   constexpr int kUnroll = kLongCopyUnroll, kThreads = kLongCopyThreads;
-  const uint32_t vpr = (uint32_t)(row_bytes / sizeof(Vec));
   if (vpr > 256) {
     const uint32_t cpr = (vpr + kThreads * kUnroll - 1) / (kThreads * kUnroll);
     if (nrows * cpr > 0x7ffffff0ull) return APEX_ERR_TOO_LARGE;
@@ -267,23 +293,23 @@ int launch_copy(const void *src, const RowMap &smap, void *dst, const RowMap &dm
                 hipStream_t stream, SideJobs *jobs = nullptr)
 {
   if (nrows == 0) return APEX_OK;
-  const uintptr_t mis = (uintptr_t)src | (uintptr_t)dst | (uintptr_t)row_bytes;
-  const uint8_t *s = static_cast<const uint8_t *>(src);
-  uint8_t *d = static_cast<uint8_t *>(dst);
-  if ((mis & 15) == 0) return launch_copy_t<u32x4>(s, smap, d, dmap, nrows, row_bytes, stream, jobs);
-  if ((mis & 3) == 0) return launch_copy_t<uint32_t>(s, smap, d, dmap, nrows, row_bytes, stream, jobs);
-  return launch_copy_t<uint8_t>(s, smap, d, dmap, nrows, row_bytes, stream, jobs);
+  const RowPieces rp = row_pieces((uintptr_t)src | (uintptr_t)dst, row_bytes);
+  const uint32_t vpr = (uint32_t)pieces_per_row(rp, row_bytes);
+  return with_pieces(rp, [&](auto p) {
+    return launch_copy_t<decltype(p)>(static_cast<const uint8_t *>(src), smap, static_cast<uint8_t *>(dst), dmap, nrows,
+                                      row_bytes, vpr, stream, jobs);
+  });
 }
 
-// One launch of the fused learner step (see learner_step_kernel) for vectors of sizeof(Vec) bytes.
-// Steps whose rows are decoded on their way out (16-byte vectors; riders: none, or the masses of an add round).
+// One launch of the fused learner step (see learner_step_kernel).
+// Steps whose rows are decoded on their way out (aligned 16-byte pieces; riders: none, or the masses of an add round).
 void launch_step_codec(const StepArgs &a, uint32_t wgs, uint32_t threads, int rider, hipStream_t stream)
 {
   const dim3 grid(wgs), block(threads);
   if (rider == kLeavesRide)
-    learner_step_kernel<u32x4, kStepThreads, kStepUnroll, kLeavesRide, true><<<grid, block, 0, stream>>>(a);
+    learner_step_kernel<Piece16, kStepThreads, kStepUnroll, kLeavesRide, true><<<grid, block, 0, stream>>>(a);
   else
-    learner_step_kernel<u32x4, kStepThreads, kStepUnroll, kNoRider, true><<<grid, block, 0, stream>>>(a);
+    learner_step_kernel<Piece16, kStepThreads, kStepUnroll, kNoRider, true><<<grid, block, 0, stream>>>(a);
 }
 
 template <typename Vec>
@@ -301,13 +327,13 @@ void launch_step_t(const StepArgs &a, uint32_t wgs, uint32_t threads, int rider,
 // A small add round (observations of at most 1 KB per row) as one launch: n-step priorities, payload,
 // masses.  Same effect as apex_nstep_priorities + apex_replay_add.
 
-// Arguments of such a round for workgroups of `threads` lanes and vectors of vector_bytes bytes;
+// Arguments of such a round for workgroups of `threads` lanes and pieces of the kind rp;
 // *blocks: the workgroups it takes.
-int add_round_args(const apex_replay *r, const NstepArgs &ns, const void *obs, const void *act, uint32_t vector_bytes,
+int add_round_args(const apex_replay *r, const NstepArgs &ns, const void *obs, const void *act, RowPieces rp,
                    uint32_t threads, AddRoundArgs *out, uint32_t *blocks)
 {
   const uint64_t count = (uint64_t)ns.S * ns.T;
-  const uint32_t vpr = r->cfg.obs_bytes / vector_bytes;
+  const uint32_t vpr = (uint32_t)pieces_per_row(rp, r->cfg.obs_bytes);
   uint32_t lanes_log2 = 0;
   while ((1u << lanes_log2) < vpr && lanes_log2 < 6) ++lanes_log2;  // at most one wave per row
   const uint64_t rows_per_block = threads >> lanes_log2;
@@ -320,12 +346,11 @@ int add_round_args(const apex_replay *r, const NstepArgs &ns, const void *obs, c
   return APEX_OK;
 }
 
-// Whether a round can go that way, and the widest vector its rows allow (16, 4 or 1 bytes).
-bool add_round_small_fits(const apex_replay *r, const NstepArgs &ns, const void *obs, uint32_t *vector_bytes)
+// Whether a round can go that way, and how its rows are moved.
+bool add_round_small_fits(const apex_replay *r, const NstepArgs &ns, const void *obs, RowPieces *rp)
 {
   if (!obs || r->cfg.obs_bytes > 1024 || (uint64_t)ns.S * ns.T == 0) return false;
-  const uintptr_t mis = (uintptr_t)obs | (uintptr_t)r->obs() | (uintptr_t)r->cfg.obs_bytes;
-  *vector_bytes = (mis & 15) == 0 ? 16 : (mis & 3) == 0 ? 4 : 1;
+  *rp = row_pieces((uintptr_t)obs | (uintptr_t)r->obs(), r->cfg.obs_bytes);
   return true;
 }
 
@@ -342,17 +367,16 @@ int add_round_small(apex_replay *r, const NstepArgs &ns, const void *obs, const 
                     hipStream_t stream)
 {
   const uint64_t count = (uint64_t)ns.S * ns.T;
-  uint32_t vb = 0, blocks = 0;
-  if (!add_round_small_fits(r, ns, obs, &vb)) return APEX_ERR_NOT_READY;
+  RowPieces rp = kPieces1;
+  uint32_t blocks = 0;
+  if (!add_round_small_fits(r, ns, obs, &rp)) return APEX_ERR_NOT_READY;
   if ((r->tail - r->head) + count > r->cfg.max_slots) return APEX_ERR_FULL;
   const uint64_t second = r->second_words();
   AddRoundArgs a;
-  const int rc = add_round_args(r, ns, obs, act, vb, kAddRoundThreads, &a, &blocks);
+  const int rc = add_round_args(r, ns, obs, act, rp, kAddRoundThreads, &a, &blocks);
   if (rc != APEX_OK) return rc;
   const dim3 grid(blocks), block(kAddRoundThreads);
-  if (vb == 16) add_round_small_kernel<u32x4><<<grid, block, 0, stream>>>(a);
-  else if (vb == 4) add_round_small_kernel<uint32_t><<<grid, block, 0, stream>>>(a);
-  else add_round_small_kernel<uint8_t><<<grid, block, 0, stream>>>(a);
+  with_pieces(rp, [&](auto p) { add_round_small_kernel<decltype(p)><<<grid, block, 0, stream>>>(a); });
   APEX_HIP(hipGetLastError());
   add_round_published(r, count, second, first_key_out);
   return APEX_OK;
@@ -369,10 +393,8 @@ struct PayloadRing {
 
 template <typename Vec>
 int add_payload_short_t(const PayloadRing &pr, uint64_t count, const void *obs, const void *act, const float *ret,
-                        const float *gacc, const RowMap &to, hipStream_t stream)
+                        const float *gacc, const RowMap &to, uint32_t vpr, hipStream_t stream)
 {
-  const uint32_t vpr = (uint32_t)(pr.obs_bytes / sizeof(Vec));
-  if (vpr > 256) return APEX_ERR_NOT_READY;
   uint32_t lanes_log2 = 0;
   while ((1u << lanes_log2) < vpr) ++lanes_log2;
   const uint64_t rows_per_block = 256u >> lanes_log2;
@@ -387,10 +409,12 @@ int add_payload_short_t(const PayloadRing &pr, uint64_t count, const void *obs, 
 int add_payload_short(const PayloadRing &pr, uint64_t count, const void *obs, const void *act, const float *ret,
                       const float *gacc, const RowMap &to, hipStream_t stream)
 {
-  const uintptr_t mis = (uintptr_t)obs | (uintptr_t)pr.obs | (uintptr_t)pr.obs_bytes;
-  if ((mis & 15) == 0) return add_payload_short_t<u32x4>(pr, count, obs, act, ret, gacc, to, stream);
-  if ((mis & 3) == 0) return add_payload_short_t<uint32_t>(pr, count, obs, act, ret, gacc, to, stream);
-  return add_payload_short_t<uint8_t>(pr, count, obs, act, ret, gacc, to, stream);
+  const RowPieces rp = row_pieces((uintptr_t)obs | (uintptr_t)pr.obs, pr.obs_bytes);
+  const uint64_t vpr = pieces_per_row(rp, pr.obs_bytes);
+  if (vpr > 256) return APEX_ERR_NOT_READY;
+  return with_pieces(rp, [&](auto p) {
+    return add_payload_short_t<decltype(p)>(pr, count, obs, act, ret, gacc, to, (uint32_t)vpr, stream);
+  });
 }
 
 // The three small columns (action bytes, partial return, accumulated discount) in one launch:
@@ -403,7 +427,7 @@ int add_small_columns(const PayloadRing &pr, uint64_t count, const void *act, co
   const uint64_t rows_per_block = 256u >> lanes_log2;
   const uint64_t blocks = (count + rows_per_block - 1) / rows_per_block;
   if (blocks > 0x7fffffffull) return APEX_ERR_TOO_LARGE;
-  add_payload_short_kernel<uint8_t><<<dim3((uint32_t)blocks), dim3(256), 0, stream>>>(
+  add_payload_short_kernel<Piece1><<<dim3((uint32_t)blocks), dim3(256), 0, stream>>>(
       nullptr, static_cast<const uint8_t *>(act), ret, gacc, pr.obs, pr.act, pr.ret, pr.gacc, to, count,
       /*vecs_per_row=*/0, lanes_log2, pr.obs_bytes, pr.act_bytes);
   return hip_failed(hipGetLastError()) ? APEX_ERR_HIP : APEX_OK;
@@ -715,12 +739,12 @@ int finish_impl(apex_replay *r, uint32_t num_batches, uint32_t k, float beta, co
 // learner_step_kernel.  Batch i goes to sets[(first_set + i) % depth]; kernel i reads the sets of
 // batches i-1 and i and writes that of batch i+1, hence depth >= 3.
 // Returns APEX_ERR_NOT_READY - with nothing enqueued - when the shapes do not fit the fused launch.
-// The widest vector that the rows of the ring and of the batch buffers allow: 16, 4 or 1 bytes.
-uint32_t step_vector_bytes(const apex_replay *r, uint32_t depth, const apex_batch_buffers_t *sets)
+// How the rows of the ring and of the batch buffers are moved.
+RowPieces step_pieces(const apex_replay *r, uint32_t depth, const apex_batch_buffers_t *sets)
 {
-  uintptr_t mis = (uintptr_t)r->obs() | (uintptr_t)r->cfg.obs_bytes;
+  uintptr_t mis = (uintptr_t)r->obs();
   for (uint32_t i = 0; i < depth; ++i) mis |= (uintptr_t)sets[i].obs;
-  return (mis & 15) == 0 ? 16 : (mis & 3) == 0 ? 4 : 1;
+  return row_pieces(mis, r->cfg.obs_bytes);
 }
 
 bool fused_steps_fit(const apex_replay *r, uint32_t num_batches, uint32_t k, uint32_t depth,
@@ -732,16 +756,14 @@ bool fused_steps_fit(const apex_replay *r, uint32_t num_batches, uint32_t k, uin
   return true;
 }
 
-void launch_step(const StepArgs &args, uint32_t vector_bytes, uint32_t wgs, uint32_t threads, hipStream_t stream,
+void launch_step(const StepArgs &args, RowPieces rp, uint32_t wgs, uint32_t threads, hipStream_t stream,
                  int rider = kNoRider)
 {
   StepArgs a = args;
   a.next_top = a.next.tv.level[a.next.tv.nlev - 1];
   a.next_k_div = make_fast_div(a.next.k);
   if (a.codec.raw_bytes && a.slot) return launch_step_codec(a, wgs, threads, rider, stream);
-  if (vector_bytes == 16) launch_step_t<u32x4>(a, wgs, threads, rider, stream);
-  else if (vector_bytes == 4) launch_step_t<uint32_t>(a, wgs, threads, rider, stream);
-  else launch_step_t<uint8_t>(a, wgs, threads, rider, stream);
+  with_pieces(rp, [&](auto p) { launch_step_t<decltype(p)>(a, wgs, threads, rider, stream); });
 }
 
 // A step launch that has been prepared but not issued: the last one of a call, held back while a small
@@ -749,33 +771,34 @@ void launch_step(const StepArgs &args, uint32_t vector_bytes, uint32_t wgs, uint
 struct HeldStep {
   bool valid = false;
   StepArgs a;
-  uint32_t vector_bytes;
+  RowPieces rp;
 };
 
 int issue_held_step(HeldStep *h, hipStream_t stream)
 {
   if (!h->valid) return APEX_OK;
   h->valid = false;
-  launch_step(h->a, h->vector_bytes, h->a.k, kStepThreads, stream);
+  launch_step(h->a, h->rp, h->a.k, kStepThreads, stream);
   APEX_HIP(hipGetLastError());
   return APEX_OK;
 }
 
 // The held step and a small add round in one launch.  APEX_ERR_NOT_READY - with nothing enqueued - if
-// there is no held step or the two do not fit together (the round's rows allow only narrower vectors).
+// there is no held step or the two do not fit together (the round's rows allow only narrower pieces).
 int issue_held_step_with_round(apex_replay *r, HeldStep *h, const NstepArgs &ns, const void *obs, const void *act,
                                uint64_t *first_key_out, hipStream_t stream)
 {
   const uint64_t count = (uint64_t)ns.S * ns.T;
-  uint32_t vb = 0, blocks = 0;
-  if (!h->valid || h->a.codec.raw_bytes || !add_round_small_fits(r, ns, obs, &vb) || vb < h->vector_bytes)
+  RowPieces rp = kPieces1;
+  uint32_t blocks = 0;
+  if (!h->valid || h->a.codec.raw_bytes || !add_round_small_fits(r, ns, obs, &rp) || rp > h->rp)
     return APEX_ERR_NOT_READY;
   if ((r->tail - r->head) + count > r->cfg.max_slots) return APEX_ERR_FULL;
   const uint64_t second = r->second_words();
-  const int rc = add_round_args(r, ns, obs, act, h->vector_bytes, kStepThreads, &h->a.add, &blocks);
+  const int rc = add_round_args(r, ns, obs, act, h->rp, kStepThreads, &h->a.add, &blocks);
   if (rc != APEX_OK) return rc;
   h->valid = false;
-  launch_step(h->a, h->vector_bytes, h->a.k + blocks, kStepThreads, stream, kRoundRides);
+  launch_step(h->a, h->rp, h->a.k + blocks, kStepThreads, stream, kRoundRides);
   APEX_HIP(hipGetLastError());
   add_round_published(r, count, second, first_key_out);
   return APEX_OK;
@@ -791,7 +814,7 @@ int issue_held_step_with_leaves(apex_replay *r, HeldStep *h, uint64_t count, con
   const uint64_t second = r->second_words();
   h->a.leaves = AddLeavesArgs{r->tv, second, r->state(), count, prio, r->qp};
   h->valid = false;
-  launch_step(h->a, h->vector_bytes, h->a.k + blocks_for(count, kStepThreads), kStepThreads, stream, kLeavesRide);
+  launch_step(h->a, h->rp, h->a.k + blocks_for(count, kStepThreads), kStepThreads, stream, kLeavesRide);
   APEX_HIP(hipGetLastError());
   add_round_published(r, count, second, first_key_out);
   return APEX_OK;
@@ -809,7 +832,7 @@ int fused_steps(apex_replay *r, uint32_t n, uint32_t k, float beta, const uint64
   const auto idx = [&](uint32_t i) { return (first_set + i) % depth; };
   const auto set = [&](uint32_t i) -> const apex_batch_buffers_t & { return sets[idx(i)]; };
   const apex_batch_buffers_t &b0 = set(0);
-  const uint32_t vb = step_vector_bytes(r, depth, sets);
+  const RowPieces rp = step_pieces(r, depth, sets);
   if (new_prio) {
     // Launch i reads one copy of the tree and writes the other; the first draw is launch "-1" of that
     // scheme (it reads the first copy and writes the first batch's changes into the second), so both
@@ -830,7 +853,7 @@ int fused_steps(apex_replay *r, uint32_t n, uint32_t k, float beta, const uint64
     a.next.mass = b0.mass;
     a.next_prio = new_prio;
     a.next_dq = r->stepq(idx(0));
-    launch_step(a, vb, k, kWave, stream);
+    launch_step(a, rp, k, kWave, stream);
     APEX_HIP(hipGetLastError());
   } else {
     const int rc = sample_begin_impl(r, 1, k, rnd, b0.key, b0.slot, b0.mass, nullptr, nullptr, nullptr, stream);
@@ -844,7 +867,7 @@ int fused_steps(apex_replay *r, uint32_t n, uint32_t k, float beta, const uint64
     a.src = r->obs();
     a.dst = static_cast<uint8_t *>(b.obs);
     a.row_bytes = r->cfg.obs_bytes;
-    a.vecs_per_row = (uint32_t)(a.row_bytes / vb);
+    a.vecs_per_row = (uint32_t)pieces_per_row(rp, a.row_bytes);
     if (codec_raw_bytes) {  // rows decoded on their way out: the set's obs buffer is [k, raw bytes]
       a.codec = codec_shape(codec_raw_bytes);
       a.vecs_per_row = codec_raw_bytes / 16;
@@ -881,9 +904,9 @@ int fused_steps(apex_replay *r, uint32_t n, uint32_t k, float beta, const uint64
     if (hold && i + 1 == n) {  // issued by the caller's next call, perhaps together with an add round
       hold->valid = true;
       hold->a = a;
-      hold->vector_bytes = vb;
+      hold->rp = rp;
     } else {
-      launch_step(a, vb, k, kStepThreads, stream);
+      launch_step(a, rp, k, kStepThreads, stream);
     }
   }
   // (every change has now been applied to both copies)

@@ -73,7 +73,7 @@ __global__ __launch_bounds__(256) void pe_add_kernel(PeView v, PeState *__restri
 // transitions together (add_runs_to_ancestors).  act, ret, gacc may be null.
 constexpr uint32_t kPeAddThreads = 1024;
 
-template <typename Vec>
+template <typename P>
 __global__ __launch_bounds__(kPeAddThreads) void pe_add_rows_kernel(PeView v, PeState *__restrict__ st, uint64_t count,
                                                                     NstepArgs ns, const float *__restrict__ prio,
                                                                     const uint8_t *__restrict__ obs,
@@ -96,7 +96,7 @@ __global__ __launch_bounds__(kPeAddThreads) void pe_add_rows_kernel(PeView v, Pe
   if (i < count) {
     const uint64_t slot = v.free_ring[ring_slot(v.ts, st->free_head + i)];
     if (vv < vecs_per_row)
-      reinterpret_cast<Vec *>(obs_ring + slot * obs_bytes)[vv] = reinterpret_cast<const Vec *>(obs + i * obs_bytes)[vv];
+      store_piece<P>(obs_ring + slot * obs_bytes, vv, obs_bytes, load_piece<P>(obs + i * obs_bytes, vv, obs_bytes));
     if (act)
       for (uint32_t by = vv; by < act_bytes; by += lanes) act_ring[slot * act_bytes + by] = act[i * act_bytes + by];
     if (vv == 0) {
@@ -568,6 +568,14 @@ SampleArgs pe_sample_args(apex_pe_replay *r, uint32_t k, const uint64_t *rnd, ui
   return a;
 }
 
+// The fused calls take rows of at most 256 of the widest aligned units (16, 4 or 1 bytes) that the row length and both
+// addresses divide by: a limit of the interface.
+bool pe_rows_too_long(const apex_pe_replay *r, const void *rows)
+{
+  const uintptr_t mis = (uintptr_t)rows | (uintptr_t)r->obs() | (uintptr_t)r->cfg.obs_bytes;
+  return r->cfg.obs_bytes / ((mis & 15) == 0 ? 16 : (mis & 3) == 0 ? 4 : 1) > 256;
+}
+
 void pe_free(apex_pe_replay *r)
 {
   if (r->snap_ev) (void)hipEventDestroy(r->snap_ev);
@@ -680,9 +688,8 @@ int apex_pe_add(apex_pe_replay_t *r, uint64_t count, const void *obs, const void
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   const RowMap freed{r->v.free_ring, &r->state()->free_head, r->cfg.max_slots, r->v.ts.p_div};  // the next free slots, in order
   const PayloadRing pr{r->obs(), r->act(), r->ret(), r->gacc(), r->cfg.obs_bytes, r->cfg.act_bytes};
-  const uintptr_t mis = (uintptr_t)obs | (uintptr_t)r->obs() | (uintptr_t)r->cfg.obs_bytes;
-  const uint32_t vb = (mis & 15) == 0 ? 16 : (mis & 3) == 0 ? 4 : 1;
-  const uint32_t vpr = r->cfg.obs_bytes / vb;
+  const RowPieces rp = row_pieces((uintptr_t)obs | (uintptr_t)r->obs(), r->cfg.obs_bytes);
+  const uint32_t vpr = (uint32_t)pieces_per_row(rp, r->cfg.obs_bytes);
   if (obs && vpr <= 256) {  // short rows: payload and masses in one launch
     uint32_t lanes_log2 = 0;
     while ((1u << lanes_log2) < vpr) ++lanes_log2;
@@ -691,14 +698,11 @@ int apex_pe_add(apex_pe_replay_t *r, uint64_t count, const void *obs, const void
     if (blocks > 0x7fffffffull) return APEX_ERR_TOO_LARGE;
     const dim3 grid((uint32_t)blocks), block(kPeAddThreads);
     const uint8_t *o8 = static_cast<const uint8_t *>(obs), *a8 = static_cast<const uint8_t *>(act);
-#define APEX_PE_ADD_SHORT(Vec)                                                                                        \
-  pe_add_rows_kernel<Vec><<<grid, block, 0, stream>>>(r->v, r->state(), count, NstepArgs{}, prio, o8, a8, ret, gacc,   \
-                                                      pr.obs, pr.act, pr.ret, pr.gacc, vpr, lanes_log2, pr.obs_bytes, \
-                                                      pr.act_bytes)
-    if (vb == 16) APEX_PE_ADD_SHORT(u32x4);
-    else if (vb == 4) APEX_PE_ADD_SHORT(uint32_t);
-    else APEX_PE_ADD_SHORT(uint8_t);
-#undef APEX_PE_ADD_SHORT
+    with_pieces(rp, [&](auto p) {
+      pe_add_rows_kernel<decltype(p)><<<grid, block, 0, stream>>>(r->v, r->state(), count, NstepArgs{}, prio, o8, a8, ret,
+                                                                  gacc, pr.obs, pr.act, pr.ret, pr.gacc, vpr, lanes_log2,
+                                                                  pr.obs_bytes, pr.act_bytes);
+    });
   } else {
     const int rc = add_payload_rows(pr, count, obs, act, ret, gacc, freed, stream);
     if (rc != APEX_OK) return rc;
@@ -805,10 +809,9 @@ int apex_pe_add_round(apex_pe_replay_t *r, uint32_t S, uint32_t T, uint32_t n, u
     return APEX_ERR_INVALID_ARG;
   const uint64_t count = (uint64_t)S * T;
   if ((uint64_t)T + n > 0xffffffffull) return APEX_ERR_TOO_LARGE;
-  const uintptr_t mis = (uintptr_t)obs | (uintptr_t)r->obs() | (uintptr_t)r->cfg.obs_bytes;
-  const uint32_t vb = (mis & 15) == 0 ? 16 : (mis & 3) == 0 ? 4 : 1;
-  const uint32_t vpr = r->cfg.obs_bytes / vb;
-  if (vpr > 256) return APEX_ERR_TOO_LARGE;  // long rows: apex_nstep_priorities + apex_pe_add
+  if (pe_rows_too_long(r, obs)) return APEX_ERR_TOO_LARGE;  // apex_nstep_priorities + apex_pe_add take them
+  const RowPieces rp = row_pieces((uintptr_t)obs | (uintptr_t)r->obs(), r->cfg.obs_bytes);
+  const uint32_t vpr = (uint32_t)pieces_per_row(rp, r->cfg.obs_bytes);
   APEX_TRY(pe_check_room(r, count));
   uint32_t lanes_log2 = 0;
   while ((1u << lanes_log2) < vpr) ++lanes_log2;
@@ -819,14 +822,11 @@ int apex_pe_add_round(apex_pe_replay_t *r, uint32_t S, uint32_t T, uint32_t n, u
   const NstepArgs ns{S, T, n, A, q_online, q_target, action, reward, discount};
   const dim3 grid((uint32_t)blocks), block(kPeAddThreads);
   const uint8_t *o8 = static_cast<const uint8_t *>(obs), *a8 = static_cast<const uint8_t *>(act);
-#define APEX_PE_ADD_ROUND(Vec)                                                                                          \
-  pe_add_rows_kernel<Vec><<<grid, block, 0, stream>>>(r->v, r->state(), count, ns, nullptr, o8, a8, nullptr, nullptr,    \
-                                                      r->obs(), r->act(), r->ret(), r->gacc(), vpr, lanes_log2,         \
-                                                      r->cfg.obs_bytes, r->cfg.act_bytes)
-  if (vb == 16) APEX_PE_ADD_ROUND(u32x4);
-  else if (vb == 4) APEX_PE_ADD_ROUND(uint32_t);
-  else APEX_PE_ADD_ROUND(uint8_t);
-#undef APEX_PE_ADD_ROUND
+  with_pieces(rp, [&](auto p) {
+    pe_add_rows_kernel<decltype(p)><<<grid, block, 0, stream>>>(r->v, r->state(), count, ns, nullptr, o8, a8, nullptr,
+                                                                nullptr, r->obs(), r->act(), r->ret(), r->gacc(), vpr,
+                                                                lanes_log2, r->cfg.obs_bytes, r->cfg.act_bytes);
+  });
   APEX_HIP(hipGetLastError());
   r->inserted += count;
   return APEX_OK;
@@ -839,10 +839,7 @@ int apex_pe_sample_update(apex_pe_replay_t *r, uint32_t k, float beta, const uin
   if (!r || !k || !rnd || !new_prio || !key_out || !slot_out || !(beta >= 0.0f) || !(beta <= 1.0f))
     return APEX_ERR_INVALID_ARG;
   if (k > 1024) return APEX_ERR_TOO_LARGE;
-  const uintptr_t mis = (uintptr_t)obs_out | (uintptr_t)r->obs() | (uintptr_t)r->cfg.obs_bytes;
-  const uint32_t vb = (mis & 15) == 0 ? 16 : (mis & 3) == 0 ? 4 : 1;
-  const uint32_t vpr = r->cfg.obs_bytes / vb;
-  if (obs_out && vpr > 256) return APEX_ERR_TOO_LARGE;  // long rows: apex_pe_sample + apex_pe_update_priorities
+  if (obs_out && pe_rows_too_long(r, obs_out)) return APEX_ERR_TOO_LARGE;  // apex_pe_sample + apex_pe_update_priorities
   if (r->size() == 0) return APEX_ERR_EMPTY;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   SampleArgs a = pe_sample_args(r, k, rnd, key_out, slot_out, act_out, ret_out, gacc_out);

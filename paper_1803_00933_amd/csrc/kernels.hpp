@@ -271,6 +271,51 @@ __device__ __forceinline__ uint64_t map_row(const RowMap &m, uint64_t i)
 }
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32_any __attribute__((aligned(1)));
+typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(1)));
+
+// The pieces in which a kernel moves a row: Reg in registers, Mem in memory; piece v of a row of n bytes starts at
+// byte at(v, n), and a row has count(n) of them.
+template <typename Vec>
+struct Piece {  // whole pieces, all aligned
+  typedef Vec Reg;
+  typedef Vec Mem;
+  static constexpr bool kWhole = true;
+  static __device__ __forceinline__ uint64_t at(uint32_t v, uint64_t) { return (uint64_t)v * sizeof(Vec); }
+};
+// Rows of at least 16 bytes at any alignment and of any length: pieces of 16 bytes, the last one overlapping the one
+// before it (both carry the same bytes there).  The hardware takes unaligned vector accesses; in the widest units that
+// length and addresses divide by, rows of odd lengths went byte by byte (999 rows of 5003 bytes: 11.4 us, now 6.1).
+struct PieceAny {
+  typedef u32x4 Reg;
+  typedef u32x4_any Mem;
+  static constexpr bool kWhole = false;
+  static __device__ __forceinline__ uint64_t at(uint32_t v, uint64_t n) { return min((uint64_t)v * 16, n - 16); }
+};
+typedef Piece<u32x4> Piece16;
+typedef Piece<uint32_t> Piece4;
+typedef Piece<uint8_t> Piece1;
+
+template <typename P>
+__device__ __forceinline__ typename P::Reg load_piece(const uint8_t *row, uint32_t v, uint64_t n)
+{
+  return *reinterpret_cast<const typename P::Mem *>(row + P::at(v, n));
+}
+template <typename P>
+__device__ __forceinline__ typename P::Reg load_piece_streaming(const uint8_t *row, uint32_t v, uint64_t n)
+{
+  return __builtin_nontemporal_load(reinterpret_cast<const typename P::Mem *>(row + P::at(v, n)));
+}
+template <typename P>
+__device__ __forceinline__ void store_piece(uint8_t *row, uint32_t v, uint64_t n, typename P::Reg x)
+{
+  *reinterpret_cast<typename P::Mem *>(row + P::at(v, n)) = x;
+}
+template <typename P>
+__device__ __forceinline__ void store_piece_streaming(uint8_t *row, uint32_t v, uint64_t n, typename P::Reg x)
+{
+  __builtin_nontemporal_store(x, reinterpret_cast<typename P::Mem *>(row + P::at(v, n)));
+}
 
 // --------------------------------------------------------------------------------------------
 // Observations stored through the block codec (Section 4.1: observations are kept compressed in the
@@ -560,7 +605,7 @@ __global__ __launch_bounds__(256) void batch_weights_kernel(WeightArgs wa)
 //                over the whole chip;
 //   kWeights     the first weight_blocks workgroups (after workgroup 0 if kUpdate = 1) write one
 //                batch's importance weights each.
-template <typename Vec, int kUnroll, bool kWeights, int kUpdate>
+template <typename P, int kUnroll, bool kWeights, int kUpdate>
 __global__ __launch_bounds__(kLongCopyThreads) void copy_rows_long_kernel(const uint8_t *__restrict__ src, RowMap smap,
                                                                           uint8_t *__restrict__ dst, RowMap dmap,
                                                                           uint32_t vecs_per_row, uint32_t chunks_per_row,
@@ -570,14 +615,14 @@ __global__ __launch_bounds__(kLongCopyThreads) void copy_rows_long_kernel(const 
   const uint32_t blk = blockIdx.x;
   const uint32_t row = blk / chunks_per_row;
   const uint32_t chunk = blk - row * chunks_per_row;
-  const Vec *s = reinterpret_cast<const Vec *>(src + map_row(smap, row) * row_bytes);
-  Vec *d = reinterpret_cast<Vec *>(dst + map_row(dmap, row) * row_bytes);
+  const uint8_t *s = src + map_row(smap, row) * row_bytes;
+  uint8_t *d = dst + map_row(dmap, row) * row_bytes;
   const uint32_t v0 = chunk * (kUnroll * blockDim.x) + threadIdx.x;
-  Vec tmp[kUnroll];
+  typename P::Reg tmp[kUnroll];
 #pragma unroll
   for (int u = 0; u < kUnroll; ++u) {
     const uint32_t v = v0 + u * blockDim.x;
-    if (v < vecs_per_row) tmp[u] = __builtin_nontemporal_load(s + v);
+    if (v < vecs_per_row) tmp[u] = load_piece_streaming<P>(s, v, row_bytes);
   }
   // side-job loads go out behind the row loads; the row is stored as soon as it has arrived
   UpdateLane ul{};
@@ -596,7 +641,7 @@ __global__ __launch_bounds__(kLongCopyThreads) void copy_rows_long_kernel(const 
 #pragma unroll
   for (int u = 0; u < kUnroll; ++u) {
     const uint32_t v = v0 + u * blockDim.x;
-    if (v < vecs_per_row) __builtin_nontemporal_store(tmp[u], d + v);
+    if (v < vecs_per_row) store_piece_streaming<P>(d, v, row_bytes, tmp[u]);
   }
   if (kUpdate == 1) {
     __shared__ uint32_t h_slot[kDedupeSlots];
@@ -627,26 +672,30 @@ __global__ __launch_bounds__(kLongCopyThreads) void copy_rows_long_kernel(const 
 // boundaries, so that every lane carries a full load (a 28,224-byte row fills only 86 % of a workgroup's
 // 2048 vector slots); each vector finds its destination row by one division.  (For gathers, whose source
 // rows are looked up per row, one workgroup per row is faster.)
-template <typename Vec, int kUnroll>
+template <typename P, int kUnroll>
 __global__ __launch_bounds__(kLongCopyThreads) void copy_rows_dense_kernel(const uint8_t *__restrict__ src,
                                                                            uint8_t *__restrict__ dst, RowMap dmap,
                                                                            uint32_t vecs_per_row, uint64_t row_bytes,
                                                                            uint32_t total_vecs)
 {
   const uint32_t f0 = blockIdx.x * (kUnroll * blockDim.x) + threadIdx.x;
-  const Vec *s = reinterpret_cast<const Vec *>(src);
-  Vec tmp[kUnroll];
+  typename P::Reg tmp[kUnroll];
 #pragma unroll
   for (int u = 0; u < kUnroll; ++u) {
     const uint32_t f = f0 + u * blockDim.x;
-    if (f < total_vecs) tmp[u] = __builtin_nontemporal_load(s + f);
+    if constexpr (P::kWhole) {  // the source is one run of pieces
+      if (f < total_vecs) tmp[u] = load_piece_streaming<P>(src, f, 0);
+    } else {
+      const uint32_t row = f / vecs_per_row, v = f - row * vecs_per_row;
+      if (f < total_vecs) tmp[u] = load_piece_streaming<P>(src + row * row_bytes, v, row_bytes);
+    }
   }
 #pragma unroll
   for (int u = 0; u < kUnroll; ++u) {
     const uint32_t f = f0 + u * blockDim.x;
     if (f < total_vecs) {
       const uint32_t row = f / vecs_per_row, v = f - row * vecs_per_row;
-      __builtin_nontemporal_store(tmp[u], reinterpret_cast<Vec *>(dst + map_row(dmap, row) * row_bytes) + v);
+      store_piece_streaming<P>(dst + map_row(dmap, row) * row_bytes, v, row_bytes, tmp[u]);
     }
   }
 }
@@ -657,7 +706,7 @@ __global__ __launch_bounds__(kLongCopyThreads) void copy_rows_dense_kernel(const
 // each instead of copying.
 constexpr uint32_t kPackedRows = 10;  // rows longer than 256 vectors: 2048 / 257 + 2
 
-template <typename Vec, int kUnroll, bool kWeights>
+template <typename P, int kUnroll, bool kWeights>
 __global__ __launch_bounds__(kLongCopyThreads) void copy_rows_packed_kernel(const uint8_t *__restrict__ src, RowMap smap,
                                                                             uint8_t *__restrict__ dst, RowMap dmap,
                                                                             uint32_t nrows, uint32_t vecs_per_row,
@@ -678,7 +727,7 @@ __global__ __launch_bounds__(kLongCopyThreads) void copy_rows_packed_kernel(cons
     dst_off[threadIdx.x] = map_row(dmap, r0 + threadIdx.x) * row_bytes;
   }
   __syncthreads();
-  Vec tmp[kUnroll];
+  typename P::Reg tmp[kUnroll];
   uint32_t ri[kUnroll], v[kUnroll];
 #pragma unroll
   for (int u = 0; u < kUnroll; ++u) {
@@ -686,12 +735,12 @@ __global__ __launch_bounds__(kLongCopyThreads) void copy_rows_packed_kernel(cons
     const uint32_t row = f / vecs_per_row;
     ri[u] = row - r0;
     v[u] = f - row * vecs_per_row;
-    if (f < total_vecs) tmp[u] = __builtin_nontemporal_load(reinterpret_cast<const Vec *>(src + src_off[ri[u]]) + v[u]);
+    if (f < total_vecs) tmp[u] = load_piece_streaming<P>(src + src_off[ri[u]], v[u], row_bytes);
   }
 #pragma unroll
   for (int u = 0; u < kUnroll; ++u) {
     const uint32_t f = first + threadIdx.x + u * blockDim.x;
-    if (f < total_vecs) __builtin_nontemporal_store(tmp[u], reinterpret_cast<Vec *>(dst + dst_off[ri[u]]) + v[u]);
+    if (f < total_vecs) store_piece_streaming<P>(dst + dst_off[ri[u]], v[u], row_bytes, tmp[u]);
   }
 }
 
@@ -706,28 +755,27 @@ struct ShortCopyArgs {
   uint64_t row_bytes;
 };
 
-template <typename Vec>
+template <typename P>
 __device__ __forceinline__ void copy_rows_short_block(const ShortCopyArgs &c, uint32_t blk)
 {
   const uint32_t rows_per_block = blockDim.x >> c.lanes_log2;
   const uint64_t row = (uint64_t)blk * rows_per_block + (threadIdx.x >> c.lanes_log2);
   const uint32_t v = threadIdx.x & ((1u << c.lanes_log2) - 1);
   if (row >= c.nrows || v >= c.vecs_per_row) return;
-  const Vec *s = reinterpret_cast<const Vec *>(c.src + map_row(c.smap, row) * c.row_bytes);
-  Vec *d = reinterpret_cast<Vec *>(c.dst + map_row(c.dmap, row) * c.row_bytes);
-  d[v] = s[v];
+  const uint8_t *s = c.src + map_row(c.smap, row) * c.row_bytes;
+  store_piece<P>(c.dst + map_row(c.dmap, row) * c.row_bytes, v, c.row_bytes, load_piece<P>(s, v, c.row_bytes));
 }
 
-template <typename Vec>
+template <typename P>
 __global__ __launch_bounds__(256) void copy_rows_short_kernel(ShortCopyArgs c)
 {
-  copy_rows_short_block<Vec>(c, blockIdx.x);
+  copy_rows_short_block<P>(c, blockIdx.x);
 }
 
 // All four payload columns of an add round with short observation rows, in one launch: 2^lanes_log2
 // lanes per transition copy its observation, its action bytes, and (first lane) its partial
 // return and accumulated discount.  act, ret, gacc may be null.
-template <typename Vec>
+template <typename P>
 __global__ __launch_bounds__(256) void add_payload_short_kernel(const uint8_t *__restrict__ obs,
                                                                 const uint8_t *__restrict__ act,
                                                                 const float *__restrict__ ret,
@@ -746,7 +794,7 @@ __global__ __launch_bounds__(256) void add_payload_short_kernel(const uint8_t *_
   if (row >= nrows) return;
   const uint64_t to = map_row(dmap, row);
   if (v < vecs_per_row)
-    reinterpret_cast<Vec *>(obs_ring + to * obs_bytes)[v] = reinterpret_cast<const Vec *>(obs + row * obs_bytes)[v];
+    store_piece<P>(obs_ring + to * obs_bytes, v, obs_bytes, load_piece<P>(obs + row * obs_bytes, v, obs_bytes));
   if (act)
     for (uint32_t by = v; by < act_bytes; by += lanes) act_ring[to * act_bytes + by] = act[row * act_bytes + by];
   if (v == 0) {
@@ -820,7 +868,7 @@ struct AddRoundArgs {
 };
 
 // Workgroup blk of n_wgs of such a round; sh_slot, sh_q: blockDim words of LDS each.
-template <typename Vec>
+template <typename P>
 __device__ __forceinline__ void add_round_small_block(const AddRoundArgs &a, uint32_t blk, uint32_t n_wgs,
                                                       uint64_t *sh_slot, uint64_t *sh_q)
 {
@@ -835,8 +883,8 @@ __device__ __forceinline__ void add_round_small_block(const AddRoundArgs &a, uin
   if (in_range) {
     const uint64_t slot = ring_slot(a.tv, tail + i);
     for (uint32_t vv = v; vv < a.vecs_per_row; vv += lanes)
-      reinterpret_cast<Vec *>(a.obs_ring + slot * a.obs_bytes)[vv] =
-          reinterpret_cast<const Vec *>(a.obs + i * a.obs_bytes)[vv];
+      store_piece<P>(a.obs_ring + slot * a.obs_bytes, vv, a.obs_bytes,
+                     load_piece<P>(a.obs + i * a.obs_bytes, vv, a.obs_bytes));
     if (a.act)
       for (uint32_t by = v; by < a.act_bytes; by += lanes)
         a.act_ring[slot * a.act_bytes + by] = a.act[i * a.act_bytes + by];
@@ -862,11 +910,11 @@ __device__ __forceinline__ void add_round_small_block(const AddRoundArgs &a, uin
   advance_state(&a.st->ticket_add, &a.st->tail, tail + count, n_wgs);
 }
 
-template <typename Vec>
+template <typename P>
 __global__ __launch_bounds__(kAddRoundThreads) void add_round_small_kernel(AddRoundArgs a)
 {
   __shared__ uint64_t sh_slot[kAddRoundThreads], sh_q[kAddRoundThreads];
-  add_round_small_block<Vec>(a, blockIdx.x, gridDim.x, sh_slot, sh_q);
+  add_round_small_block<P>(a, blockIdx.x, gridDim.x, sh_slot, sh_q);
 }
 
 // evict: zero the masses of the e oldest keys and take them out of the upper levels
@@ -926,14 +974,14 @@ __global__ __launch_bounds__(256) void update_claim_kernel(ClaimArgs c) { update
 // Everything that only needs the results of a draw of short rows, in one launch: the gather of the rows,
 // the importance weights, and the first pass of a priority update of the drawn keys.  Workgroups
 // [0, copy_blocks) copy, the next batches * weight_parts write weights, the rest claim.
-template <typename Vec>
+template <typename P>
 __global__ __launch_bounds__(256) void finish_short_kernel(ShortCopyArgs c, uint32_t copy_blocks, WeightArgs wa,
                                                            uint32_t batches, uint32_t weight_parts, ClaimArgs cl)
 {
   __shared__ uint64_t red[256 / kWave];
   const uint32_t blk = blockIdx.x, weight_blocks = batches * weight_parts;
   if (blk < copy_blocks) {
-    copy_rows_short_block<Vec>(c, blk);
+    copy_rows_short_block<P>(c, blk);
   } else if (blk < copy_blocks + weight_blocks) {
     const uint32_t wb = blk - copy_blocks;
     batch_weights(wa, wb / weight_parts, red, wb % weight_parts, weight_parts);
@@ -1180,12 +1228,6 @@ __device__ __forceinline__ void row_descend(RowWalk &w, const uint64_t *lv, uint
   w.mass = __shfl(m, src, kWave);
 }
 
-// Rows at any alignment and of any length are copied in pieces of 16 bytes, the last one overlapping the one before it
-// (the hardware takes unaligned vector accesses; in units that the row length divides by, 5003-byte rows went byte by
-// byte).
-typedef uint32_t u32_any __attribute__((aligned(1)));
-typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(1)));
-
 // An observation row by one 16-lane row of a wave.  Everything that the wave has issued before is through when the
 // first piece is stored.
 __device__ __forceinline__ void copy_row_by_16(uint8_t *__restrict__ d, const uint8_t *__restrict__ s, uint32_t bytes)
@@ -1403,7 +1445,7 @@ struct StepArgs {
   // gather of batch i: row j of dst = row slot[j] of src; the small columns likewise
   const uint8_t *src;
   uint8_t *dst;
-  uint32_t vecs_per_row;  // vectors of sizeof(Vec) bytes
+  uint32_t vecs_per_row;  // pieces per row
   uint64_t row_bytes;
   const uint8_t *act;
   uint32_t act_bytes;
@@ -1528,15 +1570,15 @@ __device__ __forceinline__ void draw_in_first_wave(const StepArgs &a, uint32_t r
 //   wave 2       gathers the action bytes of the row
 //   wave 3       in the first ceil(k / 64) workgroups: importance weights of 64 samples
 // kRider: what the workgroups beyond the first k carry (StepArgs::add or ::leaves).
-// kCodec: the rows are decoded on their way out (StepArgs::codec; Vec is 16 bytes wide).
-template <typename Vec, int kThreads, int kUnroll, int kRider, bool kCodec = false>
+// kCodec: the rows are decoded on their way out (StepArgs::codec; the pieces are Piece16).
+template <typename P, int kThreads, int kUnroll, int kRider, bool kCodec = false>
 __global__ __launch_bounds__(kThreads) void learner_step_kernel(StepArgs a)
 {
   const uint32_t row = blockIdx.x, tid = threadIdx.x, nthr = blockDim.x;
   if constexpr (kRider == kRoundRides) {
     if (row >= a.k) {
       __shared__ uint64_t sh_slot[kThreads], sh_q[kThreads];
-      add_round_small_block<Vec>(a.add, row - a.k, gridDim.x - a.k, sh_slot, sh_q);
+      add_round_small_block<P>(a.add, row - a.k, gridDim.x - a.k, sh_slot, sh_q);
       return;
     }
   }
@@ -1597,19 +1639,20 @@ __global__ __launch_bounds__(kThreads) void learner_step_kernel(StepArgs a)
 
   // ---- the row
   const uint32_t copiers = nthr - first;
-  const Vec *s = reinterpret_cast<const Vec *>(a.src + (uint64_t)my_slot * a.row_bytes);
-  Vec *d = reinterpret_cast<Vec *>(a.dst + (uint64_t)row * (kCodec ? (uint64_t)a.codec.raw_bytes : a.row_bytes));
+  const uint64_t out_bytes = kCodec ? (uint64_t)a.codec.raw_bytes : a.row_bytes;
+  const uint8_t *s = a.src + (uint64_t)my_slot * a.row_bytes;
+  uint8_t *d = a.dst + (uint64_t)row * out_bytes;
   const uint32_t v_last = a.vecs_per_row - 1;
-  Vec tmp[kUnroll];
+  typename P::Reg tmp[kUnroll];
   CodecFetched fetched[kCodec ? kUnroll : 1] = {};
 #pragma unroll
   for (int u = 0; u < kUnroll; ++u) {
     const uint32_t v = min(tid - first + u * copiers, v_last);
     if constexpr (kCodec) {  // the pieces as the image holds them; mask and block bytes follow below
       fetched[u].data = __builtin_nontemporal_load(
-          reinterpret_cast<const u32x4 *>(reinterpret_cast<const uint8_t *>(s) + a.codec.image_off) + v);
+          reinterpret_cast<const u32x4 *>(s + a.codec.image_off) + v);
     } else {
-      tmp[u] = __builtin_nontemporal_load(s + v);
+      tmp[u] = load_piece_streaming<P>(s, v, a.row_bytes);
     }
   }
   if constexpr (kCodec) {
@@ -1618,7 +1661,7 @@ __global__ __launch_bounds__(kThreads) void learner_step_kernel(StepArgs a)
       const uint32_t v = tid - first + u * copiers, v_first = v - lane;  // the wave's 64 pieces start at v_first
       if (v_first < a.vecs_per_row) {  // the same for all lanes of the wave
         u32x4 bytes;
-        codec_fetch_wave_scalars(reinterpret_cast<const uint8_t *>(s), a.codec, v_first, &fetched[u].word, &bytes);
+        codec_fetch_wave_scalars(s, a.codec, v_first, &fetched[u].word, &bytes);
         fetched[u].byte = codec_wave_byte(bytes, lane);
         fetched[u].bit = (v / 4) & 63;
       }
@@ -1642,8 +1685,7 @@ __global__ __launch_bounds__(kThreads) void learner_step_kernel(StepArgs a)
   if constexpr (kCodec) {
 #pragma unroll
     for (int u = 0; u < kUnroll; ++u) {
-      const u32x4 piece = codec_piece(fetched[u]);
-      __builtin_memcpy(&tmp[u], &piece, sizeof(Vec));
+      tmp[u] = codec_piece(fetched[u]);
     }
   }
   // One store at a time per wave (a wave waits for its last store before it issues the next): with a wave's
@@ -1655,7 +1697,7 @@ __global__ __launch_bounds__(kThreads) void learner_step_kernel(StepArgs a)
   for (int u = 0; u < kUnroll; ++u) {
     const uint32_t v = tid - first + u * copiers;
     if (u > 0 && v - lane < a.vecs_per_row) wait_for_all_loads();  // the same for all lanes of the wave
-    if (v < a.vecs_per_row) d[v] = tmp[u];
+    if (v < a.vecs_per_row) store_piece<P>(d, v, out_bytes, tmp[u]);
   }
 
   // ---- what the side jobs write
@@ -1680,17 +1722,16 @@ __global__ __launch_bounds__(kThreads) void learner_step_kernel(StepArgs a)
     for (int u = 0; u < kUnroll; ++u) {
       const uint32_t v = min(base + tid - first + u * copiers, v_last);
       if constexpr (kCodec) {
-        const u32x4 piece = codec_piece(codec_fetch_all(reinterpret_cast<const uint8_t *>(s), a.codec, v));
-        __builtin_memcpy(&tmp[u], &piece, sizeof(Vec));
+        tmp[u] = codec_piece(codec_fetch_all(s, a.codec, v));
       } else {
-        tmp[u] = __builtin_nontemporal_load(s + v);
+        tmp[u] = load_piece_streaming<P>(s, v, a.row_bytes);
       }
     }
     wait_for_all_loads();
 #pragma unroll
     for (int u = 0; u < kUnroll; ++u) {
       const uint32_t v = base + tid - first + u * copiers;
-      if (v < a.vecs_per_row) __builtin_nontemporal_store(tmp[u], d + v);
+      if (v < a.vecs_per_row) store_piece_streaming<P>(d, v, out_bytes, tmp[u]);
     }
   }
   if (wave == 2 && a.act_out && !act_early)  // long action rows: after the row, which they would hold up

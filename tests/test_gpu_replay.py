@@ -129,6 +129,44 @@ def test_sample_in_one_launch(ob, ab, nb, k):
         sample_both(gp, op, rng, nb, k)
 
 
+@pytest.mark.parametrize("ob", [12, 15, 16, 17, 31, 100, 1028, 1039, 4096, 4097, 5003, 8207, 32772])
+def test_rows_of_any_length_at_any_alignment(ob):
+    """Observation rows around the edges of the 16-byte pieces, of a launch's share of a row and of the short and long
+    row kernels, from and to addresses that divide by nothing: add, gather, sample, and the pipeline's steps."""
+    from paper_1803_00933_amd import apex
+    rng = np.random.default_rng(ob)
+    g, o = make_pair(2100, 2500, ob, 3)
+    for n in (1100, 1000):                                   # (from 1024 long rows on they are copied as one run)
+        prio = rng.lognormal(0, 1, n).astype(F32)
+        obs, act = rng.integers(0, 256, (n, ob), dtype=np.uint8), rng.integers(0, 256, (n, 3), dtype=np.uint8)
+        ret, gacc = rng.standard_normal(n).astype(F32), rng.random(n).astype(F32)
+        assert o.add(prio, obs, act, ret, gacc)[0] == 0
+        shifted = torch.empty(n * ob + 1, dtype=torch.uint8, device="cuda:0")[1:].view(n, ob)
+        shifted.copy_(torch.from_numpy(obs))
+        assert g.add(dev(prio), shifted, dev(act), dev(ret), dev(gacc))[0] == 0
+    sample_both(g, o, rng, 2, 77)
+    rnd = rng.integers(0, U64, 70, dtype=np.uint64)
+    oo = o.sample(1, 70, 0.4, rnd)[1]
+    for shift in (0, 1):
+        buf = torch.full((70 * ob + 3,), 255, dtype=torch.uint8, device="cuda:0")
+        to = buf[shift:shift + 70 * ob].view(70, ob)
+        assert g.gather(dev(oo["slot"].astype(np.uint32)), obs=to) == 0
+        torch.cuda.synchronize()
+        assert np.array_equal(host(to), oo["obs"])
+        assert bool((buf[shift + 70 * ob:] == 255).all()) and bool((buf[:shift] == 255).all())
+    pipe = apex.Pipeline(g, 3, 1, 70)
+    rnd, newp = rng.integers(0, U64, (3, 70), dtype=np.uint64), rng.lognormal(0, 1, (3, 70)).astype(F32)
+    d_rnd, d_newp = dev(rnd), dev(newp)
+    assert pipe.fork() == 0 and pipe.steps(3, 0.4, d_rnd, d_newp)[0] == 0 and pipe.join() == 0
+    torch.cuda.synchronize()
+    for s in range(3):
+        oo = o.sample(1, 70, 0.4, rnd[s])[1]
+        o.update_priorities(oo["key"], newp[s])
+        assert_sample_equal(pipe.sets[s], oo)
+    check_gpu_tree(g, o)
+    pipe.close()
+
+
 @pytest.mark.parametrize("P,C,ob,ab", [(5000, 4000, 48, 8), (3000, 2500, 4112, 4)])
 def test_add_with_payload_written_in_place(P, C, ob, ab):
     """A producer writes observations and actions of the coming keys straight into the ring (row
