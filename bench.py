@@ -758,7 +758,7 @@ def profile_loop(job, n, log):
     with other rows or uniforms every time, so that per-kernel averages of counters mean something:
     (a) learner steps as one launch each (learner_step_kernel: gather + weights + write-back + next draw),
     (b) plain gathers of 512 frame stacks (copy_rows_long_kernel, no side jobs),
-    (c) draws of 512 samples (sample_descent_kernel),
+    (c) draws of 512 samples (sample_kernel),
     (d) gathers of 16 batches = 8192 frame stacks with their weights (copy_rows_long_kernel with weights)."""
     torch, w, rep = job.torch, job.w, job.rep
     job.setup_pipeline()
