@@ -263,3 +263,23 @@ def test_fused_calls_on_small_and_ragged_shapes(P, C, ob, ab, S, T, n, A, k):
             rco, eo = o.evict(rounds, rnd_e)
             assert g.evict_enqueue(rounds, dev(rnd_e)) == (rco, e)
         check(g, o)
+
+
+@pytest.mark.parametrize("e", [1, 1023, 1025, 4097, 65_535, 65_536, 65_537, 70_000])
+def test_rounds_at_the_edges_of_the_removal(e):
+    """Rounds of whole and ragged workgroups (1024 candidates), on both sides of the line (65,536) above which a launch
+    of its own counts the candidates; heavy-tailed priorities, so that rounds have long runs of equal candidates.
+    Two evictions in a row: the second starts from the counters that the first has left."""
+    from paper_1803_00933_amd import apex
+    rng = np.random.default_rng(e)
+    cap, rounds = max(100, e // 2), 3
+    P = cap + e
+    g = apex.PeReplay(cap, P, 4, 4, alpha_evict=0.4)
+    o = oracle.PrioritizedEvictionReplay(cap, P, 4, 4, alpha_evict=0.4)
+    for _ in range(2):
+        prio = rng.lognormal(0, 3.0, P - o.size).astype(F32)
+        assert o.add(prio)[0] == 0
+        assert g.add(dev(prio)) == 0
+        rnd = rng.integers(0, U64, (rounds, o.size - cap), dtype=np.uint64)
+        assert g.evict(rounds, dev(rnd)) == o.evict(rounds, rnd)
+        check(g, o)
