@@ -406,12 +406,17 @@ int add_payload_short_t(const PayloadRing &pr, uint64_t count, const void *obs, 
   return hip_failed(hipGetLastError()) ? APEX_ERR_HIP : APEX_OK;
 }
 
+// Whether rows like these are added by add_payload_short_kernel.
+bool short_rows(const PayloadRing &pr, const void *obs)
+{
+  return pieces_per_row(row_pieces((uintptr_t)obs | (uintptr_t)pr.obs, pr.obs_bytes), pr.obs_bytes) <= 256;
+}
+
 int add_payload_short(const PayloadRing &pr, uint64_t count, const void *obs, const void *act, const float *ret,
                       const float *gacc, const RowMap &to, hipStream_t stream)
 {
   const RowPieces rp = row_pieces((uintptr_t)obs | (uintptr_t)pr.obs, pr.obs_bytes);
   const uint64_t vpr = pieces_per_row(rp, pr.obs_bytes);
-  if (vpr > 256) return APEX_ERR_NOT_READY;
   return with_pieces(rp, [&](auto p) {
     return add_payload_short_t<decltype(p)>(pr, count, obs, act, ret, gacc, to, (uint32_t)vpr, stream);
   });
@@ -439,7 +444,7 @@ int add_payload_rows(const PayloadRing &pr, uint64_t count, const void *obs, con
 {
   const RowMap ident{nullptr, nullptr, 0, {}};
   int rc;
-  if (obs && (rc = add_payload_short(pr, count, obs, act, ret, gacc, to, stream)) != APEX_ERR_NOT_READY) return rc;
+  if (obs && short_rows(pr, obs)) return add_payload_short(pr, count, obs, act, ret, gacc, to, stream);
   if (obs && (rc = launch_copy(obs, ident, pr.obs, to, count, pr.obs_bytes, stream)) != APEX_OK) return rc;
   if (act || ret || gacc) return add_small_columns(pr, count, act, ret, gacc, to, stream);
   return APEX_OK;
@@ -553,6 +558,33 @@ int apex_nstep_priorities(uint32_t S, uint32_t T, uint32_t n, uint32_t A, const 
   return APEX_OK;
 }
 
+}  // extern "C"
+
+namespace {
+
+// Enters `count` transitions under the next keys; columns: as far as their small columns are to be copied too.
+int publish(apex_replay_t *r, uint64_t count, const float *prio, const AddColumns &columns, uint64_t *first_key_out,
+            void *hip_stream)
+{
+  if (!r || (count && !prio)) return APEX_ERR_INVALID_ARG;
+  if ((r->tail - r->head) + count > r->cfg.max_slots) return APEX_ERR_FULL;
+  if (count) {
+    hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+    const uint64_t second = r->second_words();
+    r->tree_changed(second);
+    add_leaves_kernel<<<dim3(blocks_for(count, kLeavesThreads)), dim3(kLeavesThreads), 0, stream>>>(
+        AddLeavesArgs{r->tv, second, r->state(), count, prio, r->qp}, columns);
+    APEX_HIP(hipGetLastError());
+  }
+  if (first_key_out) *first_key_out = r->tail;
+  r->tail += count;
+  return APEX_OK;
+}
+
+}  // namespace
+
+extern "C" {
+
 int apex_replay_add_payload(apex_replay_t *r, uint64_t count, const void *obs, const void *act, const float *ret,
                             const float *gacc, void *hip_stream)
 {
@@ -568,28 +600,22 @@ int apex_replay_add_payload(apex_replay_t *r, uint64_t count, const void *obs, c
 int apex_replay_add_publish(apex_replay_t *r, uint64_t count, const float *prio, uint64_t *first_key_out,
                             void *hip_stream)
 {
-  if (!r || (count && !prio)) return APEX_ERR_INVALID_ARG;
-  if ((r->tail - r->head) + count > r->cfg.max_slots) return APEX_ERR_FULL;
-  if (count) {
-    hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    const uint64_t second = r->second_words();
-    r->tree_changed(second);
-    add_leaves_kernel<<<dim3(blocks_for(count, kLeavesThreads)), dim3(kLeavesThreads), 0, stream>>>(
-        AddLeavesArgs{r->tv, second, r->state(), count, prio, r->qp});
-    APEX_HIP(hipGetLastError());
-  }
-  if (first_key_out) *first_key_out = r->tail;
-  r->tail += count;
-  return APEX_OK;
+  return publish(r, count, prio, AddColumns{}, first_key_out, hip_stream);
 }
 
 int apex_replay_add(apex_replay_t *r, uint64_t count, const void *obs, const void *act, const float *ret,
                     const float *gacc, const float *prio, uint64_t *first_key_out, void *hip_stream)
 {
   if (!r || (count && !prio)) return APEX_ERR_INVALID_ARG;
-  const int rc = apex_replay_add_payload(r, count, obs, act, ret, gacc, hip_stream);
+  const PayloadRing pr{r->obs(), r->act(), r->ret(), r->gacc(), r->cfg.obs_bytes, r->cfg.act_bytes};
+  if ((obs && short_rows(pr, obs)) || r->cfg.act_bytes > kColumnsInAddBytes) {
+    const int rc = apex_replay_add_payload(r, count, obs, act, ret, gacc, hip_stream);
+    return rc != APEX_OK ? rc : apex_replay_add_publish(r, count, prio, first_key_out, hip_stream);
+  }
+  const int rc = apex_replay_add_payload(r, count, obs, nullptr, nullptr, nullptr, hip_stream);
   if (rc != APEX_OK) return rc;
-  return apex_replay_add_publish(r, count, prio, first_key_out, hip_stream);
+  const AddColumns columns{static_cast<const uint8_t *>(act), ret, gacc, r->act(), r->ret(), r->gacc(), r->cfg.act_bytes};
+  return publish(r, count, prio, columns, first_key_out, hip_stream);
 }
 
 namespace {

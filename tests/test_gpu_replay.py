@@ -994,3 +994,37 @@ def test_update_from_learner_q_values(m, A):
         assert np.array_equal(host(p_out).view(np.uint32), p_ref.view(np.uint32))
         check_gpu_tree(g, o)
     sample_both(g, o, rng, 2, 128)
+
+
+@pytest.mark.parametrize("act_bytes", [1, 2, 3, 4, 5, 7, 15, 16, 17])
+@pytest.mark.parametrize("obs_bytes,with_obs", [(4112, True), (64, False)])
+def test_small_columns_of_a_whole_add(act_bytes, obs_bytes, with_obs):
+    """The columns that a whole add brings along with the masses (up to 16 action bytes) or in a launch of their own,
+    each of them possibly missing, on a ring that wraps: what is there lands in its rows, the rest stays."""
+    from paper_1803_00933_amd import apex
+    rng = np.random.default_rng(act_bytes)
+    P, count = 2500, 1100  # more than one workgroup of transitions
+    g = apex.Replay(1200, P, obs_bytes, act_bytes)
+    for view in (g.obs_view(), g.act_view(), g.ret_view(), g.gacc_view()):
+        view.zero_()
+    want = [np.zeros((P, act_bytes), np.uint8), np.zeros(P, np.float32), np.zeros(P, np.float32)]
+    obs = rng.integers(0, 256, (count, obs_bytes), dtype=np.uint8)
+    for it in range(8):
+        cols = [rng.integers(0, 256, (count, act_bytes), dtype=np.uint8), rng.standard_normal(count).astype(np.float32),
+                rng.random(count).astype(np.float32)]
+        given = [it & (1 << b) == 0 for b in range(3)]
+        args = [dev(c) if there else None for c, there in zip(cols, given)]
+        prio = rng.lognormal(0, 1, count).astype(np.float32)
+        rc, first = g.add(dev(prio), dev(obs) if with_obs else None, *args)
+        assert rc == 0 and first == it * count
+        rows = (first + np.arange(count)) % P
+        for w, c, there in zip(want, cols, given):
+            if there:
+                w[rows] = c
+        torch.cuda.synchronize()
+        assert np.array_equal(host(g.act_view(), np.uint8).reshape(P, act_bytes), want[0])
+        assert np.array_equal(host(g.ret_view(), np.float32), want[1])
+        assert np.array_equal(host(g.gacc_view(), np.float32), want[2])
+        if with_obs:
+            assert np.array_equal(host(g.obs_view(), np.uint8).reshape(P, obs_bytes)[rows], obs)
+        assert g.evict()[0] == 0
