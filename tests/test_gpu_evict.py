@@ -141,6 +141,7 @@ def test_control_schedule_without_the_host_in_the_loop():
     w = synth.WORKLOADS["control"]
     g = apex.PeReplay(w.capacity, w.max_slots, w.obs_bytes, w.act_bytes)
     o = oracle.PrioritizedEvictionReplay(w.capacity, w.max_slots, w.obs_bytes, w.act_bytes)
+    g.storage.zero_()   # the bulk add names no actions and returns: those columns stay as they are, zero in the oracle
     prio = synth.priorities("lognormal1", w.seed, 0, w.capacity, tag="bulk")
     obs0 = np.zeros((w.capacity, w.obs_bytes), np.uint8)
     assert o.add(prio, obs0)[0] == 0 and g.add(dev(prio), dev(obs0)) == 0
