@@ -140,6 +140,11 @@ int geometry(const apex_replay_config_t *c, Geometry *g)
   return APEX_OK;
 }
 
+// The sample launches on one memory that have taken tickets (see sample_kernel), and the most batches one of them had.
+struct TicketUse {
+  uint32_t launches = 0, batches = 0;
+};
+
 }  // namespace
 
 struct apex_replay {
@@ -149,6 +154,7 @@ struct apex_replay {
   uint64_t *tree;
   uint8_t *scratch;
   uint64_t head, tail;  // host mirror of the device state
+  TicketUse ticket_use;
   QuantParams qp;
   TreeView tv;
   // Second copy of the tree, behind the first in the tree region: used by sequences of fused learner
@@ -627,12 +633,17 @@ int launch_weights(const WeightArgs &wa, uint32_t num_batches, hipStream_t strea
   return hip_failed(hipGetLastError()) ? APEX_ERR_HIP : APEX_OK;
 }
 
-// a.k samples of each of num_batches batches (with a.k_dev: at most a.k).
-int launch_sample(SampleArgs &a, uint32_t num_batches, hipStream_t stream)
+// a.k samples of each of num_batches batches (with a.k_dev: at most a.k).  tickets may be null where a.weight_out is.
+int launch_sample(SampleArgs &a, uint32_t num_batches, hipStream_t stream, TicketUse *tickets = nullptr)
 {
   a.k_div = make_fast_div(a.k);
-  const uint32_t threads = sample_threads(a.k, a.weight_out != nullptr);
-  sample_kernel<<<dim3(blocks_for(a.k, threads / 16), num_batches), dim3(threads), 0, stream>>>(a);
+  const uint32_t threads = sample_threads(a.k, a.weight_out != nullptr), wgs = blocks_for(a.k, threads / 16);
+  if (a.weight_out && wgs > 1) {
+    a.ticket_set = tickets->launches++ & (kTicketSets - 1);
+    if (num_batches > tickets->batches) tickets->batches = num_batches;
+    a.ticket_batches = tickets->batches;
+  }
+  sample_kernel<<<dim3(wgs, num_batches), dim3(threads), 0, stream>>>(a);
   return hip_failed(hipGetLastError()) ? APEX_ERR_HIP : APEX_OK;
 }
 
@@ -694,7 +705,7 @@ int sample_in_one(apex_replay *r, uint32_t num_batches, uint32_t k, float beta, 
   a.beta = beta;
   a.ticket = r->tickets();
   a.claim = claim ? r->claim() : nullptr;
-  const int rl = launch_sample(a, num_batches, stream);
+  const int rl = launch_sample(a, num_batches, stream, &r->ticket_use);
   return rl != APEX_OK || a.weight_out == weight_out ? rl
                                                      : launch_weights(WeightArgs{mass_out, weight_out, k, beta}, num_batches, stream);
 }

@@ -475,6 +475,7 @@ struct apex_pe_replay {
   uint64_t evicted_confirmed = 0;  // the last value read back from the device: evicted >= evicted_confirmed
   bool pending = false;            // a snapshot has been requested and not looked at yet
   uint64_t pending_claim = 0;      // what `evicted` was taken to be when it was requested
+  TicketUse ticket_use;
   PeState *snap = nullptr;         // pinned host memory that the snapshot lands in
   hipEvent_t snap_ev = nullptr;    // recorded behind the snapshot's copy
   PeView v;
@@ -746,7 +747,7 @@ int apex_pe_sample(apex_pe_replay_t *r, uint32_t num_batches, uint32_t k, float 
     a.beta = beta;
     jobs.wa.weight_out = nullptr;
   }
-  APEX_TRY(launch_sample(a, num_batches, stream));
+  APEX_TRY(launch_sample(a, num_batches, stream, &r->ticket_use));
   if (obs_out && !gather) {
     const RowMap by_slot{slot_out, nullptr, 0, {}};
     const RowMap ident{nullptr, nullptr, 0, {}};

@@ -1080,11 +1080,14 @@ struct SampleArgs {
   uint8_t *obs_out;          // null: the rows are gathered by another launch (copy_rows_*)
   float *weight_out;         // null: no weights, or written by another launch (batch_weights)
   float beta;
-  uint32_t *ticket;          // with weight_out: one word per batch, kTicketStride words apart, 0 between launches
+  uint32_t *ticket;          // with weight_out: kTicketSets words per batch, batches kTicketStride words apart ...
+  uint32_t ticket_set;       // ... of which this launch uses this one (0 before and after) ...
+  uint32_t ticket_batches;   // ... and clears another one of this many batches, see sample_kernel
   uint32_t *claim;           // not null: the first pass of an update of the drawn keys (update_claim_block) as well
 };
 
 constexpr uint32_t kTicketStride = 16;
+constexpr uint32_t kTicketSets = 4;  // a power of two
 
 // Waits until every load (and store) that this wave has issued is through.
 __device__ __forceinline__ void wait_for_all_loads()
@@ -1307,6 +1310,9 @@ __host__ __device__ inline uint32_t sample_threads(uint32_t k, bool weights)
 // The weights need the smallest mass of the whole batch: every workgroup writes its masses through to memory (agent
 // scope), takes the batch's ticket, and the one with the last ticket reads all of them back and writes the batch's
 // weights.  Only these words cross between workgroups, so no cache has to be written back or invalidated for it.
+// A launch leaves its ticket words at 0.  Launches take turns on kTicketSets words per batch, and each also clears the
+// words that the launch two turns on will use: whatever left a word at another value (calls that overlapped although
+// they must be ordered), the calls after it find their last workgroups again.
 // Bound by a chain of round trips (top level, its eight nodes again, a row of children per level, the payload row, with
 // weights the ticket and the masses).  In one launch instead of two (draw; gather and weights): 16 x 512 rows of 64
 // bytes from 2^21 slots 6.2 + 3.8 -> 9.2 us, 4096 of 128 bytes from 2^24 7.2 + 7.4 -> 10.9, 256 of 268 bytes from 2^20
@@ -1393,6 +1399,9 @@ __global__ __launch_bounds__(1024) void sample_kernel(SampleArgs a)
   }
   if (!a.weight_out) return;
 
+  if (blockIdx.x == 0 && b == 0)
+    for (uint32_t i = threadIdx.x; i < a.ticket_batches; i += nthr)
+      a.ticket[i * kTicketStride + ((a.ticket_set + 2) & (kTicketSets - 1))] = 0;
   if (gridDim.x == 1) {  // the whole batch is here
     const uint64_t wave_mn = wave_min(my_mass);
     if (lane == 0) red[threadIdx.x / kWave] = wave_mn;
@@ -1403,7 +1412,7 @@ __global__ __launch_bounds__(1024) void sample_kernel(SampleArgs a)
     return;
   }
   __syncthreads();
-  uint32_t *const ticket = a.ticket + (uint64_t)b * kTicketStride;
+  uint32_t *const ticket = a.ticket + (uint64_t)b * kTicketStride + a.ticket_set;
   if (threadIdx.x == 0) sh_ticket = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   __syncthreads();
   if (sh_ticket != gridDim.x - 1) return;

@@ -129,6 +129,33 @@ def test_sample_in_one_launch(ob, ab, nb, k):
         sample_both(gp, op, rng, nb, k)
 
 
+@pytest.mark.parametrize("prioritized_eviction", [False, True])
+def test_sample_recovers_from_stale_tickets(prioritized_eviction):
+    """Sample calls that overlapped although they must be ordered can leave the tickets of the weights at any value
+    (planted here, in every word): after two more calls with weights from several workgroups, every later one is right
+    again, whatever calls without tickets or of fewer batches lie in between."""
+    from paper_1803_00933_amd import apex
+    rng = np.random.default_rng(8)
+    if prioritized_eviction:
+        g, o = apex.PeReplay(3000, 4000, 32, 4), oracle.PrioritizedEvictionReplay(3000, 4000, 32, 4)
+        prio = rng.random(3000).astype(F32)
+        obs, act = (rng.integers(0, 256, (3000, n), dtype=np.uint8) for n in (32, 4))
+        assert o.add(prio, obs, act, prio, prio)[0] == 0
+        assert g.add(dev(prio), dev(obs), dev(act), dev(prio), dev(prio)) == 0
+    else:
+        g, o = make_pair(3000, 4000, 32, 4)
+        assert add_both(g, o, rng, 3000) == 0
+    words = g.scratch[256:256 + 1024 * 16 * 4].view(torch.int32)   # behind the device state: 16 words per batch
+    assert int(words.abs().max()) == 0
+    sample_both(g, o, rng, 3, 40)
+    words.fill_(1000)                 # no launch below has as many workgroups per batch
+    for nb in (3, 1):
+        assert g.sample(nb, 512, 0.4, dev(rng.integers(0, U64, nb * 512, dtype=np.uint64)))[0] == 0
+    for nb, k in ((1, 512), (1, 33), (1, 512), (1, 512), (3, 200), (1, 32), (1, 32), (1, 32), (3, 512), (2, 4096), (3, 2048)):
+        sample_both(g, o, rng, nb, k)
+    assert int(words.view(1024, 16)[:3, :4].abs().max()) == 0
+
+
 @pytest.mark.parametrize("ob", [12, 15, 16, 17, 31, 100, 1028, 1039, 4096, 4097, 5003, 8207, 32772])
 def test_rows_of_any_length_at_any_alignment(ob):
     """Observation rows around the edges of the 16-byte pieces, of a launch's share of a row and of the short and long
