@@ -520,7 +520,8 @@ int apex_pe_evict(apex_pe_replay_t *r, uint32_t rounds, const uint64_t *rnd, uin
                   void *hip_stream);
 /*
  * apex_pe_evict without the host in the loop: enqueues the same rounds for e = size - capacity transitions and
- * returns; *requested_out (host, may be NULL) receives e.  rnd is [rounds, e] as above.  The host's own count of
+ * returns; *requested_out (host, may be NULL) receives e.  rnd is [rounds, e] as above (with rnd NULL the call only
+ * reports e: APEX_ERR_INVALID_ARG, nothing enqueued, or APEX_OK if e is 0).  The host's own count of
  * stored transitions (which decides APEX_ERR_FULL, APEX_ERR_EMPTY and the next e) takes all e to be gone; behind
  * the rounds the call copies the device's counters into host memory of the library's, and the next calls look at
  * that copy once it has arrived: if the rounds ran out before e distinct transitions were found, the host's

@@ -398,6 +398,20 @@ class Pipeline:
         return rc, int(first.value), int(ev.value)
 
 
+def eviction_uniforms(rnd, rounds, e):
+    """The uniforms of an eviction of e transitions as the library addresses them: rounds rows of e words.  How many are
+    due is settled at the call (an eviction before may have fallen short), so a caller's tensor may lack some words of
+    the last rows: its words are then used again from the start.  (Round i draws only what is still to go and so reads
+    the first words of row i; it reaches the repeated ones only if nearly nothing was removed before.)  The first round
+    needs e words of its own."""
+    have = rnd.numel()
+    if have >= rounds * e:
+        return rnd
+    if have < e:
+        raise ValueError("an eviction of %d transitions needs at least as many uniforms, got %d" % (e, have))
+    return rnd.reshape(-1).repeat(-(-rounds * e // have))
+
+
 class PeReplay:
     """Binding of apex_pe_*: the memory with prioritized eviction.  Owns its three device regions."""
 
@@ -470,14 +484,27 @@ class PeReplay:
     def update_priorities(self, key, prio, stream=None):
         return lib.apex_pe_update_priorities(self.h, key.shape[0], _ptr(key), _ptr(prio), _stream(stream))
 
-    def evict(self, rounds, rnd, stream=None):
+    def _checked_uniforms(self, rounds, rnd, stream):
+        """rnd, long enough for whatever the next eviction will ask for (see eviction_uniforms)."""
+        if rnd is None or rnd.numel() >= rounds * (self.max_slots - self.capacity):   # the most there can be to evict
+            return rnd
         e = _u64(0)
+        lib.apex_pe_evict_enqueue(self.h, 0, None, C.byref(e), None)   # without uniforms it only tells the number
+        if e.value > PE_MAX_EVICT_PER_CALL:
+            return rnd                                                 # refused by the call that follows
+        whole = eviction_uniforms(rnd, rounds, e.value)
+        if whole is not rnd and stream is not None:
+            whole.record_stream(stream)
+        return whole
+
+    def evict(self, rounds, rnd, stream=None):
+        e, rnd = _u64(0), self._checked_uniforms(rounds, rnd, stream)
         rc = lib.apex_pe_evict(self.h, rounds, _ptr(rnd), C.byref(e), _stream(stream))
         return rc, int(e.value)
 
     def evict_enqueue(self, rounds, rnd, stream=None):
         """apex_pe_evict_enqueue: returns (rc, number of evictions asked for) without waiting for the eviction."""
-        e = _u64(0)
+        e, rnd = _u64(0), self._checked_uniforms(rounds, rnd, stream)
         rc = lib.apex_pe_evict_enqueue(self.h, rounds, _ptr(rnd), C.byref(e), _stream(stream))
         return rc, int(e.value)
 

@@ -99,3 +99,21 @@ def test_null_handles_are_refused_without_a_gpu():
     pe = apex.PeConfig(1_000_000, 1 << 20, 256, 32, 0.6, -0.4, 1e-6, 24)
     assert lib.apex_pe_workspace_bytes(C.byref(pe), C.byref(a), None, None) == apex.OK and a.value >= (1 << 20) * 256
     assert int(lib.apex_codec_row_bytes(28224)) == 28736 and int(lib.apex_codec_row_bytes(100)) == 0
+
+
+def test_uniforms_of_an_eviction_cover_what_the_library_addresses():
+    """Whatever number of evictions turns out to be due, the library is handed rounds * e words or the call is refused:
+    a tensor that is long enough as it is, a shorter one with its words repeated, one too short for the first round not."""
+    import pytest
+    import torch
+    from paper_1803_00933_amd import apex
+    rnd = torch.arange(12).view(3, 4)
+    for rounds, e in ((3, 4), (3, 0), (2, 6), (1, 12), (0, 50)):
+        assert apex.eviction_uniforms(rnd, rounds, e) is rnd
+    for rounds, e in ((3, 5), (3, 12), (7, 11)):
+        whole = apex.eviction_uniforms(rnd, rounds, e)
+        assert whole.is_contiguous() and whole.numel() >= rounds * e
+        assert torch.equal(whole, torch.arange(whole.numel()) % 12)
+    for rounds, e in ((1, 13), (3, 100)):
+        with pytest.raises(ValueError):
+            apex.eviction_uniforms(rnd, rounds, e)

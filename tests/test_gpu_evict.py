@@ -266,6 +266,28 @@ def test_fused_calls_on_small_and_ragged_shapes(P, C, ob, ab, S, T, n, A, k):
         check(g, o)
 
 
+@pytest.mark.parametrize("enqueue", [False, True])
+def test_eviction_with_uniforms_for_fewer_than_are_due(enqueue):
+    """A program that sizes its uniforms for what it adds meets a larger eviction after one that fell short: the binding
+    repeats the words it has, and refuses a tensor that lacks words of the first round; nothing is read past the end."""
+    from paper_1803_00933_amd import apex
+    rng = np.random.default_rng(3)
+    cap, P, n, rounds = 600, 1000, 300, 3
+    g = apex.PeReplay(cap, P, 4, 4, alpha_evict=0.4)
+    o = oracle.PrioritizedEvictionReplay(cap, P, 4, 4, alpha_evict=0.4)
+    prio = rng.lognormal(0, 3.0, cap + n + 7).astype(F32)
+    assert o.add(prio)[0] == 0 and g.add(dev(prio)) == 0
+    evict = g.evict_enqueue if enqueue else g.evict
+    with pytest.raises(ValueError):
+        evict(rounds, dev(rng.integers(0, U64, n + 6, dtype=np.uint64)))
+    check(g, o)
+    rnd = rng.integers(0, U64, (rounds, n), dtype=np.uint64)   # 900 words for 3 x 307
+    rco, gone = o.evict(rounds, np.concatenate([rnd.reshape(-1)] * 2))
+    rcg, told = evict(rounds, dev(rnd))
+    assert (rcg, told) == (rco, n + 7 if enqueue else gone)
+    check(g, o)
+
+
 @pytest.mark.parametrize("e", [1, 1023, 1025, 4097, 65_535, 65_536, 65_537, 70_000])
 def test_rounds_at_the_edges_of_the_removal(e):
     """Rounds of whole and ragged workgroups (1024 candidates), on both sides of the line (65,536) above which a launch
