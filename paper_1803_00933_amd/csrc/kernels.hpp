@@ -1058,17 +1058,22 @@ __global__ __launch_bounds__(256) void update_apply_kernel(TreeView tv, DeviceSt
 // smallest mass of a whole batch; they are written by the kernel that runs next (the gather,
 // or batch_weights_kernel), so this one needs no fence or counter between workgroups.
 // --------------------------------------------------------------------------------------------
-struct SampleArgs {
+// What every draw needs, and no more: the step kernel has these among its arguments, and with 8 bytes more in them its
+// launches took 0.2 us longer.
+struct DrawArgs {
   TreeView tv;
   const DeviceState *st;
   uint32_t k;                // samples per batch
-  const uint64_t *k_dev;     // not null: the number of samples is read here, on the device (waves beyond it idle)
-  FastDiv k_div;             // division by k (unused with k_dev)
-  const uint32_t *gen;       // not null: keys are (generation of the slot << 32) | slot instead of ring keys
   const uint64_t *rnd;       // [nb,k]
   uint64_t *key_out;         // [nb,k] or null
   uint32_t *slot_out;        // [nb,k]
   uint64_t *mass;            // [nb,k]: mass of each drawn transition, for the weights
+};
+
+struct SampleArgs : DrawArgs {
+  const uint64_t *k_dev;     // not null: the number of samples is read here, on the device (waves beyond it idle)
+  FastDiv k_div;             // division by k (unused with k_dev)
+  const uint32_t *gen;       // not null: keys are (generation of the slot << 32) | slot instead of ring keys
   // payload columns and their outputs (each output may be null)
   const uint8_t *act;
   uint32_t act_bytes;
@@ -1168,49 +1173,38 @@ struct TopLevel {
   }
 };
 
-// One wavefront walks from its places in the top level down to the slots whose cumulative-mass intervals
-// hold the points: the loads of all samples go out together on every level, so that several draws take
-// the time of one.  Called by all 64 lanes.
+// One wavefront walks from its place in the top level down to the slot whose cumulative-mass interval holds the point.
+// Called by all 64 lanes.
 // between(): called once, when the loads of the first level below the top are on their way (right away if
 // the tree has no such level): arithmetic that does not depend on the walk costs nothing there.
-template <int kSamples, typename Between>
-__device__ __forceinline__ void walk_down(const TreeView &tv, const TopHit (&top)[kSamples], Drawn (&out)[kSamples],
-                                          Between between)
+template <typename Between>
+__device__ __forceinline__ Drawn walk_down(const TreeView &tv, const TopHit &top, Between between)
 {
   const uint32_t lane = lane_id();
   // the two lowest levels' addresses are at fixed places of the arguments: fetched with them, not on the way down
   const uint64_t *const low0 = tv.level[0], *const low1 = tv.level[1];
-  uint64_t x[kSamples], idx[kSamples], mass[kSamples];
-#pragma unroll
-  for (int s = 0; s < kSamples; ++s) x[s] = top[s].x, idx[s] = top[s].idx, mass[s] = top[s].mass;
+  uint64_t x = top.x, idx = top.idx, mass = top.mass;
   // up to 64 children per step, prefix sum across the wave, first child whose running sum exceeds the remainder
-  bool called = false;
-  uint32_t fl = tv.top_log2;  // of the node the walk stands on
-  for (int l = (int)tv.nlev - 2; l >= 0; --l) {
-    const uint64_t *const lv = l == 0 ? low0 : l == 1 ? low1 : tv.level[l];
-    uint64_t c[kSamples];
-#pragma unroll
-    for (int s = 0; s < kSamples; ++s) c[s] = lv[(idx[s] << fl) + (lane & ((1u << fl) - 1))];
-    if (!called) {
-      between();
-      called = true;
-    }
-#pragma unroll
-    for (int s = 0; s < kSamples; ++s) {
-      if (lane >> fl) c[s] = 0;  // a summit's node has fewer children than the wave has lanes
-      const uint64_t sc = wave_inclusive_scan(c[s]);
-      const uint64_t hit = __ballot(sc > x[s]);
-      const uint32_t sel = hit ? __ffsll((unsigned long long)hit) - 1 : (1u << fl) - 1;
-      const uint64_t c_sel = read_lane_u64(c[s], sel);
-      x[s] -= read_lane_u64(sc, sel) - c_sel;
-      idx[s] = (idx[s] << fl) + sel;
-      mass[s] = c_sel;
-    }
-    fl = kFanoutLog2;
+  auto select = [&](uint64_t c, uint32_t fl) {
+    const uint64_t sc = wave_inclusive_scan(c);
+    const uint64_t hit = __ballot(sc > x);
+    const uint32_t sel = hit ? __ffsll((unsigned long long)hit) - 1 : (1u << fl) - 1;
+    mass = read_lane_u64(c, sel);
+    x -= read_lane_u64(sc, sel) - mass;
+    idx = (idx << fl) + sel;
+  };
+  auto level = [&](int l) { return l == 0 ? low0 : l == 1 ? low1 : tv.level[l]; };
+  int l = (int)tv.nlev - 2;
+  if (l < 0) {
+    between();
+  } else {
+    const uint32_t fl = tv.top_log2;  // a summit's node has fewer children than the wave has lanes
+    const uint64_t c = level(l)[(idx << fl) + (lane & ((1u << fl) - 1))];
+    between();
+    select(lane >> fl ? 0 : c, fl);
+    for (--l; l >= 0; --l) select(level(l)[idx * kFanout + lane], kFanoutLog2);
   }
-  if (!called) between();
-#pragma unroll
-  for (int s = 0; s < kSamples; ++s) out[s] = Drawn{idx[s], mass[s], x[s]};
+  return Drawn{idx, mass, x};
 }
 
 // The ring key of a drawn slot: head + its distance from the head's slot around the ring.
@@ -1499,7 +1493,7 @@ struct StepArgs {
   const uint64_t *dq;     // [k] its changes: new mass - mass as drawn; null: nothing is written back in this sequence
   TreeView wr;            // the copy that is written
   WeightArgs wa;          // weights of batch i
-  SampleArgs next;        // draw of batch i+1 from next.tv, the copy that is read; next.rnd == null: none
+  DrawArgs next;          // draw of batch i+1 from next.tv, the copy that is read; next.rnd == null: none
   const uint64_t *next_top;  // the top level of next.tv (its address at a fixed place of the arguments)
   FastDiv next_k_div;        // division by next.k
   const float *next_prio; // [k] new priorities of batch i+1 (null: none) ...
@@ -1557,22 +1551,22 @@ __device__ __forceinline__ void draw_in_first_wave(const StepArgs &a, uint32_t r
   const uint64_t total = top.scan();
   const uint64_t w = fast_div(total, a.next_k_div);
   const uint64_t point = (uint64_t)row * w + __umul64hi(un0, w), next_point = (uint64_t)(row + 1) * w + __umul64hi(un1, w);
-  const TopHit hit[1] = {top.find(point)};
+  const TopHit hit = top.find(point);
 
   bool clamped = false;
   uint64_t q_next = 0, head_slot = 0;
   uint32_t *const slot_out = a.next.slot_out;
   uint64_t *const key_out = a.next.key_out, *const mass_out = a.next.mass, *const dq_out = a.next_dq;
   uint64_t *const wr0 = a.wr.level[0], *const wr1 = a.wr.level[1], *const wr2 = a.wr.level[2];
-  const uint32_t wr_nlev = a.wr.nlev;
+  // (the two copies of the tree have one shape, which the walk has fetched)
   auto add_to_written_copy = [&](uint64_t slot, uint64_t delta) {  // one lane
     if (!delta) return;
     atomic_add_u64(wr0 + slot, delta);
     uint64_t idx = slot;
-    if (wr_nlev > 1) atomic_add_u64(wr1 + (idx >>= fanout_log2(a.wr, 1)), delta);
-    if (wr_nlev > 2) atomic_add_u64(wr2 + (idx >>= fanout_log2(a.wr, 2)), delta);
-    for (uint32_t l = 3; l < wr_nlev; ++l) {
-      idx >>= fanout_log2(a.wr, l);
+    if (rd.nlev > 1) atomic_add_u64(wr1 + (idx >>= fanout_log2(rd, 1)), delta);
+    if (rd.nlev > 2) atomic_add_u64(wr2 + (idx >>= fanout_log2(rd, 2)), delta);
+    for (uint32_t l = 3; l < rd.nlev; ++l) {
+      idx >>= fanout_log2(rd, l);
       atomic_add_u64(a.wr.level[l] + idx, delta);
     }
   };
@@ -1582,19 +1576,18 @@ __device__ __forceinline__ void draw_in_first_wave(const StepArgs &a, uint32_t r
     if (a.next_prio) q_next = quantise_priority(prio_next, a.qp, &clamped);
     head_slot = ring_slot(rd, head);
   };
-  Drawn dr[1];
-  walk_down<1>(rd, hit, dr, between);
-  const bool next_has_same_slot = second && next_point - point < dr[0].mass - dr[0].x;
+  const Drawn drawn = walk_down(rd, hit, between);
+  const bool next_has_same_slot = second && next_point - point < drawn.mass - drawn.x;
   // Outputs first, atomics last: nothing that the compiler makes wait for an atomic's completion follows them.
   // (The small payload columns of the drawn batch are gathered by the launch that copies its rows.)
   if (lane == 0) {
-    const uint64_t slot = dr[0].slot;
+    const uint64_t slot = drawn.slot;
     slot_out[row] = (uint32_t)slot;
     if (key_out) key_out[row] = ring_key(slot, head, head_slot, rd.P);
-    mass_out[row] = dr[0].mass;
+    mass_out[row] = drawn.mass;
     if (a.next_prio) {
       // the change this pair brings: none if the next pair has the same slot (the later one counts)
-      const uint64_t delta = next_has_same_slot ? 0 : q_next - dr[0].mass;
+      const uint64_t delta = next_has_same_slot ? 0 : q_next - drawn.mass;
       dq_out[row] = delta;
       add_to_written_copy(slot, delta);
       if (clamped) atomic_add_u64(&a.st->n_clamped, 1);
@@ -1685,10 +1678,15 @@ __global__ __launch_bounds__(kThreads) void learner_step_kernel(StepArgs a)
   const uint8_t *s = a.src + (uint64_t)my_slot * a.row_bytes;
   uint8_t *d = a.dst + (uint64_t)row * out_bytes;
   const uint32_t v_last = a.vecs_per_row - 1;
+  // piece of this wave's first lane: a wave loads nothing where the row has no pieces for it.  (Clamped loads keep the
+  // memory pipelines of the compute unit as busy as others do: a learner step of 512 rows of 60 bytes 6.0 us, now 5.6; of
+  // 1028 bytes 6.1 and 5.7.  Decoded rows are long, and the branch cost their launch 0.2 us.)
+  const uint32_t v_wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid - first));
   typename P::Reg tmp[kUnroll];
   CodecFetched fetched[kCodec ? kUnroll : 1] = {};
 #pragma unroll
   for (int u = 0; u < kUnroll; ++u) {
+    if (!kCodec && v_wave + u * copiers >= a.vecs_per_row) break;
     const uint32_t v = min(tid - first + u * copiers, v_last);
     if constexpr (kCodec) {  // the pieces as the image holds them; mask and block bytes follow below
       fetched[u].data = __builtin_nontemporal_load(
