@@ -639,7 +639,9 @@ int launch_sample(SampleArgs &a, uint32_t num_batches, hipStream_t stream, Ticke
   a.k_div = make_fast_div(a.k);
   const uint32_t threads = sample_threads(a.k, a.weight_out != nullptr), wgs = blocks_for(a.k, threads / 16);
   if (a.weight_out && wgs > 1) {
-    a.ticket_set = tickets->launches++ & (kTicketSets - 1);
+    const uint32_t set = tickets->launches++ & (kTicketSets - 1);
+    a.ticket_ahead = a.ticket + ((set + 2) & (kTicketSets - 1));
+    a.ticket += set;
     if (num_batches > tickets->batches) tickets->batches = num_batches;
     a.ticket_batches = tickets->batches;
   }

@@ -1085,9 +1085,9 @@ struct SampleArgs : DrawArgs {
   uint8_t *obs_out;          // null: the rows are gathered by another launch (copy_rows_*)
   float *weight_out;         // null: no weights, or written by another launch (batch_weights)
   float beta;
-  uint32_t *ticket;          // with weight_out: kTicketSets words per batch, batches kTicketStride words apart ...
-  uint32_t ticket_set;       // ... of which this launch uses this one (0 before and after) ...
-  uint32_t ticket_batches;   // ... and clears another one of this many batches, see sample_kernel
+  uint32_t *ticket;          // with weight_out: one word per batch, kTicketStride words apart, 0 before and after
+  uint32_t *ticket_ahead;    // the words that a launch to come will use, of this many batches: cleared by this launch
+  uint32_t ticket_batches;
   uint32_t *claim;           // not null: the first pass of an update of the drawn keys (update_claim_block) as well
 };
 
@@ -1293,11 +1293,16 @@ constexpr uint32_t kWeightsInDrawMaxK = 4096;
 // one workgroup, whose waves agree on the smallest mass through LDS (32 samples: 5.7 instead of 6.5 us through tickets
 // and memory; with 64 the sixteen waves of the workgroup slow one another down, 8.8 us); a large one has fewer tickets to take and more threads for its weights with 32 (4096 samples: 10.9 us,
 // with 16 and with 64 samples per workgroup 17.6 and 13.0).
-__host__ __device__ inline uint32_t sample_threads(uint32_t k, bool weights)
+constexpr uint32_t kSampleMaxThreads = 512;
+constexpr int kHeldMasses = 8;  // masses per thread of the workgroup that writes a batch's weights
+
+__host__ __device__ constexpr uint32_t sample_threads(uint32_t k, bool weights)
 {
   if (!weights) return 256;
-  return k <= 32 ? (k + 3) / 4 * kWave : k > 2048 ? 512 : 256;
+  return k <= 32 ? (k + 3) / 4 * kWave : k > 2048 ? kSampleMaxThreads : 256;
 }
+static_assert(kHeldMasses * sample_threads(2048, true) >= 2048 && sample_threads(32, true) <= kSampleMaxThreads &&
+              kHeldMasses * sample_threads(kWeightsInDrawMaxK, true) >= kWeightsInDrawMaxK);
 
 // Four consecutive samples of a batch per wave: the walks, and with them whatever of replay.Sample the caller wants in
 // the same launch: the gather of short observation rows, the importance weights, the first pass of an update.
@@ -1311,9 +1316,9 @@ __host__ __device__ inline uint32_t sample_threads(uint32_t k, bool weights)
 // weights the ticket and the masses).  In one launch instead of two (draw; gather and weights): 16 x 512 rows of 64
 // bytes from 2^21 slots 6.2 + 3.8 -> 9.2 us, 4096 of 128 bytes from 2^24 7.2 + 7.4 -> 10.9, 256 of 268 bytes from 2^20
 // 6.0 + 3.1 -> 8.0, each with one launch (3 us on the host, 1 between two kernels) less.
-__global__ __launch_bounds__(1024) void sample_kernel(SampleArgs a)
+__global__ __launch_bounds__(kSampleMaxThreads) void sample_kernel(SampleArgs a)
 {
-  __shared__ uint64_t red[1024 / kWave];
+  __shared__ uint64_t red[kSampleMaxThreads / kWave];
   __shared__ uint32_t sh_ticket;
   const TreeView &tv = a.tv;
   const uint32_t lane = lane_id(), gl = lane & 15, b = blockIdx.y;
@@ -1393,9 +1398,6 @@ __global__ __launch_bounds__(1024) void sample_kernel(SampleArgs a)
   }
   if (!a.weight_out) return;
 
-  if (blockIdx.x == 0 && b == 0)
-    for (uint32_t i = threadIdx.x; i < a.ticket_batches; i += nthr)
-      a.ticket[i * kTicketStride + ((a.ticket_set + 2) & (kTicketSets - 1))] = 0;
   if (gridDim.x == 1) {  // the whole batch is here
     const uint64_t wave_mn = wave_min(my_mass);
     if (lane == 0) red[threadIdx.x / kWave] = wave_mn;
@@ -1406,40 +1408,30 @@ __global__ __launch_bounds__(1024) void sample_kernel(SampleArgs a)
     return;
   }
   __syncthreads();
-  uint32_t *const ticket = a.ticket + (uint64_t)b * kTicketStride + a.ticket_set;
+  uint32_t *const ticket = a.ticket + (uint64_t)b * kTicketStride;
   if (threadIdx.x == 0) sh_ticket = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   __syncthreads();
+  if (blockIdx.x == 0 && b == 0)
+    for (uint32_t i = threadIdx.x; i < a.ticket_batches; i += nthr) a.ticket_ahead[i * kTicketStride] = 0;
   if (sh_ticket != gridDim.x - 1) return;
   if (threadIdx.x == 0) *ticket = 0;
   const uint64_t *const bm = a.mass + (uint64_t)b * k;
   float *const bw = a.weight_out + (uint64_t)b * k;
-  constexpr int kHeld = 8;  // enough for kWeightsInDrawMaxK / 512
-  // kHeld masses per thread are on their way at a time; the first of them stay in registers between the two passes
-  uint64_t first[kHeld], mn = ~0ull;
-  for (uint32_t i0 = threadIdx.x; i0 < k; i0 += kHeld * nthr) {
-    uint64_t m[kHeld];
+  // every mass of the batch in a register of this workgroup: all loads on their way together
+  uint64_t m[kHeldMasses], mn = ~0ull;
 #pragma unroll
-    for (int t = 0; t < kHeld; ++t)
-      m[t] = __hip_atomic_load(bm + min(i0 + t * nthr, k - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  for (int t = 0; t < kHeldMasses; ++t)
+    m[t] = __hip_atomic_load(bm + min(threadIdx.x + t * nthr, k - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
-    for (int t = 0; t < kHeld; ++t) {
-      mn = m[t] < mn ? m[t] : mn;
-      if (i0 == threadIdx.x) first[t] = m[t];
-    }
-  }
+  for (int t = 0; t < kHeldMasses; ++t) mn = m[t] < mn ? m[t] : mn;
   mn = wave_min(mn);
   if (lane == 0) red[threadIdx.x / kWave] = mn;
   __syncthreads();
   for (uint32_t v = 0; v < nthr / kWave; ++v) mn = red[v] < mn ? red[v] : mn;
-  for (uint32_t i0 = threadIdx.x; i0 < k; i0 += kHeld * nthr) {
-    uint64_t m[kHeld];
 #pragma unroll
-    for (int t = 0; t < kHeld; ++t)
-      m[t] = i0 == threadIdx.x ? first[t]
-                               : __hip_atomic_load(bm + min(i0 + t * nthr, k - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-#pragma unroll
-    for (int t = 0; t < kHeld; ++t)
-      if (i0 + t * nthr < k) bw[i0 + t * nthr] = batch_weight(mn, m[t], a.beta);
+  for (int t = 0; t < kHeldMasses; ++t) {
+    const uint32_t i = threadIdx.x + t * nthr;
+    if (i < k) bw[i] = batch_weight(mn, m[t], a.beta);
   }
 }
 
