@@ -123,7 +123,7 @@ int geometry(const apex_replay_config_t *c, Geometry *g)
   g->top_log2 = kFanoutLog2;
   if (n > kTopMax) {  // the summit
     g->top_log2 = 0;
-    while (((n - 1) >> g->top_log2) + 1 > kTopMax) ++g->top_log2;
+    while (((n - 1) >> g->top_log2) + 1 > kSummitMax) ++g->top_log2;
     g->level_off[l] = off;
     g->level_size[l] = ((n - 1) >> g->top_log2) + 1;
     off += round_up(g->level_size[l], kFanout);

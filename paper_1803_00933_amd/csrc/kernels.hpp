@@ -7,12 +7,14 @@
 //                  nodes.  A wavefront reads the 64 children of a node as one coalesced 512-byte row.
 //                  If the last of these levels has more than kTopMax nodes, a summit stands above it:
 //                  node i = sum of 2^top_log2 of its nodes, the smallest power of two that leaves at
-//                  most kTopMax.  So the level a walk starts from always fits the registers of one wave
-//                  (8 nodes per lane).  Where every workgroup staged the whole top in LDS instead, a
-//                  draw of 4096 from 2^24 slots (4352 nodes) took 11.5 us, now 7.2; the learner steps on
-//                  2^18 slots (4096 nodes) 10.6 us per launch, now 8.6.  Not fewer nodes than that:
-//                  every change of a mass is an atomic on every level, and atomics of different waves
-//                  on one address take about 10 ns one after the other.
+//                  most kSummitMax.  So the level a walk starts from always fits the registers of one wave
+//                  (8 nodes per lane, 16 if there are more than 512).  Where every workgroup staged the
+//                  whole top in LDS instead, a draw of 4096 from 2^24 slots (4352 nodes) took 16.3 us, now
+//                  11.0; the learner steps on 2^18 slots (4096 nodes) 8.8 us per launch, now 5.6.
+//                  Between 513 and 1024 nodes no summit: its round trip and its atomics cost more than the
+//                  wider read (steps of 512 on 50,000 slots, 782 nodes: 5.6 us with one, 5.2 without).
+//                  Not fewer nodes than that: every change of a mass is an atomic on every level, and
+//                  atomics of different waves on one cache line take some 6 ns one after the other.
 //   device state   head, tail, counters: read by the kernels, so the same launches can be replayed.
 // The set of transitions and the sampled indices do not depend on this shape: a sample is
 // defined by the cumulative mass in slot order, whatever tree sums it up.
@@ -28,7 +30,8 @@ namespace apex {
 constexpr uint32_t kFanoutLog2 = 6;
 constexpr uint32_t kFanout = 1u << kFanoutLog2;
 constexpr uint32_t kExportedTopMax = 4608;  // covers 2^24 + 2^20 slots with three levels
-constexpr uint32_t kTopMax = 512;           // nodes of the level that walks start from
+constexpr uint32_t kTopMax = 1024;          // nodes of the level that walks start from ...
+constexpr uint32_t kSummitMax = 512;        // ... where that is a summit
 constexpr uint32_t kMaxLevels = 8;
 
 struct DeviceState {
@@ -1123,53 +1126,87 @@ __device__ __forceinline__ uint64_t read_lane_u64(uint64_t v, uint32_t l)
 typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
 
 // The top level in the registers of one wave: lane l holds the masses v[0..8) of nodes 8l .. 8l+7 (zero beyond
-// the level).  load() only issues the loads (16 bytes wide), scan() waits for them.
+// the level), and, of a level of more than 512 nodes, w[0..8) of nodes 512 + 8l .. 512 + 8l+7.  load() only issues
+// the loads (16 bytes wide), scan() waits for them.
 struct TopLevel {
-  uint64_t v[8];
-  uint64_t before;  // sum of all nodes before this lane's
+  uint64_t v[8], w[8];
+  uint64_t before, before_w;  // sum of all nodes before this lane's (before_w: of the whole level if there are none)
+  bool wide;                  // the same for all lanes
+
+  static __device__ __forceinline__ void load_8(uint64_t (&r)[8], const uint64_t *top, uint32_t i0, uint32_t n_pad)
+  {
+#pragma unroll
+    for (int t = 0; t < 8; ++t) r[t] = 0;
+    if (i0 < n_pad) {
+#pragma unroll
+      for (int t = 0; t < 8; t += 2) {
+        const u64x2 v2 = *reinterpret_cast<const u64x2 *>(top + i0 + t);
+        r[t] = v2.x, r[t + 1] = v2.y;
+      }
+    }
+  }
 
   __device__ __forceinline__ void load(const uint64_t *top, uint32_t n_top)
   {
     const uint32_t i0 = 8 * (uint32_t)lane_id();
     const uint32_t n_pad = (n_top + kFanout - 1) & ~(kFanout - 1);  // the level is zero-padded to this in memory
+    wide = n_top > 512;
+    load_8(v, top, i0, n_pad);
+    if (wide) load_8(w, top, 512 + i0, n_pad);
+  }
+
+  static __device__ __forceinline__ uint64_t sum_8(const uint64_t (&r)[8])
+  {
+    uint64_t sum = 0;
 #pragma unroll
-    for (int t = 0; t < 8; ++t) v[t] = 0;
-    if (i0 < n_pad) {
-#pragma unroll
-      for (int t = 0; t < 8; t += 2) {
-        const u64x2 v2 = *reinterpret_cast<const u64x2 *>(top + i0 + t);
-        v[t] = v2.x, v[t + 1] = v2.y;
-      }
-    }
+    for (int t = 0; t < 8; ++t) sum += r[t];
+    return sum;
   }
 
   // Returns the sum of the whole level.
   __device__ __forceinline__ uint64_t scan()
   {
-    uint64_t mine = 0;
-#pragma unroll
-    for (int t = 0; t < 8; ++t) mine += v[t];
-    const uint64_t incl = wave_inclusive_scan(mine);
+    const uint64_t mine = sum_8(v), incl = wave_inclusive_scan(mine);
     before = incl - mine;
-    return read_lane_u64(incl, kWave - 1);
+    uint64_t total = read_lane_u64(incl, kWave - 1);
+    before_w = total;
+    if (wide) {
+      const uint64_t mine_w = sum_8(w), incl_w = wave_inclusive_scan(mine_w);
+      before_w = total + incl_w - mine_w;
+      total += read_lane_u64(incl_w, kWave - 1);
+    }
+    return total;
   }
 
-  // The last node whose prefix sum is <= x: the lane by one ballot, the node inside the lane by eight comparisons
-  // that every lane makes for itself, the winner's values by lane reads.
-  __device__ __forceinline__ TopHit find(uint64_t x) const
+  // The group of eight nodes (one lane's v or w) that holds x: the last one whose prefix sum is <= x.
+  __device__ __forceinline__ uint32_t find_group(uint64_t x) const
   {
-    const uint32_t l = __popcll(__ballot(before <= x)) - 1;  // lane 0 has before = 0 <= x
-    uint64_t p = before, p_hit = before, v_hit = v[0];
+    // lane 0 has before = 0 <= x; without w the second ballot is empty, x being below the level's sum
+    return __popcll(__ballot(before <= x)) + __popcll(__ballot(before_w <= x)) - 1;
+  }
+
+  static __device__ __forceinline__ TopHit find_in(const uint64_t (&r)[8], uint64_t before_r, uint32_t group, uint64_t x)
+  {
+    const uint32_t l = group & (kWave - 1);
+    uint64_t p = before_r, p_hit = before_r, v_hit = r[0];
     uint32_t t_hit = 0;
 #pragma unroll
     for (int t = 1; t < 8; ++t) {
-      p += v[t - 1];
+      p += r[t - 1];
       const bool le = p <= x;  // true for the first few t only: the prefix sums do not decrease
       t_hit = le ? t : t_hit;
       p_hit = le ? p : p_hit;
-      v_hit = le ? v[t] : v_hit;
+      v_hit = le ? r[t] : v_hit;
     }
-    return TopHit{8ull * l + read_lane_u32(t_hit, l), x - read_lane_u64(p_hit, l), read_lane_u64(v_hit, l)};
+    return TopHit{8ull * group + read_lane_u32(t_hit, l), x - read_lane_u64(p_hit, l), read_lane_u64(v_hit, l)};
+  }
+
+  // The last node whose prefix sum is <= x: the group by ballots, the node inside it by eight comparisons that every
+  // lane makes for itself, the winner's values by lane reads.
+  __device__ __forceinline__ TopHit find(uint64_t x) const
+  {
+    const uint32_t group = find_group(x);
+    return group < kWave ? find_in(v, before, group, x) : find_in(w, before_w, group, x);
   }
 };
 
@@ -1344,10 +1381,15 @@ __global__ __launch_bounds__(kSampleMaxThreads) void sample_kernel(SampleArgs a)
     uint32_t l = 0;
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
-      const uint32_t ls = __popcll(__ballot(top.before <= read_lane_u64(walk.x, 16 * s))) - 1;
+      const uint32_t ls = top.find_group(read_lane_u64(walk.x, 16 * s));
       l = lane / 16 == (uint32_t)s ? ls : l;
     }
-    walk.x -= __shfl(top.before, l, kWave);
+    uint64_t before = __shfl(top.before, l & (kWave - 1), kWave);
+    if (top.wide) {
+      const uint64_t before_w = __shfl(top.before_w, l & (kWave - 1), kWave);
+      before = l < kWave ? before : before_w;
+    }
+    walk.x -= before;
     walk.idx = l;
     row_descend(walk, top_level, 3);
     const uint64_t head_slot = ring_slot(tv, head);

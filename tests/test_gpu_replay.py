@@ -77,12 +77,13 @@ def test_random_operation_sequences(P, C, ob, ab):
         sample_both(g, o, rng, 2, 64)
 
 
-@pytest.mark.parametrize("P", [512, 513, 1025, 4608, 4609, 32_768, 32_769, 294_912, 294_913])
+@pytest.mark.parametrize("P", [512, 513, 1024, 1025, 4608, 4609, 32_768, 32_769, 65_536, 65_537, 294_912, 294_913])
 def test_tree_shapes_around_the_summit(P):
     """Sizes on both sides of every border of the tree's shape: the level that walks start from is the leaves themselves
-    (512), a summit of 2, 4 and 16 children per node (513, 1025, 4608; 32,769 and 294,912 above more levels), or an
-    ordinary level.  Rounds that wrap around the ring and cross several workgroups, draws at the very ends of the
-    cumulative mass, updates and evictions, bit for bit against the oracle."""
+    (512 in one read, 513 and 1024 in two), a summit of 4 and 16 children per node (1025, 4608; 65,537 and 294,912 above
+    more levels), or an ordinary level (32,768 in one read, 32,769 and 65,536 in two).  Rounds that wrap around the ring
+    and cross several workgroups, draws at the very ends of the cumulative mass, updates and evictions, bit for bit
+    against the oracle."""
     rng = np.random.default_rng(P)
     C = P * 3 // 4
     g, o = make_pair(C, P, 16, 4)
@@ -893,13 +894,15 @@ def test_pipeline_graph_replays(nb, k, ob):
     (5000, 4000, 1024, 32768),       # as many samples as a workgroup has lanes, largest fused row
     (5000, 4000, 1, 4224),           # batches of one
     (60_000, 50_000, 512, 256),      # short rows (feature vectors): a few lanes of each workgroup copy
-    (70_000, 60_000, 300, 4224),     # a top level of 1094 nodes: the drawing wave stages it in chunks of four passes
-    (280_000, 250_000, 256, 1040),   # a ragged top level of 4375 nodes (three chunks)
-    (4608, 4000, 64, 4112),          # one level of the largest size
-    (33_000, 30_000, 517, 2064),     # 516 top nodes (two passes of the drawing wave), k no multiple of 8
+    (70_000, 60_000, 300, 4224),     # a summit of 274 nodes over 1094
+    (280_000, 250_000, 256, 1040),   # a summit of 274 nodes over 4375, a ragged one
+    (4608, 4000, 64, 4112),          # a summit over the leaves
+    (33_000, 30_000, 517, 2064),     # 516 top nodes (two reads of the drawing wave), k no multiple of 8
+    (65_536, 60_000, 128, 4112),     # 1024 top nodes, the most without a summit
+    (1000, 900, 64, 64),             # 1000 top nodes that are the leaves
     (9000, 8000, 1000, 48),          # two passes over the pending pairs, a ragged last one
-    (5000, 4000, 100, 4100),         # rows that are no multiple of 16 bytes: 4-byte vectors, several passes per row
-    (3000, 2500, 64, 1001),          # odd row size: byte copies
+    (5000, 4000, 100, 4100),         # rows that are no multiple of 16 bytes: the last piece overlaps the one before
+    (3000, 2500, 64, 1001),          # odd row size: unaligned pieces
     (3000, 2500, 96, 56448),         # rows longer than one pass of a workgroup (two frame stacks per transition)
     (3000, 2500, 40, 32784),         # just beyond one pass
 ])
