@@ -91,14 +91,19 @@ __device__ __forceinline__ uint32_t fanout_log2(const TreeView &tv, uint32_t l)
   return l + 1 == tv.nlev ? tv.top_log2 : kFanoutLog2;
 }
 
-// Adds delta (mod 2^64) to every ancestor of `slot` above level 0.
-__device__ __forceinline__ void add_to_ancestors(const TreeView &tv, uint64_t slot, uint64_t delta)
+// Adds delta (mod 2^64) to every ancestor of `slot` above level 0 (below level `levels`).
+__device__ __forceinline__ void add_to_ancestors(const TreeView &tv, uint64_t slot, uint64_t delta, uint32_t levels)
 {
   uint64_t idx = slot;
-  for (uint32_t l = 1; l < tv.nlev; ++l) {
+  for (uint32_t l = 1; l < levels; ++l) {
     idx >>= fanout_log2(tv, l);
     atomic_add_u64(tv.level[l] + idx, delta);
   }
+}
+
+__device__ __forceinline__ void add_to_ancestors(const TreeView &tv, uint64_t slot, uint64_t delta)
+{
+  add_to_ancestors(tv, slot, delta, tv.nlev);
 }
 
 // Where the runs of neighbouring lanes with equal `node` lie that a prefix sum of the lanes' values is cut into.
@@ -484,9 +489,17 @@ __device__ __forceinline__ UpdateLane update_batch_load(const UpdateArgs &ua)
   return u;
 }
 
-// Second half.  h_slot, h_pos: LDS, kDedupeSlots words each.  Called by every thread of the workgroup.
+// A batch of more pairs than this on a tree with a summit collects what it adds to the summit in LDS.  The changes of one
+// batch meet on few cache lines there, and one compute unit sends all of its atomics: 1024 drawn keys of 2^18 slots 6.1 us
+// without, 5.6 so, of 70,000 slots 7.2 and 5.8, of 2^24 7.0 and 6.8; 513 to 768 keys 4.3 - 7.1 and 4.2 - 6.2.  For 512 the
+// two are even, and below that clearing and reading the sums costs more than it saves (32 keys: 4.0 and 4.9).
+constexpr uint32_t kSummitInLdsAbove = 512;
+
+// Second half.  h_slot, h_pos: LDS, kDedupeSlots words each; summit: with kSummitInLds, kSummitMax words of it.  Called
+// by every thread of the workgroup.
+template <bool kSummitInLds = false>
 __device__ __forceinline__ void update_batch_apply(const UpdateArgs &ua, UpdateLane u, uint32_t *h_slot,
-                                                   uint32_t *h_pos)
+                                                   uint32_t *h_pos, unsigned long long *summit = nullptr)
 {
   const TreeView &tv = ua.tv;
   const uint32_t i = threadIdx.x;
@@ -494,6 +507,8 @@ __device__ __forceinline__ void update_batch_apply(const UpdateArgs &ua, UpdateL
     h_slot[t] = 0xffffffffu;  // no slot has this number: max_slots <= 2^31
     h_pos[t] = 0;
   }
+  if (kSummitInLds)
+    for (uint32_t t = i; t < kSummitMax; t += blockDim.x) summit[t] = 0;
   __syncthreads();
   const bool valid = i < ua.m && u.key >= u.head && u.key < u.tail;
   const bool stale = i < ua.m && !valid;
@@ -518,9 +533,16 @@ __device__ __forceinline__ void update_batch_apply(const UpdateArgs &ua, UpdateL
   }
   if (stale && ua.qs.q_taken && ua.qs.prio_out) ua.qs.prio_out[i] = 0.0f;
   __syncthreads();
-  if (valid && h_pos[h] == i + 1) {
+  const bool wins = valid && h_pos[h] == i + 1;
+  if constexpr (kSummitInLds) {  // (ahead of the atomics on memory: no wave waits for those at the barrier)
+    if (wins) atomicAdd(&summit[slot >> (kFanoutLog2 * (tv.nlev - 2) + tv.top_log2)], (unsigned long long)(q - old));
+    __syncthreads();
+    for (uint32_t t = i; t < tv.n_top; t += blockDim.x)
+      if (summit[t]) atomic_add_u64(tv.level[tv.nlev - 1] + t, summit[t]);
+  }
+  if (wins) {
     tv.level[0][slot] = q;
-    add_to_ancestors(tv, slot, q - old);
+    add_to_ancestors(tv, slot, q - old, kSummitInLds ? tv.nlev - 1 : tv.nlev);
   }
   const uint64_t ns = __popcll(__ballot(stale)), nc = __popcll(__ballot(clamped));
   if (lane_id() == 0) {
@@ -529,16 +551,19 @@ __device__ __forceinline__ void update_batch_apply(const UpdateArgs &ua, UpdateL
   }
 }
 
-__device__ __forceinline__ void update_batch_in_block(const UpdateArgs &ua, uint32_t *h_slot, uint32_t *h_pos)
-{
-  update_batch_apply(ua, update_batch_load(ua), h_slot, h_pos);
-}
-
 __global__ __launch_bounds__(1024) void update_small_kernel(UpdateArgs ua)
 {
   __shared__ uint32_t h_slot[kDedupeSlots];
   __shared__ uint32_t h_pos[kDedupeSlots];
-  update_batch_in_block(ua, h_slot, h_pos);
+  update_batch_apply(ua, update_batch_load(ua), h_slot, h_pos);
+}
+
+__global__ __launch_bounds__(1024) void update_small_summit_kernel(UpdateArgs ua)
+{
+  __shared__ uint32_t h_slot[kDedupeSlots];
+  __shared__ uint32_t h_pos[kDedupeSlots];
+  __shared__ unsigned long long summit[kSummitMax];
+  update_batch_apply<true>(ua, update_batch_load(ua), h_slot, h_pos, summit);
 }
 
 // Importance-sampling weights of one batch of k samples, by one workgroup:

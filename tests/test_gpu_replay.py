@@ -130,6 +130,28 @@ def test_sample_in_one_launch(ob, ab, nb, k):
         sample_both(gp, op, rng, nb, k)
 
 
+@pytest.mark.parametrize("P", [1025, 4608, 70_000, 294_912])
+@pytest.mark.parametrize("m", [512, 513, 1024])
+def test_updates_on_trees_with_a_summit(P, m):
+    """Batches on both sides of the line above which what they add to the summit is collected on the way: random keys,
+    the keys of a batch, one key again and again, stale ones; given priorities and those of the learner's Q-values."""
+    rng = np.random.default_rng(P + m)
+    g, o = make_pair(P - 200, P, 16, 4)
+    assert add_both(g, o, rng, P - 200) == 0 and add_both(g, o, rng, 150) == 0
+    assert g.evict() == o.evict()
+    for keys in (rng.integers(0, o.tail + 50, m), sample_both(g, o, rng, 1, m)["key"], np.full(m, o.head + 5)):
+        keys, pr = keys.astype(np.uint64), rng.lognormal(0, 2, m).astype(F32)
+        assert g.update_priorities(dev(keys), dev(pr)) == o.update_priorities(keys, pr) == 0
+        check_gpu_tree(g, o)
+        q = [rng.standard_normal(shape).astype(F32) for shape in (m, (m, 3), (m, 3))]
+        p_out = torch.empty(m, dtype=torch.float32, device="cuda:0")
+        rc, p_ref = o.update_from_q(keys, *q)
+        assert g.update_from_q(dev(keys), *(dev(x) for x in q), p_out) == rc == 0
+        assert np.array_equal(host(p_out).view(np.uint32), p_ref.view(np.uint32))
+        check_gpu_tree(g, o)
+    sample_both(g, o, rng, 1, m)
+
+
 @pytest.mark.parametrize("prioritized_eviction", [False, True])
 def test_sample_recovers_from_stale_tickets(prioritized_eviction):
     """Sample calls that overlapped although they must be ordered can leave the tickets of the weights at any value
