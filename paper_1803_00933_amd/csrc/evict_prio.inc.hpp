@@ -34,6 +34,23 @@ __device__ __forceinline__ bool pe_key_valid(const PeView &v, uint64_t key, uint
   return v.gen[slot] == (uint32_t)(key >> 32) && v.ts.level[0][slot] != 0;
 }
 
+// add_runs_to_ancestors for both trees: the runs lie alike, so they are found once.
+__device__ __forceinline__ void pe_add_runs(const PeView &v, bool active, uint32_t slot, uint64_t d1, uint64_t d2)
+{
+  const uint64_t incl1 = wave_inclusive_scan(active ? d1 : 0), incl2 = wave_inclusive_scan(active ? d2 : 0);
+  uint64_t idx = slot;
+  for (uint32_t l = 1; l < v.ts.nlev; ++l) {
+    idx >>= fanout_log2(v.ts, l);
+    const LaneRuns run = lane_runs(active ? idx : ~0ull);
+    const int lane_before = run.first > 0 ? run.first - 1 : 0;
+    const uint64_t before1 = __shfl(incl1, lane_before, kWave), before2 = __shfl(incl2, lane_before, kWave);
+    if (active && run.ends) {
+      atomic_add_u64(v.ts.level[l] + idx, incl1 - (run.first > 0 ? before1 : 0));
+      atomic_add_u64(v.te.level[l] + idx, incl2 - (run.first > 0 ? before2 : 0));
+    }
+  }
+}
+
 __global__ __launch_bounds__(256) void pe_add_kernel(PeView v, PeState *__restrict__ st, uint64_t count,
                                                      const float *__restrict__ prio)
 {
@@ -50,8 +67,7 @@ __global__ __launch_bounds__(256) void pe_add_kernel(PeView v, PeState *__restri
     v.te.level[0][slot] = q2;
     nclamp = (uint32_t)c1 + (uint32_t)c2;
   }
-  add_runs_to_ancestors(v.ts, i < count, slot, q1);
-  add_runs_to_ancestors(v.te, i < count, slot, q2);
+  pe_add_runs(v, i < count, slot, q1, q2);
   const uint64_t nc = wave_sum(nclamp);
   if (nc && lane_id() == 0) atomic_add_u64(&st->base.n_clamped, nc);
   // the last workgroup to finish moves the free ring's head and the insertion count on
@@ -132,8 +148,7 @@ __global__ __launch_bounds__(kPeAddThreads) void pe_add_rows_kernel(PeView v, Pe
       v.te.level[0][slot] = q2;
       nclamp = (uint32_t)c1 + (uint32_t)c2;
     }
-    add_runs_to_ancestors(v.ts, active, slot, q1);
-    add_runs_to_ancestors(v.te, active, slot, q2);
+    pe_add_runs(v, active, slot, q1, q2);
     const uint64_t nc = wave_sum(nclamp);
     if (nc && lane_id() == 0) atomic_add_u64(&st->base.n_clamped, nc);
   }
@@ -188,8 +203,7 @@ __device__ __forceinline__ void pe_update_small_block(const PeView &v, PeState *
     v.ts.level[0][slot] = q1;
     v.te.level[0][slot] = q2;
   }
-  add_runs_to_ancestors(v.ts, wins, slot, d1);  // the keys of a drawn batch ascend: neighbours share their ancestors
-  add_runs_to_ancestors(v.te, wins, slot, d2);
+  pe_add_runs(v, wins, slot, d1, d2);  // the keys of a drawn batch ascend: neighbours share their ancestors
   const uint64_t ns = __popcll(__ballot(stale)), nc = wave_sum(nclamp);
   if (lane_id() == 0) {
     if (ns) atomic_add_u64(&st->base.n_stale, ns);
@@ -231,8 +245,7 @@ __device__ __forceinline__ void pe_writeback_block(const PeView &v, PeState *__r
       v.te.level[0][s] = q2;
     }
   }
-  add_runs_to_ancestors(v.ts, wins, s, d1);
-  add_runs_to_ancestors(v.te, wins, s, d2);
+  pe_add_runs(v, wins, s, d1, d2);
   const uint64_t nc = wave_sum(nclamp);
   if (nc && lane_id() == 0) atomic_add_u64(&st->base.n_clamped, nc);
 }
@@ -274,24 +287,23 @@ __global__ __launch_bounds__(256) void pe_update_apply_kernel(PeView v, PeState 
                                                               uint32_t *__restrict__ claim)
 {
   const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-  uint32_t nclamp = 0;
-  if (i < m) {
-    uint32_t slot;
-    if (pe_key_valid(v, key[i], &slot)) {  // a winner only ever writes non-zero masses, so this cannot flip
-      bool c1, c2;
-      const float p = prio[i];
-      const uint64_t q1 = quantise_priority(p, v.qs, &c1), q2 = quantise_priority(p, v.qe, &c2);
-      nclamp = (uint32_t)c1 + (uint32_t)c2;
-      if (claim[slot] == i + 1) {
-        const uint64_t o1 = v.ts.level[0][slot], o2 = v.te.level[0][slot];
-        v.ts.level[0][slot] = q1;
-        v.te.level[0][slot] = q2;
-        add_to_ancestors(v.ts, slot, q1 - o1);
-        add_to_ancestors(v.te, slot, q2 - o2);
-        claim[slot] = 0;
-      }
+  uint32_t nclamp = 0, slot = 0;
+  bool wins = false;
+  uint64_t d1 = 0, d2 = 0;
+  if (i < m && pe_key_valid(v, key[i], &slot)) {  // a winner only ever writes non-zero masses, so this cannot flip
+    bool c1, c2;
+    const float p = prio[i];
+    const uint64_t q1 = quantise_priority(p, v.qs, &c1), q2 = quantise_priority(p, v.qe, &c2);
+    nclamp = (uint32_t)c1 + (uint32_t)c2;
+    if (claim[slot] == i + 1) {
+      wins = true;
+      d1 = q1 - v.ts.level[0][slot], d2 = q2 - v.te.level[0][slot];
+      v.ts.level[0][slot] = q1;
+      v.te.level[0][slot] = q2;
+      claim[slot] = 0;
     }
   }
+  pe_add_runs(v, wins, slot, d1, d2);  // the keys of a drawn batch ascend: neighbours share their ancestors
   const uint64_t nc = wave_sum(nclamp);
   if (nc && lane_id() == 0) atomic_add_u64(&st->base.n_clamped, nc);
 }
@@ -375,8 +387,7 @@ __global__ __launch_bounds__(kPeScanThreads) void pe_remove_kernel(PeView v, PeS
     v.te.level[0][slot] = 0;
     v.free_ring[ring_slot(v.ts, st->free_tail + place)] = slot;
   }
-  add_runs_to_ancestors(v.ts, counts, slot, 0 - o1);  // the candidates ascend: neighbours share their ancestors
-  add_runs_to_ancestors(v.te, counts, slot, 0 - o2);
+  pe_add_runs(v, counts, slot, 0 - o1, 0 - o2);  // the candidates ascend: neighbours share their ancestors
   // the last workgroup to have read the round's counters closes the round: its ticket comes with what the others
   // have removed (ticket in the low word, removals in the high one)
   __syncthreads();
