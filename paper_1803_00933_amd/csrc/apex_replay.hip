@@ -222,12 +222,22 @@ struct SideJobs {
   ClaimArgs claim{};                        // claim.m != 0: first pass of a larger update (short rows only)
 };
 
+// The write-back of a batch that has just been drawn, spread over the workgroups that copy its rows (kUpdate = 2 of
+// copy_rows_long_kernel), up to this many pairs (every pair looks through those behind it for its slot) ...
+constexpr uint64_t kSpreadWritebackMax = 1024;
+// ... and for rows above this length.  (Steps of 1024 on 2^20 slots, rows of 1028 bytes: 16.1 us so, 22.8 with the update
+// in one workgroup of a launch of its own; 2 x 512 of 4092 bytes 15.9 and 22.8; 8 x 128 of 1028 bytes from 20,000 slots, where
+// it gains least, 15.5 and 15.0.)
+constexpr uint64_t kSpreadWritebackAbove = 1024;
+
 template <typename Vec>
 int launch_copy_t(const uint8_t *src, const RowMap &smap, uint8_t *dst, const RowMap &dmap, uint64_t nrows,
                   uint64_t row_bytes, uint32_t vpr, hipStream_t stream, SideJobs *jobs)
 {
   constexpr int kUnroll = kLongCopyUnroll, kThreads = kLongCopyThreads;
-  if (vpr > 256) {
+  const bool spread = jobs && jobs->ua.m && jobs->ua.slot_hint && jobs->ua.m <= kSpreadWritebackMax &&
+                      row_bytes > kSpreadWritebackAbove;
+  if (vpr > 256 || spread) {
     const uint32_t cpr = (vpr + kThreads * kUnroll - 1) / (kThreads * kUnroll);
     if (nrows * cpr > 0x7ffffff0ull) return APEX_ERR_TOO_LARGE;
     const uint32_t blocks = (uint32_t)(nrows * cpr);
@@ -685,6 +695,12 @@ int sample_begin_impl(apex_replay *r, uint32_t num_batches, uint32_t k, const ui
   SampleArgs a;
   const int rc = sample_args(r, num_batches, k, rnd, key_out, slot_out, mass_out, act_out, ret_out, gacc_out, &a);
   return rc != APEX_OK ? rc : launch_sample(a, num_batches, stream);
+}
+
+// Whether a batch of `per` samples goes that way when its own priorities are written back.
+bool writeback_spreads(const apex_replay *r, uint64_t per)
+{
+  return per <= kSpreadWritebackMax && r->cfg.obs_bytes > kSpreadWritebackAbove;
 }
 
 // Whether the rows' gather rides in the draw's launch: short rows do (the wave that has drawn a sample copies its row);

@@ -272,7 +272,7 @@ int apex_pipeline_steps(apex_pipeline_t *p, uint32_t n, float beta, const uint64
       ++p->step;
       continue;
     }
-    if (gather_in_draw(p->r)) {
+    if (gather_in_draw(p->r) && !(new_prio && writeback_spreads(p->r, per))) {
       // short rows: draw, gather, weights (and the first pass of a large update) in one launch, then the update
       const bool claim = new_prio && per > 1024;
       APEX_TRY(sample_in_one(p->r, p->nb, p->k, beta, rnd + i * per, b.key, b.slot, b.mass, b.weight, b.obs, b.act,

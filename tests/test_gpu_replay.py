@@ -977,6 +977,42 @@ def test_one_launch_per_learner_step(P, C, k, ob):
     pipe.close()
 
 
+@pytest.mark.parametrize("ob", [1024, 1025, 1028, 4096, 4097])
+@pytest.mark.parametrize("nb,k", [(1, 1024), (2, 512), (5, 33), (2, 513)])
+def test_steps_that_are_no_single_launch(ob, nb, k):
+    """Pipeline steps of two buffer sets or several batches, rows and batches on both sides of the lines between the
+    write-back spread over the copying workgroups and an update of its own, and the same through the plain halves.
+    Heavy-tailed priorities: batches draw slots several times."""
+    from paper_1803_00933_amd import apex
+    rng = np.random.default_rng(ob + k)
+    g, o = make_pair(3000, 3500, ob, 4)
+    heavy = lambda rng, n: rng.pareto(0.4, n) + 1e-3
+    assert add_both(g, o, rng, 3000, heavy) == 0
+    n, per = 3, nb * k
+    pipe = apex.Pipeline(g, 2, nb, k)
+    rnd, newp = rng.integers(0, U64, (n, per), dtype=np.uint64), heavy(rng, (n, per)).astype(F32)
+    d_rnd, d_newp = dev(rnd), dev(newp)
+    assert pipe.fork() == 0 and pipe.steps(n, 0.4, d_rnd, d_newp)[0] == 0 and pipe.join() == 0
+    torch.cuda.synchronize()
+    for i in range(n):
+        oo = o.sample(nb, k, 0.4, rnd[i])[1]
+        assert len(np.unique(oo["slot"])) < per
+        assert o.update_priorities(oo["key"], newp[i]) == 0
+        if i >= n - 2:
+            assert_sample_equal(pipe.sets[i % 2], oo)
+    check_gpu_tree(g, o)
+    out = g.alloc_sample_outputs(nb, k)
+    out["mass"] = torch.empty(per, dtype=torch.int64, device="cuda:0")
+    oo = o.sample(nb, k, 0.4, rnd[0])[1]
+    assert o.update_priorities(oo["key"], newp[1]) == 0
+    assert g.sample_begin(nb, k, d_rnd[0], out) == 0
+    assert g.sample_finish_writeback(nb, k, 0.4, out, d_newp[1]) == 0
+    torch.cuda.synchronize()
+    assert_sample_equal(out, oo)
+    check_gpu_tree(g, o)
+    pipe.close()
+
+
 @pytest.mark.parametrize("ob,k,extra", [(28224, 512, 0), (4224, 100, 0), (64, 128, 0), (4224, 700, 600),
                                         (64, 700, 600), (7, 512, 700)])   # short rows, more than 1024 pairs
 def test_finish_with_update_riding_along(ob, k, extra):
