@@ -5,6 +5,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <mutex>
 #include <new>
 #include <vector>
@@ -578,6 +579,14 @@ int apex_nstep_priorities(uint32_t S, uint32_t T, uint32_t n, uint32_t A, const 
 
 namespace {
 
+// Threads per workgroup of add_leaves_kernel and evict_leaves_kernel for `count` transitions: no more than there is work
+// for (add and eviction of 1 to 130 transitions of 2^20 slots 9.2 - 9.8 us, 8.5 - 9.2 so), but two waves, so that the
+// ticket's round trip runs beside those of the first wave's atomics.
+uint32_t leaves_threads(uint64_t count)
+{
+  return (uint32_t)std::clamp<uint64_t>(round_up(count, kWave), 2 * kWave, kLeavesThreads);
+}
+
 // Enters `count` transitions under the next keys; columns: as far as their small columns are to be copied too.
 int publish(apex_replay_t *r, uint64_t count, const float *prio, const AddColumns &columns, uint64_t *first_key_out,
             void *hip_stream)
@@ -588,7 +597,8 @@ int publish(apex_replay_t *r, uint64_t count, const float *prio, const AddColumn
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     const uint64_t second = r->second_words();
     r->tree_changed(second);
-    add_leaves_kernel<<<dim3(blocks_for(count, kLeavesThreads)), dim3(kLeavesThreads), 0, stream>>>(
+    const uint32_t threads = leaves_threads(count);
+    add_leaves_kernel<<<dim3(blocks_for(count, threads)), dim3(threads), 0, stream>>>(
         AddLeavesArgs{r->tv, second, r->state(), count, prio, r->qp}, columns);
     APEX_HIP(hipGetLastError());
   }
@@ -1095,7 +1105,8 @@ int apex_replay_evict(apex_replay_t *r, uint64_t *evicted_out, void *hip_stream)
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   const uint64_t second = r->second_words();
   r->tree_changed(second);
-  evict_leaves_kernel<<<dim3(blocks_for(e, kLeavesThreads)), dim3(kLeavesThreads), 0, stream>>>(EvictLeavesArgs{r->tv, second, r->state(), e});
+  const uint32_t threads = leaves_threads(e);
+  evict_leaves_kernel<<<dim3(blocks_for(e, threads)), dim3(threads), 0, stream>>>(EvictLeavesArgs{r->tv, second, r->state(), e});
   APEX_HIP(hipGetLastError());
   r->head += e;
   return APEX_OK;

@@ -865,7 +865,7 @@ __device__ __forceinline__ void add_leaves_block(const AddLeavesArgs &a, uint32_
   if (nc && lane_id() == 0) atomic_add_u64(&a.st->n_clamped, nc);
 }
 
-constexpr int kLeavesThreads = 1024;  // workgroups of add_leaves_kernel and evict_leaves_kernel
+constexpr int kLeavesThreads = 1024;  // most threads per workgroup of add_leaves_kernel and evict_leaves_kernel
 
 // Small payload columns of the transitions that add_leaves_kernel enters (each may be null).
 struct AddColumns {

@@ -152,6 +152,21 @@ def test_updates_on_trees_with_a_summit(P, m):
     sample_both(g, o, rng, 1, m)
 
 
+@pytest.mark.parametrize("P", [3000, 100_000])
+def test_adds_and_evictions_at_the_edges_of_their_workgroups(P):
+    """Rounds of one wave, of whole and ragged workgroups and just beyond the largest one, each evicted again."""
+    rng = np.random.default_rng(P)
+    C = P - 1100
+    g, o = make_pair(C, P, 16, 4)
+    assert add_both(g, o, rng, C) == 0
+    for cnt in (1, 63, 64, 65, 128, 129, 191, 1023, 1024, 1025):
+        assert add_both(g, o, rng, cnt) == 0
+        check_gpu_tree(g, o)
+        assert g.evict() == o.evict() == (0, cnt)
+        check_gpu_tree(g, o)
+    sample_both(g, o, rng, 1, 256)
+
+
 @pytest.mark.parametrize("prioritized_eviction", [False, True])
 def test_sample_recovers_from_stale_tickets(prioritized_eviction):
     """Sample calls that overlapped although they must be ordered can leave the tickets of the weights at any value
