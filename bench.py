@@ -33,13 +33,13 @@ ADD_EVERY, EVICT_EVERY = 25, 100
 STEP_ALGORITHMIC_BYTES = 512 * 57030
 
 # HBM traffic of one launch of the learner-step kernel as the hardware counters saw it.  A RECORDED figure, not
-# measured by this run: two `rocprofv3 --pmc` runs of this script (FETCH_SIZE, then WRITE_SIZE; KiB per
+# measured by this run: two `rocprofv3 --pmc` runs of `--profile-loop 200` (FETCH_SIZE, then WRITE_SIZE; KiB per
 # dispatch, averaged over the kernel's dispatches), each scaled by what the same counter reads for the plain
-# 508,032,000-byte payload copy of an add round in the same run (FETCH_SIZE: 248,074.09 KiB for 496,125 KiB
+# 508,032,000-byte payload copy of an add round in the same run (FETCH_SIZE: 248,074.0 KiB for 496,125 KiB
 # read, factor 1.9999; WRITE_SIZE: factor 1.0).  Source: profiles/learner_step_atari_hbm_traffic.txt.
 RECORDED_STEP_TRAFFIC = {
-    "fetch_kib_per_dispatch": 7647.976, "fetch_scale": 496125.0 / 248074.09,
-    "write_kib_per_dispatch": 14321.975, "write_scale": 1.0,
+    "fetch_kib_per_dispatch": 7637.306, "fetch_scale": 496125.0 / 248074.0,
+    "write_kib_per_dispatch": 14321.472, "write_scale": 1.0,
     "source": "profiles/learner_step_atari_hbm_traffic.txt (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE, recorded; "
               "not re-measured by this run)",
 }
@@ -980,7 +980,7 @@ def main():
         "hbm_frac_of_step": {"bytes_per_step": STEP_ALGORITHMIC_BYTES,
                              "pipeline_learner_only": frac(dt_pipe_learner / K * 1e6),
                              "pipeline_16_batches_per_call_learner_only": frac(us16)},
-        "roofline": {"bound": "hbm", "kernel": "learner_step_kernel<u32x4,512,4,1,0> (gather of one batch of frame "
+        "roofline": {"bound": "hbm", "kernel": "learner_step_kernel<Piece16,512,4,0> (gather of one batch of frame "
                                                "stacks + IS weights + priority write-back + draw of the next "
                                                "batch; distinct rows every launch)",
                      "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
@@ -989,7 +989,7 @@ def main():
                      "us_per_launch": step_us, "launches_timed": K_roof,
                      "timing": "HIP events around back-to-back launches of the learner-only loop: launch to "
                                "launch, gaps included"},
-        "roofline_add_payload": {"bound": "hbm", "kernel": "copy_rows_dense_kernel<u32x4,2> (18,000 frame stacks "
+        "roofline_add_payload": {"bound": "hbm", "kernel": "copy_rows_dense_kernel<Piece16,2> (18,000 frame stacks "
                                                            "of an add round into the ring)",
                                  "achieved": ops["add_payload_GBps"], "peak": HBM_PEAK_GBS, "unit": "GB/s",
                                  "frac": ops["add_payload_GBps"] / HBM_PEAK_GBS,

@@ -665,7 +665,11 @@ int launch_sample(SampleArgs &a, uint32_t num_batches, hipStream_t stream, Ticke
     if (num_batches > tickets->batches) tickets->batches = num_batches;
     a.ticket_batches = tickets->batches;
   }
-  sample_kernel<<<dim3(wgs, num_batches), dim3(threads), 0, stream>>>(a);
+  const dim3 grid(wgs, num_batches), block(threads);
+  if (a.tv.n_top > 512)
+    sample_kernel<true><<<grid, block, 0, stream>>>(a);
+  else
+    sample_kernel<false><<<grid, block, 0, stream>>>(a);
   return hip_failed(hipGetLastError()) ? APEX_ERR_HIP : APEX_OK;
 }
 

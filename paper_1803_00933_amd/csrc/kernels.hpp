@@ -879,7 +879,8 @@ struct AddColumns {
 // Up to this many action bytes a lane of add_leaves_kernel copies a transition's small columns on the way: both launches
 // are a few dependent loads and a round trip of atomics, so one of them goes.  More bytes would be strided accesses, one
 // cache line per lane, which add_payload_short_kernel shares out over several lanes.
-// Actor round of 18,000 frame stacks (n-step, payload, masses, eviction) 180.8 -> 178.3 us with the launch gone.
+// Actor round of 18,000 frame stacks (n-step, payload, masses, eviction): 178 - 180 us either way, the payload copy bounds it;
+// add and eviction of 700 rows of 5000 bytes 14.6 -> 11.1 us, the pieces of any alignment included.
 constexpr uint32_t kColumnsInAddBytes = 16;
 
 __global__ __launch_bounds__(kLeavesThreads) void add_leaves_kernel(AddLeavesArgs a, AddColumns c)
@@ -1082,9 +1083,10 @@ __global__ __launch_bounds__(256) void update_apply_kernel(TreeView tv, DeviceSt
 }
 
 // --------------------------------------------------------------------------------------------
-// sample: stratified descent, one wavefront per sample.  The importance weights need the
-// smallest mass of a whole batch; they are written by the kernel that runs next (the gather,
-// or batch_weights_kernel), so this one needs no fence or counter between workgroups.
+// sample: stratified descent, four samples per wavefront (sample_kernel), and in the same launch whatever of
+// replay.Sample the caller wants there.  The importance weights need the smallest mass of a whole batch, which the
+// workgroups of a batch settle through a ticket; where another launch follows anyway (the gather of long rows), or the
+// batch is too large for one workgroup's registers, that launch writes them (batch_weights).
 // --------------------------------------------------------------------------------------------
 // What every draw needs, and no more: the step kernel has these among its arguments, and with 8 bytes more in them its
 // launches took 0.2 us longer.
@@ -1153,6 +1155,8 @@ typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
 // The top level in the registers of one wave: lane l holds the masses v[0..8) of nodes 8l .. 8l+7 (zero beyond
 // the level), and, of a level of more than 512 nodes, w[0..8) of nodes 512 + 8l .. 512 + 8l+7.  load() only issues
 // the loads (16 bytes wide), scan() waits for them.
+// kMayBeWide: levels of more than 512 nodes are provided for.
+template <bool kMayBeWide>
 struct TopLevel {
   uint64_t v[8], w[8];
   uint64_t before, before_w;  // sum of all nodes before this lane's (before_w: of the whole level if there are none)
@@ -1175,7 +1179,7 @@ struct TopLevel {
   {
     const uint32_t i0 = 8 * (uint32_t)lane_id();
     const uint32_t n_pad = (n_top + kFanout - 1) & ~(kFanout - 1);  // the level is zero-padded to this in memory
-    wide = n_top > 512;
+    wide = kMayBeWide && n_top > 512;
     load_8(v, top, i0, n_pad);
     if (wide) load_8(w, top, 512 + i0, n_pad);
   }
@@ -1207,7 +1211,8 @@ struct TopLevel {
   __device__ __forceinline__ uint32_t find_group(uint64_t x) const
   {
     // lane 0 has before = 0 <= x; without w the second ballot is empty, x being below the level's sum
-    return __popcll(__ballot(before <= x)) + __popcll(__ballot(before_w <= x)) - 1;
+    const uint32_t l = __popcll(__ballot(before <= x)) - 1;
+    return kMayBeWide ? l + __popcll(__ballot(before_w <= x)) : l;
   }
 
   static __device__ __forceinline__ TopHit find_in(const uint64_t (&r)[8], uint64_t before_r, uint32_t group, uint64_t x)
@@ -1231,7 +1236,7 @@ struct TopLevel {
   __device__ __forceinline__ TopHit find(uint64_t x) const
   {
     const uint32_t group = find_group(x);
-    return group < kWave ? find_in(v, before, group, x) : find_in(w, before_w, group, x);
+    return !kMayBeWide || group < kWave ? find_in(v, before, group, x) : find_in(w, before_w, group, x);
   }
 };
 
@@ -1345,7 +1350,14 @@ __device__ __forceinline__ void copy_row_by_16(uint8_t *__restrict__ d, const ui
   }
 }
 
-constexpr uint32_t kGatherInDrawBytes = 4096;  // observation rows up to here can ride in the draw's launch
+// Observation rows up to here ride in the draw's launch.  Together / apart, us of device time for one batch of 32, one of 512,
+// one of 4096 and 16 of 512 from 2^18 slots (a launch less on the host, some 3 us, not counted):
+//   rows of  268 B  6.0 / 6.5    6.8 / 7.3   10.0 / 9.3    8.8 / 9.6
+//           1024 B  6.2 / 6.9    6.9 / 7.4   10.9 / 10.7   9.9 / 12.3
+//           2048 B  6.5 / 6.7    7.5 / 7.6   12.0 / 12.7  12.9 / 14.9
+//           4096 B  7.9 / 6.9    9.1 / 8.6   16.1 / 15.3  20.4 / 20.1
+//           5003 B 12.9 / 8.2   11.8 / 8.9   21.9 / 17.5  24.9 / 25.5
+constexpr uint32_t kGatherInDrawBytes = 4096;
 
 // Most samples of a batch whose weights the draw's launch can write: its last workgroup writes them all (16,384 of them
 // took that launch 21.6 us instead of 8.2 without, where a launch of its own takes 5).
@@ -1353,8 +1365,9 @@ constexpr uint32_t kWeightsInDrawMaxK = 4096;
 
 // Threads per workgroup.  16 samples (256 threads) spread the draws best over the chip; a batch of at most 32 goes into
 // one workgroup, whose waves agree on the smallest mass through LDS (32 samples: 5.7 instead of 6.5 us through tickets
-// and memory; with 64 the sixteen waves of the workgroup slow one another down, 8.8 us); a large one has fewer tickets to take and more threads for its weights with 32 (4096 samples: 10.9 us,
-// with 16 and with 64 samples per workgroup 17.6 and 13.0).
+// and memory; with 64 the sixteen waves of the workgroup slow one another down, 8.8 us); a large one has fewer tickets to
+// take and more threads for its weights with 32 samples than with 16 (4096 samples 9.9 and 12.1 us, 3000 9.1 and 10.7,
+// 2048 8.5 and 8.6, 1500 8.2 and 7.9, 512 7.7 and 6.8).
 constexpr uint32_t kSampleMaxThreads = 512;
 constexpr int kHeldMasses = 8;  // masses per thread of the workgroup that writes a batch's weights
 
@@ -1378,6 +1391,9 @@ static_assert(kHeldMasses * sample_threads(2048, true) >= 2048 && sample_threads
 // weights the ticket and the masses).  In one launch instead of two (draw; gather and weights): 16 x 512 rows of 64
 // bytes from 2^21 slots 6.2 + 3.8 -> 9.2 us, 4096 of 128 bytes from 2^24 7.2 + 7.4 -> 10.9, 256 of 268 bytes from 2^20
 // 6.0 + 3.1 -> 8.0, each with one launch (3 us on the host, 1 between two kernels) less.
+// kWide: the top level has more than 512 nodes.  (With the branch in the kernel 256 samples from 2^20 slots and their
+// update took 11.76 us, without 11.55.)
+template <bool kWide>
 __global__ __launch_bounds__(kSampleMaxThreads) void sample_kernel(SampleArgs a)
 {
   __shared__ uint64_t red[kSampleMaxThreads / kWave];
@@ -1391,7 +1407,7 @@ __global__ __launch_bounds__(kSampleMaxThreads) void sample_kernel(SampleArgs a)
   uint64_t my_mass = ~0ull;
   if (j0 < k) {
     const uint64_t o = (uint64_t)b * k + min(j, k - 1);  // a row without a sample repeats the last one and writes nothing
-    TopLevel top;
+    TopLevel<kWide> top;
     const uint64_t *const top_level = tv.level[tv.nlev - 1];
     top.load(top_level, tv.n_top);
     const uint64_t u = a.rnd[o];
@@ -1596,7 +1612,7 @@ __device__ __forceinline__ void draw_in_first_wave(const StepArgs &a, uint32_t r
   const uint32_t lane = lane_id();
   const bool second = a.next_prio && row + 1 < a.next.k;              // a next sample to compare slots with
   __builtin_amdgcn_s_setprio(2);
-  TopLevel top;
+  TopLevel<true> top;
   top.load(a.next_top, rd.n_top);
   // no load below is conditional: a branch around a load would make the wave wait for it there
   const uint64_t un0 = a.next.rnd[row], un1 = a.next.rnd[second ? row + 1 : row];

@@ -218,8 +218,8 @@ def test_enqueued_eviction_that_falls_short_is_noticed():
 
 
 @pytest.mark.parametrize("P,C,ob,ab,S,T,n,A,k", [
-    (600, 400, 12, 4, 3, 7, 3, 4, 33),          # 4-byte vectors, one tree level, ragged everything
-    (5000, 4000, 7, 3, 5, 11, 2, 1, 100),       # byte copies, critic values
+    (600, 400, 12, 4, 3, 7, 3, 4, 33),          # rows of three words, one tree level, ragged everything
+    (5000, 4000, 7, 3, 5, 11, 2, 1, 100),       # rows of single bytes, critic values
     (70_000, 60_000, 4096, 8, 4, 50, 5, 18, 512),  # the longest rows the fused calls take, three levels
 ])
 def test_fused_calls_on_small_and_ragged_shapes(P, C, ob, ab, S, T, n, A, k):
