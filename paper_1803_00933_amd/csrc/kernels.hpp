@@ -152,7 +152,7 @@ __device__ __forceinline__ void add_runs_to_ancestors(const TreeView &tv, bool a
 // sums on level 1 (at most three runs a wave: 64 slots that cross one node's border and the ring's end) are
 // collected in LDS, and one wave enters them into the levels above, which so receive one atomic per workgroup and
 // node instead of one per wave: all waves of a round meet on one or two nodes there (51,200 transitions of 2^24:
-// 800 atomics on one address, about 10 ns each; the launch took 8.6 us, now 3.9).  Contains a barrier.  Called by
+// 800 atomics on one address, about 10 ns each; the launch took 8.6 us, now 4.4).  Contains a barrier.  Called by
 // every thread.
 struct DenseSums {
   uint64_t sum[64];
@@ -1294,8 +1294,8 @@ __device__ __forceinline__ uint64_t row_inclusive_scan(uint64_t v)
 // The walk of four samples at once, one per 16-lane row of the wave (every lane of a row holds its sample's values):
 // a lane takes four neighbouring children, so that a level costs four steps of a prefix sum for four samples
 // instead of six for one.  With a whole wave per sample the arithmetic of the scans, not memory, was what a call
-// of many samples took (8192 samples from 2^21 slots: 11.0 us, now 6.2; the 32,000 of an eviction round: 14.9, now
-// 5.6); a call of few is bound by its chain of round trips (256 from 2^20 slots: 7.0 us, now 6.0).
+// of many samples took (replay.Sample of 16 x 512 from 2^21 slots: 13.6 us, now 9.1; an eviction of 65,536 in three
+// rounds: 115, now 55); a call of few is bound by its chain of round trips (256 from 2^20 slots, alone: 7.0 us, now 6.1).
 struct RowWalk {
   uint64_t idx, x, mass;
 };
@@ -1388,9 +1388,9 @@ static_assert(kHeldMasses * sample_threads(2048, true) >= 2048 && sample_threads
 // words that the launch two turns on will use: whatever left a word at another value (calls that overlapped although
 // they must be ordered), the calls after it find their last workgroups again.
 // Bound by a chain of round trips (top level, its eight nodes again, a row of children per level, the payload row, with
-// weights the ticket and the masses).  In one launch instead of two (draw; gather and weights): 16 x 512 rows of 64
-// bytes from 2^21 slots 6.2 + 3.8 -> 9.2 us, 4096 of 128 bytes from 2^24 7.2 + 7.4 -> 10.9, 256 of 268 bytes from 2^20
-// 6.0 + 3.1 -> 8.0, each with one launch (3 us on the host, 1 between two kernels) less.
+// weights the ticket and the masses).  Against a wave per sample and a second launch for gather and weights: 16 x 512 rows
+// of 64 bytes from 2^21 slots 13.6 -> 9.1 us, 4096 of 128 bytes from 2^24 16.2 -> 11.0, 256 of 268 bytes from 2^20
+// 7.3 -> 6.7, each with one launch (3 us on the host) less.  (Both halves' times: kGatherInDrawBytes.)
 // kWide: the top level has more than 512 nodes.  (With the branch in the kernel 256 samples from 2^20 slots and their
 // update took 11.76 us, without 11.55.)
 template <bool kWide>
