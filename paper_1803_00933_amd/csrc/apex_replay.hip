@@ -759,13 +759,13 @@ int launch_update(apex_replay *r, uint64_t m, const uint64_t *key, const float *
                   const QSource &qs = QSource{}, bool claimed = false)
 {
   ++r->tree_version;
-  if (m <= 1024) {
+  if (m <= kUpdateOneLaunchMax && !claimed) {
     const UpdateArgs ua{r->tv, r->state(), (uint32_t)m, key, prio, r->qp, nullptr, nullptr, qs};
-    const dim3 block((uint32_t)round_up(m, kWave));
-    if (r->geo.nlev > r->geo.exported_nlev && m > kSummitInLdsAbove)  // (a summit)
-      update_small_summit_kernel<<<dim3(1), block, 0, stream>>>(ua);
+    const dim3 grid(blocks_for(m, kWave)), block((uint32_t)std::clamp<uint64_t>(round_up(m, kWave), kUpdateMinThreads, kUpdateThreads));
+    if (m <= kUpdateThreads)
+      update_small_kernel<1><<<grid, block, 0, stream>>>(ua);
     else
-      update_small_kernel<<<dim3(1), block, 0, stream>>>(ua);
+      update_small_kernel<2><<<grid, block, 0, stream>>>(ua);
   } else {
     const dim3 grid(blocks_for(m, 256)), block(256);
     if (!claimed)

@@ -209,6 +209,35 @@ struct NstepOut {
   float p, R, G;  // priority |delta|, partial return, accumulated discount
 };
 
+// argmax_a row[a], the lowest action of several.  Eight values on their way together (one by one, every value was a round
+// trip).  Where fewer than eight are left the last one is read again: a value is never above itself.  One or two at the end
+// are not worth the seven reads too many.
+// n-step priorities of 18,000 transitions of 18 actions 4.5 -> 4.2 us, of 3300 of 40 actions, eleven steps, 9.2 -> 8.1.
+__device__ __forceinline__ uint32_t greedy_action(const float *row, uint32_t A)
+{
+  constexpr uint32_t kAhead = 8;
+  uint32_t best = 0, b = 1;
+  float vbest = row[0];
+  auto take = [&](float v, uint32_t at) {
+    const bool above = v > vbest;
+    vbest = above ? v : vbest;
+    best = above ? at : best;
+  };
+  for (; b + 2 < A; b += kAhead) {
+    float v[kAhead];
+#pragma unroll
+    for (uint32_t t = 0; t < kAhead; ++t) v[t] = row[min(b + t, A - 1)];
+#pragma unroll
+    for (uint32_t t = 0; t < kAhead; ++t) take(v[t], b + t);
+  }
+  for (; b < A; ++b) take(row[b], b);
+  return best;
+}
+
+// Up to this many steps the rewards and discounts of a transition are read together (3200 transitions of five steps, one
+// action: 3.3 -> 2.9 us).
+constexpr int kNstepHeld = 8;
+
 // Transition gid = s * T + t of an add round (gid < S * T).
 __device__ __forceinline__ NstepOut nstep_one(const NstepArgs &a, uint64_t gid)
 {
@@ -218,20 +247,20 @@ __device__ __forceinline__ NstepOut nstep_one(const NstepArgs &a, uint64_t gid)
   const float *rw = a.reward + row0 + t;
   const float *dc = a.discount + row0 + t;
 
-  float R = 0.0f;
-  for (int j = (int)n - 1; j >= 0; --j) R = __builtin_fmaf(dc[j], R, rw[j]);  // Horner, one rounding per step
-  float G = 1.0f;
-  for (uint32_t j = 0; j < n; ++j) G = G * dc[j];
-
-  const float *qrow = a.q_online + (row0 + t + n) * A;
-  uint32_t best = 0;
-  float vbest = qrow[0];
-  for (uint32_t b = 1; b < A; ++b) {
-    const float v = qrow[b];
-    if (v > vbest) {
-      vbest = v;
-      best = b;
-    }
+  const uint32_t best = greedy_action(a.q_online + (row0 + t + n) * A, A);
+  float R = 0.0f, G = 1.0f;
+  if (n <= kNstepHeld) {
+    float r[kNstepHeld], d[kNstepHeld];
+#pragma unroll
+    for (int j = 0; j < kNstepHeld; ++j)
+      if ((uint32_t)j < n) r[j] = rw[j], d[j] = dc[j];
+#pragma unroll
+    for (int j = kNstepHeld - 1; j >= 0; --j) R = (uint32_t)j < n ? __builtin_fmaf(d[j], R, r[j]) : R;  // Horner, one rounding per step
+#pragma unroll
+    for (int j = 0; j < kNstepHeld; ++j) G = (uint32_t)j < n ? G * d[j] : G;
+  } else {
+    for (int j = (int)n - 1; j >= 0; --j) R = __builtin_fmaf(dc[j], R, rw[j]);
+    for (uint32_t j = 0; j < n; ++j) G = G * dc[j];
   }
   const float boot = a.q_target[(row0 + t + n) * A + best];
   uint32_t at = (uint32_t)a.action[row0 + t];
@@ -409,9 +438,9 @@ __device__ __forceinline__ u32x4 codec_piece(const CodecFetched &f)
   return (f.word >> f.bit & 1) ? f.data : u32x4{x, x, x, x};
 }
 
-// A learner batch (m <= blockDim) handled by one workgroup: duplicates are resolved in an LDS hash
-// table keyed by slot (the highest position wins), so no pass over global memory is needed for
-// it, and the old mass is fetched while the table is being filled.
+// A learner batch (m <= blockDim) handled by one workgroup, beside rows that others copy: duplicates are resolved in an
+// LDS hash table keyed by slot (the highest position wins), so no pass over global memory is needed for it, and the old
+// mass is fetched while the table is being filled.
 constexpr uint32_t kDedupeSlots = 2048;  // >= 2 * 1024 pairs: linear probing stays short
 
 // Learner-side ComputePriorities (Algorithm 2) fused into the write-back: the new priority of a
@@ -428,21 +457,22 @@ struct QSource {
   float *prio_out;             // [m] or null: the priorities that were computed (0 for skipped pairs)
 };
 
-__device__ __forceinline__ float td_priority(const QSource &qs, uint32_t i, uint64_t slot)
+// What does not depend on the transition's slot: q_target_next of the greedy action, and q_taken.
+struct TdInputs {
+  float boot, taken;
+};
+
+__device__ __forceinline__ TdInputs td_inputs(const QSource &qs, uint32_t i)
 {
-  const float *row = qs.q_online_next + (uint64_t)i * qs.A;
-  uint32_t best = 0;
-  float vbest = row[0];
-  for (uint32_t a = 1; a < qs.A; ++a) {
-    const float v = row[a];
-    if (v > vbest) {
-      vbest = v;
-      best = a;
-    }
-  }
-  const float boot = qs.q_target_next[(uint64_t)i * qs.A + best];
-  const float target = __builtin_fmaf(qs.gacc[slot], boot, qs.ret[slot]);
-  return __builtin_fabsf(target - qs.q_taken[i]);
+  const float taken = qs.q_taken[i];
+  const uint32_t best = greedy_action(qs.q_online_next + (uint64_t)i * qs.A, qs.A);
+  return TdInputs{qs.q_target_next[(uint64_t)i * qs.A + best], taken};
+}
+
+__device__ __forceinline__ float td_priority(const QSource &qs, const TdInputs &in, uint64_t slot)
+{
+  const float target = __builtin_fmaf(qs.gacc[slot], in.boot, qs.ret[slot]);
+  return __builtin_fabsf(target - in.taken);
 }
 
 struct UpdateArgs {
@@ -474,7 +504,7 @@ __device__ __forceinline__ UpdateLane update_batch_load(const UpdateArgs &ua)
   UpdateLane u{0, 0, 0, 0.0f, 0, ~0ull};
   const uint32_t i = threadIdx.x;
   if (i < ua.m) {
-    if (!ua.qs.q_taken) u.prio = ua.prio[i];
+    u.prio = ua.prio[i];
     if (ua.slot_hint) {
       u.slot = ua.slot_hint[i];
       u.old = ua.mass_hint[i];
@@ -489,17 +519,8 @@ __device__ __forceinline__ UpdateLane update_batch_load(const UpdateArgs &ua)
   return u;
 }
 
-// A batch of more pairs than this on a tree with a summit collects what it adds to the summit in LDS.  The changes of one
-// batch meet on few cache lines there, and one compute unit sends all of its atomics: 1024 drawn keys of 2^18 slots 6.1 us
-// without, 5.6 so, of 70,000 slots 7.2 and 5.8, of 2^24 7.0 and 6.8; 513 to 768 keys 4.3 - 7.1 and 4.2 - 6.2.  For 512 the
-// two are even, and below that clearing and reading the sums costs more than it saves (32 keys: 4.0 and 4.9).
-constexpr uint32_t kSummitInLdsAbove = 512;
-
-// Second half.  h_slot, h_pos: LDS, kDedupeSlots words each; summit: with kSummitInLds, kSummitMax words of it.  Called
-// by every thread of the workgroup.
-template <bool kSummitInLds = false>
-__device__ __forceinline__ void update_batch_apply(const UpdateArgs &ua, UpdateLane u, uint32_t *h_slot,
-                                                   uint32_t *h_pos, unsigned long long *summit = nullptr)
+// Second half.  h_slot, h_pos: LDS, kDedupeSlots words each.  Called by every thread of the workgroup.
+__device__ __forceinline__ void update_batch_apply(const UpdateArgs &ua, UpdateLane u, uint32_t *h_slot, uint32_t *h_pos)
 {
   const TreeView &tv = ua.tv;
   const uint32_t i = threadIdx.x;
@@ -507,8 +528,6 @@ __device__ __forceinline__ void update_batch_apply(const UpdateArgs &ua, UpdateL
     h_slot[t] = 0xffffffffu;  // no slot has this number: max_slots <= 2^31
     h_pos[t] = 0;
   }
-  if (kSummitInLds)
-    for (uint32_t t = i; t < kSummitMax; t += blockDim.x) summit[t] = 0;
   __syncthreads();
   const bool valid = i < ua.m && u.key >= u.head && u.key < u.tail;
   const bool stale = i < ua.m && !valid;
@@ -527,22 +546,13 @@ __device__ __forceinline__ void update_batch_apply(const UpdateArgs &ua, UpdateL
       h = (h + 1) & (kDedupeSlots - 1);
     }
     atomicMax(&h_pos[h], i + 1);
-    const float p = ua.qs.q_taken ? td_priority(ua.qs, i, slot) : u.prio;
-    q = quantise_priority(p, ua.qp, &clamped);
-    if (ua.qs.q_taken && ua.qs.prio_out) ua.qs.prio_out[i] = p;
+    q = quantise_priority(u.prio, ua.qp, &clamped);
   }
-  if (stale && ua.qs.q_taken && ua.qs.prio_out) ua.qs.prio_out[i] = 0.0f;
   __syncthreads();
   const bool wins = valid && h_pos[h] == i + 1;
-  if constexpr (kSummitInLds) {  // (ahead of the atomics on memory: no wave waits for those at the barrier)
-    if (wins) atomicAdd(&summit[slot >> (kFanoutLog2 * (tv.nlev - 2) + tv.top_log2)], (unsigned long long)(q - old));
-    __syncthreads();
-    for (uint32_t t = i; t < tv.n_top; t += blockDim.x)
-      if (summit[t]) atomic_add_u64(tv.level[tv.nlev - 1] + t, summit[t]);
-  }
   if (wins) {
     tv.level[0][slot] = q;
-    add_to_ancestors(tv, slot, q - old, kSummitInLds ? tv.nlev - 1 : tv.nlev);
+    add_to_ancestors(tv, slot, q - old);
   }
   const uint64_t ns = __popcll(__ballot(stale)), nc = __popcll(__ballot(clamped));
   if (lane_id() == 0) {
@@ -551,19 +561,90 @@ __device__ __forceinline__ void update_batch_apply(const UpdateArgs &ua, UpdateL
   }
 }
 
-__global__ __launch_bounds__(1024) void update_small_kernel(UpdateArgs ua)
-{
-  __shared__ uint32_t h_slot[kDedupeSlots];
-  __shared__ uint32_t h_pos[kDedupeSlots];
-  update_batch_apply(ua, update_batch_load(ua), h_slot, h_pos);
-}
+// An update of up to kHeld * kUpdateThreads pairs in one launch.  A workgroup writes 64 of them back, those of one of its
+// waves; which of several pairs naming one slot is the last, every workgroup finds out for itself, by a table in LDS of all
+// keys of the update (the highest position wins).  So nothing has to be settled between workgroups, and what one compute
+// unit would take one after the other - scattered masses, rows of Q-values, the atomics on every level - is shared out.
+// Bound by its chain: key, slot, mass, atomics, 3.3 us for 16 pairs and 3.9 for 1024 (a launch of nothing: 2.5).  us, drawn
+// or random keys, against one workgroup for everything up to 1024 pairs and two launches (below) beyond:
+//   512 pairs, 2^18 / 2^24 slots      4.4 - 4.7 / 5.4  -> 3.6 / 3.7
+//   1024 pairs, 2^18 / 2^24 slots     5.5 - 6.3 / 7.4 - 8.1 -> 3.9 / 4.1
+//   2048 pairs, 2^18 / 2^24 slots     6.2 - 6.8 / 6.2 - 6.9 -> 5.1 / 5.3 - 5.7
+//   512 / 1024 pairs from the learner's Q-values, 18 actions, 2^21 slots  7.4 / 15.2 -> 4.3 / 4.5
+// With twice instead of four times as many places as pairs 1024 take 4.4 us and 2048 take 6.0 - 7.2 (probing); 4096 pairs
+// with four per thread take 8 - 10 us, two launches 6 - 7.5.
+constexpr uint32_t kUpdateThreads = 1024;       // most threads per workgroup ...
+constexpr uint32_t kUpdateMinThreads = 256;     // ... and fewest: one wave alone is slow to clear the table (32 pairs 3.8 us)
+constexpr uint32_t kUpdateOneLaunchMax = 2 * kUpdateThreads;
 
-__global__ __launch_bounds__(1024) void update_small_summit_kernel(UpdateArgs ua)
+template <int kHeld>
+__global__ __launch_bounds__(kUpdateThreads) void update_small_kernel(UpdateArgs ua)
 {
-  __shared__ uint32_t h_slot[kDedupeSlots];
-  __shared__ uint32_t h_pos[kDedupeSlots];
-  __shared__ unsigned long long summit[kSummitMax];
-  update_batch_apply<true>(ua, update_batch_load(ua), h_slot, h_pos, summit);
+  constexpr uint32_t kPlaces = 4 * kUpdateThreads * kHeld;
+  __shared__ __align__(16) uint32_t h_slot[kPlaces];
+  __shared__ __align__(16) uint32_t h_pos[kPlaces];
+  const TreeView &tv = ua.tv;
+  const uint32_t tid = threadIdx.x, nthr = blockDim.x, per = nthr / kWave;
+  // the pairs that are written back here: number own_t of those that the lanes of wave own_wave hold
+  const uint32_t own_t = kHeld == 1 ? 0 : blockIdx.x / per, own_wave = kHeld == 1 ? blockIdx.x : blockIdx.x - own_t * per;
+  const bool own = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid / kWave)) == own_wave;
+  uint64_t key[kHeld];
+#pragma unroll
+  for (int t = 0; t < kHeld; ++t) key[t] = ua.key[min(t * nthr + tid, ua.m - 1)];
+  const uint32_t i = own_t * nthr + tid;
+  const uint64_t head = ua.st->head, tail = ua.st->tail;
+  float prio = 0.f;
+  TdInputs td{};
+  if (own && !ua.qs.q_taken) prio = ua.prio[min(i, ua.m - 1)];
+  for (uint32_t t = tid; t < kPlaces / 4; t += nthr) {
+    reinterpret_cast<u32x4 *>(h_slot)[t] = u32x4{~0u, ~0u, ~0u, ~0u};  // no slot has this number: max_slots <= 2^31
+    reinterpret_cast<u32x4 *>(h_pos)[t] = u32x4{0, 0, 0, 0};
+  }
+  if (own && ua.qs.q_taken) td = td_inputs(ua.qs, min(i, ua.m - 1));
+  __syncthreads();
+  uint32_t slot[kHeld], h[kHeld], prev[kHeld];
+  bool valid[kHeld], valid_own = false;
+  uint32_t slot_own = 0, h_own = 0;
+  uint64_t old = 0;
+#pragma unroll
+  for (int t = 0; t < kHeld; ++t) {
+    valid[t] = t * nthr + tid < ua.m && key[t] >= head && key[t] < tail;
+    slot[t] = (uint32_t)ring_slot(tv, key[t]);
+    h[t] = (slot[t] * 2654435761u) / (0xffffffffu / kPlaces + 1);
+    if (own && t == (int)own_t && valid[t]) old = tv.level[0][slot[t]];
+    if (valid[t]) prev[t] = atomicCAS(&h_slot[h[t]], 0xffffffffu, slot[t]);
+  }
+#pragma unroll
+  for (int t = 0; t < kHeld; ++t) {
+    if (valid[t]) {
+      while (prev[t] != 0xffffffffu && prev[t] != slot[t]) {
+        h[t] = (h[t] + 1) & (kPlaces - 1);
+        prev[t] = atomicCAS(&h_slot[h[t]], 0xffffffffu, slot[t]);
+      }
+      atomicMax(&h_pos[h[t]], t * nthr + tid + 1);
+    }
+    if (t == (int)own_t) valid_own = valid[t], slot_own = slot[t], h_own = h[t];
+  }
+  bool clamped = false;
+  uint64_t q = 0;
+  if (own && valid_own) {
+    const float p = ua.qs.q_taken ? td_priority(ua.qs, td, slot_own) : prio;
+    q = quantise_priority(p, ua.qp, &clamped);
+    if (ua.qs.q_taken && ua.qs.prio_out) ua.qs.prio_out[i] = p;
+  }
+  __syncthreads();
+  if (!own) return;
+  const bool stale = i < ua.m && !valid_own;
+  if (stale && ua.qs.q_taken && ua.qs.prio_out) ua.qs.prio_out[i] = 0.0f;
+  if (valid_own && h_pos[h_own] == i + 1) {
+    tv.level[0][slot_own] = q;
+    add_to_ancestors(tv, slot_own, q - old);
+  }
+  const uint64_t ns = __popcll(__ballot(stale)), nc = __popcll(__ballot(clamped));
+  if (lane_id() == 0) {
+    if (ns) atomic_add_u64(&ua.st->n_stale, ns);
+    if (nc) atomic_add_u64(&ua.st->n_clamped, nc);
+  }
 }
 
 // Importance-sampling weights of one batch of k samples, by one workgroup:
@@ -1062,9 +1143,10 @@ __global__ __launch_bounds__(256) void update_apply_kernel(TreeView tv, DeviceSt
   uint64_t slot = 0, delta = 0;
   if (i < m) {
     const uint64_t k = key[i];
+    const TdInputs td = qs.q_taken ? td_inputs(qs, i) : TdInputs{};
     if (k >= st->head && k < st->tail) {
       slot = ring_slot(tv, k);
-      const float p = qs.q_taken ? td_priority(qs, i, slot) : prio[i];
+      const float p = qs.q_taken ? td_priority(qs, td, slot) : prio[i];
       if (qs.q_taken && qs.prio_out) qs.prio_out[i] = p;
       const uint64_t q = quantise_priority(p, qp, &clamped);
       if (claim[slot] == i + 1) {

@@ -22,7 +22,7 @@ def both(qo, qt, ac, rw, dc, n, alpha=0.6, eps=1e-6, F=24, P=0, same_net=False):
 
 
 @pytest.mark.parametrize("S,T,A,n", [(8, 50, 4, 3), (360, 50, 18, 3), (64, 50, 1, 5), (3, 37, 7, 4), (1, 1, 2, 1),
-                                     (1024, 50, 18, 3), (5, 257, 3, 8)])
+                                     (1024, 50, 18, 3), (5, 257, 3, 8), (7, 33, 9, 9), (2, 70, 2, 2), (4, 20, 41, 17)])
 def test_nstep_parity(S, T, A, n):
     rng = np.random.default_rng(S * 1000 + T)
     L = T + n

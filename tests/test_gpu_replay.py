@@ -152,6 +152,33 @@ def test_updates_on_trees_with_a_summit(P, m):
     sample_both(g, o, rng, 1, m)
 
 
+@pytest.mark.parametrize("m", [1, 63, 64, 65, 255, 257, 1023, 1024, 1025, 1087, 2047, 2048, 2049])
+@pytest.mark.parametrize("A", [1, 2, 3, 9, 18])
+def test_updates_at_the_edges_of_their_workgroups(m, A):
+    """Updates of any number of pairs around the workgroups' shares and the line between one launch and two: repeats
+    across the shares (the last one wins), stale keys at both ends, given priorities and the learner's, with ties of the
+    greedy action and Q-values that compare with nothing."""
+    rng = np.random.default_rng(100 * m + A)
+    g, o = make_pair(3000, 4097, 16, 4)
+    assert add_both(g, o, rng, 3000) == 0 and add_both(g, o, rng, 1000) == 0
+    assert g.evict() == o.evict()                        # valid keys: [1000, 4000)
+    for distinct in (3, 400, 3100):                      # few keys often, many once, some stale
+        keys = (950 + rng.integers(0, distinct, m)).astype(np.uint64)
+        keys[rng.random(m) < 0.5] += np.uint64(60)
+        pr = rng.lognormal(0, 1, m).astype(F32)
+        assert g.update_priorities(dev(keys), dev(pr)) == o.update_priorities(keys, pr) == 0
+        check_gpu_tree(g, o)
+        q_on = np.round(rng.standard_normal((m, A)) * 2).astype(F32) / 2
+        q_on[rng.random((m, A)) < 0.1] = np.nan
+        q_on[rng.random(m) < 0.1] = -np.inf
+        q = [rng.standard_normal(m).astype(F32), q_on, rng.standard_normal((m, A)).astype(F32)]
+        p_out = torch.empty(m, dtype=torch.float32, device="cuda:0")
+        rc, p_ref = o.update_from_q(keys, *q)
+        assert g.update_from_q(dev(keys), *(dev(x) for x in q), p_out) == rc == 0
+        assert np.array_equal(host(p_out).view(np.uint32), p_ref.view(np.uint32))
+        check_gpu_tree(g, o)
+
+
 @pytest.mark.parametrize("P", [3000, 100_000])
 def test_adds_and_evictions_at_the_edges_of_their_workgroups(P):
     """Rounds of one wave, of whole and ragged workgroups and just beyond the largest one, each evicted again."""
