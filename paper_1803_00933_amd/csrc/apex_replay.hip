@@ -141,9 +141,9 @@ int geometry(const apex_replay_config_t *c, Geometry *g)
   return APEX_OK;
 }
 
-// The sample launches on one memory that have taken tickets (see sample_kernel), and the most batches one of them had.
+// The sample launches on one memory that have taken tickets (see sample_kernel), and the most words one of them used.
 struct TicketUse {
-  uint32_t launches = 0, batches = 0;
+  uint32_t launches = 0, lines = 0;
 };
 
 }  // namespace
@@ -653,18 +653,50 @@ int launch_weights(const WeightArgs &wa, uint32_t num_batches, hipStream_t strea
   return hip_failed(hipGetLastError()) ? APEX_ERR_HIP : APEX_OK;
 }
 
+// Gives a launch that takes tickets its set of words.
+void take_tickets(SampleArgs &a, uint32_t lines, TicketUse *tickets)
+{
+  const uint32_t set = tickets->launches++ & (kTicketSets - 1);
+  a.ticket_ahead = a.ticket + ((set + 2) & (kTicketSets - 1));
+  a.ticket += set;
+  tickets->lines = std::max(tickets->lines, lines);
+  a.ticket_lines = tickets->lines;
+}
+
+// Whether num_batches x k samples with rows of obs_bytes go into sample_rows_kernel rather than sample_kernel (rows of up to
+// kGatherInDrawBytes) or two launches.  (The times on both sides of the lines are at the kernel.)
+bool sample_by_rows(uint64_t obs_bytes, uint32_t num_batches, uint32_t k)
+{
+  const uint64_t samples = (uint64_t)num_batches * k;
+  if (obs_bytes < 16 || k > kSampleRowsMaxK || samples > kSampleRowsMax) return false;
+  if (obs_bytes > kGatherInDrawBytes) return true;
+  return obs_bytes >= 2048 ? k <= obs_bytes / 4 : samples <= 448;
+}
+
+// a.k samples of each of num_batches batches, as sample_by_rows has it.  Two pieces per lane as long as the chip holds all
+// waves at once, else four (28,224 bytes: 256 samples 7.3 us with two and 8.2 with four, 999 samples 16.4 and 14.0).
+int launch_sample_rows(SampleArgs &a, uint32_t num_batches, hipStream_t stream, TicketUse *tickets)
+{
+  a.k_div = make_fast_div(a.k);
+  const uint32_t groups = blocks_for(a.k, kTicketGroup);
+  if (a.weight_out) take_tickets(a, num_batches * (groups > 1 ? 1 + groups : 1), tickets);
+  const uint32_t vpr = (uint32_t)((a.obs_bytes + 15) / 16);
+  const auto waves = [&](uint32_t pieces) { return std::min(1 + blocks_for(vpr, pieces * kWave), 1024u / kWave); };
+  const bool two = (uint64_t)num_batches * a.k * waves(2) <= kChipWaves, wide = a.tv.n_top > 512;
+  const dim3 grid(a.k, num_batches), block(waves(two ? 2 : 4) * kWave);
+  if (two && wide) sample_rows_kernel<2, true><<<grid, block, 0, stream>>>(a, vpr);
+  else if (two) sample_rows_kernel<2, false><<<grid, block, 0, stream>>>(a, vpr);
+  else if (wide) sample_rows_kernel<4, true><<<grid, block, 0, stream>>>(a, vpr);
+  else sample_rows_kernel<4, false><<<grid, block, 0, stream>>>(a, vpr);
+  return hip_failed(hipGetLastError()) ? APEX_ERR_HIP : APEX_OK;
+}
+
 // a.k samples of each of num_batches batches (with a.k_dev: at most a.k).  tickets may be null where a.weight_out is.
 int launch_sample(SampleArgs &a, uint32_t num_batches, hipStream_t stream, TicketUse *tickets = nullptr)
 {
   a.k_div = make_fast_div(a.k);
   const uint32_t threads = sample_threads(a.k, a.weight_out != nullptr), wgs = blocks_for(a.k, threads / 16);
-  if (a.weight_out && wgs > 1) {
-    const uint32_t set = tickets->launches++ & (kTicketSets - 1);
-    a.ticket_ahead = a.ticket + ((set + 2) & (kTicketSets - 1));
-    a.ticket += set;
-    if (num_batches > tickets->batches) tickets->batches = num_batches;
-    a.ticket_batches = tickets->batches;
-  }
+  if (a.weight_out && wgs > 1) take_tickets(a, num_batches, tickets);
   const dim3 grid(wgs, num_batches), block(threads);
   if (a.tv.n_top > 512)
     sample_kernel<true><<<grid, block, 0, stream>>>(a);
@@ -721,7 +753,7 @@ bool writeback_spreads(const apex_replay *r, uint64_t per)
 // of long ones a workgroup per row moves more bytes per second (copy_rows_long_kernel).
 bool gather_in_draw(const apex_replay *r) { return r->cfg.obs_bytes <= kGatherInDrawBytes; }
 
-// apex_replay_sample for rows that gather_in_draw: one launch (two for the weights of very large batches).  claim: the
+// apex_replay_sample for rows that gather_in_draw or sample_by_rows: one launch (two for the weights of very large batches).  claim: the
 // first pass of an update of all drawn keys rides along.
 int sample_in_one(apex_replay *r, uint32_t num_batches, uint32_t k, float beta, const uint64_t *rnd, uint64_t *key_out,
                   uint32_t *slot_out, uint64_t *mass_out, float *weight_out, void *obs_out, void *act_out,
@@ -737,7 +769,9 @@ int sample_in_one(apex_replay *r, uint32_t num_batches, uint32_t k, float beta, 
   a.beta = beta;
   a.ticket = r->tickets();
   a.claim = claim ? r->claim() : nullptr;
-  const int rl = launch_sample(a, num_batches, stream, &r->ticket_use);
+  const int rl = !claim && obs_out && sample_by_rows(a.obs_bytes, num_batches, k)
+                     ? launch_sample_rows(a, num_batches, stream, &r->ticket_use)
+                     : launch_sample(a, num_batches, stream, &r->ticket_use);
   return rl != APEX_OK || a.weight_out == weight_out ? rl
                                                      : launch_weights(WeightArgs{mass_out, weight_out, k, beta}, num_batches, stream);
 }
@@ -1038,7 +1072,7 @@ int apex_replay_sample(apex_replay_t *r, uint32_t num_batches, uint32_t k, float
                        float *ret_out, float *gacc_out, void *hip_stream)
 {
   if (!r || !(beta >= 0.0f) || !(beta <= 1.0f)) return APEX_ERR_INVALID_ARG;
-  if (!obs_out || gather_in_draw(r))
+  if (!obs_out || gather_in_draw(r) || sample_by_rows(r->cfg.obs_bytes, num_batches, k))
     return sample_in_one(r, num_batches, k, beta, rnd, key_out, slot_out, r->mass(), weight_out, obs_out, act_out, ret_out,
                          gacc_out, /*claim=*/false, static_cast<hipStream_t>(hip_stream));
   const int rc = apex_replay_sample_begin(r, num_batches, k, rnd, key_out, slot_out, r->mass(), act_out, ret_out,

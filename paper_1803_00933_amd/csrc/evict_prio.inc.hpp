@@ -752,13 +752,15 @@ int apex_pe_sample(apex_pe_replay_t *r, uint32_t num_batches, uint32_t k, float 
   SampleArgs a = pe_sample_args(r, k, rnd, key_out, slot_out, act_out, ret_out, gacc_out);
   SideJobs jobs;
   jobs.wa = WeightArgs{r->mass(), weight_out, k, beta};
-  const bool gather = obs_out && r->cfg.obs_bytes <= kGatherInDrawBytes;
+  const bool by_rows = obs_out && sample_by_rows(r->cfg.obs_bytes, num_batches, k);
+  const bool gather = obs_out && (by_rows || r->cfg.obs_bytes <= kGatherInDrawBytes);
   if (gather) a.obs_out = static_cast<uint8_t *>(obs_out);
   if ((gather || !obs_out) && k <= kWeightsInDrawMaxK) {
     a.weight_out = weight_out;
     a.beta = beta;
     jobs.wa.weight_out = nullptr;
   }
+  if (by_rows) return launch_sample_rows(a, num_batches, stream, &r->ticket_use);
   APEX_TRY(launch_sample(a, num_batches, stream, &r->ticket_use));
   if (obs_out && !gather) {
     const RowMap by_slot{slot_out, nullptr, 0, {}};

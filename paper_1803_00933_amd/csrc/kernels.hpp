@@ -1197,9 +1197,9 @@ struct SampleArgs : DrawArgs {
   uint8_t *obs_out;          // null: the rows are gathered by another launch (copy_rows_*)
   float *weight_out;         // null: no weights, or written by another launch (batch_weights)
   float beta;
-  uint32_t *ticket;          // with weight_out: one word per batch, kTicketStride words apart, 0 before and after
-  uint32_t *ticket_ahead;    // the words that a launch to come will use, of this many batches: cleared by this launch
-  uint32_t ticket_batches;
+  uint32_t *ticket;          // with weight_out: words that lie kTicketStride apart, 0 before and after: one per batch ...
+  uint32_t *ticket_ahead;    // the words that a launch to come will use, at most this many: cleared by this launch
+  uint32_t ticket_lines;
   uint32_t *claim;           // not null: the first pass of an update of the drawn keys (update_claim_block) as well
 };
 
@@ -1577,7 +1577,7 @@ __global__ __launch_bounds__(kSampleMaxThreads) void sample_kernel(SampleArgs a)
   if (threadIdx.x == 0) sh_ticket = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   __syncthreads();
   if (blockIdx.x == 0 && b == 0)
-    for (uint32_t i = threadIdx.x; i < a.ticket_batches; i += nthr) a.ticket_ahead[i * kTicketStride] = 0;
+    for (uint32_t i = threadIdx.x; i < a.ticket_lines; i += nthr) a.ticket_ahead[i * kTicketStride] = 0;
   if (sh_ticket != gridDim.x - 1) return;
   if (threadIdx.x == 0) *ticket = 0;
   const uint64_t *const bm = a.mass + (uint64_t)b * k;
@@ -1598,6 +1598,125 @@ __global__ __launch_bounds__(kSampleMaxThreads) void sample_kernel(SampleArgs a)
     const uint32_t i = threadIdx.x + t * nthr;
     if (i < k) bw[i] = batch_weight(mn, m[t], a.beta);
   }
+}
+
+// replay.Sample in one launch with a workgroup per sample: its first wave draws the sample and, in the batch's last
+// workgroup, writes the weights; the others wait for the slot and copy the row, the last of them the small columns.
+// For rows too long for 16 lanes, and for few samples, where it spreads the draws over more of the chip and the weights'
+// chain (mass, tickets, masses) runs beside the copies.  Against the draw and a copying launch with the weights (rows above
+// 4 KB) or sample_kernel, us:
+//                     1 x 16        1 x 64       1 x 256      1 x 512      1 x 1024      2 x 512       5 x 400
+//   rows of   32 B   5.5 -> 5.0   6.5 -> 5.5   6.6 -> 6.1   6.8    6.8   7.4    8.4    6.8    7.0    6.9    7.5
+//           1028 B   5.7 -> 5.1   6.6 -> 5.6   6.7 -> 6.2   6.9    6.9   7.5    8.6    7.0    7.2    7.9    7.8
+//           2048 B   5.8 -> 4.9   6.7 -> 5.5   6.8 -> 6.1   7.1 -> 6.8   7.9    8.4    7.7 -> 7.1    8.8 -> 8.0
+//           4096 B   6.3 -> 4.9   7.3 -> 5.4   7.4 -> 6.1   8.3 -> 6.9   9.5 -> 8.6    9.4 -> 7.2   10.4 -> 9.3
+//           8192 B   7.9 -> 4.9   8.2 -> 5.5   8.1 -> 6.2   8.4 -> 7.0   9.8    9.9    9.9 -> 8.3   12.6 -> 11.8
+//         28,224 B   8.8 -> 5.1   9.3 -> 5.8   9.5 -> 7.3  11.7 -> 10.1 17.0 -> 15.1  16.9 -> 13.9  26.6    26.4
+// Beyond 1024 samples in a batch one wave is too few for the weights (2048 samples 13 us, 9.2 apart).
+// The tickets of a batch in two steps, a word per kTicketGroup samples and then the batch's own: an atomic that returns to
+// one address takes its turn of some 14 ns (512 samples of 1028 bytes on one word 11.5 us).
+// The weights in a short loop over masses in LDS: unrolled over masses in registers they are kilobytes of code that every
+// launch has to fetch (0.5 us at 16 samples, 0.7 at 512).
+constexpr uint32_t kTicketGroup = 32;
+constexpr uint32_t kSampleRowsMaxK = 1024;
+constexpr uint32_t kSampleRowsMax = 1536;   // samples of a call: beyond, long rows are bound by memory either way
+constexpr uint32_t kChipWaves = 8192;       // waves that the chip holds at once
+
+template <int kUnroll, bool kWide>
+__global__ __launch_bounds__(1024) void sample_rows_kernel(SampleArgs a, uint32_t vecs_per_row)
+{
+  __shared__ uint32_t sh_slot;
+  __shared__ uint64_t sh_mass[kSampleRowsMaxK];  // of one wave
+  const TreeView &tv = a.tv;
+  const uint32_t tid = threadIdx.x, lane = lane_id(), j = blockIdx.x, b = blockIdx.y, k = a.k;
+  const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid / kWave));
+  const uint64_t o = (uint64_t)b * k + j;
+  if (wave == 0) {
+    __builtin_amdgcn_s_setprio(2);
+    TopLevel<kWide> top;
+    top.load(tv.level[tv.nlev - 1], tv.n_top);
+    const uint64_t u = a.rnd[o], head = a.st->head;
+    const uint64_t w = fast_div(top.scan(), a.k_div);  // stratum width
+    uint64_t head_slot = 0;
+    const Drawn drawn = walk_down(tv, top.find((uint64_t)j * w + __umul64hi(u, w)), [&] { head_slot = ring_slot(tv, head); });
+    if (lane == 0) {
+      sh_slot = (uint32_t)drawn.slot;
+      __hip_atomic_store(a.mass + o, drawn.mass, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      a.slot_out[o] = (uint32_t)drawn.slot;
+      if (a.key_out) a.key_out[o] = a.gen ? ((uint64_t)a.gen[drawn.slot] << 32) | drawn.slot : ring_key(drawn.slot, head, head_slot, tv.P);
+    }
+    __builtin_amdgcn_s_setprio(0);
+  }
+  __syncthreads();
+  if (wave != 0) {
+    const uint64_t slot = sh_slot;
+    const uint32_t copiers = blockDim.x - kWave, c0 = tid - kWave;
+    const uint8_t *const s = a.obs + slot * a.obs_bytes;
+    uint8_t *const d = a.obs_out + o * a.obs_bytes;
+    for (uint32_t v0 = 0; v0 < vecs_per_row; v0 += copiers * kUnroll) {
+      PieceAny::Reg t[kUnroll];
+#pragma unroll
+      for (int u = 0; u < kUnroll; ++u) {
+        const uint32_t v = v0 + u * copiers + c0;
+        if (v < vecs_per_row) t[u] = load_piece_streaming<PieceAny>(s, v, a.obs_bytes);
+      }
+#pragma unroll
+      for (int u = 0; u < kUnroll; ++u) {
+        const uint32_t v = v0 + u * copiers + c0;
+        if (v < vecs_per_row) store_piece_streaming<PieceAny>(d, v, a.obs_bytes, t[u]);
+      }
+    }
+    if (wave == blockDim.x / kWave - 1) {
+      if (a.ret_out && lane == 0) a.ret_out[o] = a.ret[slot];
+      if (a.gacc_out && lane == 1) a.gacc_out[o] = a.gacc[slot];
+      if (a.act_out) {
+        const uint8_t *const act = a.act + slot * a.act_bytes;
+        uint8_t *const act_out = a.act_out + o * a.act_bytes;
+        if (a.act_bytes < 4) {
+          if (lane < a.act_bytes) act_out[lane] = act[lane];
+        } else {
+          for (uint32_t at = 4 * lane; at < a.act_bytes; at += 4 * kWave) {  // the last piece overlaps the one before it
+            const uint32_t p = min(at, a.act_bytes - 4);
+            *reinterpret_cast<u32_any *>(act_out + p) = *reinterpret_cast<const u32_any *>(act + p);
+          }
+        }
+      }
+    }
+    return;
+  }
+  if (!a.weight_out) return;
+  wait_for_all_loads();  // this sample's mass is in memory from here on
+  if (j == 0 && b == 0)
+    for (uint32_t i = lane; i < a.ticket_lines; i += kWave) a.ticket_ahead[i * kTicketStride] = 0;
+  auto last_of = [&](uint32_t line, uint32_t n) {
+    uint32_t *const t = a.ticket + (uint64_t)line * kTicketStride;
+    uint32_t taken = 0;
+    if (lane == 0) taken = __hip_atomic_fetch_add(t, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const bool last = read_lane_u32(taken, 0) == n - 1;
+    if (last && lane == 0) *t = 0;
+    return last;
+  };
+  const uint32_t groups = (k + kTicketGroup - 1) / kTicketGroup, g = j / kTicketGroup;
+  if (groups > 1 && !last_of(gridDim.y + b * groups + g, min(kTicketGroup, k - g * kTicketGroup))) return;
+  if (!last_of(b, groups > 1 ? groups : k)) return;
+  const uint64_t *const bm = a.mass + (uint64_t)b * k;
+  float *const bw = a.weight_out + (uint64_t)b * k;
+  uint64_t mn = ~0ull;
+#pragma unroll 1
+  for (uint32_t i0 = lane; i0 < k + lane; i0 += 8 * kWave) {  // eight loads in flight
+    uint64_t m[8];
+#pragma unroll
+    for (int t = 0; t < 8; ++t)
+      m[t] = __hip_atomic_load(bm + min(i0 + t * kWave, k - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+      mn = m[t] < mn ? m[t] : mn;
+      sh_mass[i0 + t * kWave] = m[t];
+    }
+  }
+  mn = wave_min(mn);
+#pragma unroll 2
+  for (uint32_t i = lane; i < k; i += kWave) bw[i] = batch_weight(mn, sh_mass[i], a.beta);
 }
 
 // --------------------------------------------------------------------------------------------

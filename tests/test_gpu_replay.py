@@ -130,6 +130,31 @@ def test_sample_in_one_launch(ob, ab, nb, k):
         sample_both(gp, op, rng, nb, k)
 
 
+@pytest.mark.parametrize("ob,ab,nb,k", [
+    (16, 1, 448, 1), (16, 2, 1, 448), (17, 3, 1, 449), (31, 4, 14, 32), (32, 5, 13, 33), (100, 255, 7, 64), (100, 257, 1, 65),
+    (2047, 4, 2, 224), (2048, 4, 3, 512), (2048, 4, 1, 513), (4095, 4, 1, 1023), (4096, 4, 1, 1024),       # lines of the rule
+    (4097, 4, 1, 1024), (4100, 4, 1, 1025), (8207, 4, 1, 1), (8207, 4, 48, 32), (8207, 4, 47, 33),
+    (28224, 4, 3, 333), (30720, 4, 1, 600), (30721, 4, 1, 300), (61441, 4, 1, 200), (70000, 4, 1, 700),  # pieces per lane
+])
+@pytest.mark.parametrize("P", [900, 40_000])     # one level of tree, two with a wide top
+def test_sample_with_a_workgroup_per_sample(P, ob, ab, nb, k):
+    """Around the lines where replay.Sample changes between a workgroup per sample, 16 lanes per sample and two launches,
+    in turn with calls of the other kinds on the same tickets."""
+    if P * ob > 1 << 28:
+        P = 2000
+    rng = np.random.default_rng(ob + k)
+    g, o = make_pair(P - 50, P, ob, ab)
+    assert add_both(g, o, rng, P - 60) == 0 and add_both(g, o, rng, 50) == 0 and g.evict() == o.evict()
+    for n in (nb, 1, nb, nb):
+        sample_both(g, o, rng, n, k)
+        sample_both(g, o, rng, 2, 40)
+    if ob < 100:
+        sample_both(g, o, rng, 3, 700)
+    sample_both(g, o, rng, nb, k)
+    torch.cuda.synchronize()
+    assert int(g.scratch[256:256 + 1024 * 16 * 4].view(torch.int32).abs().max()) == 0
+
+
 @pytest.mark.parametrize("P", [1025, 4608, 70_000, 294_912])
 @pytest.mark.parametrize("m", [512, 513, 1024])
 def test_updates_on_trees_with_a_summit(P, m):
