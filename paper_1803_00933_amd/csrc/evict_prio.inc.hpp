@@ -88,6 +88,9 @@ __global__ __launch_bounds__(256) void pe_add_kernel(PeView v, PeState *__restri
 // Algorithm 1, ComputePriorities; the partial return and accumulated discount are then the computed ones) - and
 // leaves slot and priority in LDS.  Then one lane per transition enters the masses, whole waves of neighbouring
 // transitions together (add_runs_to_ancestors).  act, ret, gacc may be null.
+// The workgroups are as large as they can be, for the sake of the atomics on the top levels: rounds of 3200 rows of 256
+// bytes 5.5 us with 1024 threads and 7 with 256, of 7680 rows of 1000 bytes 13 and 32.  (64 transitions per workgroup
+// whatever the rows, in several passes: 6.2 and 18.)
 constexpr uint32_t kPeAddThreads = 1024;
 
 template <typename P>
@@ -110,8 +113,9 @@ __global__ __launch_bounds__(kPeAddThreads) void pe_add_rows_kernel(PeView v, Pe
   const uint32_t r = threadIdx.x >> lanes_log2;
   const uint64_t i = (uint64_t)blockIdx.x * rows_per_block + r;
   const uint32_t vv = threadIdx.x & (lanes - 1);
+  const uint64_t free_head = st->free_head, tail = st->base.tail;
   if (i < count) {
-    const uint64_t slot = v.free_ring[ring_slot(v.ts, st->free_head + i)];
+    const uint64_t slot = v.free_ring[ring_slot(v.ts, free_head + i)];
     if (vv < vecs_per_row)
       store_piece<P>(obs_ring + slot * obs_bytes, vv, obs_bytes, load_piece<P>(obs + i * obs_bytes, vv, obs_bytes));
     if (act)
@@ -133,6 +137,16 @@ __global__ __launch_bounds__(kPeAddThreads) void pe_add_rows_kernel(PeView v, Pe
     }
   }
   __syncthreads();
+  // the last workgroup to have read the free ring's head moves it and the insertion count on (by its last lane: the
+  // ticket's round trip then runs beside those of the first wave; at the end of the launch it took 0.5 us more)
+  if (threadIdx.x == blockDim.x - 1) {
+    const uint32_t t = __hip_atomic_fetch_add(&st->base.ticket_add, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (t == gridDim.x - 1) {
+      st->base.ticket_add = 0;
+      st->free_head = free_head + count;
+      st->base.tail = tail + count;
+    }
+  }
   if (threadIdx.x < ((rows_per_block + kWave - 1) & ~(uint32_t)(kWave - 1))) {  // whole waves
     const uint32_t e = threadIdx.x;
     const bool active = e < rows_per_block && (uint64_t)blockIdx.x * rows_per_block + e < count;
@@ -151,16 +165,6 @@ __global__ __launch_bounds__(kPeAddThreads) void pe_add_rows_kernel(PeView v, Pe
     pe_add_runs(v, active, slot, q1, q2);
     const uint64_t nc = wave_sum(nclamp);
     if (nc && lane_id() == 0) atomic_add_u64(&st->base.n_clamped, nc);
-  }
-  // the last workgroup to finish moves the free ring's head and the insertion count on
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    const uint32_t t = __hip_atomic_fetch_add(&st->base.ticket_add, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (t == gridDim.x - 1) {
-      st->base.ticket_add = 0;
-      st->free_head += count;
-      st->base.tail += count;
-    }
   }
 }
 
@@ -223,45 +227,44 @@ __global__ __launch_bounds__(1024) void pe_update_small_kernel(PeView v, PeState
 // The write-back of the batch that the launch before has drawn, nothing having touched the trees since: pair i
 // is valid, lives in slot[i] and weighs mass[i] in the sampling tree, so the loads key -> generation -> mass and
 // the hash table are not needed; the drawn slots do not decrease (the strata ascend), so pairs naming one slot
-// are neighbours and the last of them is the one that stands.  One workgroup of at least m lanes.
-__device__ __forceinline__ void pe_writeback_block(const PeView &v, PeState *__restrict__ st, uint32_t m,
-                                                   const uint32_t *__restrict__ slot, const uint64_t *__restrict__ mass,
-                                                   const float *__restrict__ prio)
+// are neighbours and the last of them is the one that stands.  Lane i % 64 of one wave has pair i.
+__device__ __forceinline__ void pe_writeback_wave(const PeView &v, PeState *__restrict__ st, uint32_t m, uint32_t i,
+                                                  const uint32_t *__restrict__ slot, const uint64_t *__restrict__ mass,
+                                                  const float *__restrict__ prio)
 {
-  const uint32_t i = threadIdx.x;
   const bool in = i < m;
-  const uint32_t s = in ? slot[i] : 0, s_next = i + 1 < m ? slot[i + 1] : 0xffffffffu;
-  const bool wins = in && s != s_next;
+  const uint32_t at = min(i, m - 1), s = slot[at], s_next = slot[min(i + 1, m - 1)];
+  const uint64_t drawn = mass[at];
+  const float p = prio[at];
+  const bool wins = in && (i + 1 == m || s != s_next);
   uint64_t d1 = 0, d2 = 0;
-  uint32_t nclamp = 0;
-  if (in) {
-    bool c1, c2;
-    const float p = prio[i];
-    const uint64_t q1 = quantise_priority(p, v.qs, &c1), q2 = quantise_priority(p, v.qe, &c2);
-    nclamp = (uint32_t)c1 + (uint32_t)c2;  // counted for pairs that lose too, as when they are applied one by one
-    if (wins) {
-      d1 = q1 - mass[i], d2 = q2 - v.te.level[0][s];
-      v.ts.level[0][s] = q1;
-      v.te.level[0][s] = q2;
-    }
+  const uint64_t old2 = v.te.level[0][s];
+  bool c1, c2;
+  const uint64_t q1 = quantise_priority(p, v.qs, &c1), q2 = quantise_priority(p, v.qe, &c2);
+  if (wins) {
+    d1 = q1 - drawn, d2 = q2 - old2;
+    v.ts.level[0][s] = q1;
+    v.te.level[0][s] = q2;
   }
   pe_add_runs(v, wins, s, d1, d2);
-  const uint64_t nc = wave_sum(nclamp);
+  const uint64_t nc = wave_sum(in ? (uint32_t)c1 + (uint32_t)c2 : 0);  // of pairs that lose too, as when they are applied one by one
   if (nc && lane_id() == 0) atomic_add_u64(&st->base.n_clamped, nc);
 }
 
-// What follows the draw and gather of one batch whose new priorities are known: one workgroup writes the importance
-// weights, another writes the batch's new priorities back (m = k <= 1024 pairs).
-__global__ __launch_bounds__(1024) void pe_finish_update_kernel(WeightArgs wa, PeView v, PeState *__restrict__ st,
-                                                                uint32_t m, const uint32_t *__restrict__ slot,
-                                                                const float *__restrict__ prio)
+// What follows the draw and gather of one batch whose new priorities are known: the first half of the workgroups (one wave
+// each) write the new priorities of 64 pairs back (m = k <= 1024 pairs in all), the others the weights of as many samples.
+// One workgroup for all pairs is one compute unit that reads the scattered eviction masses and sends every atomic: draw
+// and this, 512 pairs of 1,114,112 slots 11.0 us, 8.9 so; 1024 pairs 14.1 and 8.9.
+__global__ __launch_bounds__(kWave) void pe_finish_update_kernel(WeightArgs wa, PeView v, PeState *__restrict__ st,
+                                                                 uint32_t m, const uint32_t *__restrict__ slot,
+                                                                 const float *__restrict__ prio)
 {
-  __shared__ uint64_t red[1024 / kWave];
-  if (blockIdx.x == 0) {
-    pe_writeback_block(v, st, m, slot, wa.mass, prio);
-  } else if (wa.weight_out) {
-    batch_weights(wa, 0, red);
-  }
+  __shared__ uint64_t red[1];
+  const uint32_t shares = (m + kWave - 1) / kWave;
+  if (blockIdx.x < shares)
+    pe_writeback_wave(v, st, m, blockIdx.x * kWave + threadIdx.x, slot, wa.mass, prio);
+  else
+    batch_weights(wa, 0, red, blockIdx.x - shares, shares);
 }
 
 __global__ __launch_bounds__(256) void pe_update_claim_kernel(PeView v, PeState *__restrict__ st, uint32_t m,
@@ -352,7 +355,9 @@ __global__ __launch_bounds__(kPeScanThreads) void pe_remove_kernel(PeView v, PeS
 {
   __shared__ uint32_t wave_before[kPeScanThreads / kWave], wave_own[kPeScanThreads / kWave];
   const uint32_t t = threadIdx.x, wave = t / kWave;
-  const uint64_t rem = first_rem ? first_rem : st->remaining;
+  const uint64_t rem = first_rem ? first_rem : st->remaining, head = st->base.head;
+  uint64_t free_tail = st->free_tail;
+  asm volatile("" : "+s"(free_tail));  // read here, ahead of this workgroup's ticket, and not where it is used
   const uint64_t j0 = (uint64_t)blockIdx.x * kPeScanThreads, j = j0 + t;
   uint32_t before = 0;
   if (block_sums) {
@@ -379,6 +384,18 @@ __global__ __launch_bounds__(kPeScanThreads) void pe_remove_kernel(PeView v, PeS
     place += wave_before[w] + (w < wave ? wave_own[w] : 0);
     own += wave_own[w];
   }
+  // the last workgroup to have read the round's counters closes the round: its ticket comes with what the others
+  // remove (ticket in the low word, removals in the high one); the round trip runs beside those of the other lanes
+  if (t == kPeScanThreads - 1) {
+    const uint64_t tk = __hip_atomic_fetch_add(&st->round_done, ((uint64_t)own << 32) | 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if ((uint32_t)tk == gridDim.x - 1) {
+      const uint64_t removed = (tk >> 32) + own;
+      st->round_done = 0;
+      st->free_tail = free_tail + removed;
+      st->base.head = head + removed;
+      st->remaining = rem - removed;
+    }
+  }
   uint32_t slot = 0;
   uint64_t o1 = 0, o2 = 0;
   if (counts) {
@@ -386,22 +403,9 @@ __global__ __launch_bounds__(kPeScanThreads) void pe_remove_kernel(PeView v, PeS
     o1 = v.ts.level[0][slot], o2 = v.te.level[0][slot];
     v.ts.level[0][slot] = 0;
     v.te.level[0][slot] = 0;
-    v.free_ring[ring_slot(v.ts, st->free_tail + place)] = slot;
+    v.free_ring[ring_slot(v.ts, free_tail + place)] = slot;
   }
   pe_add_runs(v, counts, slot, 0 - o1, 0 - o2);  // the candidates ascend: neighbours share their ancestors
-  // the last workgroup to have read the round's counters closes the round: its ticket comes with what the others
-  // have removed (ticket in the low word, removals in the high one)
-  __syncthreads();
-  if (t == 0) {
-    const uint64_t tk = __hip_atomic_fetch_add(&st->round_done, ((uint64_t)own << 32) | 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if ((uint32_t)tk == gridDim.x - 1) {
-      const uint64_t removed = (tk >> 32) + own;
-      st->round_done = 0;
-      st->free_tail += removed;
-      st->base.head += removed;
-      st->remaining = rem - removed;
-    }
-  }
 }
 
 __global__ __launch_bounds__(256) void pe_init_free_ring_kernel(uint32_t *ring, uint64_t P, PeState *st)
@@ -874,9 +878,10 @@ int apex_pe_sample_update(apex_pe_replay_t *r, uint32_t k, float beta, const uin
   SampleArgs a = pe_sample_args(r, k, rnd, key_out, slot_out, act_out, ret_out, gacc_out);
   a.obs_out = static_cast<uint8_t *>(obs_out);
   APEX_TRY(launch_sample(a, 1, stream));
-  // weights and the write-back of the batch just drawn: one launch of two workgroups
+  // weights and the write-back of the batch just drawn: one launch
   const WeightArgs wa{r->mass(), weight_out, k, beta};
-  pe_finish_update_kernel<<<dim3(2), dim3(1024), 0, stream>>>(wa, r->v, r->state(), k, slot_out, new_prio);
+  const dim3 grid(blocks_for(k, kWave) * (weight_out ? 2 : 1));
+  pe_finish_update_kernel<<<grid, dim3(kWave), 0, stream>>>(wa, r->v, r->state(), k, slot_out, new_prio);
   APEX_HIP(hipGetLastError());
   return APEX_OK;
 }

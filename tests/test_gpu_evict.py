@@ -306,3 +306,33 @@ def test_rounds_at_the_edges_of_the_removal(e):
         rnd = rng.integers(0, U64, (rounds, o.size - cap), dtype=np.uint64)
         assert g.evict(rounds, dev(rnd)) == o.evict(rounds, rnd)
         check(g, o)
+
+
+@pytest.mark.parametrize("k", [1, 63, 64, 65, 128, 129, 1000, 1023, 1024])
+@pytest.mark.parametrize("weights", [True, False])
+def test_write_back_at_the_edges_of_its_waves(k, weights):
+    """apex_pe_sample_update for batches around the waves' shares of 64 pairs, on few transitions of which some are drawn
+    again and again, across the shares too (the last pair of a slot stands)."""
+    from paper_1803_00933_amd import apex
+    rng = np.random.default_rng(k)
+    C, P = 700, 900
+    g, o = apex.PeReplay(C, P, 20, 4), oracle.PrioritizedEvictionReplay(C, P, 20, 4)
+    prio = (rng.pareto(0.5, C) + 1e-3).astype(F32)
+    obs, act = (rng.integers(0, 256, (C, n), dtype=np.uint8) for n in (20, 4))
+    ret, gacc = rng.standard_normal(C).astype(F32), rng.random(C).astype(F32)
+    assert o.add(prio, obs, act, ret, gacc)[0] == 0 and g.add(dev(prio), dev(obs), dev(act), dev(ret), dev(gacc)) == 0
+    for it in range(4):
+        rnd = rng.integers(0, U64, k, dtype=np.uint64)
+        newp = (rng.pareto(0.5, k) + 1e-3).astype(F32)
+        newp[rng.random(k) < 0.1] = np.inf
+        rco, oo = o.sample(1, k, 0.7, rnd)
+        assert rco == 0 and o.update_priorities(oo["key"], newp) == 0
+        out = g.alloc_sample_outputs(1, k)
+        if not weights:
+            out["weight"] = None
+        assert g.sample_update(k, 0.7, dev(rnd), dev(newp), out) == 0
+        torch.cuda.synchronize()
+        if not weights:
+            out["weight"] = torch.from_numpy(oo["weight"].astype(F32))
+        assert_sample_equal(out, oo)
+        check(g, o)
