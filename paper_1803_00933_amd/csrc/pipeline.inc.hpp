@@ -34,6 +34,15 @@ struct apex_pipeline {
   // eviction has just freed, so it waits for the gathers of batches drawn before that eviction
   hipEvent_t last_gather[2] = {nullptr, nullptr};
   hipEvent_t fork_ev = nullptr, join_ev = nullptr;
+  // Work issued on each stream, and how much of it the tree stream has waited for (indices as in streams(); the tree
+  // stream's are not used): join asks the caller's stream to wait for a copy stream only if something on it is left.
+  // fork makes a copy stream wait when it is next used.  An event's record and the wait of another stream for it are some
+  // 10 us of host time each (fork, four launches, join: 27 us with one stream, 42 with two, 55 with three, the launches 10).
+  uint64_t issued[3] = {}, covered[3] = {};
+  uint64_t payload_at = 0;                // issued[1] when payload_done was recorded
+  std::vector<uint64_t> gathered_at;      // the same for gathered
+  bool fork_pending[3] = {};
+  hipStream_t fork_after = nullptr;       // the stream of the latest fork
   std::vector<hipEvent_t> capture_events;
 
   uint64_t step = 0;          // learner steps issued so far
@@ -92,6 +101,21 @@ int mark_wait(apex_pipeline::Mark &m, hipStream_t s)
 {
   if (m.cur) APEX_HIP(hipStreamWaitEvent(s, m.cur, 0));
   return APEX_OK;
+}
+
+int wait_for_fork(apex_pipeline *p, int i)
+{
+  if (p->fork_pending[i] && p->streams(i)) APEX_HIP(hipStreamWaitEvent(p->streams(i), p->fork_ev, 0));
+  p->fork_pending[i] = false;
+  return APEX_OK;
+}
+
+// To be called before work is issued on copy stream i.
+int use_stream(apex_pipeline *p, int i)
+{
+  const int rc = wait_for_fork(p, i);
+  ++p->issued[i];
+  return rc;
 }
 
 void forget_marks(apex_pipeline *p)
@@ -172,6 +196,7 @@ int apex_pipeline_create(apex_replay_t *r, uint32_t depth, const apex_batch_buff
   if (p->wide) {
     ok = ok && !hip_failed(hipStreamCreateWithFlags(&p->add2, hipStreamNonBlocking));
     p->gathered.resize(depth);
+    p->gathered_at.resize(depth);
     for (apex_pipeline::Mark &m : p->gathered) ok = ok && new_mark_event(&m.own);
   }
   if (!ok) {
@@ -196,9 +221,15 @@ int apex_pipeline_fork(apex_pipeline_t *p, void *after)
 {
   if (!p || p->capturing) return APEX_ERR_INVALID_ARG;
   APEX_TRY(issue_held_step(&p->held, p->tree));
-  APEX_HIP(hipEventRecord(p->fork_ev, static_cast<hipStream_t>(after)));
-  for (int i = 0; i < apex_pipeline::kStreams; ++i)
-    if (p->streams(i)) APEX_HIP(hipStreamWaitEvent(p->streams(i), p->fork_ev, 0));
+  const hipStream_t s = static_cast<hipStream_t>(after);
+  // A wait that is due covers this fork too if it is on the same stream; one for another stream's work is made now, before
+  // the event is recorded anew.  (hipStreamPerThread names a stream per host thread.)
+  if (s != p->fork_after || s == hipStreamPerThread)
+    for (int i = 1; i < apex_pipeline::kStreams; ++i) APEX_TRY(wait_for_fork(p, i));
+  APEX_HIP(hipEventRecord(p->fork_ev, s));
+  APEX_HIP(hipStreamWaitEvent(p->tree, p->fork_ev, 0));
+  p->fork_after = s;
+  for (int i = 1; i < apex_pipeline::kStreams; ++i) p->fork_pending[i] = true;
   return APEX_OK;
 }
 
@@ -207,7 +238,7 @@ int apex_pipeline_join(apex_pipeline_t *p, void *stream)
   if (!p || p->capturing) return APEX_ERR_INVALID_ARG;
   APEX_TRY(issue_held_step(&p->held, p->tree));
   for (int i = 0; i < apex_pipeline::kStreams; ++i) {
-    if (!p->streams(i)) continue;
+    if (i != 0 && p->covered[i] == p->issued[i]) continue;
     APEX_HIP(hipEventRecord(p->join_ev, p->streams(i)));
     APEX_HIP(hipStreamWaitEvent(static_cast<hipStream_t>(stream), p->join_ev, 0));
   }
@@ -254,10 +285,16 @@ int apex_pipeline_steps(apex_pipeline_t *p, uint32_t n, float beta, const uint64
     const apex_batch_buffers_t &b = p->sets[set];
     if (p->wide) {
       APEX_TRY(mark_wait(p->gathered[set], p->tree));  // the set's last gather has read slot and mass
+      if (p->step >= p->depth) {
+        const int on = (p->step - p->depth) & 1 ? 2 : 1;
+        p->covered[on] = std::max(p->covered[on], p->gathered_at[set]);
+      }
       APEX_TRY(apex_replay_sample_begin(p->r, p->nb, p->k, rnd + i * per, b.key, b.slot, b.mass, b.act, b.ret, b.gacc,
                                         p->tree));
       APEX_TRY(mark_record(p, p->drawn, p->tree));
-      hipStream_t gs = (p->step & 1) ? p->add2 : p->add;
+      const int gi = (p->step & 1) ? 2 : 1;
+      hipStream_t gs = p->streams(gi);
+      APEX_TRY(use_stream(p, gi));
       APEX_TRY(mark_wait(p->drawn, gs));
       if (p->codec_raw_bytes) {  // weights, then the rows through the decoder
         APEX_TRY(apex_replay_sample_finish(p->r, p->nb, p->k, beta, b.slot, b.mass, b.weight, nullptr, gs));
@@ -267,6 +304,7 @@ int apex_pipeline_steps(apex_pipeline_t *p, uint32_t n, float beta, const uint64
         APEX_TRY(apex_replay_sample_finish(p->r, p->nb, p->k, beta, b.slot, b.mass, b.weight, b.obs, gs));
       }
       APEX_TRY(mark_record(p, p->gathered[set], gs));
+      p->gathered_at[set] = p->issued[gi];
       p->last_gather[p->step & 1] = p->gathered[set].cur;
       if (new_prio) APEX_TRY(apex_replay_update_priorities(p->r, per, b.key, new_prio + i * per, p->tree));
       ++p->step;
@@ -316,6 +354,7 @@ int apex_pipeline_add_begin(apex_pipeline_t *p, uint32_t S, uint32_t T, uint32_t
   } else {
     hipStream_t s = p->add_on_tree ? p->tree : p->add;
     if (!p->add_on_tree) {
+      APEX_TRY(use_stream(p, 1));
       if (p->tail_unmarked) {  // small rounds have moved the tail since the last mark
         APEX_TRY(mark_record(p, p->tail_ready, p->tree));
         p->tail_unmarked = false;
@@ -329,7 +368,10 @@ int apex_pipeline_add_begin(apex_pipeline_t *p, uint32_t S, uint32_t T, uint32_t
       APEX_TRY(apex_replay_add_payload_encoded(r, count, obs, p->codec_raw_bytes, act, ret, gacc, s));
     else
       APEX_TRY(apex_replay_add_payload(r, count, obs, act, ret, gacc, s));
-    if (!p->add_on_tree) APEX_TRY(mark_record(p, p->payload_done, p->add));
+    if (!p->add_on_tree) {
+      APEX_TRY(mark_record(p, p->payload_done, p->add));
+      p->payload_at = p->issued[1];
+    }
   }
   p->add_open = true;
   p->add_count = count;
@@ -340,7 +382,10 @@ int apex_pipeline_add_begin(apex_pipeline_t *p, uint32_t S, uint32_t T, uint32_t
 int apex_pipeline_add_end(apex_pipeline_t *p, int evict, uint64_t *first_key_out, uint64_t *evicted_out)
 {
   if (!p || !p->add_open) return APEX_ERR_INVALID_ARG;
-  if (!p->add_on_tree) APEX_TRY(mark_wait(p->payload_done, p->tree));
+  if (!p->add_on_tree) {
+    APEX_TRY(mark_wait(p->payload_done, p->tree));
+    p->covered[1] = std::max(p->covered[1], p->payload_at);
+  }
   if (p->add_deferred) {
     // in the launch of the step that was held back for it, if there is one and the two fit together
     int rc = issue_held_step_with_round(p->r, &p->held, p->add_ns, p->add_obs, p->add_act, first_key_out, p->tree);
@@ -367,8 +412,11 @@ int apex_pipeline_capture_begin(apex_pipeline_t *p)
 {
   if (!p || p->capturing || p->add_open) return APEX_ERR_INVALID_ARG;
   APEX_TRY(issue_held_step(&p->held, p->tree));
-  for (int i = 0; i < apex_pipeline::kStreams; ++i)  // drained: nothing older to wait for
+  for (int i = 1; i < apex_pipeline::kStreams; ++i) APEX_TRY(wait_for_fork(p, i));  // not to be recorded
+  for (int i = 0; i < apex_pipeline::kStreams; ++i) {  // drained: nothing older to wait for
     if (p->streams(i)) APEX_HIP(hipStreamSynchronize(p->streams(i)));
+    p->covered[i] = p->issued[i];
+  }
   drop_graph(p);
   forget_marks(p);
   APEX_HIP(hipStreamBeginCapture(p->tree, hipStreamCaptureModeRelaxed));

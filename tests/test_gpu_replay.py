@@ -656,6 +656,52 @@ def test_pipeline_matches_the_plain_call_order(nb, k, ob, depth):
     pipe.close()
 
 
+@pytest.mark.parametrize("nb,k", [(1, 64), (16, 128)])      # steps of one launch, steps with gathers on the copy streams
+@pytest.mark.parametrize("second_fork", [None, "same", "other"])
+def test_fork_and_join_order_the_copy_streams(nb, k, second_fork):
+    """The copy streams are only asked to wait where they have to be: what a caller's stream writes late before a fork is
+    seen by a payload copy of a later call, a further fork on the same stream or another one notwithstanding, and a stream
+    that is joined sees the payload of a round that is still open and the rows that the copy streams gather."""
+    from paper_1803_00933_amd import apex
+    rng = np.random.default_rng(nb)
+    T, ob, P = 240, 28224, 4000                     # 6.8 MB of observations: a round on the copy stream
+    g, o = make_pair(P, P, ob, 4)
+    assert add_both(g, o, rng, 2000) == 0
+    pipe = apex.Pipeline(g, 3, nb, k)
+    a, b, c = (torch.cuda.Stream() for _ in range(3))
+    L = T + 1
+    q = torch.zeros((1, L, 2), device="cuda:0")
+    small = [torch.ones((1, L), device="cuda:0") for _ in range(2)]
+    action = torch.zeros((1, L), dtype=torch.int32, device="cuda:0")
+    act = torch.zeros((T, 4), dtype=torch.uint8, device="cuda:0")
+    scratch = [torch.empty(T, device="cuda:0") for _ in range(3)]
+    real = dev(rng.integers(0, 256, (T, ob), dtype=np.uint8))
+    rnd, newp = dev(rng.integers(0, U64, (3, nb * k), dtype=np.uint64)), torch.ones((3, nb * k), device="cuda:0")
+    for it in range(3):
+        obs = torch.zeros((T, ob), dtype=torch.uint8, device="cuda:0")
+        ring = g.obs_view()[2000 + it * T:2000 + (it + 1) * T]
+        torch.cuda.synchronize()
+        with torch.cuda.stream(a):
+            torch.cuda._sleep(20_000_000)           # some ms
+            obs.copy_(real)
+        assert pipe.fork(a) == 0
+        if second_fork:
+            assert pipe.fork(a if second_fork == "same" else b) == 0
+        assert pipe.add_begin(q, q, action, *small, 1, obs, act, *scratch) == 0
+        assert pipe.steps(3, 0.4, rnd, newp)[0] == 0
+        assert pipe.join(c) == 0
+        with torch.cuda.stream(c):
+            seen = [ring.clone()] + [s["obs"].clone() for s in pipe.sets]
+        c.synchronize()
+        torch.cuda.synchronize()
+        assert torch.equal(seen[0], real)
+        assert all(torch.equal(x, s["obs"]) for x, s in zip(seen[1:], pipe.sets))
+        assert pipe.add_end()[0] == 0
+        assert pipe.join(c) == 0
+        torch.cuda.synchronize()
+    pipe.close()
+
+
 @pytest.mark.parametrize("streams", [48, 30])      # a round on the copy stream (5 MB), one on the learner's stream
 def test_wide_steps_are_gathered_before_their_slots_are_reused(streams):
     """A ring with no slack: every add round lands in the slots that the eviction before it has just freed, and
