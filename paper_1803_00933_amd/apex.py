@@ -1,8 +1,9 @@
-"""Thin ctypes binding of ``libapex_replay.so`` (declared in ``include/apex_replay.h``).
+"""Thin binding of ``libapex_replay.so`` (declared in ``include/apex_replay.h``).
 
 Argument marshalling only: every step of the replay path runs in the library's HIP kernels.
 PyTorch supplies device memory (``tensor.data_ptr()``) and the current stream, nothing else.
-There is no fallback: if the library has not been built, importing this module raises.
+The calls of the path itself are marshalled by ``apex_binding.so`` (``csrc/binding.cpp``), set-up and the rest by ctypes.
+There is no fallback: if either has not been built, importing this module raises.
 """
 import ctypes as C
 import os
@@ -80,6 +81,9 @@ if not os.path.exists(LIB_PATH):
     raise ImportError("%s is missing: build it first (python paper_1803_00933_amd/build.py or "
                       "__graft_entry__.build()); there is no fallback path" % LIB_PATH)
 
+if not os.path.exists(os.path.join(_HERE, "apex_binding.so")):
+    raise ImportError("apex_binding.so is missing from %s: build it first, as libapex_replay.so" % _HERE)
+
 lib = C.CDLL(LIB_PATH)
 _vp, _u32, _u64, _f32 = C.c_void_p, C.c_uint32, C.c_uint64, C.c_float
 lib.apex_replay_workspace_bytes.argtypes = [C.POINTER(Config)] + [C.POINTER(C.c_size_t)] * 3
@@ -150,6 +154,11 @@ def _stream(stream=None):
     return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
+from . import apex_binding as _call  # noqa: E402  (behind torch, whose libraries it needs, and the checks above)
+
+_call.load(os.path.abspath(LIB_PATH), _ptr, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
+
+
 def workspace_bytes(cfg: Config):
     a, b, c = C.c_size_t(0), C.c_size_t(0), C.c_size_t(0)
     rc = lib.apex_replay_workspace_bytes(C.byref(cfg), C.byref(a), C.byref(b), C.byref(c))
@@ -170,9 +179,8 @@ def nstep_priorities(q_online, q_target, action, reward, discount, n, alpha, eps
         fx = torch.empty((S, T), dtype=torch.int64, device=dev) if want_fx else None
     else:
         prio, ret, gacc, fx = out
-    rc = lib.apex_nstep_priorities(S, T, n, A, _ptr(q_online), _ptr(q_target), _ptr(action), _ptr(reward),
-                                   _ptr(discount), alpha, eps, frac_bits, max_slots, _ptr(prio), _ptr(ret),
-                                   _ptr(gacc), _ptr(fx), _stream(stream))
+    rc = _call.nstep_priorities(S, T, n, A, q_online, q_target, action, reward, discount, alpha, eps, frac_bits, max_slots,
+                                prio, ret, gacc, fx, stream)
     return rc, prio, ret, gacc, fx
 
 
@@ -195,7 +203,7 @@ class Replay:
                                     self.scratch.data_ptr(), C.byref(h))
         if rc != OK:
             raise RuntimeError("apex_replay_create: %s (hip %d)" % (STATUS_NAMES.get(rc, rc), lib.apex_last_hip_error()))
-        self.h = h
+        self.h, self._raw = h, h.value
         self.capacity, self.max_slots, self.obs_bytes, self.act_bytes = capacity, max_slots, obs_bytes, act_bytes
         lay = Layout()
         lib.apex_replay_layout(self.h, C.byref(lay))
@@ -204,7 +212,7 @@ class Replay:
     def close(self):
         if getattr(self, "h", None) and lib is not None:     # (lib is None while the interpreter shuts down)
             lib.apex_replay_destroy(self.h)
-            self.h = None
+            self.h = self._raw = None
 
     __del__ = close
 
@@ -231,10 +239,7 @@ class Replay:
 
     # -- the replay verbs -----------------------------------------------------------------------
     def add(self, prio, obs=None, act=None, ret=None, gacc=None, stream=None):
-        first = _u64(0)
-        rc = lib.apex_replay_add(self.h, prio.shape[0], _ptr(obs), _ptr(act), _ptr(ret), _ptr(gacc), _ptr(prio),
-                                 C.byref(first), _stream(stream))
-        return rc, int(first.value)
+        return _call.add(self._raw, prio.shape[0], obs, act, ret, gacc, prio, stream)
 
     def alloc_sample_outputs(self, num_batches, k, payload=True):
         n, dev = num_batches * k, self.device
@@ -251,25 +256,21 @@ class Replay:
     def sample(self, num_batches, k, beta, rnd, out=None, payload=True, stream=None):
         if out is None:
             out = self.alloc_sample_outputs(num_batches, k, payload)
-        rc = lib.apex_replay_sample(self.h, num_batches, k, beta, _ptr(rnd), _ptr(out.get("key")), _ptr(out["slot"]),
-                                    _ptr(out.get("weight")), _ptr(out.get("obs")), _ptr(out.get("act")),
-                                    _ptr(out.get("ret")), _ptr(out.get("gacc")), _stream(stream))
-        return rc, out
+        get = out.get
+        return _call.sample(self._raw, num_batches, k, beta, rnd, get("key"), out["slot"], get("weight"), get("obs"),
+                            get("act"), get("ret"), get("gacc"), stream), out
 
     def sample_noalloc(self, num_batches, k, beta, rnd, out, stream=None):
         """apex_replay_sample_noalloc into caller-made outputs (see alloc_sample_outputs)."""
-        return lib.apex_replay_sample_noalloc(self.h, num_batches, k, beta, _ptr(rnd), _ptr(out.get("key")),
-                                              _ptr(out["slot"]), _ptr(out.get("weight")), _ptr(out.get("obs")),
-                                              _ptr(out.get("act")), _ptr(out.get("ret")), _ptr(out.get("gacc")),
-                                              _stream(stream))
+        get = out.get
+        return _call.sample_noalloc(self._raw, num_batches, k, beta, rnd, get("key"), out["slot"], get("weight"),
+                                    get("obs"), get("act"), get("ret"), get("gacc"), stream)
 
     def add_payload(self, count, obs=None, act=None, ret=None, gacc=None, stream=None):
-        return lib.apex_replay_add_payload(self.h, count, _ptr(obs), _ptr(act), _ptr(ret), _ptr(gacc), _stream(stream))
+        return _call.add_payload(self._raw, count, obs, act, ret, gacc, stream)
 
     def add_publish(self, prio, stream=None):
-        first = _u64(0)
-        rc = lib.apex_replay_add_publish(self.h, prio.shape[0], _ptr(prio), C.byref(first), _stream(stream))
-        return rc, int(first.value)
+        return _call.add_publish(self._raw, prio.shape[0], prio, stream)
 
     def sample_begin(self, num_batches, k, rnd, out, stream=None):
         """out needs 'slot' and 'mass' (int64 [nb*k]); 'key', 'act', 'ret', 'gacc' are optional."""
@@ -300,12 +301,12 @@ class Replay:
                                       _stream(stream))
 
     def update_priorities(self, key, prio, stream=None):
-        return lib.apex_replay_update_priorities(self.h, key.shape[0], _ptr(key), _ptr(prio), _stream(stream))
+        return _call.update_priorities(self._raw, key.shape[0], key, prio, stream)
 
     def add_payload_encoded(self, raw_obs, act=None, ret=None, gacc=None, stream=None):
         """raw_obs: uint8 [count, raw_bytes], stored through the observation codec."""
-        return lib.apex_replay_add_payload_encoded(self.h, raw_obs.shape[0], _ptr(raw_obs), raw_obs.shape[1], _ptr(act),
-                                                   _ptr(ret), _ptr(gacc), _stream(stream))
+        count, raw_bytes = raw_obs.shape[0], raw_obs.shape[1]
+        return _call.add_payload_encoded(self._raw, count, raw_obs, raw_bytes, act, ret, gacc, stream)
 
     def gather_decoded(self, slot, obs, act=None, ret=None, gacc=None, stream=None):
         """obs: uint8 [count, raw_bytes] receives the decoded observations of the slots."""
@@ -313,14 +314,11 @@ class Replay:
                                               _ptr(ret), _ptr(gacc), _stream(stream))
 
     def update_from_q(self, key, q_taken, q_online_next, q_target_next, prio_out=None, stream=None):
-        return lib.apex_replay_update_from_q(self.h, key.shape[0], _ptr(key), q_online_next.shape[1], _ptr(q_taken),
-                                             _ptr(q_online_next), _ptr(q_target_next), _ptr(prio_out),
-                                             _stream(stream))
+        return _call.update_from_q(self._raw, key.shape[0], key, q_online_next.shape[1], q_taken, q_online_next,
+                                   q_target_next, prio_out, stream)
 
     def evict(self, stream=None):
-        e = _u64(0)
-        rc = lib.apex_replay_evict(self.h, C.byref(e), _stream(stream))
-        return rc, int(e.value)
+        return _call.evict(self._raw, stream)
 
     def stats(self, stream=None):
         st = Stats()
@@ -347,20 +345,20 @@ class Pipeline:
         rc = lib.apex_pipeline_create(rep.h, depth, arr, num_batches, k, C.byref(h))
         if rc != OK:
             raise RuntimeError("apex_pipeline_create: %s" % STATUS_NAMES.get(rc, rc))
-        self.h = h
+        self.h, self._raw = h, h.value
 
     def close(self):
         if getattr(self, "h", None) and lib is not None:
             lib.apex_pipeline_destroy(self.h)
-            self.h = None
+            self.h = self._raw = None
 
     __del__ = close
 
     def fork(self, after=None):
-        return lib.apex_pipeline_fork(self.h, _stream(after))
+        return _call.pipeline_fork(self._raw, after)
 
     def join(self, stream=None):
-        return lib.apex_pipeline_join(self.h, _stream(stream))
+        return _call.pipeline_join(self._raw, stream)
 
     def set_codec(self, raw_bytes):
         """Observations through the block codec: the sets' 'obs' become [nb*k, raw_bytes] views of their buffers."""
@@ -373,15 +371,12 @@ class Pipeline:
         return rc
 
     def steps(self, n, beta, rnd, new_prio=None):
-        first = _u32(0)
-        rc = lib.apex_pipeline_steps(self.h, n, beta, _ptr(rnd), _ptr(new_prio), C.byref(first))
-        return rc, int(first.value)
+        return _call.pipeline_steps(self._raw, n, beta, rnd, new_prio)
 
     def add_begin(self, q_online, q_target, action, reward, discount, n, obs, act, prio, ret, gacc):
         S, L, A = q_online.shape
-        return lib.apex_pipeline_add_begin(self.h, S, L - n, n, A, _ptr(q_online), _ptr(q_target), _ptr(action),
-                                           _ptr(reward), _ptr(discount), _ptr(obs), _ptr(act), _ptr(prio), _ptr(ret),
-                                           _ptr(gacc))
+        return _call.pipeline_add_begin(self._raw, S, L - n, n, A, q_online, q_target, action, reward, discount, obs, act,
+                                        prio, ret, gacc)
 
     def capture_begin(self):
         return lib.apex_pipeline_capture_begin(self.h)
@@ -393,9 +388,7 @@ class Pipeline:
         return lib.apex_pipeline_replay(self.h, times)
 
     def add_end(self, evict=False):
-        first, ev = _u64(0), _u64(0)
-        rc = lib.apex_pipeline_add_end(self.h, int(evict), C.byref(first), C.byref(ev))
-        return rc, int(first.value), int(ev.value)
+        return _call.pipeline_add_end(self._raw, int(evict))
 
 
 def eviction_uniforms(rnd, rounds, e):
@@ -432,7 +425,7 @@ class PeReplay:
                                 self.scratch.data_ptr(), C.byref(h))
         if rc != OK:
             raise RuntimeError("apex_pe_create: %s" % STATUS_NAMES.get(rc, rc))
-        self.h = h
+        self.h, self._raw = h, h.value
         self.capacity, self.max_slots, self.obs_bytes, self.act_bytes = capacity, max_slots, obs_bytes, act_bytes
         self.layout = PeLayout()
         lib.apex_pe_layout(self.h, C.byref(self.layout))
@@ -440,7 +433,7 @@ class PeReplay:
     def close(self):
         if getattr(self, "h", None) and lib is not None:
             lib.apex_pe_destroy(self.h)
-            self.h = None
+            self.h = self._raw = None
 
     __del__ = close
 
@@ -461,8 +454,7 @@ class PeReplay:
         return self.storage[o:o + self.max_slots * self.obs_bytes].view(self.max_slots, self.obs_bytes)
 
     def add(self, prio, obs=None, act=None, ret=None, gacc=None, stream=None):
-        return lib.apex_pe_add(self.h, prio.shape[0], _ptr(obs), _ptr(act), _ptr(ret), _ptr(gacc), _ptr(prio),
-                               _stream(stream))
+        return _call.pe_add(self._raw, prio.shape[0], obs, act, ret, gacc, prio, stream)
 
     def alloc_sample_outputs(self, num_batches, k):
         n, dev = num_batches * k, self.device
@@ -476,13 +468,12 @@ class PeReplay:
     def sample(self, num_batches, k, beta, rnd, out=None, stream=None):
         if out is None:
             out = self.alloc_sample_outputs(num_batches, k)
-        rc = lib.apex_pe_sample(self.h, num_batches, k, beta, _ptr(rnd), _ptr(out.get("key")), _ptr(out["slot"]),
-                                _ptr(out.get("weight")), _ptr(out.get("obs")), _ptr(out.get("act")),
-                                _ptr(out.get("ret")), _ptr(out.get("gacc")), _stream(stream))
-        return rc, out
+        get = out.get
+        return _call.pe_sample(self._raw, num_batches, k, beta, rnd, get("key"), out["slot"], get("weight"), get("obs"),
+                               get("act"), get("ret"), get("gacc"), stream), out
 
     def update_priorities(self, key, prio, stream=None):
-        return lib.apex_pe_update_priorities(self.h, key.shape[0], _ptr(key), _ptr(prio), _stream(stream))
+        return _call.pe_update_priorities(self._raw, key.shape[0], key, prio, stream)
 
     def _checked_uniforms(self, rounds, rnd, stream):
         """rnd, long enough for whatever the next eviction will ask for (see eviction_uniforms)."""
@@ -504,19 +495,16 @@ class PeReplay:
 
     def evict_enqueue(self, rounds, rnd, stream=None):
         """apex_pe_evict_enqueue: returns (rc, number of evictions asked for) without waiting for the eviction."""
-        e, rnd = _u64(0), self._checked_uniforms(rounds, rnd, stream)
-        rc = lib.apex_pe_evict_enqueue(self.h, rounds, _ptr(rnd), C.byref(e), _stream(stream))
-        return rc, int(e.value)
+        return _call.pe_evict_enqueue(self._raw, rounds, self._checked_uniforms(rounds, rnd, stream), stream)
 
     def add_round(self, q_online, q_target, action, reward, discount, n, obs, act=None, stream=None):
         S, L, A = q_online.shape
-        return lib.apex_pe_add_round(self.h, S, L - n, n, A, _ptr(q_online), _ptr(q_target), _ptr(action), _ptr(reward),
-                                     _ptr(discount), _ptr(obs), _ptr(act), _stream(stream))
+        return _call.pe_add_round(self._raw, S, L - n, n, A, q_online, q_target, action, reward, discount, obs, act, stream)
 
     def sample_update(self, k, beta, rnd, new_prio, out, stream=None):
-        return lib.apex_pe_sample_update(self.h, k, beta, _ptr(rnd), _ptr(new_prio), _ptr(out["key"]), _ptr(out["slot"]),
-                                         _ptr(out.get("weight")), _ptr(out.get("obs")), _ptr(out.get("act")),
-                                         _ptr(out.get("ret")), _ptr(out.get("gacc")), _stream(stream))
+        get = out.get
+        return _call.pe_sample_update(self._raw, k, beta, rnd, new_prio, out["key"], out["slot"], get("weight"), get("obs"),
+                                      get("act"), get("ret"), get("gacc"), stream)
 
     def stats(self, stream=None):
         st = PeStats()

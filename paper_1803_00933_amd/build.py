@@ -1,6 +1,9 @@
-"""Builds ``libapex_replay.so`` (HIP, gfx950) next to this file.  Cross-compiles without a GPU."""
+"""Builds ``libapex_replay.so`` (HIP, gfx950) and ``apex_binding.so`` (its binding for Python and PyTorch) next to this
+file.  Cross-compiles without a GPU."""
+import importlib.util
 import os
 import subprocess
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -39,10 +42,29 @@ def build_library(verbose=False, sanitize_host=False):
     return out
 
 
+BINDING = os.path.join(HERE, "apex_binding.so")
+
+
+def build_binding(verbose=False):
+    """The Python calls of the path (csrc/binding.cpp), against the headers of this interpreter and its PyTorch."""
+    torch_dir = os.path.dirname(importlib.util.find_spec("torch").origin)
+    tmp = BINDING + ".tmp.%d" % os.getpid()
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-shared", "-fPIC", "-fvisibility=hidden", "-Wall", "-Wextra",
+           "-Wno-unused-parameter", "-I", os.path.join(ROOT, "include"), "-isystem", sysconfig.get_paths()["include"],
+           "-isystem", os.path.join(torch_dir, "include"), "-o", tmp, os.path.join(HERE, "csrc", "binding.cpp"),
+           "-L", os.path.join(torch_dir, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    if verbose:
+        print(" ".join(cmd))
+    subprocess.check_call(cmd)
+    os.replace(tmp, BINDING)
+    return BINDING
+
+
 def asan_runtime():
     """Path of the AddressSanitizer runtime that belongs to hipcc's host compiler."""
     return subprocess.check_output([HIPCC, "-print-file-name=libclang_rt.asan-x86_64.so"], text=True).strip()
 
 
 if __name__ == "__main__":
+    print(build_binding(verbose=True))
     print(build_library(verbose=True))

@@ -117,3 +117,33 @@ def test_uniforms_of_an_eviction_cover_what_the_library_addresses():
     for rounds, e in ((1, 13), (3, 100)):
         with pytest.raises(ValueError):
             apex.eviction_uniforms(rnd, rounds, e)
+
+
+def test_binding_refuses_what_it_cannot_address():
+    """The calls marshalled by the extension: the library's status for a missing handle, and errors for tensors that have
+    no device address to give, for numbers that are none, and for a wrong count of arguments."""
+    import pytest
+    import torch
+    from paper_1803_00933_amd import apex
+    call, bad = apex._call, apex.ERR_INVALID_ARG
+
+    class stream:
+        cuda_stream = 0
+
+    assert call.update_priorities(None, 0, None, None, stream) == bad
+    assert call.evict(None, stream) == (bad, 0) and call.pipeline_add_end(None, 1) == (bad, 0, 0)
+    assert call.pipeline_steps(None, 1, 0.4, None, None) == (bad, 0) and call.pipeline_fork(None, stream) == bad
+    for t in (torch.zeros(4), torch.zeros((4, 4)).t()):
+        with pytest.raises(AssertionError):
+            call.update_priorities(None, 1, t, None, stream)
+    with pytest.raises(AttributeError):
+        call.update_priorities(None, 1, 4096, None, stream)             # a bare address is no tensor
+    for args in ((None, 1.0, None, None, stream), (None, "1", None, None, stream), ("h", 1, None, None, stream)):
+        with pytest.raises(TypeError):
+            call.update_priorities(*args)
+    with pytest.raises(TypeError):
+        call.update_priorities(None, 0, None, None)
+    with pytest.raises(TypeError):
+        call.pipeline_steps(None, 1, "0.4", None, None)
+    with pytest.raises(AttributeError):
+        call.evict(None, 7)                                             # no stream
