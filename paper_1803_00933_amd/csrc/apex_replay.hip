@@ -670,7 +670,7 @@ bool sample_by_rows(uint64_t obs_bytes, uint32_t num_batches, uint32_t k)
   const uint64_t samples = (uint64_t)num_batches * k;
   if (obs_bytes < 16 || k > kSampleRowsMaxK || samples > kSampleRowsMax) return false;
   if (obs_bytes > kGatherInDrawBytes) return true;
-  return obs_bytes >= 2048 ? k <= obs_bytes / 4 : samples <= 448;
+  return obs_bytes >= 2048 ? k <= obs_bytes / 4 : samples <= 384;
 }
 
 // a.k samples of each of num_batches batches, as sample_by_rows has it.  Two pieces per lane as long as the chip holds all
@@ -680,7 +680,7 @@ int launch_sample_rows(SampleArgs &a, uint32_t num_batches, hipStream_t stream, 
   a.k_div = make_fast_div(a.k);
   const uint32_t groups = blocks_for(a.k, kTicketGroup);
   if (a.weight_out) take_tickets(a, num_batches * (groups > 1 ? 1 + groups : 1), tickets);
-  const uint32_t vpr = (uint32_t)((a.obs_bytes + 15) / 16);
+  const uint32_t vpr = (uint32_t)((a.g.obs_bytes + 15) / 16);
   const auto waves = [&](uint32_t pieces) { return std::min(1 + blocks_for(vpr, pieces * kWave), 1024u / kWave); };
   const bool two = (uint64_t)num_batches * a.k * waves(2) <= kChipWaves, wide = a.tv.n_top > 512;
   const dim3 grid(a.k, num_batches), block(waves(two ? 2 : 4) * kWave);
@@ -724,13 +724,13 @@ int sample_args(apex_replay *r, uint32_t num_batches, uint32_t k, const uint64_t
   a.key_out = key_out;
   a.slot_out = slot_out;
   a.mass = mass_out;
-  a.act = r->act();
-  a.act_bytes = r->cfg.act_bytes;
-  a.ret = r->ret();
-  a.gacc = r->gacc();
-  a.act_out = static_cast<uint8_t *>(act_out);
-  a.ret_out = ret_out;
-  a.gacc_out = gacc_out;
+  a.g.act = r->act();
+  a.g.act_bytes = r->cfg.act_bytes;
+  a.g.ret = r->ret();
+  a.g.gacc = r->gacc();
+  a.g.act_out = static_cast<uint8_t *>(act_out);
+  a.g.ret_out = ret_out;
+  a.g.gacc_out = gacc_out;
   return APEX_OK;
 }
 
@@ -762,14 +762,14 @@ int sample_in_one(apex_replay *r, uint32_t num_batches, uint32_t k, float beta, 
   SampleArgs a;
   const int rc = sample_args(r, num_batches, k, rnd, key_out, slot_out, mass_out, act_out, ret_out, gacc_out, &a);
   if (rc != APEX_OK) return rc;
-  a.obs = r->obs();
-  a.obs_bytes = r->cfg.obs_bytes;
-  a.obs_out = static_cast<uint8_t *>(obs_out);
+  a.g.obs = r->obs();
+  a.g.obs_bytes = r->cfg.obs_bytes;
+  a.g.obs_out = static_cast<uint8_t *>(obs_out);
   a.weight_out = k <= kWeightsInDrawMaxK ? weight_out : nullptr;
   a.beta = beta;
   a.ticket = r->tickets();
   a.claim = claim ? r->claim() : nullptr;
-  const int rl = !claim && obs_out && sample_by_rows(a.obs_bytes, num_batches, k)
+  const int rl = !claim && obs_out && sample_by_rows(a.g.obs_bytes, num_batches, k)
                      ? launch_sample_rows(a, num_batches, stream, &r->ticket_use)
                      : launch_sample(a, num_batches, stream, &r->ticket_use);
   return rl != APEX_OK || a.weight_out == weight_out ? rl
@@ -1018,6 +1018,78 @@ int fused_steps(apex_replay *r, uint32_t n, uint32_t k, float beta, const uint64
   }
   // (every change has now been applied to both copies)
   if (new_prio) r->second_version = ++r->tree_version;
+  APEX_HIP(hipGetLastError());
+  return APEX_OK;
+}
+
+// Whether n steps of num_batches x k samples go that way: several batches, or one that is too large for a workgroup per
+// sample, of rows that sample_kernel gathers, with room for their changes in the scratch region.
+// The second copy of the tree may have to be brought up to date first, at some 5 TB/s; a step gains 7 us.
+constexpr uint64_t kTreeWordsPerStep = 2u << 20;
+
+bool multi_steps_fit(const apex_replay *r, uint32_t n, uint32_t num_batches, uint32_t k, uint32_t depth)
+{
+  const uint64_t samples = (uint64_t)num_batches * k;
+  if ((num_batches == 1 && k <= kStepMaxK) || depth < 2 || depth * samples > (uint64_t)kStepSets * kStepMaxK) return false;
+  if (r->second_version != r->tree_version && (n + 1) * kTreeWordsPerStep < 2 * r->geo.tree_words) return false;
+  return gather_in_draw(r);
+}
+
+// n learner steps of num_batches x k each whose new priorities are known, in strict order, as one launch per step and one
+// for the first draw: see multi_step_kernel.
+int multi_steps(apex_replay *r, uint32_t n, uint32_t num_batches, uint32_t k, float beta, const uint64_t *rnd,
+                const float *new_prio, const apex_batch_buffers_t *sets, uint32_t depth, uint32_t first_set,
+                hipStream_t stream)
+{
+  const uint64_t size = r->tail - r->head;  // the gate of apex_replay_sample, before anything is enqueued
+  if (size < r->cfg.min_size_to_sample) return APEX_ERR_NOT_READY;
+  if (size == 0) return APEX_ERR_EMPTY;
+  const uint32_t samples = num_batches * k;
+  if (r->second_version != r->tree_version)
+    copy_words_kernel<<<dim3(2048), dim3(256), 0, stream>>>(r->tv2.level[0], r->tv.level[0], r->geo.tree_words);
+  const auto changes = [&](uint32_t set) { return r->stepq(0) + (uint64_t)set * samples; };
+  for (uint32_t i = 0; i <= n; ++i) {  // launch i gathers step i - 1 and draws step i
+    MultiStepArgs a{};
+    a.samples = samples;
+    a.batches = num_batches;
+    a.qp = r->qp;
+    a.st = r->state();
+    a.wr = i & 1 ? r->tv : r->tv2;
+    uint32_t weight_wgs = 0;
+    if (i > 0) {
+      const uint32_t set = (first_set + i - 1) % depth;
+      const apex_batch_buffers_t &b = sets[set];
+      a.g = GatherArgs{r->act(), r->cfg.act_bytes, r->ret(), r->gacc(), static_cast<uint8_t *>(b.act), b.ret, b.gacc,
+                       r->obs(), r->cfg.obs_bytes, static_cast<uint8_t *>(b.obs)};
+      a.slot = b.slot;
+      a.dq = changes(set);
+      a.wa = WeightArgs{b.mass, b.weight, k, beta};
+      a.gather_wgs = blocks_for(samples, kMultiStepRows);
+      weight_wgs = num_batches;
+    }
+    if (i < n) {
+      const uint32_t set = (first_set + i) % depth;
+      const apex_batch_buffers_t &b = sets[set];
+      a.next.tv = i & 1 ? r->tv2 : r->tv;
+      a.next.st = r->state();
+      a.next.k = k;
+      a.next.rnd = rnd + (uint64_t)i * samples;
+      a.next.key_out = b.key;
+      a.next.slot_out = b.slot;
+      a.next.mass = b.mass;
+      a.next_k_div = make_fast_div(k);
+      a.next_prio = new_prio + (uint64_t)i * samples;
+      a.next_dq = changes(set);
+      a.draw_wgs_per_batch = blocks_for(k, kMultiStepRows);
+      a.draw_wgs = num_batches * a.draw_wgs_per_batch;
+    }
+    const dim3 grid(a.draw_wgs + a.gather_wgs + weight_wgs), block(kMultiStepThreads);
+    if (r->tv.n_top > 512)
+      multi_step_kernel<true><<<grid, block, 0, stream>>>(a);
+    else
+      multi_step_kernel<false><<<grid, block, 0, stream>>>(a);
+  }
+  r->second_version = ++r->tree_version;  // every change is in both copies
   APEX_HIP(hipGetLastError());
   return APEX_OK;
 }

@@ -554,11 +554,11 @@ int pe_enqueue_eviction(apex_pe_replay *r, uint64_t e, uint32_t rounds, const ui
   a.key_out = nullptr;
   a.slot_out = r->cand();
   a.mass = r->mass();
-  a.act = nullptr;
-  a.act_bytes = 0;
-  a.ret = a.gacc = nullptr;
-  a.act_out = nullptr;
-  a.ret_out = a.gacc_out = nullptr;
+  a.g.act = nullptr;
+  a.g.act_bytes = 0;
+  a.g.ret = a.g.gacc = nullptr;
+  a.g.act_out = nullptr;
+  a.g.ret_out = a.g.gacc_out = nullptr;
   const dim3 grid(blocks_for(e, kPeScanThreads)), block(kPeScanThreads);  // <= 1024 workgroups since e <= 2^20
   uint32_t *const sums = e > kPeRecountMax ? r->sums() : nullptr;
   for (uint32_t rd = 0; rd < rounds; ++rd) {
@@ -586,15 +586,15 @@ SampleArgs pe_sample_args(apex_pe_replay *r, uint32_t k, const uint64_t *rnd, ui
   a.key_out = key_out;
   a.slot_out = slot_out;
   a.mass = r->mass();
-  a.act = r->act();
-  a.act_bytes = r->cfg.act_bytes;
-  a.ret = r->ret();
-  a.gacc = r->gacc();
-  a.act_out = static_cast<uint8_t *>(act_out);
-  a.ret_out = ret_out;
-  a.gacc_out = gacc_out;
-  a.obs = r->obs();
-  a.obs_bytes = r->cfg.obs_bytes;
+  a.g.act = r->act();
+  a.g.act_bytes = r->cfg.act_bytes;
+  a.g.ret = r->ret();
+  a.g.gacc = r->gacc();
+  a.g.act_out = static_cast<uint8_t *>(act_out);
+  a.g.ret_out = ret_out;
+  a.g.gacc_out = gacc_out;
+  a.g.obs = r->obs();
+  a.g.obs_bytes = r->cfg.obs_bytes;
   a.ticket = r->tickets();
   return a;
 }
@@ -758,7 +758,7 @@ int apex_pe_sample(apex_pe_replay_t *r, uint32_t num_batches, uint32_t k, float 
   jobs.wa = WeightArgs{r->mass(), weight_out, k, beta};
   const bool by_rows = obs_out && sample_by_rows(r->cfg.obs_bytes, num_batches, k);
   const bool gather = obs_out && (by_rows || r->cfg.obs_bytes <= kGatherInDrawBytes);
-  if (gather) a.obs_out = static_cast<uint8_t *>(obs_out);
+  if (gather) a.g.obs_out = static_cast<uint8_t *>(obs_out);
   if ((gather || !obs_out) && k <= kWeightsInDrawMaxK) {
     a.weight_out = weight_out;
     a.beta = beta;
@@ -876,7 +876,7 @@ int apex_pe_sample_update(apex_pe_replay_t *r, uint32_t k, float beta, const uin
   if (r->size() == 0) return APEX_ERR_EMPTY;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   SampleArgs a = pe_sample_args(r, k, rnd, key_out, slot_out, act_out, ret_out, gacc_out);
-  a.obs_out = static_cast<uint8_t *>(obs_out);
+  a.g.obs_out = static_cast<uint8_t *>(obs_out);
   APEX_TRY(launch_sample(a, 1, stream));
   // weights and the write-back of the batch just drawn: one launch
   const WeightArgs wa{r->mass(), weight_out, k, beta};

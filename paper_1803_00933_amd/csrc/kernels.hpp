@@ -1182,11 +1182,8 @@ struct DrawArgs {
   uint64_t *mass;            // [nb,k]: mass of each drawn transition, for the weights
 };
 
-struct SampleArgs : DrawArgs {
-  const uint64_t *k_dev;     // not null: the number of samples is read here, on the device (waves beyond it idle)
-  FastDiv k_div;             // division by k (unused with k_dev)
-  const uint32_t *gen;       // not null: keys are (generation of the slot << 32) | slot instead of ring keys
-  // payload columns and their outputs (each output may be null)
+// The payload columns of a transition and where a gather writes them (each output may be null).
+struct GatherArgs {
   const uint8_t *act;
   uint32_t act_bytes;
   const float *ret, *gacc;
@@ -1194,7 +1191,14 @@ struct SampleArgs : DrawArgs {
   float *ret_out, *gacc_out;
   const uint8_t *obs;
   uint64_t obs_bytes;
-  uint8_t *obs_out;          // null: the rows are gathered by another launch (copy_rows_*)
+  uint8_t *obs_out;
+};
+
+struct SampleArgs : DrawArgs {
+  const uint64_t *k_dev;     // not null: the number of samples is read here, on the device (waves beyond it idle)
+  FastDiv k_div;             // division by k (unused with k_dev)
+  const uint32_t *gen;       // not null: keys are (generation of the slot << 32) | slot instead of ring keys
+  GatherArgs g;              // obs_out null: the rows are gathered by another launch (copy_rows_*)
   float *weight_out;         // null: no weights, or written by another launch (batch_weights)
   float beta;
   uint32_t *ticket;          // with weight_out: words that lie kTicketStride apart, 0 before and after: one per batch ...
@@ -1432,6 +1436,73 @@ __device__ __forceinline__ void copy_row_by_16(uint8_t *__restrict__ d, const ui
   }
 }
 
+// The walks of four samples, one per 16-lane row, from points (every lane of a row holds its sample's) down to the slots.
+// between(): called when the walk has left the top level.
+template <bool kWide, typename Between>
+__device__ __forceinline__ RowWalk walk_four(const TreeView &tv, const TopLevel<kWide> &top, const uint64_t *top_level,
+                                             uint64_t point, Between between)
+{
+  const uint32_t lane = lane_id();
+  // top level: the lane that holds the node by a ballot per sample, then its eight nodes anew (they are in the
+  // first cache), as if they were the children of a node
+  uint32_t l = 0;
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    const uint32_t ls = top.find_group(read_lane_u64(point, 16 * s));
+    l = lane / 16 == (uint32_t)s ? ls : l;
+  }
+  uint64_t before = __shfl(top.before, l & (kWave - 1), kWave);
+  if (top.wide) {
+    const uint64_t before_w = __shfl(top.before_w, l & (kWave - 1), kWave);
+    before = l < kWave ? before : before_w;
+  }
+  RowWalk walk;
+  walk.x = point - before;
+  walk.idx = l;
+  row_descend(walk, top_level, 3);
+  between();
+  uint32_t fl = tv.top_log2;
+  for (int lv = (int)tv.nlev - 2; lv >= 0; --lv) {
+    row_descend(walk, tv.level[lv], fl);
+    fl = kFanoutLog2;
+  }
+  return walk;
+}
+
+// Transition `slot` into place o of the outputs, by one 16-lane row of a wave.  Everything that the wave has issued before
+// is through when the first output is stored.
+__device__ __forceinline__ void gather_by_16(const GatherArgs &a, uint64_t slot, uint64_t o)
+{
+  // the small columns' loads go out with those of the observation row: partial return, accumulated discount, and the first
+  // 64 action bytes (four per lane; fewer than four in all: one per lane)
+  const uint32_t gl = lane_id() & 15;
+  const uint8_t *const act = a.act + slot * a.act_bytes;
+  uint8_t *const act_out = a.act_out + o * a.act_bytes;
+  const bool whole_words = a.act_bytes >= 4;
+  const uint32_t act_last = a.act_bytes - (whole_words ? 4 : 1), act_at = min(whole_words ? 4 * gl : gl, act_last);
+  float col = 0.f;
+  uint32_t act_piece = 0;
+  const bool ret_lane = gl == 1 && a.ret_out, gacc_lane = gl == 2 && a.gacc_out;
+  if (ret_lane) col = a.ret[slot];
+  if (gacc_lane) col = a.gacc[slot];
+  if (a.act_out) {
+    if (whole_words) act_piece = *reinterpret_cast<const u32_any *>(act + act_at);
+    else act_piece = act[act_at];
+  }
+  if (a.obs_out) copy_row_by_16(a.obs_out + o * a.obs_bytes, a.obs + slot * a.obs_bytes, (uint32_t)a.obs_bytes);
+  else wait_for_all_loads();
+  if (a.act_out) {
+    if (whole_words) *reinterpret_cast<u32_any *>(act_out + act_at) = act_piece;
+    else act_out[act_at] = (uint8_t)act_piece;
+    for (uint32_t at = 64 + 4 * gl; at < a.act_bytes; at += 64) {
+      const uint32_t p = min(at, act_last);
+      *reinterpret_cast<u32_any *>(act_out + p) = *reinterpret_cast<const u32_any *>(act + p);
+    }
+  }
+  if (ret_lane) a.ret_out[o] = col;
+  if (gacc_lane) a.gacc_out[o] = col;
+}
+
 // Observation rows up to here ride in the draw's launch.  Together / apart, us of device time for one batch of 32, one of 512,
 // one of 4096 and 16 of 512 from 2^18 slots (a launch less on the host, some 3 us, not counted):
 //   rows of  268 B  6.0 / 6.5    6.8 / 7.3   10.0 / 9.3    8.8 / 9.6
@@ -1496,69 +1567,22 @@ __global__ __launch_bounds__(kSampleMaxThreads) void sample_kernel(SampleArgs a)
     const uint64_t head = a.st->head;
     const uint64_t total = top.scan();
     const uint64_t w = a.k_dev ? total / k : fast_div(total, a.k_div);  // stratum width
-    RowWalk walk;
-    walk.x = (uint64_t)min(j, k - 1) * w + __umul64hi(u, w);  // point inside stratum j
-
-    // top level: the lane that holds the node by a ballot per sample, then its eight nodes anew (they are in the
-    // first cache), as if they were the children of a node
-    uint32_t l = 0;
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      const uint32_t ls = top.find_group(read_lane_u64(walk.x, 16 * s));
-      l = lane / 16 == (uint32_t)s ? ls : l;
-    }
-    uint64_t before = __shfl(top.before, l & (kWave - 1), kWave);
-    if (top.wide) {
-      const uint64_t before_w = __shfl(top.before_w, l & (kWave - 1), kWave);
-      before = l < kWave ? before : before_w;
-    }
-    walk.x -= before;
-    walk.idx = l;
-    row_descend(walk, top_level, 3);
-    const uint64_t head_slot = ring_slot(tv, head);
-    uint32_t fl = tv.top_log2;
-    for (int lv = (int)tv.nlev - 2; lv >= 0; --lv) {
-      row_descend(walk, tv.level[lv], fl);
-      fl = kFanoutLog2;
-    }
+    const uint64_t point = (uint64_t)min(j, k - 1) * w + __umul64hi(u, w);  // inside stratum j
+    uint64_t head_slot = 0;
+    const RowWalk walk = walk_four(tv, top, top_level, point, [&] { head_slot = ring_slot(tv, head); });
     if (j < k) {
       const uint64_t slot = walk.idx;
       my_mass = walk.mass;
+      uint32_t gen = 0;
       if (gl == 0) {
         __hip_atomic_store(a.mass + o, walk.mass, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         a.slot_out[o] = (uint32_t)slot;
         if (a.claim) __hip_atomic_fetch_max(a.claim + slot, (uint32_t)o + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (a.gen) gen = a.gen[slot];
       }
-      // the small columns' loads go out with those of the observation row: partial return, accumulated discount,
-      // generation, and the first 64 action bytes (four per lane; fewer than four in all: one per lane)
-      const uint8_t *const act = a.act + slot * a.act_bytes;
-      uint8_t *const act_out = a.act_out + o * a.act_bytes;
-      const bool whole_words = a.act_bytes >= 4;
-      const uint32_t act_last = a.act_bytes - (whole_words ? 4 : 1), act_at = min(whole_words ? 4 * gl : gl, act_last);
-      float col = 0.f;
-      uint32_t gen = 0, act_piece = 0;
-      const bool ret_lane = gl == 1 && a.ret_out, gacc_lane = gl == 2 && a.gacc_out;
-      if (ret_lane) col = a.ret[slot];
-      if (gacc_lane) col = a.gacc[slot];
-      if (gl == 0 && a.gen) gen = a.gen[slot];
-      if (a.act_out) {
-        if (whole_words) act_piece = *reinterpret_cast<const u32_any *>(act + act_at);
-        else act_piece = act[act_at];
-      }
-      if (a.obs_out) copy_row_by_16(a.obs_out + o * a.obs_bytes, a.obs + slot * a.obs_bytes, (uint32_t)a.obs_bytes);
-      else wait_for_all_loads();  // (either way: this wave's masses are in memory from here on)
-      if (a.act_out) {
-        if (whole_words) *reinterpret_cast<u32_any *>(act_out + act_at) = act_piece;
-        else act_out[act_at] = (uint8_t)act_piece;
-        for (uint32_t at = 64 + 4 * gl; at < a.act_bytes; at += 64) {
-          const uint32_t p = min(at, act_last);
-          *reinterpret_cast<u32_any *>(act_out + p) = *reinterpret_cast<const u32_any *>(act + p);
-        }
-      }
+      gather_by_16(a.g, slot, o);  // (this wave's masses are in memory from here on)
       if (gl == 0 && a.key_out)
         a.key_out[o] = a.gen ? ((uint64_t)gen << 32) | slot : ring_key(slot, head, head_slot, tv.P);
-      if (ret_lane) a.ret_out[o] = col;
-      if (gacc_lane) a.gacc_out[o] = col;
     }
   }
   if (!a.weight_out) return;
@@ -1651,32 +1675,32 @@ __global__ __launch_bounds__(1024) void sample_rows_kernel(SampleArgs a, uint32_
   if (wave != 0) {
     const uint64_t slot = sh_slot;
     const uint32_t copiers = blockDim.x - kWave, c0 = tid - kWave;
-    const uint8_t *const s = a.obs + slot * a.obs_bytes;
-    uint8_t *const d = a.obs_out + o * a.obs_bytes;
+    const uint8_t *const s = a.g.obs + slot * a.g.obs_bytes;
+    uint8_t *const d = a.g.obs_out + o * a.g.obs_bytes;
     for (uint32_t v0 = 0; v0 < vecs_per_row; v0 += copiers * kUnroll) {
       PieceAny::Reg t[kUnroll];
 #pragma unroll
       for (int u = 0; u < kUnroll; ++u) {
         const uint32_t v = v0 + u * copiers + c0;
-        if (v < vecs_per_row) t[u] = load_piece_streaming<PieceAny>(s, v, a.obs_bytes);
+        if (v < vecs_per_row) t[u] = load_piece_streaming<PieceAny>(s, v, a.g.obs_bytes);
       }
 #pragma unroll
       for (int u = 0; u < kUnroll; ++u) {
         const uint32_t v = v0 + u * copiers + c0;
-        if (v < vecs_per_row) store_piece_streaming<PieceAny>(d, v, a.obs_bytes, t[u]);
+        if (v < vecs_per_row) store_piece_streaming<PieceAny>(d, v, a.g.obs_bytes, t[u]);
       }
     }
     if (wave == blockDim.x / kWave - 1) {
-      if (a.ret_out && lane == 0) a.ret_out[o] = a.ret[slot];
-      if (a.gacc_out && lane == 1) a.gacc_out[o] = a.gacc[slot];
-      if (a.act_out) {
-        const uint8_t *const act = a.act + slot * a.act_bytes;
-        uint8_t *const act_out = a.act_out + o * a.act_bytes;
-        if (a.act_bytes < 4) {
-          if (lane < a.act_bytes) act_out[lane] = act[lane];
+      if (a.g.ret_out && lane == 0) a.g.ret_out[o] = a.g.ret[slot];
+      if (a.g.gacc_out && lane == 1) a.g.gacc_out[o] = a.g.gacc[slot];
+      if (a.g.act_out) {
+        const uint8_t *const act = a.g.act + slot * a.g.act_bytes;
+        uint8_t *const act_out = a.g.act_out + o * a.g.act_bytes;
+        if (a.g.act_bytes < 4) {
+          if (lane < a.g.act_bytes) act_out[lane] = act[lane];
         } else {
-          for (uint32_t at = 4 * lane; at < a.act_bytes; at += 4 * kWave) {  // the last piece overlaps the one before it
-            const uint32_t p = min(at, a.act_bytes - 4);
+          for (uint32_t at = 4 * lane; at < a.g.act_bytes; at += 4 * kWave) {  // the last piece overlaps the one before it
+            const uint32_t p = min(at, a.g.act_bytes - 4);
             *reinterpret_cast<u32_any *>(act_out + p) = *reinterpret_cast<const u32_any *>(act + p);
           }
         }
@@ -2053,6 +2077,112 @@ __global__ __launch_bounds__(kThreads) void learner_step_kernel(StepArgs a)
   if (wave == 2 && a.act_out && !act_early)  // long action rows: after the row, which they would hold up
     for (uint32_t by = lane; by < a.act_bytes; by += kWave)
       a.act_out[(uint64_t)row * a.act_bytes + by] = a.act[(uint64_t)my_slot * a.act_bytes + by];
+}
+
+// --------------------------------------------------------------------------------------------
+// The same for steps of several batches, or of one large one, of short rows (four samples per wave): launch i gathers the
+// batches of step i, writes their weights, draws those of step i+1 from the copy of the tree that holds every write-back up
+// to step i, and adds the changes of both steps to the other copy.  All batches of a step are drawn from the same state.
+//
+// Of all pairs of a step that share a slot the last one counts.  The wave that draws a sample can tell from the uniforms
+// alone: a batch has a point in the slot's interval of cumulative mass only if it has one in a stratum that the interval
+// meets, and it has one for certain where the interval covers a stratum.  So a later batch has drawn the slot exactly if
+// its point in the sample's own stratum, or in the one below or above it, lies in the interval (were the interval to reach
+// further, it would cover the neighbour): three points per later batch, one batch per lane of the sample's row.  In the
+// sample's own batch it is the point above.
+// As two launches per step (sample_kernel with the first pass of the update, update_apply_kernel), 16 x 512 of 2^21
+// slots: 15.7 us, so 9.4; 2 x 128 14 and 7.4; one batch of 4096 17 and 10.5.
+// --------------------------------------------------------------------------------------------
+struct MultiStepArgs {
+  // workgroups: first those that draw, per batch of step i+1, then those that gather step i, then one per batch for weights
+  uint32_t draw_wgs, draw_wgs_per_batch, gather_wgs;
+  GatherArgs g;           // step i: row o of the outputs = row slot[o]
+  uint32_t samples;       // of a step
+  const uint32_t *slot;
+  const uint64_t *dq;     // its changes: new mass - mass as drawn
+  WeightArgs wa;
+  TreeView wr;            // the copy that is written
+  DrawArgs next;          // step i+1, from the copy that is read
+  FastDiv next_k_div;
+  uint32_t batches;
+  const float *next_prio; // its new priorities ...
+  uint64_t *next_dq;      // ... and the changes they bring
+  QuantParams qp;
+  DeviceState *st;
+};
+
+constexpr int kMultiStepThreads = 256;
+constexpr uint32_t kMultiStepRows = kMultiStepThreads / 16;  // samples per workgroup
+
+template <bool kWide>
+__global__ __launch_bounds__(kMultiStepThreads) void multi_step_kernel(MultiStepArgs a)
+{
+  __shared__ uint64_t red[kMultiStepThreads / kWave];
+  const uint32_t lane = lane_id(), gl = lane & 15, blk = blockIdx.x;
+  if (blk >= a.draw_wgs + a.gather_wgs) {
+    batch_weights(a.wa, blk - a.draw_wgs - a.gather_wgs, red);
+    return;
+  }
+  if (blk >= a.draw_wgs) {
+    const uint32_t o = (blk - a.draw_wgs) * kMultiStepRows + threadIdx.x / 16;
+    if (o >= a.samples) return;
+    const uint32_t slot = a.slot[o];
+    const uint64_t dq = a.dq[o];
+    if (gl == 0) add_delta(a.wr, slot, dq);
+    gather_by_16(a.g, slot, o);
+    return;
+  }
+  const TreeView &rd = a.next.tv;
+  const uint32_t k = a.next.k, b = blk / a.draw_wgs_per_batch;
+  const uint32_t j0 = (blk - b * a.draw_wgs_per_batch) * kMultiStepRows + threadIdx.x / kWave * 4;
+  if (j0 >= k) return;
+  const bool in = j0 + lane / 16 < k;
+  const uint32_t j = min(j0 + lane / 16, k - 1);  // a row without a sample repeats the last one and writes nothing
+  const uint32_t o = b * k + j;
+  TopLevel<kWide> top;
+  const uint64_t *const top_level = rd.level[rd.nlev - 1];
+  top.load(top_level, rd.n_top);
+  const uint64_t u = a.next.rnd[o];
+  const uint32_t below = max(j, 1u) - 1, above = min(j + 1, k - 1);
+  const uint64_t *const mine = a.next.rnd + (uint64_t)min(b + gl, a.batches - 1) * k;  // batch b + gl is this lane's
+  uint64_t u_below = mine[below], u_same = mine[j], u_above = mine[above];
+  const float prio = a.next_prio[o];
+  const uint64_t head = a.next.st->head;
+  const uint64_t w = fast_div(top.scan(), a.next_k_div);  // stratum width
+  const uint64_t base = (uint64_t)j * w, point = base + __umul64hi(u, w);
+  uint64_t head_slot = 0, q = 0;
+  bool clamped = false;
+  const RowWalk walk = walk_four(rd, top, top_level, point, [&] {
+    head_slot = ring_slot(rd, head);
+    q = quantise_priority(prio, a.qp, &clamped);
+  });
+  const uint64_t lo = point - walk.x, hi = lo + walk.mass;
+  bool later = false;
+  for (uint32_t c0 = b;;) {
+    const uint32_t c = c0 + gl;
+    if (c < a.batches) {
+      later |= j + 1 < k && base + w + __umul64hi(u_above, w) < hi;
+      if (c != b) {
+        const uint64_t p = base + __umul64hi(u_same, w);
+        later |= (p >= lo && p < hi) || (j > 0 && base - w + __umul64hi(u_below, w) >= lo);
+      }
+    }
+    c0 += 16;
+    if (c0 >= a.batches) break;
+    const uint64_t *const r = a.next.rnd + (uint64_t)min(c0 + gl, a.batches - 1) * k;
+    u_below = r[below], u_same = r[j], u_above = r[above];
+  }
+  const bool loses = (uint32_t)(__ballot(later) >> (lane & 48)) & 0xffffu;
+  if (in && gl == 0) {
+    a.next.slot_out[o] = (uint32_t)walk.idx;
+    if (a.next.key_out) a.next.key_out[o] = ring_key(walk.idx, head, head_slot, rd.P);
+    a.next.mass[o] = walk.mass;
+    const uint64_t delta = loses ? 0 : q - walk.mass;
+    a.next_dq[o] = delta;
+    add_delta(a.wr, (uint32_t)walk.idx, delta);
+  }
+  const uint64_t nc = __popcll(__ballot(in && gl == 0 && clamped));
+  if (nc && lane == 0) atomic_add_u64(&a.st->n_clamped, nc);
 }
 
 // dst[i] = src[i]: brings the second copy of the tree up to date

@@ -279,6 +279,12 @@ int apex_pipeline_steps(apex_pipeline_t *p, uint32_t n, float beta, const uint64
     p->step += n;
     return APEX_OK;
   }
+  if (n && new_prio && !p->wide && !p->codec_raw_bytes && multi_steps_fit(p->r, n, p->nb, p->k, p->depth)) {
+    APEX_TRY(multi_steps(p->r, n, p->nb, p->k, beta, rnd, new_prio, p->sets.data(), p->depth,
+                         (uint32_t)(p->step % p->depth), p->tree));
+    p->step += n;
+    return APEX_OK;
+  }
   if (n && p->codec_raw_bytes && !p->wide) return APEX_ERR_INVALID_ARG;  // set_codec has checked the step mode
   for (uint32_t i = 0; i < n; ++i) {
     const uint32_t set = (uint32_t)(p->step % p->depth);

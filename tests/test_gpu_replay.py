@@ -131,8 +131,8 @@ def test_sample_in_one_launch(ob, ab, nb, k):
 
 
 @pytest.mark.parametrize("ob,ab,nb,k", [
-    (16, 1, 448, 1), (16, 2, 1, 448), (17, 3, 1, 449), (31, 4, 14, 32), (32, 5, 13, 33), (100, 255, 7, 64), (100, 257, 1, 65),
-    (2047, 4, 2, 224), (2048, 4, 3, 512), (2048, 4, 1, 513), (4095, 4, 1, 1023), (4096, 4, 1, 1024),       # lines of the rule
+    (16, 1, 384, 1), (16, 2, 1, 384), (17, 3, 1, 385), (31, 4, 12, 32), (32, 5, 11, 33), (100, 255, 6, 64), (100, 257, 1, 65),
+    (2047, 4, 2, 192), (2048, 4, 3, 512), (2048, 4, 1, 513), (4095, 4, 1, 1023), (4096, 4, 1, 1024),       # lines of the rule
     (4097, 4, 1, 1024), (4100, 4, 1, 1025), (8207, 4, 1, 1), (8207, 4, 48, 32), (8207, 4, 47, 33),
     (28224, 4, 3, 333), (30720, 4, 1, 600), (30721, 4, 1, 300), (61441, 4, 1, 200), (70000, 4, 1, 700),  # pieces per lane
 ])
@@ -1123,6 +1123,79 @@ def test_steps_that_are_no_single_launch(ob, nb, k):
     torch.cuda.synchronize()
     assert_sample_equal(out, oo)
     check_gpu_tree(g, o)
+    pipe.close()
+
+
+@pytest.mark.parametrize("P,ob,nb,k,depth,bits", [
+    (900, 16, 33, 3, 2, 24), (900, 20, 17, 50, 3, 24), (3000, 64, 16, 65, 4, 24), (3000, 7, 100, 2, 2, 24),   # batches per row
+    (40_000, 100, 2, 1100, 2, 24), (70_000, 12, 40, 40, 3, 24), (5000, 300, 1, 1025, 3, 24),   # wide top, summit, one batch
+    (30, 16, 5, 64, 2, 0), (30, 16, 20, 17, 3, 1), (4000, 4096, 3, 16, 5, 24),                 # no mass for a stratum
+])
+def test_steps_of_several_batches_in_one_launch_each(P, ob, nb, k, depth, bits):
+    """Sequences of steps of several batches (or of one large one) against the oracle: batches that draw one another's
+    slots again and again (which of them is the last is told from the uniforms), strata smaller than a mass and of no
+    width at all, calls of one and of several steps, add rounds, evictions, plain updates and steps without write-back in
+    between, and replays of a captured sequence."""
+    from paper_1803_00933_amd import apex
+    rng = np.random.default_rng(P + nb * k)
+    C = P - P // 10
+    g, o = make_pair(C, P, ob, 4, frac_bits=bits)
+    heavy = lambda rng, n: np.where(rng.random(n) < 0.2, 0.0, rng.pareto(0.5, n) + 1e-3)
+    assert add_both(g, o, rng, C, heavy) == 0
+    pipe, per, at = apex.Pipeline(g, depth, nb, k), nb * k, 0
+
+    def steps(n, write_back=True):
+        nonlocal at
+        rnd, newp = rng.integers(0, U64, (n, per), dtype=np.uint64), heavy(rng, (n, per)).astype(F32)
+        rnd[0, ::5], rnd[0, 1::5] = 0, U64 - 1
+        newp[rng.random((n, per)) < 0.05] = np.inf
+        args = dev(rnd), dev(newp) if write_back else None
+        torch.cuda.synchronize()
+        assert pipe.fork() == 0
+        assert pipe.steps(n, 0.4, *args) == (0, at % depth)
+        assert pipe.join() == 0
+        torch.cuda.synchronize()
+        for i in range(n):
+            rco, oo = o.sample(nb, k, 0.4, rnd[i])
+            assert rco == 0
+            if write_back:
+                assert o.update_priorities(oo["key"], newp[i]) == 0
+            if i >= n - depth:
+                assert_sample_equal(pipe.sets[(at + i) % depth], oo)
+        at += n
+        return check_gpu_tree(g, o)
+
+    for it in range(4):
+        steps(3)
+        steps(1)
+        assert add_both(g, o, rng, P // 20, heavy) == 0
+        steps(2)
+        assert g.evict() == o.evict()
+        steps(1)
+        oo = sample_both(g, o, rng, 1, 40)
+        pr = rng.lognormal(0, 1, 40).astype(F32)
+        assert g.update_priorities(dev(oo["key"]), dev(pr)) == o.update_priorities(oo["key"], pr) == 0
+        steps(1 if it % 2 else 2)
+        steps(2, write_back=False)
+    rnd, newp = rng.integers(0, U64, (2, per), dtype=np.uint64), heavy(rng, (2, per)).astype(F32)
+    args = dev(rnd), dev(newp)
+    torch.cuda.synchronize()
+    assert pipe.capture_begin() == 0
+    assert pipe.steps(2, 0.4, *args)[0] == 0
+    assert pipe.capture_end() == 0
+    first = at
+    at += 2
+    for it in range(3):
+        assert pipe.replay() == 0 and pipe.join() == 0
+        torch.cuda.synchronize()
+        for i in range(2):
+            rco, oo = o.sample(nb, k, 0.4, rnd[i])
+            assert rco == 0 and o.update_priorities(oo["key"], newp[i]) == 0
+            assert_sample_equal(pipe.sets[(first + i) % depth], oo)
+        check_gpu_tree(g, o)
+        oo = sample_both(g, o, rng, 1, 33)
+        assert g.update_priorities(dev(oo["key"]), dev(np.ones(33, F32))) == o.update_priorities(oo["key"], np.ones(33, F32)) == 0
+    steps(3)
     pipe.close()
 
 
