@@ -587,24 +587,31 @@ uint32_t leaves_threads(uint64_t count)
   return (uint32_t)std::clamp<uint64_t>(round_up(count, kWave), 2 * kWave, kLeavesThreads);
 }
 
-// Enters `count` transitions under the next keys; columns: as far as their small columns are to be copied too.
-int publish(apex_replay_t *r, uint64_t count, const float *prio, const AddColumns &columns, uint64_t *first_key_out,
-            void *hip_stream)
+// Enters `count` transitions under the next keys: launch(arguments) enqueues the launch that does it.
+template <typename F>
+int publish_with(apex_replay_t *r, uint64_t count, const float *prio, uint64_t *first_key_out, F launch)
 {
-  if (!r || (count && !prio)) return APEX_ERR_INVALID_ARG;
   if ((r->tail - r->head) + count > r->cfg.max_slots) return APEX_ERR_FULL;
   if (count) {
-    hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     const uint64_t second = r->second_words();
     r->tree_changed(second);
-    const uint32_t threads = leaves_threads(count);
-    add_leaves_kernel<<<dim3(blocks_for(count, threads)), dim3(threads), 0, stream>>>(
-        AddLeavesArgs{r->tv, second, r->state(), count, prio, r->qp}, columns);
+    launch(AddLeavesArgs{r->tv, second, r->state(), count, prio, r->qp});
     APEX_HIP(hipGetLastError());
   }
   if (first_key_out) *first_key_out = r->tail;
   r->tail += count;
   return APEX_OK;
+}
+
+// columns: as far as the small columns are to be copied too.
+int publish(apex_replay_t *r, uint64_t count, const float *prio, const AddColumns &columns, uint64_t *first_key_out,
+            void *hip_stream)
+{
+  if (!r || (count && !prio)) return APEX_ERR_INVALID_ARG;
+  return publish_with(r, count, prio, first_key_out, [&](const AddLeavesArgs &a) {
+    const uint32_t threads = leaves_threads(count);
+    add_leaves_kernel<<<dim3(blocks_for(count, threads)), dim3(threads), 0, static_cast<hipStream_t>(hip_stream)>>>(a, columns);
+  });
 }
 
 }  // namespace
@@ -634,14 +641,24 @@ int apex_replay_add(apex_replay_t *r, uint64_t count, const void *obs, const voi
 {
   if (!r || (count && !prio)) return APEX_ERR_INVALID_ARG;
   const PayloadRing pr{r->obs(), r->act(), r->ret(), r->gacc(), r->cfg.obs_bytes, r->cfg.act_bytes};
+  const AddColumns columns{static_cast<const uint8_t *>(act), ret, gacc, r->act(), r->ret(), r->gacc(), r->cfg.act_bytes};
+  if (obs && r->cfg.obs_bytes <= kAddRowsInOneBytes && r->cfg.act_bytes <= kColumnsInAddBytes) {
+    const RowPieces rp = row_pieces((uintptr_t)obs | (uintptr_t)r->obs(), r->cfg.obs_bytes);
+    const uint32_t vpr = (uint32_t)pieces_per_row(rp, r->cfg.obs_bytes), lanes_log2 = ceil_log2(vpr);
+    const uint32_t threads = std::min(leaves_threads(count), add_rows_threads(count));
+    return publish_with(r, count, prio, first_key_out, [&](const AddLeavesArgs &a) {
+      with_pieces(rp, [&](auto p) {
+        add_rows_kernel<decltype(p)><<<dim3(blocks_for(count, threads)), dim3(threads), 0, static_cast<hipStream_t>(hip_stream)>>>(
+            a, columns, static_cast<const uint8_t *>(obs), r->obs(), vpr, lanes_log2, r->cfg.obs_bytes);
+      });
+    });
+  }
   if ((obs && short_rows(pr, obs)) || r->cfg.act_bytes > kColumnsInAddBytes) {
     const int rc = apex_replay_add_payload(r, count, obs, act, ret, gacc, hip_stream);
     return rc != APEX_OK ? rc : apex_replay_add_publish(r, count, prio, first_key_out, hip_stream);
   }
   const int rc = apex_replay_add_payload(r, count, obs, nullptr, nullptr, nullptr, hip_stream);
-  if (rc != APEX_OK) return rc;
-  const AddColumns columns{static_cast<const uint8_t *>(act), ret, gacc, r->act(), r->ret(), r->gacc(), r->cfg.act_bytes};
-  return publish(r, count, prio, columns, first_key_out, hip_stream);
+  return rc != APEX_OK ? rc : publish(r, count, prio, columns, first_key_out, hip_stream);
 }
 
 namespace {

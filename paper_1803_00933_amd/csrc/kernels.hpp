@@ -964,27 +964,69 @@ struct AddColumns {
 // add and eviction of 700 rows of 5000 bytes 14.6 -> 11.1 us, the pieces of any alignment included.
 constexpr uint32_t kColumnsInAddBytes = 16;
 
+// The small columns of transition i into slot, by one lane.
+__device__ __forceinline__ void add_columns(const AddColumns &c, uint64_t i, uint64_t slot)
+{
+  if (c.ret) c.ret_ring[slot] = c.ret[i];
+  if (c.gacc) c.gacc_ring[slot] = c.gacc[i];
+  if (!c.act) return;
+  const uint8_t *const s = c.act + i * c.act_bytes;
+  uint8_t *const d = c.act_ring + slot * c.act_bytes;
+  if (c.act_bytes < 4) {
+    for (uint32_t at = 0; at < c.act_bytes; ++at) d[at] = s[at];
+  } else {
+    for (uint32_t at = 0; at < c.act_bytes; at += 4) {  // the last piece overlaps the one before it
+      const uint32_t p = min(at, c.act_bytes - 4);
+      *reinterpret_cast<u32_any *>(d + p) = *reinterpret_cast<const u32_any *>(s + p);
+    }
+  }
+}
+
 __global__ __launch_bounds__(kLeavesThreads) void add_leaves_kernel(AddLeavesArgs a, AddColumns c)
 {
   __shared__ DenseSums sh;
   const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < a.count && (c.act || c.ret || c.gacc)) {  // (the tail moves on only after a barrier of add_leaves_block)
-    const uint64_t slot = ring_slot(a.tv, a.st->tail + i);
-    if (c.ret) c.ret_ring[slot] = c.ret[i];
-    if (c.gacc) c.gacc_ring[slot] = c.gacc[i];
-    if (c.act) {
-      const uint8_t *const s = c.act + i * c.act_bytes;
-      uint8_t *const d = c.act_ring + slot * c.act_bytes;
-      if (c.act_bytes < 4) {
-        for (uint32_t at = 0; at < c.act_bytes; ++at) d[at] = s[at];
-      } else {
-        for (uint32_t at = 0; at < c.act_bytes; at += 4) {  // the last piece overlaps the one before it
-          const uint32_t p = min(at, c.act_bytes - 4);
-          *reinterpret_cast<u32_any *>(d + p) = *reinterpret_cast<const u32_any *>(s + p);
-        }
-      }
+  if (i < a.count && (c.act || c.ret || c.gacc))  // (the tail moves on only after a barrier of add_leaves_block)
+    add_columns(c, i, ring_slot(a.tv, a.st->tail + i));
+  add_leaves_block(a, blockIdx.x, gridDim.x, sh);
+}
+
+// A whole add of short observation rows in one launch: a workgroup copies the rows of as many transitions as it has
+// threads, 2^lanes_log2 lanes per row, then each of its threads has the small columns and the mass of one.  The two launches
+// that it replaces are each a few dependent loads; the atomics on the upper levels ask for large workgroups, the rows for
+// many.  Add and eviction, us, as two launches / with 256 / 512 / 1024 threads:
+//    3000 rows of  32 B of 2^20 slots  10.0 /  8.0 /  8.1 /  8.5      51,200   11.3 / 10.6 /  9.5 /  9.5
+//    3000 rows of 256 B of 2^20 slots  10.0 /  9.1 /  9.6 / 12.2      51,200   14.5 / 12.8 / 12.6 / 14.9
+//    3000 rows of 128 B of 2^24 slots  10.4 /  8.8 /  8.9 / 10.7      51,200   12.3 / 12.0 / 11.1 / 12.1
+//     400 rows of 500 B of 2^20 slots   8.7 /  9.2 /  9.7 /  9.8      18,000   13.6 / 12.2 / 13.1 / 17.6
+constexpr uint32_t kAddRowsInOneBytes = 256;
+
+constexpr uint32_t add_rows_threads(uint64_t count) { return count > 16384 ? 512 : 256; }
+
+template <typename P>
+__global__ __launch_bounds__(kLeavesThreads) void add_rows_kernel(AddLeavesArgs a, AddColumns c, const uint8_t *__restrict__ obs,
+                                                                  uint8_t *__restrict__ obs_ring, uint32_t vecs_per_row,
+                                                                  uint32_t lanes_log2, uint64_t obs_bytes)
+{
+  constexpr uint32_t kAhead = 8;  // pieces per lane in flight
+  __shared__ DenseSums sh;
+  const uint64_t i0 = (uint64_t)blockIdx.x * blockDim.x;
+  const uint32_t n = (uint32_t)min((uint64_t)blockDim.x, a.count - i0), rows = blockDim.x >> lanes_log2;  // per pass
+  const uint32_t v = threadIdx.x & ((1u << lanes_log2) - 1);
+  const uint64_t first = ring_slot(a.tv, a.st->tail + i0);
+  auto slot_of = [&](uint32_t r) { return first + r < a.tv.P ? first + r : first + r - a.tv.P; };
+  if (v < vecs_per_row) {
+    for (uint32_t r0 = threadIdx.x >> lanes_log2; r0 < n; r0 += kAhead * rows) {
+      typename P::Reg t[kAhead];
+#pragma unroll
+      for (uint32_t u = 0; u < kAhead; ++u)
+        if (r0 + u * rows < n) t[u] = load_piece<P>(obs + (i0 + r0 + u * rows) * obs_bytes, v, obs_bytes);
+#pragma unroll
+      for (uint32_t u = 0; u < kAhead; ++u)
+        if (r0 + u * rows < n) store_piece<P>(obs_ring + slot_of(r0 + u * rows) * obs_bytes, v, obs_bytes, t[u]);
     }
   }
+  if (threadIdx.x < n) add_columns(c, i0 + threadIdx.x, slot_of(threadIdx.x));
   add_leaves_block(a, blockIdx.x, gridDim.x, sh);
 }
 

@@ -107,6 +107,7 @@ def test_tree_shapes_around_the_summit(P):
     (1, 1, 1, 32), (15, 3, 1, 33), (16, 4, 2, 31), (17, 5, 3, 64), (67 * 4, 21 * 4, 1, 256), (2048, 64, 1, 100),
     (2049, 65, 2, 65), (4095, 130, 1, 200), (4096, 2, 1, 32), (4097, 7, 1, 40),       # row lengths and action bytes
     (24, 4, 1, 2048), (24, 4, 1, 2049), (20, 4, 1, 4096), (20, 4, 2, 4097), (12, 8, 700, 3),  # batch sizes and counts
+    (1024, 4, 1, 2049), (1025, 4, 1, 2049), (7, 3, 1, 3000), (24, 4, 2, 2049),
 ])
 def test_sample_in_one_launch(ob, ab, nb, k):
     """replay.Sample of short rows as one launch, at the edges of what its lanes and workgroups hold: rows and action
@@ -202,6 +203,34 @@ def test_updates_at_the_edges_of_their_workgroups(m, A):
         assert g.update_from_q(dev(keys), *(dev(x) for x in q), p_out) == rc == 0
         assert np.array_equal(host(p_out).view(np.uint32), p_ref.view(np.uint32))
         check_gpu_tree(g, o)
+
+
+@pytest.mark.parametrize("obs_bytes", [1, 3, 4, 12, 15, 16, 17, 100, 128, 255, 256, 257])
+@pytest.mark.parametrize("act_bytes", [1, 16, 17])
+def test_adds_of_short_rows_in_one_launch(obs_bytes, act_bytes):
+    """Whole adds around the lines between one launch and two and the edges of the workgroups and passes, from aligned and
+    misaligned rows, over the end of the ring."""
+    rng = np.random.default_rng(obs_bytes)
+    P = 21_000
+    g, o = make_pair(1000, P, obs_bytes, act_bytes)
+    for it, cnt in enumerate((1, 64, 127, 129, 255, 256, 257, 1023, 2100, 16_384, 16_385, 3000, 20_000, 700)):
+        obs, act = (rng.integers(0, 256, (cnt, n), dtype=np.uint8) for n in (obs_bytes, act_bytes))
+        ret, gacc, prio = rng.standard_normal(cnt).astype(F32), rng.random(cnt).astype(F32), rng.lognormal(0, 1, cnt).astype(F32)
+        d_obs = torch.empty(cnt * obs_bytes + 16, dtype=torch.uint8, device="cuda:0")[it % 3:][:cnt * obs_bytes].view(cnt, obs_bytes)
+        d_obs.copy_(dev(obs))
+        rc, first = g.add(dev(prio), d_obs, dev(act), dev(ret), dev(gacc))
+        assert (rc, first) == o.add(prio, obs, act, ret, gacc) and rc == 0
+        rows = (first + np.arange(cnt)) % P
+        torch.cuda.synchronize()
+        assert np.array_equal(host(g.obs_view()).reshape(P, obs_bytes)[rows], obs)
+        assert np.array_equal(host(g.act_view()).reshape(P, act_bytes)[rows], act)
+        assert np.array_equal(host(g.ret_view())[rows], ret) and np.array_equal(host(g.gacc_view())[rows], gacc)
+        check_gpu_tree(g, o)
+        assert g.evict() == o.evict()
+    check_gpu_tree(g, o)
+    full = dev(np.zeros((P, obs_bytes), np.uint8))
+    assert g.add(dev(np.ones(P, F32)), full)[0] == oracle.ERR_FULL and g.add(dev(np.ones(0, F32)), full[:0]) == (0, o.tail)
+    check_gpu_tree(g, o)
 
 
 @pytest.mark.parametrize("P", [3000, 100_000])
