@@ -1558,6 +1558,16 @@ constexpr uint32_t kGatherInDrawBytes = 4096;
 // took that launch 21.6 us instead of 8.2 without, where a launch of its own takes 5).
 constexpr uint32_t kWeightsInDrawMaxK = 4096;
 
+// One batch of more samples than this of rows up to this length is gathered by a launch of its own after all, which writes the
+// weights as well: with the draw, the last workgroup's weights are the tail of the launch (us with / apart):
+//    rows of   32 B   2048  8.5 /  7.6   3000  9.2 / 8.1   4096  9.9 /  8.5
+//             268 B         9.0 /  8.4         9.7 / 9.5        10.8 / 10.2
+//            1024 B         9.1 /  8.4        10.1 / 9.8        11.1 / 11.1
+//            2048 B        10.1 / 10.3        11.3 / 11.4       12.4 / 13.0
+// (up to 2048 samples the update that follows is one launch, and the host would be slower than the device with one more).
+constexpr uint32_t kGatherApartAboveK = 2048;
+constexpr uint64_t kGatherApartBytes = 1024;
+
 // Threads per workgroup.  16 samples (256 threads) spread the draws best over the chip; a batch of at most 32 goes into
 // one workgroup, whose waves agree on the smallest mass through LDS (32 samples: 5.7 instead of 6.5 us through tickets
 // and memory; with 64 the sixteen waves of the workgroup slow one another down, 8.8 us); a large one has fewer tickets to
