@@ -815,8 +815,10 @@ int launch_update(apex_replay *r, uint64_t m, const uint64_t *key, const float *
     const dim3 grid(blocks_for(m, kWave)), block((uint32_t)std::clamp<uint64_t>(round_up(m, kWave), kUpdateMinThreads, kUpdateThreads));
     if (m <= kUpdateThreads)
       update_small_kernel<1><<<grid, block, 0, stream>>>(ua);
-    else
+    else if (m <= 2 * kUpdateThreads)
       update_small_kernel<2><<<grid, block, 0, stream>>>(ua);
+    else
+      update_many_kernel<<<grid, dim3(kUpdateManyThreads), 0, stream>>>(ua);
   } else {
     const dim3 grid(blocks_for(m, 256)), block(256);
     if (!claimed)

@@ -566,16 +566,15 @@ __device__ __forceinline__ void update_batch_apply(const UpdateArgs &ua, UpdateL
 // keys of the update (the highest position wins).  So nothing has to be settled between workgroups, and what one compute
 // unit would take one after the other - scattered masses, rows of Q-values, the atomics on every level - is shared out.
 // Bound by its chain: key, slot, mass, atomics, 3.3 us for 16 pairs and 3.9 for 1024 (a launch of nothing: 2.5).  us, drawn
-// or random keys, against one workgroup for everything up to 1024 pairs and two launches (below) beyond:
+// or random keys, against one workgroup for everything up to 1024 pairs and two launches beyond:
 //   512 pairs, 2^18 / 2^24 slots      4.4 - 4.7 / 5.4  -> 3.6 / 3.7
 //   1024 pairs, 2^18 / 2^24 slots     5.5 - 6.3 / 7.4 - 8.1 -> 3.9 / 4.1
 //   2048 pairs, 2^18 / 2^24 slots     6.2 - 6.8 / 6.2 - 6.9 -> 5.1 / 5.3 - 5.7
 //   512 / 1024 pairs from the learner's Q-values, 18 actions, 2^21 slots  7.4 / 15.2 -> 4.3 / 4.5
 // With twice instead of four times as many places as pairs 1024 take 4.4 us and 2048 take 6.0 - 7.2 (probing); 4096 pairs
-// with four per thread take 8 - 10 us, two launches 6 - 7.5.
+// with four per thread take 8 - 10 us.
 constexpr uint32_t kUpdateThreads = 1024;       // most threads per workgroup ...
 constexpr uint32_t kUpdateMinThreads = 256;     // ... and fewest: one wave alone is slow to clear the table (32 pairs 3.8 us)
-constexpr uint32_t kUpdateOneLaunchMax = 2 * kUpdateThreads;
 
 template <int kHeld>
 __global__ __launch_bounds__(kUpdateThreads) void update_small_kernel(UpdateArgs ua)
@@ -646,6 +645,111 @@ __global__ __launch_bounds__(kUpdateThreads) void update_small_kernel(UpdateArgs
     if (nc) atomic_add_u64(&ua.st->n_clamped, nc);
   }
 }
+
+// The same for more pairs, up to kUpdateOneLaunchMax: a workgroup puts only its own 64 into a table and looks every later
+// pair of the update up, first in a map of bits, in which a look-up is one read that depends on none before (64 of 16,384
+// bits are set), and only where that says so in the table.  The sums of neighbouring keys go to a node together: without it
+// drawn keys are 0.6 - 1.5 us slower.  Against the two launches below, us, drawn / random keys:
+//   2049 pairs, 2^18 / 2^24 slots   6.2 / 6.8, 6.2 / 6.9 -> 5.4 / 5.5, 5.5 / 5.6     (2048 in the kernel above 5.1, 5.5)
+//   4096 pairs, 2^18 / 2^24 slots   6.2 / 7.3, 6.4 / 7.8 -> 5.7 / 6.0, 5.8 / 6.6     5000: 6.2 / 7.6, 6.5 / 8.3 -> 6.0 / 6.3, 6.1 / 7.0
+//   4096 pairs from the learner's Q-values, 18 actions, 2^24 slots   8.6 -> 6.8
+// and one launch less on the host.  Beyond, every key is read by too many workgroups (8192 drawn keys 7.1, 6.2 apart).
+constexpr uint32_t kUpdateOneLaunchMax = 4096;
+constexpr uint32_t kUpdateManyThreads = 1024;
+constexpr uint32_t kUpdateManyAhead = 4;       // keys that a thread looks up together
+constexpr uint32_t kOwnPlaces = 4 * kWave;     // places of the table
+constexpr uint32_t kSeenWords = 512;           // of the map
+
+__global__ __launch_bounds__(kUpdateManyThreads) void update_many_kernel(UpdateArgs ua)
+{
+  __shared__ unsigned long long own_key[kOwnPlaces];
+  __shared__ uint32_t own_last[kOwnPlaces];  // 1 + the last of this workgroup's pairs that names the key; ~0: a later one does
+  __shared__ uint32_t seen[kSeenWords];
+  const TreeView &tv = ua.tv;
+  const uint32_t tid = threadIdx.x;
+  const bool first_wave = __builtin_amdgcn_readfirstlane((int)tid) == 0;
+  const uint32_t i = blockIdx.x * kWave + (tid & (kWave - 1)), mine = min(i, ua.m - 1);
+  const uint32_t later = min((blockIdx.x + 1) * kWave, ua.m);
+  const uint64_t key = ua.key[mine];
+  uint64_t ahead[kUpdateManyAhead];
+  auto read_ahead = [&](uint32_t j0) {  // (the last pair again and again beyond the end: it is a later one all the same)
+#pragma unroll
+    for (uint32_t t = 0; t < kUpdateManyAhead; ++t) ahead[t] = ua.key[min(j0 + t * kUpdateManyThreads + tid, ua.m - 1)];
+  };
+  read_ahead(later);
+  const uint64_t head = ua.st->head, tail = ua.st->tail;
+  if (tid < kSeenWords) seen[tid] = 0;
+  if (tid < kOwnPlaces) {
+    own_key[tid] = ~0ull;  // no valid key: tails stay below it
+    own_last[tid] = 0;
+  }
+  auto hash = [](uint64_t k) { return (uint32_t)k * 2654435761u; };
+  float prio = 0.f;
+  TdInputs td{};
+  uint64_t old = 0;
+  uint32_t slot = 0, h = hash(key) >> 24;
+  const bool valid = first_wave && i < ua.m && key >= head && key < tail;
+  __syncthreads();
+  if (first_wave) {
+    if (valid) {
+      slot = (uint32_t)ring_slot(tv, key);
+      old = tv.level[0][slot];  // on its way during the look-ups
+      for (;;) {
+        const uint64_t prev = atomicCAS(&own_key[h], ~0ull, key);
+        if (prev == ~0ull || prev == key) break;
+        h = (h + 1) & (kOwnPlaces - 1);
+      }
+      atomicMax(&own_last[h], tid + 1);
+      const uint32_t bit = hash(key) >> 18;
+      atomicOr(&seen[bit >> 5], 1u << (bit & 31));
+    }
+    if (ua.qs.q_taken) td = td_inputs(ua.qs, mine);
+    else prio = ua.prio[mine];
+  }
+  __syncthreads();
+  for (uint32_t j0 = later; j0 < ua.m; j0 += kUpdateManyAhead * kUpdateManyThreads) {
+    if (j0 != later) read_ahead(j0);
+    uint32_t hit = 0;
+#pragma unroll
+    for (uint32_t t = 0; t < kUpdateManyAhead; ++t) {
+      const uint32_t bit = hash(ahead[t]) >> 18;
+      hit |= (seen[bit >> 5] >> (bit & 31) & 1) << t;
+    }
+    if (hit) {
+#pragma unroll
+      for (uint32_t t = 0; t < kUpdateManyAhead; ++t) {
+        if (!(hit >> t & 1)) continue;
+        uint32_t p = hash(ahead[t]) >> 24;
+        for (uint64_t there; (there = own_key[p]) != ~0ull; p = (p + 1) & (kOwnPlaces - 1)) {
+          if (there == ahead[t]) {
+            own_last[p] = ~0u;
+            break;
+          }
+        }
+      }
+    }
+  }
+  __syncthreads();
+  if (!first_wave) return;
+  bool clamped = false;
+  uint64_t q = 0;
+  if (valid) {
+    const float p = ua.qs.q_taken ? td_priority(ua.qs, td, slot) : prio;
+    q = quantise_priority(p, ua.qp, &clamped);
+    if (ua.qs.q_taken && ua.qs.prio_out) ua.qs.prio_out[i] = p;
+  }
+  const bool stale = i < ua.m && !valid;
+  if (stale && ua.qs.q_taken && ua.qs.prio_out) ua.qs.prio_out[i] = 0.0f;
+  const bool wins = valid && own_last[h] == tid + 1;
+  if (wins) tv.level[0][slot] = q;
+  add_runs_to_ancestors(tv, wins, slot, q - old);  // the keys of a drawn batch ascend: neighbours share their upper nodes
+  const uint64_t ns = __popcll(__ballot(stale)), nc = __popcll(__ballot(clamped));
+  if (tid == 0) {
+    if (ns) atomic_add_u64(&ua.st->n_stale, ns);
+    if (nc) atomic_add_u64(&ua.st->n_clamped, nc);
+  }
+}
+static_assert(kOwnPlaces == 1 << 8 && kSeenWords == 1 << (14 - 5));
 
 // Importance-sampling weights of one batch of k samples, by one workgroup:
 //   (N P_i)^-beta / max_j (N P_j)^-beta  ==  (min_j mass_j / mass_i)^beta,   P_i = mass_i / total.

@@ -178,7 +178,7 @@ def test_updates_on_trees_with_a_summit(P, m):
     sample_both(g, o, rng, 1, m)
 
 
-@pytest.mark.parametrize("m", [1, 63, 64, 65, 255, 257, 1023, 1024, 1025, 1087, 2047, 2048, 2049])
+@pytest.mark.parametrize("m", [1, 63, 64, 65, 255, 257, 1023, 1024, 1025, 1087, 2047, 2048, 2049, 2112, 4095, 4096, 4097])
 @pytest.mark.parametrize("A", [1, 2, 3, 9, 18])
 def test_updates_at_the_edges_of_their_workgroups(m, A):
     """Updates of any number of pairs around the workgroups' shares and the line between one launch and two: repeats
