@@ -399,29 +399,35 @@ __device__ __forceinline__ CodecFetched codec_fetch_all(const uint8_t *e, const 
   return f;
 }
 
-// The same for a whole wave whose 64 lanes hold 64 consecutive pieces starting at a multiple of 64 (16
-// blocks: one word of the mask, 16 consecutive block bytes): the word and the bytes come through the
-// scalar data cache (read only), which keeps them out of the queue of the vector memory pipeline, where
-// they would wait behind the row loads of the same compute unit.  e must be 16-byte aligned.
-__device__ __forceinline__ void codec_fetch_wave_scalars(const uint8_t *e, const CodecShape &c, uint32_t v_first,
-                                                         uint64_t *word, u32x4 *bytes)
+// Mask words and block bytes of a whole wave that holds four runs of 64 consecutive pieces, run u from piece v_first[u] on,
+// a multiple of 64 (16 blocks: one word of the mask, 16 consecutive block bytes): they come through the scalar data cache
+// (read only), which keeps them out of the queue of the vector memory pipeline, and all eight loads are in flight
+// together.  e must be 16-byte aligned, the runs must start inside the row.
+__device__ __forceinline__ void codec_fetch_wave_scalars(const uint8_t *e, const CodecShape &c, const uint32_t (&v_first)[4],
+                                                         uint64_t (&word)[4], u32x4 (&bytes)[4])
 {
   const uint64_t pe = (uint64_t)(uintptr_t)e;
   // (the builtin returns a signed int: without the casts the low half would be sign-extended)
   const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(pe >> 32));
   const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)pe);
   const uint64_t base = ((uint64_t)hi << 32) | (uint64_t)lo;
-  const uint32_t vf = (uint32_t)__builtin_amdgcn_readfirstlane((int)v_first);
-  const uint64_t p_word = base + 8ull * (vf >> 8);
-  const uint64_t p_bytes = base + c.flat_off + vf / 4;
-  uint64_t w;
-  u32x4 b;
-  asm volatile("s_load_dwordx2 %0, %2, 0x0\n\ts_load_dwordx4 %1, %3, 0x0\n\ts_waitcnt lgkmcnt(0)"
-               : "=&s"(w), "=&s"(b)
-               : "s"(p_word), "s"(p_bytes)
+  uint64_t p_word[4], p_bytes[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const uint32_t vf = (uint32_t)__builtin_amdgcn_readfirstlane((int)v_first[u]);
+    p_word[u] = base + 8ull * (vf >> 8);
+    p_bytes[u] = base + c.flat_off + vf / 4;
+  }
+  asm volatile("s_load_dwordx2 %0, %8, 0x0\n\ts_load_dwordx2 %1, %9, 0x0\n\t"
+               "s_load_dwordx2 %2, %10, 0x0\n\ts_load_dwordx2 %3, %11, 0x0\n\t"
+               "s_load_dwordx4 %4, %12, 0x0\n\ts_load_dwordx4 %5, %13, 0x0\n\t"
+               "s_load_dwordx4 %6, %14, 0x0\n\ts_load_dwordx4 %7, %15, 0x0\n\t"
+               "s_waitcnt lgkmcnt(0)"
+               : "=&s"(word[0]), "=&s"(word[1]), "=&s"(word[2]), "=&s"(word[3]), "=&s"(bytes[0]), "=&s"(bytes[1]),
+                 "=&s"(bytes[2]), "=&s"(bytes[3])
+               : "s"(p_word[0]), "s"(p_word[1]), "s"(p_word[2]), "s"(p_word[3]), "s"(p_bytes[0]), "s"(p_bytes[1]),
+                 "s"(p_bytes[2]), "s"(p_bytes[3])
                : "memory");
-  *word = w;
-  *bytes = b;
 }
 
 // The byte of the block of lane `lane`'s piece out of the 16 bytes fetched above.
@@ -2140,26 +2146,43 @@ __global__ __launch_bounds__(kThreads) void learner_step_kernel(StepArgs a)
   const uint32_t v_wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid - first));
   typename P::Reg tmp[kUnroll];
   CodecFetched fetched[kCodec ? kUnroll : 1] = {};
+  // Decoded rows: the first half of a wave's pieces is asked for at once, as the pieces of a plain row are, the other half
+  // when the mask has arrived and only where it says that the image counts (other lanes read the row's first bytes, a line
+  // that has just been fetched).  All of them at once reads every image whole, all of them behind the mask costs rows
+  // without flat blocks a round trip.  Us per launch at 28,224 raw bytes, 512 rows with 0 / 80 % flat blocks: all at once
+  // 8.87 / 8.82, half 8.56 / 8.02, none 9.05 / 7.67; 1024 rows: 15.96 / 15.90, 15.91 / 14.43, 17.05 / 14.35; 128 rows of
+  // either kind 6.6, half 5.9; 1024 rows of 1 KB 7.07, half 6.83.
+  constexpr int kCodecEarly = 2;
 #pragma unroll
   for (int u = 0; u < kUnroll; ++u) {
     if (!kCodec && v_wave + u * copiers >= a.vecs_per_row) break;
     const uint32_t v = min(tid - first + u * copiers, v_last);
-    if constexpr (kCodec) {  // the pieces as the image holds them; mask and block bytes follow below
-      fetched[u].data = __builtin_nontemporal_load(
-          reinterpret_cast<const u32x4 *>(s + a.codec.image_off) + v);
+    if constexpr (kCodec) {  // the pieces as the image holds them
+      if (u < kCodecEarly) fetched[u].data = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(s + a.codec.image_off) + v);
     } else {
       tmp[u] = load_piece_streaming<P>(s, v, a.row_bytes);
     }
   }
   if constexpr (kCodec) {
+    static_assert(kUnroll == 4, "a wave holds four runs of pieces");
+    if (v_wave < a.vecs_per_row) {  // the same for all lanes of the wave
+      uint32_t v_first[4];          // the wave's 64 pieces start there
+      uint64_t word[4];
+      u32x4 bytes[4];
 #pragma unroll
-    for (int u = 0; u < kUnroll; ++u) {
-      const uint32_t v = tid - first + u * copiers, v_first = v - lane;  // the wave's 64 pieces start at v_first
-      if (v_first < a.vecs_per_row) {  // the same for all lanes of the wave
-        u32x4 bytes;
-        codec_fetch_wave_scalars(s, a.codec, v_first, &fetched[u].word, &bytes);
-        fetched[u].byte = codec_wave_byte(bytes, lane);
-        fetched[u].bit = (v / 4) & 63;
+      for (int u = 0; u < kUnroll; ++u) v_first[u] = min(v_wave + u * copiers, v_last & ~(kWave - 1));
+      codec_fetch_wave_scalars(s, a.codec, v_first, word, bytes);
+#pragma unroll
+      for (int u = 0; u < kUnroll; ++u) {
+        fetched[u].word = word[u];
+        fetched[u].byte = codec_wave_byte(bytes[u], lane);
+        fetched[u].bit = ((v_first[u] + lane) / 4) & 63;
+        if (u < kCodecEarly) continue;
+        if (v_wave + u * copiers >= a.vecs_per_row) break;
+        const uint32_t v = min(tid - first + u * copiers, v_last);
+        const bool kept = fetched[u].word >> fetched[u].bit & 1;
+        fetched[u].data = __builtin_nontemporal_load(
+            reinterpret_cast<const u32x4 *>(s + (kept ? a.codec.image_off + 16 * v : 0u)));
       }
     }
   }
@@ -2188,11 +2211,12 @@ __global__ __launch_bounds__(kThreads) void learner_step_kernel(StepArgs a)
   // four stores in flight together the launch took 0.3 - 0.8 us longer, and with every piece stored as soon
   // as it had arrived (the row's writes beside the rest of its reads) 0.2 - 0.5 us longer (each measured
   // against this on one box).  Ordinary stores, streaming loads: streaming stores, which such a wave waits
-  // for longer, cost 0.4 us per launch; ordinary loads of the rows cost 1.5.
+  // for longer, cost 0.4 us per launch; ordinary loads of the rows cost 1.5.  Decoded rows, which read less, go out two
+  // stores at a time.
 #pragma unroll
   for (int u = 0; u < kUnroll; ++u) {
     const uint32_t v = tid - first + u * copiers;
-    if (u > 0 && v - lane < a.vecs_per_row) wait_for_all_loads();  // the same for all lanes of the wave
+    if (u > 0 && (!kCodec || u == 2) && v - lane < a.vecs_per_row) wait_for_all_loads();  // the same for all lanes of the wave
     if (v < a.vecs_per_row) store_piece<P>(d, v, out_bytes, tmp[u]);
   }
 

@@ -132,6 +132,15 @@ def test_pipeline_with_the_codec(raw_bytes, flat_share, nb, k, depth):
     pipe.close()
 
 
+# A step's workgroup decodes up to 4 runs of 448 pieces of 16 bytes (512 in a launch that draws nothing), the first two
+# ahead of the mask: rows that end with a run, one block before and one block behind it.
+@pytest.mark.gpu
+@pytest.mark.parametrize("raw_bytes", [7104, 7168, 7232, 14272, 14336, 14400, 16384, 16448, 21504, 21568, 28672, 28736])
+@pytest.mark.parametrize("flat_share", [0.3, 1.0])
+def test_steps_decode_rows_that_end_at_the_edge_of_a_run(raw_bytes, flat_share):
+    test_pipeline_with_the_codec(raw_bytes, flat_share, 1, 80, 4)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("raw_bytes,nb,k,depth", [(4160, 1, 80, 3), (28224, 1, 64, 3), (4160, 4, 512, 2)])
 def test_pipeline_graph_replays_with_the_codec(raw_bytes, nb, k, depth):
