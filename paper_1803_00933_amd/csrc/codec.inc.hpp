@@ -17,9 +17,40 @@ namespace apex {
 constexpr uint32_t kCodecThreads = 512;
 constexpr uint32_t kCodecUnroll = 4;
 
-// One workgroup per row, a lane per 16-byte piece, in row order (loads and stores as a plain copy makes them):
-// the four lanes of a block agree on whether it is flat with two exchanges; a wave's ballot, every fourth
-// bit of it, is 16 bits of the mask.  No LDS, no barrier.
+// The value of the lane that kPerm, a permutation of the four lanes of a quad, names.
+template <int kPerm>
+__device__ __forceinline__ uint32_t quad_swap(uint32_t x)
+{
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, kPerm, 0xf, 0xf, true);
+}
+
+// Run `run` (64 pieces of 16 bytes, one per lane of the wave) of a row goes into the encoded row d; nothing does of a run
+// beyond its end.  The four lanes of a block agree on whether it is flat with two exchanges and a ballot; every fourth bit
+// of it is 16 bits of the mask.
+__device__ __forceinline__ void encode_run(uint8_t *d, const CodecShape &c, uint32_t run, const u32x4 &t)
+{
+  const uint32_t lane = lane_id(), nvec = c.raw_bytes / 16, v = run * kWave + lane, x = t.x;
+  // a block is flat if each of its four lanes holds one byte throughout, the same as two of the others hold
+  const bool even = x == (x & 0xffu) * 0x01010101u && t.y == x && t.z == x && t.w == x;
+  const bool same = quad_swap<0xb1>(x) == x && quad_swap<0x4e>(x) == x;
+  uint64_t flat = __ballot(even && same);
+  flat &= flat >> 1;
+  flat &= flat >> 2;
+  const uint64_t kept = ~flat & __ballot(v < nvec) & 0x1111111111111111ull;  // one bit per block, at every fourth place
+  uint64_t bits = kept;
+  bits = (bits | bits >> 3) & 0x0303030303030303ull;
+  bits = (bits | bits >> 6) & 0x000f000f000f000full;
+  bits = (bits | bits >> 12) & 0x000000ff000000ffull;
+  bits = (bits | bits >> 24) & 0xffffull;
+  if (lane == 0 && v < nvec) reinterpret_cast<uint16_t *>(d)[run] = (uint16_t)bits;
+  if (kept >> (lane & ~3u) & 1)
+    __builtin_nontemporal_store(t, reinterpret_cast<u32x4 *>(d + c.image_off) + v);
+  else if (v < nvec && (v & 3) == 0)
+    d[c.flat_off + v / 4] = (uint8_t)x;
+}
+
+// One workgroup per row, a lane per 16-byte piece, in row order (loads and stores as a plain copy makes them).  No LDS,
+// no barrier.  18,000 rows of 28,224 bytes, 80 % of the blocks flat: 125 us (4.9 TB/s).
 __global__ __launch_bounds__(kCodecThreads) void codec_encode_rows_kernel(const uint8_t *__restrict__ src,
                                                                          uint8_t *__restrict__ ring, RowMap to,
                                                                          uint64_t ring_stride, CodecShape c)
@@ -28,8 +59,8 @@ __global__ __launch_bounds__(kCodecThreads) void codec_encode_rows_kernel(const 
   const u32x4 *s = reinterpret_cast<const u32x4 *>(src + i * c.raw_bytes);
   uint8_t *d = ring + map_row(to, i) * ring_stride;
   const uint32_t tid = threadIdx.x, nvec = c.raw_bytes / 16;
-  const uint32_t groups = (c.nb + 15) / 16;  // 16-bit pieces of the mask that hold blocks
-  for (uint32_t g = groups + tid; g < c.flat_off / 2; g += kCodecThreads) reinterpret_cast<uint16_t *>(d)[g] = 0;
+  const uint32_t runs = (nvec + kWave - 1) / kWave;  // 16-bit pieces of the mask that hold blocks
+  for (uint32_t g = runs + tid; g < c.flat_off / 2; g += kCodecThreads) reinterpret_cast<uint16_t *>(d)[g] = 0;
   for (uint32_t v0 = 0; v0 < nvec; v0 += kCodecUnroll * kCodecThreads) {
     u32x4 t[kCodecUnroll];
 #pragma unroll
@@ -39,27 +70,42 @@ __global__ __launch_bounds__(kCodecThreads) void codec_encode_rows_kernel(const 
     }
 #pragma unroll
     for (int u = 0; u < (int)kCodecUnroll; ++u) {
-      const uint32_t v = v0 + u * kCodecThreads + tid, b = v / 4;
-      const uint32_t x = t[u].x;
-      bool flat = x == (x & 0xffu) * 0x01010101u && t[u].y == x && t[u].z == x && t[u].w == x;
-      // the four lanes of a block: all flat, with the same byte
-      flat = flat && __shfl_xor(x, 1, kWave) == x;
-      flat = __shfl_xor((int)flat, 1, kWave) && flat;
-      flat = flat && __shfl_xor(x, 2, kWave) == x;
-      flat = __shfl_xor((int)flat, 2, kWave) && flat;
-      const bool kept = v < nvec && !flat;
-      uint64_t bits = __ballot(kept) & 0x1111111111111111ull;  // one bit per block, at every fourth place
-      bits = (bits | bits >> 3) & 0x0303030303030303ull;
-      bits = (bits | bits >> 6) & 0x000f000f000f000full;
-      bits = (bits | bits >> 12) & 0x000000ff000000ffull;
-      bits = (bits | bits >> 24) & 0xffffull;
-      const uint32_t first_v = v0 + u * kCodecThreads + (tid & ~(kWave - 1));  // of this wave
-      if (lane_id() == 0 && first_v < nvec) reinterpret_cast<uint16_t *>(d)[first_v / 64] = (uint16_t)bits;
-      if (kept)
-        __builtin_nontemporal_store(t[u], reinterpret_cast<u32x4 *>(d + c.image_off) + v);
-      else if (v < nvec && (v & 3) == 0)
-        d[c.flat_off + b] = (uint8_t)x;
+      // a run beyond the row writes nothing (a branch around it cost 1 - 2 %)
+      encode_run(d, c, (v0 + u * kCodecThreads + tid) / kWave, t[u]);
     }
+  }
+}
+
+// Short rows: a workgroup takes 8 consecutive runs, whatever rows they belong to, a wave two of them.  A workgroup per row
+// is mostly idle lanes there (18,000 rows of 640 bytes, 80 % flat: 51 us, so 8; 3,000 of 4,160 bytes 12.4 and 7.5; 18,000 of
+// 6,400 bytes 55 and 31).
+constexpr uint32_t kEncodeWaves = 4, kEncodeRuns = 2, kEncodeRunsPerWorkgroup = kEncodeWaves * kEncodeRuns;
+__global__ __launch_bounds__(kEncodeWaves * kWave) void codec_encode_runs_kernel(const uint8_t *__restrict__ src,
+                                                                                uint8_t *__restrict__ ring, RowMap to,
+                                                                                uint64_t ring_stride, CodecShape c,
+                                                                                uint32_t runs_per_row, uint32_t total_runs)
+{
+  const uint32_t lane = lane_id(), nvec = c.raw_bytes / 16;
+  const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+  const uint32_t first = blockIdx.x * kEncodeRunsPerWorkgroup + wave * kEncodeRuns;
+  if (first >= total_runs) return;
+  uint32_t row[kEncodeRuns], run[kEncodeRuns];
+  u32x4 t[kEncodeRuns];
+#pragma unroll
+  for (int u = 0; u < (int)kEncodeRuns; ++u) {
+    const uint32_t r = min(first + u, total_runs - 1);  // a run beyond the last is read as the last, and not written
+    row[u] = r / runs_per_row;
+    run[u] = r - row[u] * runs_per_row;
+    t[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(src + (uint64_t)row[u] * c.raw_bytes) +
+                                      min(run[u] * kWave + lane, nvec - 1));
+  }
+#pragma unroll
+  for (int u = 0; u < (int)kEncodeRuns; ++u) {
+    if (first + u >= total_runs) return;
+    uint8_t *const d = ring + map_row(to, row[u]) * ring_stride;
+    encode_run(d, c, run[u], t[u]);
+    if (run[u] + 1 == runs_per_row && runs_per_row + lane < c.flat_off / 2)  // the rest of the mask (at most 7 pieces)
+      reinterpret_cast<uint16_t *>(d)[runs_per_row + lane] = 0;
   }
 }
 
@@ -129,8 +175,20 @@ int apex_replay_add_payload_encoded(apex_replay_t *r, uint64_t count, const void
   if (count > 0x7ffffff0ull) return APEX_ERR_TOO_LARGE;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   const RowMap ring{nullptr, &r->state()->tail, r->cfg.max_slots, r->tv.p_div};
-  codec_encode_rows_kernel<<<dim3((uint32_t)count), dim3(kCodecThreads), 0, stream>>>(
-      static_cast<const uint8_t *>(raw_obs), r->obs(), ring, r->cfg.obs_bytes, codec_shape(raw_bytes));
+  const CodecShape shape = codec_shape(raw_bytes);
+  const uint8_t *const src = static_cast<const uint8_t *>(raw_obs);
+  const uint32_t runs_per_row = (raw_bytes / 16 + kWave - 1) / kWave;
+  const uint64_t runs = count * runs_per_row, blocks = (runs + kEncodeRunsPerWorkgroup - 1) / kEncodeRunsPerWorkgroup;
+  // Rows shorter than the runs of a workgroup go packed.  Longer ones are faster that way as well while nothing else runs
+  // (18,000 of 28,224 bytes 125 us, packed 117), but beside learner steps they hold these up: 25 steps with such a round,
+  // twice, 662 us, packed 683; with rows of 8,192 bytes 449 and 484, with 6,400 bytes 425 and 405, with 3,200 418 and 379.
+  // (The grid's lanes are counted in 32 bits.)
+  if (runs_per_row < kEncodeRunsPerWorkgroup && blocks * kEncodeWaves * kWave <= 0xffffffffull)
+    codec_encode_runs_kernel<<<dim3((uint32_t)blocks), dim3(kEncodeWaves * kWave), 0, stream>>>(
+        src, r->obs(), ring, r->cfg.obs_bytes, shape, runs_per_row, (uint32_t)runs);
+  else
+    codec_encode_rows_kernel<<<dim3((uint32_t)count), dim3(kCodecThreads), 0, stream>>>(src, r->obs(), ring,
+                                                                                       r->cfg.obs_bytes, shape);
   APEX_HIP(hipGetLastError());
   if (act || ret || gacc) {
     const PayloadRing pr{r->obs(), r->act(), r->ret(), r->gacc(), r->cfg.obs_bytes, r->cfg.act_bytes};

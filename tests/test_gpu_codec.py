@@ -132,6 +132,28 @@ def test_pipeline_with_the_codec(raw_bytes, flat_share, nb, k, depth):
     pipe.close()
 
 
+# Rows of fewer than 8 runs of 64 pieces of 16 bytes are encoded 8 runs to a workgroup: rows on both sides of that line, of
+# whole and of partial runs, in numbers that leave the last workgroup and the last wave part of their share.
+@pytest.mark.gpu
+@pytest.mark.parametrize("raw_bytes", [64, 960, 1024, 1088, 2048, 3136, 6400, 7168, 7232, 8192])
+@pytest.mark.parametrize("flat_share", [0.0, 0.6, 1.0])
+@pytest.mark.parametrize("cnt", [1, 8, 103])
+def test_encoded_rows_share_workgroups(raw_bytes, flat_share, cnt):
+    from paper_1803_00933_amd import apex
+    rng = np.random.default_rng(raw_bytes + cnt)
+    stride = oracle.codec_row_bytes(raw_bytes)
+    P = 205
+    g = apex.Replay(P, P, stride, 4)
+    assert g.add(torch.ones(100, device="cuda:0"))[0] == 0
+    g.obs_view().fill_(7)
+    raw = frame_like(rng, cnt, raw_bytes, flat_share)
+    assert g.add_payload_encoded(dev(raw)) == 0
+    torch.cuda.synchronize()
+    ring = host(g.obs_view())
+    defined_parts_equal(ring[100:100 + len(raw), :stride], oracle.codec_encode(raw)[0], raw_bytes)
+    assert (ring[:100] == 7).all() and (ring[100 + len(raw):] == 7).all()
+
+
 # A step's workgroup decodes up to 4 runs of 448 pieces of 16 bytes (512 in a launch that draws nothing), the first two
 # ahead of the mask: rows that end with a run, one block before and one block behind it.
 @pytest.mark.gpu
