@@ -33,16 +33,19 @@ struct apex_pipeline {
   // the latest gather on each of the two copy streams: an add round's payload may overwrite slots that an
   // eviction has just freed, so it waits for the gathers of batches drawn before that eviction
   hipEvent_t last_gather[2] = {nullptr, nullptr};
-  hipEvent_t fork_ev = nullptr, join_ev = nullptr;
   // Work issued on each stream, and how much of it the tree stream has waited for (indices as in streams(); the tree
   // stream's are not used): join asks the caller's stream to wait for a copy stream only if something on it is left.
   // fork makes a copy stream wait when it is next used.  An event's record and the wait of another stream for it are some
   // 10 us of host time each (fork, four launches, join: 27 us with one stream, 42 with two, 55 with three, the launches 10).
+  hipEvent_t join_ev = nullptr;
   uint64_t issued[3] = {}, covered[3] = {};
   uint64_t payload_at = 0;                // issued[1] when payload_done was recorded
   std::vector<uint64_t> gathered_at;      // the same for gathered
-  bool fork_pending[3] = {};
-  hipStream_t fork_after = nullptr;       // the stream of the latest fork
+  // Fork number f is recorded by fork_ev[f % kForks], behind whatever stream it names: that two forks name the same handle
+  // does not make them one (a stream may have been destroyed and another created in its place).
+  static constexpr uint32_t kForks = 8;
+  hipEvent_t fork_ev[kForks] = {};
+  uint64_t forks = 0, forks_seen[3] = {};  // forks so far; those that each copy stream need not wait for any more
   std::vector<hipEvent_t> capture_events;
 
   uint64_t step = 0;          // learner steps issued so far
@@ -76,6 +79,12 @@ constexpr uint64_t kSmallPayloadBytes = 4u << 20;
 constexpr uint64_t kWideStepSamples = 2048;
 constexpr uint64_t kWideStepBytes = 8u << 20;  // ... and only if the gather moves enough to be worth two events
 
+#define APEX_TRY(call)            \
+  do {                            \
+    const int rc_ = (call);       \
+    if (rc_ != APEX_OK) return rc_; \
+  } while (0)
+
 bool new_event(hipEvent_t *e) { return !hip_failed(hipEventCreateWithFlags(e, hipEventDisableTiming)); }
 
 // Events that only order the pipeline's two streams on this device: no system-scope fence when
@@ -103,19 +112,40 @@ int mark_wait(apex_pipeline::Mark &m, hipStream_t s)
   return APEX_OK;
 }
 
-int wait_for_fork(apex_pipeline *p, int i)
+// Copy stream i waits for those forks before number `end` that it has not waited for yet.
+int wait_for_forks(apex_pipeline *p, int i, uint64_t end)
 {
-  if (p->fork_pending[i] && p->streams(i)) APEX_HIP(hipStreamWaitEvent(p->streams(i), p->fork_ev, 0));
-  p->fork_pending[i] = false;
+  for (uint64_t &f = p->forks_seen[i]; f < end; ++f)
+    if (p->streams(i)) APEX_HIP(hipStreamWaitEvent(p->streams(i), p->fork_ev[f % apex_pipeline::kForks], 0));
   return APEX_OK;
 }
 
 // To be called before work is issued on copy stream i.
 int use_stream(apex_pipeline *p, int i)
 {
-  const int rc = wait_for_fork(p, i);
+  const int rc = wait_for_forks(p, i, p->forks);
   ++p->issued[i];
   return rc;
+}
+
+// Makes the event of the next fork free: that of kForks forks ago, which a copy stream that has not been used since may
+// still have to wait for.  It does so now, unless the event is long complete, as it mostly is.
+int free_fork_event(apex_pipeline *p)
+{
+  if (p->forks < apex_pipeline::kForks) return APEX_OK;
+  const uint64_t oldest = p->forks - apex_pipeline::kForks;
+  bool complete = false, asked = false;
+  for (int i = 1; i < apex_pipeline::kStreams; ++i) {
+    if (!p->streams(i) || p->forks_seen[i] > oldest) continue;
+    if (!asked) {
+      complete = hipEventQuery(p->fork_ev[oldest % apex_pipeline::kForks]) == hipSuccess;
+      if (!complete) (void)hipGetLastError();  // not an error: nothing to report later
+      asked = true;
+    }
+    if (complete) p->forks_seen[i] = oldest + 1;
+    else APEX_TRY(wait_for_forks(p, i, oldest + 1));
+  }
+  return APEX_OK;
 }
 
 void forget_marks(apex_pipeline *p)
@@ -149,7 +179,9 @@ void drop_graph(apex_pipeline *p)
 void pipeline_free(apex_pipeline *p)
 {
   drop_graph(p);
-  for (hipEvent_t e : {p->payload_done.own, p->tail_ready.own, p->drawn.own, p->fork_ev, p->join_ev})
+  for (hipEvent_t e : {p->payload_done.own, p->tail_ready.own, p->drawn.own, p->join_ev})
+    if (e) (void)hipEventDestroy(e);
+  for (hipEvent_t e : p->fork_ev)
     if (e) (void)hipEventDestroy(e);
   for (apex_pipeline::Mark &m : p->gathered)
     if (m.own) (void)hipEventDestroy(m.own);
@@ -157,12 +189,6 @@ void pipeline_free(apex_pipeline *p)
     if (p->streams(i)) (void)hipStreamDestroy(p->streams(i));
   delete p;
 }
-
-#define APEX_TRY(call)            \
-  do {                            \
-    const int rc_ = (call);       \
-    if (rc_ != APEX_OK) return rc_; \
-  } while (0)
 
 }  // namespace
 
@@ -189,8 +215,9 @@ int apex_pipeline_create(apex_replay_t *r, uint32_t depth, const apex_batch_buff
   bool ok = true;
   for (hipStream_t *s : {&p->tree, &p->add})
     ok = ok && !hip_failed(hipStreamCreateWithFlags(s, hipStreamNonBlocking));  // default priority
-  ok = ok && new_mark_event(&p->payload_done.own) && new_mark_event(&p->tail_ready.own) && new_event(&p->fork_ev) &&
-       new_event(&p->join_ev) && new_mark_event(&p->drawn.own);
+  ok = ok && new_mark_event(&p->payload_done.own) && new_mark_event(&p->tail_ready.own) && new_event(&p->join_ev) &&
+       new_mark_event(&p->drawn.own);
+  for (hipEvent_t &e : p->fork_ev) ok = ok && new_event(&e);
   p->wide = (uint64_t)num_batches * k >= kWideStepSamples && depth >= 2 &&
             (uint64_t)num_batches * k * r->cfg.obs_bytes >= kWideStepBytes;
   if (p->wide) {
@@ -221,15 +248,18 @@ int apex_pipeline_fork(apex_pipeline_t *p, void *after)
 {
   if (!p || p->capturing) return APEX_ERR_INVALID_ARG;
   APEX_TRY(issue_held_step(&p->held, p->tree));
-  const hipStream_t s = static_cast<hipStream_t>(after);
-  // A wait that is due covers this fork too if it is on the same stream; one for another stream's work is made now, before
-  // the event is recorded anew.  (hipStreamPerThread names a stream per host thread.)
-  if (s != p->fork_after || s == hipStreamPerThread)
-    for (int i = 1; i < apex_pipeline::kStreams; ++i) APEX_TRY(wait_for_fork(p, i));
-  APEX_HIP(hipEventRecord(p->fork_ev, s));
-  APEX_HIP(hipStreamWaitEvent(p->tree, p->fork_ev, 0));
-  p->fork_after = s;
-  for (int i = 1; i < apex_pipeline::kStreams; ++i) p->fork_pending[i] = true;
+  APEX_TRY(free_fork_event(p));
+  const hipEvent_t e = p->fork_ev[p->forks % apex_pipeline::kForks];
+  APEX_HIP(hipEventRecord(e, static_cast<hipStream_t>(after)));
+  ++p->forks;
+  APEX_HIP(hipStreamWaitEvent(p->tree, e, 0));
+  // Behind a stream that the caller is capturing the copy streams join the capture at once, to be joined back by
+  // apex_pipeline_join: a later wait for an event of a capture that has ended is none.
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(static_cast<hipStream_t>(after), &status) != hipSuccess) (void)hipGetLastError();
+  if (status != hipStreamCaptureStatusNone)
+    for (int i = 1; i < apex_pipeline::kStreams; ++i)
+      if (p->streams(i)) APEX_TRY(use_stream(p, i));
   return APEX_OK;
 }
 
@@ -418,7 +448,7 @@ int apex_pipeline_capture_begin(apex_pipeline_t *p)
 {
   if (!p || p->capturing || p->add_open) return APEX_ERR_INVALID_ARG;
   APEX_TRY(issue_held_step(&p->held, p->tree));
-  for (int i = 1; i < apex_pipeline::kStreams; ++i) APEX_TRY(wait_for_fork(p, i));  // not to be recorded
+  for (int i = 1; i < apex_pipeline::kStreams; ++i) APEX_TRY(wait_for_forks(p, i, p->forks));  // not to be recorded
   for (int i = 0; i < apex_pipeline::kStreams; ++i) {  // drained: nothing older to wait for
     if (p->streams(i)) APEX_HIP(hipStreamSynchronize(p->streams(i)));
     p->covered[i] = p->issued[i];

@@ -1,0 +1,90 @@
+"""Which launches the library makes and how they are ordered, on a HIP runtime that only records them (no GPU)."""
+import recorded_hip
+
+
+# 6.8 MB of observations: a round whose payload the copy stream carries.
+FORKS = """
+r = replay(4000, 28224, filled=2000)
+p, (tree, add) = pipeline(r, 3, 1, 64)
+A, B = 0x1000, 0x2000
+hip_calls, had = [], {}
+
+def work(stream, name):      # the caller's stream has new work behind which nothing of its own is ordered
+    hip_calls.extend(take())
+    hip_calls.append(["mark", stream, name])
+
+%s
+assert add_begin(p, 1, 240) == 0 and steps(p, 2) == 0 and add_end(p) == 0
+hip_calls.extend(take())
+after, out = seen(hip_calls, had)
+result = [dict(stream="tree" if c[1] == tree else "add", kernel=c[5], behind=sorted(b)) for c, b in out]
+"""
+
+
+def check_forks(tmp_path, forks, names):
+    out = recorded_hip.run(tmp_path, FORKS % forks)
+    assert {x["stream"] for x in out} == {"tree", "add"}
+    for x in out:
+        assert set(names) <= set(x["behind"]), x
+
+
+def test_a_fork_is_waited_for_by_every_stream_that_is_used(tmp_path):
+    check_forks(tmp_path, 'work(A, "a")\nassert call("apex_pipeline_fork", p, A) == 0', ["a"])
+
+
+def test_forks_behind_two_streams(tmp_path):
+    check_forks(tmp_path, 'for s, n in ((A, "a"), (B, "b")):\n'
+                          '    work(s, n)\n    assert call("apex_pipeline_fork", p, s) == 0', ["a", "b"])
+
+
+def test_forks_behind_two_streams_of_one_handle(tmp_path):
+    """A stream that is destroyed, and one created later that gets the same handle, are two streams."""
+    check_forks(tmp_path, 'for n in ("a", "b"):\n'
+                          '    work(A, n)\n    assert call("apex_pipeline_fork", p, A) == 0', ["a", "b"])
+
+
+def test_many_forks_before_a_copy_stream_is_used(tmp_path):
+    check_forks(tmp_path, 'for i in range(20):\n'
+                          '    work(A + 16 * (i % 3), str(i))\n'
+                          '    assert call("apex_pipeline_fork", p, A + 16 * (i % 3)) == 0', [str(i) for i in range(20)])
+
+
+def test_forks_of_a_pipeline_that_uses_no_copy_stream_cost_no_waits(tmp_path):
+    """Small steps, fork and join again and again: the copy stream, which has nothing to do, is asked to wait for nothing
+    once the forks are complete, and for each fork at most once where they are not."""
+    for complete in (1, 0):
+        out = recorded_hip.run(tmp_path, """
+r = replay(4000, 64)
+p, (tree, add) = pipeline(r, 3, 1, 64)
+C.c_int.in_dll(hip, "complete").value = %d
+for i in range(50):
+    assert call("apex_pipeline_fork", p, 0x1000) == 0 and steps(p, 1) == 0 and call("apex_pipeline_join", p, 0x1000) == 0
+result = [c for c in take() if c[0] == "wait" and c[1] == add]
+""" % complete)
+        assert len(out) <= (0 if complete else 50)
+
+
+def test_a_fork_in_the_callers_own_capture_takes_the_copy_streams_along(tmp_path):
+    """All streams of the pipeline enter a capture of the caller's and are joined back, and what is waited for after it
+    has nothing of it."""
+    out = recorded_hip.run(tmp_path, """
+r = replay(4000, 28224, filled=2000)
+p, (tree, add) = pipeline(r, 3, 1, 64)
+capturing = C.c_int.in_dll(hip, "capturing")
+capturing.value = 1
+assert call("apex_pipeline_fork", p, 0x1000) == 0 and steps(p, 1) == 0 and call("apex_pipeline_join", p, 0x1000) == 0
+capturing.value = 0
+captured = take()
+assert call("apex_pipeline_fork", p, 0x1000) == 0 and add_begin(p, 1, 240) == 0
+result = [captured, take(), tree, add]
+""")
+    captured, later, tree, add = out
+    records, waits = {}, []
+    for c in captured:
+        if c[0] == "record":
+            records[c[1]] = c[2]
+        elif c[0] == "wait":
+            waits.append((c[1], records[c[2]]))
+    assert sorted(waits) == sorted([(tree, 0x1000), (add, 0x1000), (0x1000, tree), (0x1000, add)])
+    assert [c[2] for c in later if c[0] == "wait" and c[1] == add][:1] == [c[1] for c in later if c[0] == "record"][:1]
+    assert not set(records) & {c[2] for c in later if c[0] == "wait"}
