@@ -154,9 +154,16 @@ def _stream(stream=None):
     return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
+def _plain(x):
+    """What an argument that is no number itself stands for, as ctypes has it: the one that it names, the value of one of
+    ctypes' own."""
+    x = getattr(x, "_as_parameter_", x)
+    return x.value if isinstance(x, C._SimpleCData) else x
+
+
 from . import apex_binding as _call  # noqa: E402  (behind torch, whose libraries it needs, and the checks above)
 
-_call.load(os.path.abspath(LIB_PATH), _ptr, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
+_call.load(os.path.abspath(LIB_PATH), _ptr, _plain, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
 
 
 def workspace_bytes(cfg: Config):

@@ -17,9 +17,44 @@
 namespace {
 
 PyObject *g_address = nullptr;                                  // apex._ptr: address of what is no torch.Tensor
+PyObject *g_plain = nullptr;                                    // apex._plain: what an argument that is no number stands for
 PyObject *g_current_device = nullptr, *g_current_stream = nullptr;  // torch's raw handle of the current stream
 
 struct Failed {};  // a Python error is set
+
+// A reference that is given back when it goes out of scope.
+struct Ref {
+  PyObject *o;
+  explicit Ref(PyObject *owned) : o(owned)
+  {
+    if (!o) throw Failed{};
+  }
+  Ref(const Ref &) = delete;
+  ~Ref() { Py_DECREF(o); }
+};
+
+// An integer, whatever has an index (numpy's integers), or what g_plain makes one of; the value modulo 2^64.
+unsigned long long integer(PyObject *o, bool plain = false)
+{
+  if (!PyLong_Check(o)) {
+    if (PyIndex_Check(o)) return integer(Ref(PyNumber_Index(o)).o);
+    if (!plain) return integer(Ref(PyObject_CallOneArg(g_plain, o)).o, true);
+    PyErr_Format(PyExc_TypeError, "an integer is required, not %.80s", Py_TYPE(o)->tp_name);
+    throw Failed{};
+  }
+  const unsigned long long v = PyLong_AsUnsignedLongLongMask(o);
+  if (PyErr_Occurred()) throw Failed{};
+  return v;
+}
+
+// The same for addresses and handles, with None for a null pointer.
+void *pointer(PyObject *o)
+{
+  if (o == Py_None) return nullptr;
+  if (PyLong_Check(o) || PyIndex_Check(o)) return reinterpret_cast<void *>(integer(o));
+  const Ref p(PyObject_CallOneArg(g_plain, o));
+  return p.o == Py_None ? nullptr : reinterpret_cast<void *>(integer(p.o, true));
+}
 
 // Device addresses: a contiguous tensor on the GPU, or None.
 void *address(PyObject *o)
@@ -33,31 +68,15 @@ void *address(PyObject *o)
     }
     return t.data_ptr();
   }
-  PyObject *r = PyObject_CallOneArg(g_address, o);
-  if (!r) throw Failed{};
-  void *p = r == Py_None ? nullptr : PyLong_AsVoidPtr(r);
-  Py_DECREF(r);
-  if (PyErr_Occurred()) throw Failed{};
-  return p;
+  return pointer(Ref(PyObject_CallOneArg(g_address, o)).o);
 }
 
 // A stream object's handle; None: the current device's current stream.
 void *stream_handle(PyObject *o)
 {
-  PyObject *h;
-  if (o == Py_None) {
-    PyObject *dev = PyObject_CallNoArgs(g_current_device);
-    if (!dev) throw Failed{};
-    h = PyObject_CallOneArg(g_current_stream, dev);
-    Py_DECREF(dev);
-  } else {
-    h = PyObject_GetAttrString(o, "cuda_stream");
-  }
-  if (!h) throw Failed{};
-  void *p = PyLong_AsVoidPtr(h);
-  Py_DECREF(h);
-  if (PyErr_Occurred()) throw Failed{};
-  return p;
+  if (o != Py_None) return pointer(Ref(PyObject_GetAttrString(o, "cuda_stream")).o);
+  const Ref device(PyObject_CallNoArgs(g_current_device));
+  return pointer(Ref(PyObject_CallOneArg(g_current_stream, device.o)).o);
 }
 
 template <typename T>
@@ -65,54 +84,40 @@ struct From {  // pointers to device memory
   static_assert(std::is_pointer<T>::value, "");
   static T get(PyObject *o) { return static_cast<T>(address(o)); }
 };
-template <typename T>
-T handle(PyObject *o)
-{
-  void *p = o == Py_None ? nullptr : PyLong_AsVoidPtr(o);
-  if (PyErr_Occurred()) throw Failed{};
-  return static_cast<T>(p);
-}
 template <>
 struct From<apex_replay_t *> {
-  static apex_replay_t *get(PyObject *o) { return handle<apex_replay_t *>(o); }
+  static apex_replay_t *get(PyObject *o) { return static_cast<apex_replay_t *>(pointer(o)); }
 };
 template <>
 struct From<apex_pipeline_t *> {
-  static apex_pipeline_t *get(PyObject *o) { return handle<apex_pipeline_t *>(o); }
+  static apex_pipeline_t *get(PyObject *o) { return static_cast<apex_pipeline_t *>(pointer(o)); }
 };
 template <>
 struct From<apex_pe_replay_t *> {
-  static apex_pe_replay_t *get(PyObject *o) { return handle<apex_pe_replay_t *>(o); }
+  static apex_pe_replay_t *get(PyObject *o) { return static_cast<apex_pe_replay_t *>(pointer(o)); }
 };
-template <typename T>
-T integer(PyObject *o)
-{
-  if (!PyLong_Check(o)) {
-    PyErr_Format(PyExc_TypeError, "an integer is required, not %.80s", Py_TYPE(o)->tp_name);
-    throw Failed{};
-  }
-  const unsigned long long v = PyLong_AsUnsignedLongLongMask(o);
-  if (PyErr_Occurred()) throw Failed{};
-  return static_cast<T>(v);
-}
 template <>
 struct From<uint32_t> {
-  static uint32_t get(PyObject *o) { return integer<uint32_t>(o); }
+  static uint32_t get(PyObject *o) { return static_cast<uint32_t>(integer(o)); }
 };
 template <>
 struct From<uint64_t> {
-  static uint64_t get(PyObject *o) { return integer<uint64_t>(o); }
+  static uint64_t get(PyObject *o) { return static_cast<uint64_t>(integer(o)); }
 };
 template <>
 struct From<int> {
-  static int get(PyObject *o) { return integer<int>(o); }
+  static int get(PyObject *o) { return static_cast<int>(integer(o)); }
 };
 template <>
 struct From<float> {
   static float get(PyObject *o)
   {
-    const double v = PyFloat_AsDouble(o);
-    if (PyErr_Occurred()) throw Failed{};
+    double v = PyFloat_AsDouble(o);
+    if (v == -1.0 && PyErr_Occurred() && PyErr_ExceptionMatches(PyExc_TypeError)) {
+      PyErr_Clear();
+      v = PyFloat_AsDouble(Ref(PyObject_CallOneArg(g_plain, o)).o);
+    }
+    if (v == -1.0 && PyErr_Occurred()) throw Failed{};
     return static_cast<float>(v);
   }
 };
@@ -270,12 +275,12 @@ VERB(pe_sample_update, [](Pe r, uint32_t k, float beta, U64 rnd, F new_prio, uin
   return p_apex_pe_sample_update(r, k, beta, rnd, new_prio, key, slot, weight, obs, act, ret, gacc, s);
 })
 
-// load(path of the library, _ptr, current device, current raw stream)
+// load(path of the library, _ptr, _plain, current device, current raw stream)
 PyObject *load(PyObject *, PyObject *args)
 {
   const char *path;
-  PyObject *address_of, *device, *stream;
-  if (!PyArg_ParseTuple(args, "sOOO", &path, &address_of, &device, &stream)) return nullptr;
+  PyObject *address_of, *plain, *device, *stream;
+  if (!PyArg_ParseTuple(args, "sOOOO", &path, &address_of, &plain, &device, &stream)) return nullptr;
   void *const lib = dlopen(path, RTLD_NOW | RTLD_LOCAL);
   if (!lib) return PyErr_Format(PyExc_ImportError, "%s", dlerror());
 #define X(name)                                                            \
@@ -283,8 +288,9 @@ PyObject *load(PyObject *, PyObject *args)
   if (!p_##name) return PyErr_Format(PyExc_ImportError, "%s lacks %s", path, #name);
   APEX_ENTRIES(X)
 #undef X
-  Py_INCREF(address_of), Py_INCREF(device), Py_INCREF(stream);
+  Py_INCREF(address_of), Py_INCREF(plain), Py_INCREF(device), Py_INCREF(stream);
   Py_XSETREF(g_address, address_of);
+  Py_XSETREF(g_plain, plain);
   Py_XSETREF(g_current_device, device);
   Py_XSETREF(g_current_stream, stream);
   Py_RETURN_NONE;

@@ -147,3 +147,38 @@ def test_binding_refuses_what_it_cannot_address():
         call.pipeline_steps(None, 1, "0.4", None, None)
     with pytest.raises(AttributeError):
         call.evict(None, 7)                                             # no stream
+
+
+def test_binding_takes_every_number_that_ctypes_takes():
+    """Counts and exponents as numpy has them, or anything else with an index or a float value, ctypes' own scalars, objects
+    that name their argument, and streams whose handle is none of Python's integers."""
+    import numpy as np
+    import pytest
+    from paper_1803_00933_amd import apex
+    call, bad = apex._call, apex.ERR_INVALID_ARG
+
+    class Named:
+        def __init__(self, value):
+            self._as_parameter_ = value
+
+    class Indexed:
+        def __index__(self):
+            return 3
+
+    class Stream:
+        def __init__(self, handle):
+            self.cuda_stream = handle
+
+    for number in (3, True, np.int64(3), np.uint32(3), np.uint8(3), C.c_uint64(3), Named(3), Named(C.c_uint64(3)), Indexed(), -1):
+        apex.lib.apex_replay_update_priorities(None, number, None, None, None)          # ctypes takes it
+        assert call.update_priorities(None, number, None, None, Stream(0)) == bad, number
+    for number in (0.4, 1, np.float32(0.4), np.float64(0.4), np.int64(1), C.c_float(0.4), Named(0.4), Indexed()):
+        assert call.pipeline_steps(None, 1, number, None, None) == (bad, 0), number
+    for handle in (0, None, np.int64(0), C.c_void_p(), C.c_void_p(0), Named(0)):
+        assert call.evict(None, Stream(handle)) == (bad, 0), handle
+    for number in (3.0, np.float32(3), "3", None, Named("3"), C.c_float(3)):
+        with pytest.raises(TypeError):
+            call.update_priorities(None, number, None, None, Stream(0))
+    for number in ("0.4", None, Named(None), C.c_char(b"0")):
+        with pytest.raises(TypeError):
+            call.pipeline_steps(None, 1, number, None, None)
