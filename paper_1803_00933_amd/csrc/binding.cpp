@@ -145,14 +145,20 @@ PyObject *to_python(const Reported<2> &r)
   return Py_BuildValue("iKK", r.rc, (unsigned long long)r.v[0], (unsigned long long)r.v[1]);
 }
 
+// Gives the interpreter's lock up, until the end of the scope: also where an exception leaves it.
+struct Unlocked {
+  PyThreadState *const state = PyEval_SaveThread();
+  ~Unlocked() { PyEval_RestoreThread(state); }
+};
+
 template <typename R, typename... A, size_t... I>
 PyObject *invoke(R (*f)(A...), PyObject *const *args, std::index_sequence<I...>)
 {
   const std::tuple<A...> a{From<A>::get(args[I])...};
-  R r;
-  Py_BEGIN_ALLOW_THREADS
-  r = f(std::get<I>(a)...);
-  Py_END_ALLOW_THREADS
+  const R r = [&] {
+    const Unlocked unlocked;
+    return f(std::get<I>(a)...);
+  }();
   return to_python(r);
 }
 

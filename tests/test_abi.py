@@ -182,3 +182,36 @@ def test_binding_takes_every_number_that_ctypes_takes():
     for number in ("0.4", None, Named(None), C.c_char(b"0")):
         with pytest.raises(TypeError):
             call.pipeline_steps(None, 1, number, None, None)
+
+
+def test_binding_survives_an_exception_out_of_the_library(tmp_path):
+    """The interpreter's lock is given up for a call and taken back however the call ends: an exception becomes Python's."""
+    import subprocess
+    import sys
+    from paper_1803_00933_amd import apex
+    src, so = str(tmp_path / "throwing.cpp"), str(tmp_path / "throwing.so")
+    with open(src, "w") as f:
+        f.write("#include <new>\n" + "\n".join('extern "C" int %s() { throw std::bad_alloc(); }' % n for n in apex.EXPORTS))
+    subprocess.check_call(["g++", "-O1", "-shared", "-fPIC", "-o", so, src])
+    code = """
+import sys, threading, torch
+from paper_1803_00933_amd import apex
+apex._call.load(sys.argv[1], apex._ptr, apex._plain, None, None)
+class stream: cuda_stream = 0
+other, stop = [0], threading.Event()
+def count():
+    while not stop.is_set(): other[0] += 1
+t = threading.Thread(target=count)
+t.start()
+for i in range(1000):
+    try:
+        apex._call.evict(None, stream)
+    except RuntimeError as e:
+        assert "bad_alloc" in str(e)
+    else:
+        raise SystemExit("no exception")
+stop.set(); t.join()
+print("passed", other[0] > 0)
+"""
+    r = subprocess.run([sys.executable, "-c", code, so], cwd=ROOT, capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0 and "passed True" in r.stdout, (r.returncode, r.stderr[-2000:])
