@@ -2271,11 +2271,12 @@ __global__ __launch_bounds__(kThreads) void learner_step_kernel(StepArgs a)
 // further, it would cover the neighbour): three points per later batch, one batch per lane of the sample's row.  In the
 // sample's own batch it is the point above.
 // As two launches per step (sample_kernel with the first pass of the update, update_apply_kernel), 16 x 512 of 2^21
-// slots: 15.7 us, so 9.4; 2 x 128 14 and 7.4; one batch of 4096 17 and 10.5.
+// slots: 13.6 us, so 8.4; 2 x 128 9.1 and 6.6; one batch of 4096 15.0 and 7.8.
 // --------------------------------------------------------------------------------------------
 struct MultiStepArgs {
-  // workgroups: first those that draw, per batch of step i+1, then those that gather step i, then one per batch for weights
-  uint32_t draw_wgs, draw_wgs_per_batch, gather_wgs;
+  // workgroups: first those that draw, per batch of step i+1; those from gather_first and weight_first on gather step i and
+  // write its weights, weight_wgs_per_batch to a batch
+  uint32_t draw_wgs, draw_wgs_per_batch, gather_first, weight_first, weight_wgs, weight_wgs_per_batch;
   GatherArgs g;           // step i: row o of the outputs = row slot[o]
   uint32_t samples;       // of a step
   const uint32_t *slot;
@@ -2299,12 +2300,13 @@ __global__ __launch_bounds__(kMultiStepThreads) void multi_step_kernel(MultiStep
 {
   __shared__ uint64_t red[kMultiStepThreads / kWave];
   const uint32_t lane = lane_id(), gl = lane & 15, blk = blockIdx.x;
-  if (blk >= a.draw_wgs + a.gather_wgs) {
-    batch_weights(a.wa, blk - a.draw_wgs - a.gather_wgs, red);
+  if (blk >= a.weight_first && blk - a.weight_first < a.weight_wgs) {
+    const uint32_t b = (blk - a.weight_first) / a.weight_wgs_per_batch, part = blk - a.weight_first - b * a.weight_wgs_per_batch;
+    batch_weights(a.wa, b, red, part, a.weight_wgs_per_batch);
     return;
   }
-  if (blk >= a.draw_wgs) {
-    const uint32_t o = (blk - a.draw_wgs) * kMultiStepRows + threadIdx.x / 16;
+  if (blk >= a.gather_first) {
+    const uint32_t o = (blk - a.gather_first) * kMultiStepRows + threadIdx.x / 16;
     if (o >= a.samples) return;
     const uint32_t slot = a.slot[o];
     const uint64_t dq = a.dq[o];
@@ -2353,14 +2355,14 @@ __global__ __launch_bounds__(kMultiStepThreads) void multi_step_kernel(MultiStep
     u_below = r[below], u_same = r[j], u_above = r[above];
   }
   const bool loses = (uint32_t)(__ballot(later) >> (lane & 48)) & 0xffffu;
+  const uint64_t delta = loses ? 0 : q - walk.mass;
   if (in && gl == 0) {
     a.next.slot_out[o] = (uint32_t)walk.idx;
     if (a.next.key_out) a.next.key_out[o] = ring_key(walk.idx, head, head_slot, rd.P);
     a.next.mass[o] = walk.mass;
-    const uint64_t delta = loses ? 0 : q - walk.mass;
     a.next_dq[o] = delta;
-    add_delta(a.wr, (uint32_t)walk.idx, delta);
   }
+  if (in && gl == 0) add_delta(a.wr, (uint32_t)walk.idx, delta);
   const uint64_t nc = __popcll(__ballot(in && gl == 0 && clamped));
   if (nc && lane == 0) atomic_add_u64(&a.st->n_clamped, nc);
 }

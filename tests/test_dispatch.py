@@ -88,3 +88,30 @@ result = [captured, take(), tree, add]
     assert sorted(waits) == sorted([(tree, 0x1000), (add, 0x1000), (0x1000, tree), (0x1000, add)])
     assert [c[2] for c in later if c[0] == "wait" and c[1] == add][:1] == [c[1] for c in later if c[0] == "record"][:1]
     assert not set(records) & {c[2] for c in later if c[0] == "wait"}
+
+
+MULTI = """
+out = []
+for slots, nb, k, depth, n in %r:
+    r = replay(slots, 64, filled=slots if slots < 1 << 20 else 1 << 20)
+    p, streams = pipeline(r, depth, nb, k)
+    assert steps(p, n) == 0
+    out.append(launches())
+    assert call("apex_pipeline_destroy", p) == 0 and call("apex_replay_destroy", r) == 0
+result = out
+"""
+
+
+def multi_launches(tmp_path, shapes):
+    """Per shape (slots, batches, samples per batch, sets, steps of the call): the launches of multi_step_kernel, none where
+    the steps go another way."""
+    return [[x for x in launches if "multi_step" in x["kernel"]] for launches in recorded_hip.run(tmp_path, MULTI % (shapes,))]
+
+
+def test_weights_of_large_batches_are_shared_out(tmp_path):
+    """A step's launch has workgroups for 16 draws, 16 rows and 512 weights each, whatever the size of its batches."""
+    shapes = [(1 << 21, nb, k, 2, 3) for nb, k in ((1, 1025), (1, 4096), (1, 16_384), (1, 32_768), (2, 513), (3, 512), (2, 8192))]
+    for (_, nb, k, _, n), found in zip(shapes, multi_launches(tmp_path, shapes)):
+        parts = nb * -(-k // 16), -(-nb * k // 16), nb * -(-k // 512)
+        assert [x["grid"] for x in found] == [parts[0]] + [sum(parts)] * (n - 1) + [parts[1] + parts[2]], (nb, k)
+        assert all(x["block"] == 256 for x in found)
