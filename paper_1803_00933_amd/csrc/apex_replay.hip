@@ -1042,7 +1042,12 @@ int fused_steps(apex_replay *r, uint32_t n, uint32_t k, float beta, const uint64
 }
 
 // Whether n steps of num_batches x k samples go that way: several batches, or one that is too large for a workgroup per
-// sample, of rows that sample_kernel gathers, with room for their changes in the scratch region.
+// sample, of rows that sample_kernel gathers, with room for their changes in the scratch region, and
+//   - up to kMultiStepMaxBatches: a drawn sample is held against those of every later batch.  Two launches per step / one,
+//     us per step, 2^21 slots: 128 x 64 15.7 / 13.0, 160 x 32 13.1 / 11.9, 192 x 32 13.6 / 13.8, 256 x 32 14.3 / 17.3,
+//     1024 x 32 30.2 / 106.
+constexpr uint32_t kMultiStepMaxBatches = 160;
+
 // The second copy of the tree may have to be brought up to date first, at some 5 TB/s; a step gains 7 us.
 constexpr uint64_t kTreeWordsPerStep = 2u << 20;
 
@@ -1050,6 +1055,7 @@ bool multi_steps_fit(const apex_replay *r, uint32_t n, uint32_t num_batches, uin
 {
   const uint64_t samples = (uint64_t)num_batches * k;
   if ((num_batches == 1 && k <= kStepMaxK) || depth < 2 || depth * samples > (uint64_t)kStepSets * kStepMaxK) return false;
+  if (num_batches > kMultiStepMaxBatches) return false;
   if (r->second_version != r->tree_version && (n + 1) * kTreeWordsPerStep < 2 * r->geo.tree_words) return false;
   return gather_in_draw(r);
 }

@@ -115,3 +115,9 @@ def test_weights_of_large_batches_are_shared_out(tmp_path):
         parts = nb * -(-k // 16), -(-nb * k // 16), nb * -(-k // 512)
         assert [x["grid"] for x in found] == [parts[0]] + [sum(parts)] * (n - 1) + [parts[1] + parts[2]], (nb, k)
         assert all(x["block"] == 256 for x in found)
+
+
+def test_steps_of_many_batches_are_two_launches_each(tmp_path):
+    """What a drawn sample is held against grows with the number of batches: beyond a number of them two launches do less."""
+    shapes = [(1 << 21, nb, k, 2, 2) for nb, k in ((128, 64), (160, 32), (161, 32), (256, 64), (512, 16), (1024, 1), (1024, 32))]
+    assert [bool(x) for x in multi_launches(tmp_path, shapes)] == [True, True] + [False] * 5
