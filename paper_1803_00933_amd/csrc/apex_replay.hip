@@ -1045,8 +1045,13 @@ int fused_steps(apex_replay *r, uint32_t n, uint32_t k, float beta, const uint64
 // sample, of rows that sample_kernel gathers, with room for their changes in the scratch region, and
 //   - up to kMultiStepMaxBatches: a drawn sample is held against those of every later batch.  Two launches per step / one,
 //     us per step, 2^21 slots: 128 x 64 15.7 / 13.0, 160 x 32 13.1 / 11.9, 192 x 32 13.6 / 13.8, 256 x 32 14.3 / 17.3,
-//     1024 x 32 30.2 / 106.
-constexpr uint32_t kMultiStepMaxBatches = 160;
+//     1024 x 32 30.2 / 106;
+//   - up to kMultiStepMaxPerTopNode samples per node of the top level: every sample adds to it twice, and up to four
+//     neighbours together, where two launches add up whole waves of 64.  8192 samples (16 x 512) on 74 nodes 13.7 / 14.8,
+//     on 128 13.3 / 11.0, 16,384 (32 x 512) on 128 16.3 / 19.3, on 256 14.9 / 12.6, on 512 16.3 / 12.2.
+// Neighbours are added up (add_four) from kMergePerTopNode samples per top node on: without it 4 x 512 on 74 nodes take 12.4
+// us per step, so 7.2; 16 x 512 on 512 nodes 8.4 and 7.7; 2 x 512 on 512 6.2, and 6.6 with it.
+constexpr uint32_t kMultiStepMaxBatches = 160, kMultiStepMaxPerTopNode = 64, kMergePerTopNode = 8;
 
 // The second copy of the tree may have to be brought up to date first, at some 5 TB/s; a step gains 7 us.
 constexpr uint64_t kTreeWordsPerStep = 2u << 20;
@@ -1055,7 +1060,7 @@ bool multi_steps_fit(const apex_replay *r, uint32_t n, uint32_t num_batches, uin
 {
   const uint64_t samples = (uint64_t)num_batches * k;
   if ((num_batches == 1 && k <= kStepMaxK) || depth < 2 || depth * samples > (uint64_t)kStepSets * kStepMaxK) return false;
-  if (num_batches > kMultiStepMaxBatches) return false;
+  if (num_batches > kMultiStepMaxBatches || samples > (uint64_t)kMultiStepMaxPerTopNode * r->tv.n_top) return false;
   if (r->second_version != r->tree_version && (n + 1) * kTreeWordsPerStep < 2 * r->geo.tree_words) return false;
   return gather_in_draw(r);
 }
@@ -1110,16 +1115,17 @@ int multi_steps(apex_replay *r, uint32_t n, uint32_t num_batches, uint32_t k, fl
       a.draw_wgs = num_batches * a.draw_wgs_per_batch;
     }
     // The weights of large batches take longer than a gather and go ahead of it, 512 to a workgroup: one batch of 4096 of 2^21
-    // slots 9.8 us per step with one workgroup behind the gather, 7.8 so, of 16,384 36 and 25.  (Those of many small ones
+    // slots 9.8 us per step with one workgroup behind the gather, 7.7 so, of 16,384 38 and 14.  (Those of many small ones
     // would hold the gather up: 128 x 16 of 2^20 9.3 us, and 9.9 with them ahead.)
     const bool ahead = a.weight_wgs_per_batch > 1;
     a.gather_first = a.draw_wgs + (ahead ? a.weight_wgs : 0);
     a.weight_first = a.draw_wgs + (ahead ? 0 : gather_wgs);
     const dim3 grid(a.draw_wgs + gather_wgs + a.weight_wgs), block(kMultiStepThreads);
-    if (r->tv.n_top > 512)
-      multi_step_kernel<true><<<grid, block, 0, stream>>>(a);
-    else
-      multi_step_kernel<false><<<grid, block, 0, stream>>>(a);
+    const bool wide = r->tv.n_top > 512, merge = samples > kMergePerTopNode * r->tv.n_top;
+    if (wide && merge) multi_step_kernel<true, true><<<grid, block, 0, stream>>>(a);
+    else if (wide) multi_step_kernel<true, false><<<grid, block, 0, stream>>>(a);
+    else if (merge) multi_step_kernel<false, true><<<grid, block, 0, stream>>>(a);
+    else multi_step_kernel<false, false><<<grid, block, 0, stream>>>(a);
   }
   r->second_version = ++r->tree_version;  // every change is in both copies
   APEX_HIP(hipGetLastError());

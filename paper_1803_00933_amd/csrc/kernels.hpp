@@ -2270,8 +2270,13 @@ __global__ __launch_bounds__(kThreads) void learner_step_kernel(StepArgs a)
 // its point in the sample's own stratum, or in the one below or above it, lies in the interval (were the interval to reach
 // further, it would cover the neighbour): three points per later batch, one batch per lane of the sample's row.  In the
 // sample's own batch it is the point above.
-// As two launches per step (sample_kernel with the first pass of the update, update_apply_kernel), 16 x 512 of 2^21
-// slots: 13.6 us, so 8.4; 2 x 128 9.1 and 6.6; one batch of 4096 15.0 and 7.8.
+// As two launches per step (sample_kernel with the first pass of the update, update_apply_kernel) and so, us per step of
+// rows of 32 bytes, calls of eight steps:
+//                 16 x 512       8 x 512       2 x 512       1 x 4096      1 x 16,384     64 x 64       128 x 64
+//   2^14 slots   12.4 ->  8.0   11.1 -> 6.6   10.7 -> 5.8   13.7 -> 6.2   20.7 -> 15.7   11.7 -> 8.0   14.2 -> 11.7
+//   2^19         13.3 -> 11.0   11.9 -> 8.0   12.1 -> 7.0   14.5 -> 7.7   (two launches) 12.8 -> 8.6   15.4 -> 12.9
+//   2^21         13.6 ->  7.7   12.1 -> 6.7   11.4 -> 6.2   15.0 -> 7.7   20.7 -> 14.3   12.9 -> 8.5   15.7 -> 13.0
+//   2^23         15.2 ->  9.4   13.6 -> 8.1   12.0 -> 7.3   16.5 -> 8.9   23.0 -> 15.5   14.7 -> 10.0  17.4 -> 14.5
 // --------------------------------------------------------------------------------------------
 struct MultiStepArgs {
   // workgroups: first those that draw, per batch of step i+1; those from gather_first and weight_first on gather step i and
@@ -2292,10 +2297,43 @@ struct MultiStepArgs {
   DeviceState *st;
 };
 
+// Adds four changes, one per 16-lane row of the wave (every lane of a row holds its row's), to a copy of the tree.  kMerge:
+// above the leaves neighbouring rows under one node send one atomic.  The four are uniform values then, no lane has to ask
+// another one.  Atomics on one cache line take turns of some 11 ns, so this is worth its 0.2 us only where many meet: see
+// kMergePerTopNode.
+template <bool kMerge>
+__device__ __forceinline__ void add_four(const TreeView &tv, uint32_t slot, uint64_t delta)
+{
+  const uint32_t lane = lane_id(), row = lane / 16;
+  const bool first = (lane & 15) == 0;
+  if constexpr (!kMerge) {
+    if (first) add_delta(tv, slot, delta);
+    return;
+  }
+  uint32_t node[4];
+  uint64_t d[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) node[r] = read_lane_u32(slot, 16 * r), d[r] = read_lane_u64(delta, 16 * r);
+  if (first && delta) atomic_add_u64(tv.level[0] + slot, delta);
+  for (uint32_t l = 1; l < tv.nlev; ++l) {
+    const uint32_t shift = fanout_log2(tv, l);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) node[r] >>= shift;
+    const uint64_t s3 = d[3], s2 = d[2] + (node[2] == node[3] ? s3 : 0), s1 = d[1] + (node[1] == node[2] ? s2 : 0),
+                   s0 = d[0] + (node[0] == node[1] ? s1 : 0);
+    const uint32_t at = row == 0 ? node[0] : row == 1 ? node[1] : row == 2 ? node[2] : node[3];
+    const uint64_t sum = row == 0 ? s0
+                         : row == 1 ? (node[1] != node[0] ? s1 : 0)
+                         : row == 2 ? (node[2] != node[1] ? s2 : 0)
+                                    : (node[3] != node[2] ? s3 : 0);
+    if (first && sum) atomic_add_u64(tv.level[l] + at, sum);
+  }
+}
+
 constexpr int kMultiStepThreads = 256;
 constexpr uint32_t kMultiStepRows = kMultiStepThreads / 16;  // samples per workgroup
 
-template <bool kWide>
+template <bool kWide, bool kMerge>
 __global__ __launch_bounds__(kMultiStepThreads) void multi_step_kernel(MultiStepArgs a)
 {
   __shared__ uint64_t red[kMultiStepThreads / kWave];
@@ -2306,12 +2344,11 @@ __global__ __launch_bounds__(kMultiStepThreads) void multi_step_kernel(MultiStep
     return;
   }
   if (blk >= a.gather_first) {
-    const uint32_t o = (blk - a.gather_first) * kMultiStepRows + threadIdx.x / 16;
-    if (o >= a.samples) return;
-    const uint32_t slot = a.slot[o];
-    const uint64_t dq = a.dq[o];
-    if (gl == 0) add_delta(a.wr, slot, dq);
-    gather_by_16(a.g, slot, o);
+    const uint32_t o = (blk - a.gather_first) * kMultiStepRows + threadIdx.x / 16, at = min(o, a.samples - 1);
+    const uint32_t slot = a.slot[at];
+    const uint64_t dq = a.dq[at];
+    add_four<kMerge>(a.wr, slot, o < a.samples ? dq : 0);
+    if (o < a.samples) gather_by_16(a.g, slot, o);
     return;
   }
   const TreeView &rd = a.next.tv;
@@ -2362,7 +2399,7 @@ __global__ __launch_bounds__(kMultiStepThreads) void multi_step_kernel(MultiStep
     a.next.mass[o] = walk.mass;
     a.next_dq[o] = delta;
   }
-  if (in && gl == 0) add_delta(a.wr, (uint32_t)walk.idx, delta);
+  add_four<kMerge>(a.wr, (uint32_t)walk.idx, in ? delta : 0);
   const uint64_t nc = __popcll(__ballot(in && gl == 0 && clamped));
   if (nc && lane == 0) atomic_add_u64(&a.st->n_clamped, nc);
 }

@@ -121,3 +121,11 @@ def test_steps_of_many_batches_are_two_launches_each(tmp_path):
     """What a drawn sample is held against grows with the number of batches: beyond a number of them two launches do less."""
     shapes = [(1 << 21, nb, k, 2, 2) for nb, k in ((128, 64), (160, 32), (161, 32), (256, 64), (512, 16), (1024, 1), (1024, 32))]
     assert [bool(x) for x in multi_launches(tmp_path, shapes)] == [True, True] + [False] * 5
+
+
+def test_steps_that_would_crowd_the_top_level_are_two_launches_each(tmp_path):
+    """Levels of 300,000 slots: 4688 and 74 nodes; of 2^19: 8192 and 128; of 2^21: 32,768 and 512."""
+    shapes = [(slots, nb, k, 2, 2) for slots, nb, k in (
+        (300_000, 8, 512), (300_000, 16, 512), (300_000, 1, 4736), (300_000, 1, 4737), (1 << 19, 16, 512), (1 << 19, 17, 512),
+        (1 << 21, 32, 512), (1 << 21, 1, 32_768), (30, 3, 640), (30, 3, 641))]
+    assert [bool(x) for x in multi_launches(tmp_path, shapes)] == [True, False, True, False, True, False, True, True, True, False]

@@ -1333,11 +1333,12 @@ def test_small_columns_of_a_whole_add(act_bytes, obs_bytes, with_obs):
         assert g.evict()[0] == 0
 
 
-# Shares of the weights (512 samples each) of large batches, and both sides of the number of batches beyond which steps are
-# two launches each.
+# Shares of the weights (512 samples each), steps that add neighbouring changes up before they go to the upper levels and
+# steps that do not, and both sides of the lines beyond which steps are two launches each: batches, samples per top node.
 @pytest.mark.parametrize("P,ob,nb,k,depth", [
-    (3000, 16, 1, 8192, 2), (70_000, 12, 1, 8191, 2), (200_000, 7, 3, 513, 3), (9000, 20, 2, 1025, 2),
-    (5000, 20, 160, 9, 2), (5000, 20, 161, 9, 2),
+    (3000, 16, 1, 8192, 2), (70_000, 12, 1, 8191, 2), (200_000, 7, 3, 513, 3), (9000, 20, 2, 1025, 2),      # shares
+    (20_000, 16, 3, 1001, 2), (300_000, 12, 8, 512, 2), (40_000, 8, 1, 8190, 2),                            # added up
+    (300_000, 12, 16, 512, 2), (5000, 20, 160, 9, 2), (5000, 20, 161, 9, 2),                                # the lines
 ])
 def test_steps_of_large_and_of_many_batches(P, ob, nb, k, depth):
     test_steps_of_several_batches_in_one_launch_each(P, ob, nb, k, depth, 24)
