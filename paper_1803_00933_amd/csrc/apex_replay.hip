@@ -686,8 +686,8 @@ bool sample_by_rows(uint64_t obs_bytes, uint32_t num_batches, uint32_t k)
 {
   const uint64_t samples = (uint64_t)num_batches * k;
   if (obs_bytes < 16 || k > kSampleRowsMaxK || samples > kSampleRowsMax) return false;
-  if (obs_bytes > kGatherInDrawBytes) return true;
-  return obs_bytes >= 2048 ? k <= obs_bytes / 4 : samples <= 384;
+  if (obs_bytes <= kGatherInDrawBytes) return obs_bytes >= 2048 ? k <= obs_bytes / 4 : samples <= 384;
+  return obs_bytes <= (samples <= 512 ? kSampleRowsMaxBytes : kSampleRowsMaxBytesOfMany);
 }
 
 // a.k samples of each of num_batches batches, as sample_by_rows has it.  Two pieces per lane as long as the chip holds all

@@ -1798,6 +1798,14 @@ __global__ __launch_bounds__(kSampleMaxThreads) void sample_kernel(SampleArgs a)
 //           4096 B   6.3 -> 4.9   7.3 -> 5.4   7.4 -> 6.1   8.3 -> 6.9   9.5 -> 8.6    9.4 -> 7.2   10.4 -> 9.3
 //           8192 B   7.9 -> 4.9   8.2 -> 5.5   8.1 -> 6.2   8.4 -> 7.0   9.8    9.9    9.9 -> 8.3   12.6 -> 11.8
 //         28,224 B   8.8 -> 5.1   9.3 -> 5.8   9.5 -> 7.3  11.7 -> 10.1 17.0 -> 15.1  16.9 -> 13.9  26.6    26.4
+//         40,000 B   9.2 -> 5.5  10.1 -> 6.5  12.2 -> 8.5  16.1 -> 11.9 24.3 -> 22.2  24.2 -> 20.8
+//         53,000 B                                                    28.2 -> 28.1  28.1 -> 26.6
+//         65,536 B   9.5 -> 7.5  10.2 -> 8.4  12.7 -> 11.7 18.8 -> 18.0 29.9   32.1  29.9   31.0
+//         98,304 B   9.6 -> 9.2  10.5 -> 10.4 16.3 -> 15.0 24.5 -> 23.9 40.7   43.7  41.0   43.6
+//        131,072 B   9.2   10.8  10.3   12.5  18.7   18.3  29.6   30.4  51.4   57.6  52.0   57.2
+//        400,000 B   9.9   26.7  16.0   31.6  40.9   48.9  73.8   84.5 141.7  164.6 141.9  161.3
+// A workgroup holds 30 KB of a row with two pieces per lane and 60 with four; what is longer takes passes that wait for one
+// another, where two launches give every 32 KB a workgroup.
 // Beyond 1024 samples in a batch one wave is too few for the weights (2048 samples 13 us, 9.2 apart).
 // The tickets of a batch in two steps, a word per kTicketGroup samples and then the batch's own: an atomic that returns to
 // one address takes its turn of some 14 ns (512 samples of 1028 bytes on one word 11.5 us).
@@ -1807,6 +1815,7 @@ constexpr uint32_t kTicketGroup = 32;
 constexpr uint32_t kSampleRowsMaxK = 1024;
 constexpr uint32_t kSampleRowsMax = 1536;   // samples of a call: beyond, long rows are bound by memory either way
 constexpr uint32_t kChipWaves = 8192;       // waves that the chip holds at once
+constexpr uint64_t kSampleRowsMaxBytes = 96 << 10, kSampleRowsMaxBytesOfMany = 52 << 10;  // longest rows: up to 512 samples, beyond
 
 template <int kUnroll, bool kWide>
 __global__ __launch_bounds__(1024) void sample_rows_kernel(SampleArgs a, uint32_t vecs_per_row)

@@ -129,3 +129,28 @@ def test_steps_that_would_crowd_the_top_level_are_two_launches_each(tmp_path):
         (300_000, 8, 512), (300_000, 16, 512), (300_000, 1, 4736), (300_000, 1, 4737), (1 << 19, 16, 512), (1 << 19, 17, 512),
         (1 << 21, 32, 512), (1 << 21, 1, 32_768), (30, 3, 640), (30, 3, 641))]
     assert [bool(x) for x in multi_launches(tmp_path, shapes)] == [True, False, True, False, True, False, True, True, True, False]
+
+
+SAMPLES = """
+out = []
+for obs_bytes, nb, k in %r:
+    r = replay(4096, obs_bytes)
+    assert call("apex_replay_sample", r, nb, k, 0.4, memory(), memory(), memory(), memory(), memory(), memory(), memory(), memory(),
+                None) == 0
+    out.append(launches())
+    assert call("apex_replay_destroy", r) == 0
+result = out
+"""
+
+
+def test_long_rows_are_copied_by_as_many_workgroups_as_they_need(tmp_path):
+    """replay.Sample takes a workgroup per sample for rows of up to 96 KB, of more than 512 samples up to 52 KB; beyond, a
+    launch of its own copies the rows with a workgroup per 32 KB."""
+    shapes = [(ob, nb, k) for ob in (4100, 28_224, 53_000, 65_536, 98_304, 98_305, 112_896, 400_000, 4_000_000)
+              for nb, k in ((1, 1), (1, 32), (1, 512), (1, 513), (3, 300))]
+    for (ob, nb, k), found in zip(shapes, recorded_hip.run(tmp_path, SAMPLES % (shapes,))):
+        by_rows = [x for x in found if "sample_rows_kernel" in x["kernel"]]
+        limit = 96 << 10 if nb * k <= 512 else 52 << 10
+        assert bool(by_rows) == (ob <= limit), (ob, nb, k)
+        if ob > limit:
+            assert [x["grid"] for x in found if "copy_rows" in x["kernel"]] == [nb * k * -(-ob // (32 << 10))]

@@ -1342,3 +1342,15 @@ def test_small_columns_of_a_whole_add(act_bytes, obs_bytes, with_obs):
 ])
 def test_steps_of_large_and_of_many_batches(P, ob, nb, k, depth):
     test_steps_of_several_batches_in_one_launch_each(P, ob, nb, k, depth, 24)
+
+
+# replay.Sample on both sides of the lines beyond which long rows are two launches.
+@pytest.mark.parametrize("ob,nb,k", [
+    (98_304, 1, 40), (98_305, 1, 40), (98_320, 1, 33), (53_248, 1, 513), (53_249, 1, 513),
+])
+def test_samples_of_long_rows_at_the_edges_of_their_rule(ob, nb, k):
+    rng = np.random.default_rng(ob + k)
+    g, o = make_pair(700, 800, ob, 4)
+    assert add_both(g, o, rng, 700) == 0
+    for _ in range(2):
+        sample_both(g, o, rng, nb, k)
