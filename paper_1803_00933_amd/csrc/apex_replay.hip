@@ -680,6 +680,11 @@ void take_tickets(SampleArgs &a, uint32_t lines, TicketUse *tickets)
   a.ticket_lines = tickets->lines;
 }
 
+// Waves of a workgroup of sample_rows_kernel whose lanes hold `pieces` pieces of a row of vpr (a row that it does not hold
+// takes further passes), and how many such workgroups the chip has room for: a workgroup's waves are on one compute unit.
+uint32_t sample_rows_waves(uint32_t vpr, uint32_t pieces) { return std::min(1 + blocks_for(vpr, pieces * kWave), 1024u / kWave); }
+uint32_t sample_rows_at_once(uint32_t waves) { return kChipCus * (kChipWaves / kChipCus / waves); }
+
 // Whether num_batches x k samples with rows of obs_bytes go into sample_rows_kernel rather than sample_kernel (rows of up to
 // kGatherInDrawBytes) or two launches.  (The times on both sides of the lines are at the kernel.)
 bool sample_by_rows(uint64_t obs_bytes, uint32_t num_batches, uint32_t k)
@@ -687,20 +692,23 @@ bool sample_by_rows(uint64_t obs_bytes, uint32_t num_batches, uint32_t k)
   const uint64_t samples = (uint64_t)num_batches * k;
   if (obs_bytes < 16 || k > kSampleRowsMaxK || samples > kSampleRowsMax) return false;
   if (obs_bytes <= kGatherInDrawBytes) return obs_bytes >= 2048 ? k <= obs_bytes / 4 : samples <= 384;
-  return obs_bytes <= (samples <= 512 ? kSampleRowsMaxBytes : kSampleRowsMaxBytesOfMany);
+  if (obs_bytes > (samples <= 512 ? kSampleRowsMaxBytes : kSampleRowsMaxBytesOfMany)) return false;
+  // not where workgroups that copy a row in one pass come in more than one round, their batches' weights in the last one
+  return obs_bytes > kCopyRowBytes || k <= 384 ||
+         samples <= sample_rows_at_once(sample_rows_waves((uint32_t)((obs_bytes + 15) / 16), 4));
 }
 
-// a.k samples of each of num_batches batches, as sample_by_rows has it.  Two pieces per lane as long as the chip holds all
-// waves at once, else four (28,224 bytes: 256 samples 7.3 us with two and 8.2 with four, 999 samples 16.4 and 14.0).
+// a.k samples of each of num_batches batches, as sample_by_rows has it.  Two pieces per lane as long as the chip then holds
+// all workgroups at once, else four (28,224 bytes: 256 samples 7.3 us with two and 8.2 with four, 999 samples 16.4 and 14.0;
+// 896 samples of 16 KB, 9 waves to a workgroup with two, 13.6 and 11.1).
 int launch_sample_rows(SampleArgs &a, uint32_t num_batches, hipStream_t stream, TicketUse *tickets)
 {
   a.k_div = make_fast_div(a.k);
   const uint32_t groups = blocks_for(a.k, kTicketGroup);
   if (a.weight_out) take_tickets(a, num_batches * (groups > 1 ? 1 + groups : 1), tickets);
   const uint32_t vpr = (uint32_t)((a.g.obs_bytes + 15) / 16);
-  const auto waves = [&](uint32_t pieces) { return std::min(1 + blocks_for(vpr, pieces * kWave), 1024u / kWave); };
-  const bool two = (uint64_t)num_batches * a.k * waves(2) <= kChipWaves, wide = a.tv.n_top > 512;
-  const dim3 grid(a.k, num_batches), block(waves(two ? 2 : 4) * kWave);
+  const bool two = num_batches * a.k <= sample_rows_at_once(sample_rows_waves(vpr, 2)), wide = a.tv.n_top > 512;
+  const dim3 grid(a.k, num_batches), block(sample_rows_waves(vpr, two ? 2 : 4) * kWave);
   if (two && wide) sample_rows_kernel<2, true><<<grid, block, 0, stream>>>(a, vpr);
   else if (two) sample_rows_kernel<2, false><<<grid, block, 0, stream>>>(a, vpr);
   else if (wide) sample_rows_kernel<4, true><<<grid, block, 0, stream>>>(a, vpr);

@@ -1805,7 +1805,9 @@ __global__ __launch_bounds__(kSampleMaxThreads) void sample_kernel(SampleArgs a)
 //        131,072 B   9.2   10.8  10.3   12.5  18.7   18.3  29.6   30.4  51.4   57.6  52.0   57.2
 //        400,000 B   9.9   26.7  16.0   31.6  40.9   48.9  73.8   84.5 141.7  164.6 141.9  161.3
 // A workgroup holds 30 KB of a row with two pieces per lane and 60 with four; what is longer takes passes that wait for one
-// another, where two launches give every 32 KB a workgroup.
+// another, where two launches give every 32 KB a workgroup.  Rows of up to 32 KB stay with two launches where the chip does not
+// hold all their workgroups at once, unless the batches are small (28,688 bytes, 768 at once: 1024 samples 17.7 us apart and
+// 19.2, 2 x 700 21.8 and 23.6, 12 x 100 20.1 and 18.7; 20,000 bytes, 1280 at once: 3 x 512 18.0 and 18.9).
 // Beyond 1024 samples in a batch one wave is too few for the weights (2048 samples 13 us, 9.2 apart).
 // The tickets of a batch in two steps, a word per kTicketGroup samples and then the batch's own: an atomic that returns to
 // one address takes its turn of some 14 ns (512 samples of 1028 bytes on one word 11.5 us).
@@ -1814,8 +1816,9 @@ __global__ __launch_bounds__(kSampleMaxThreads) void sample_kernel(SampleArgs a)
 constexpr uint32_t kTicketGroup = 32;
 constexpr uint32_t kSampleRowsMaxK = 1024;
 constexpr uint32_t kSampleRowsMax = 1536;   // samples of a call: beyond, long rows are bound by memory either way
-constexpr uint32_t kChipWaves = 8192;       // waves that the chip holds at once
+constexpr uint32_t kChipCus = 256, kChipWaves = 8192;  // compute units of the chip, waves that it holds at once
 constexpr uint64_t kSampleRowsMaxBytes = 96 << 10, kSampleRowsMaxBytesOfMany = 52 << 10;  // longest rows: up to 512 samples, beyond
+constexpr uint64_t kCopyRowBytes = 32 << 10;  // what a workgroup of copy_rows_long_kernel moves
 
 template <int kUnroll, bool kWide>
 __global__ __launch_bounds__(1024) void sample_rows_kernel(SampleArgs a, uint32_t vecs_per_row)

@@ -154,3 +154,19 @@ def test_long_rows_are_copied_by_as_many_workgroups_as_they_need(tmp_path):
         assert bool(by_rows) == (ob <= limit), (ob, nb, k)
         if ob > limit:
             assert [x["grid"] for x in found if "copy_rows" in x["kernel"]] == [nb * k * -(-ob // (32 << 10))]
+
+
+def test_samples_by_rows_fill_the_chip_once(tmp_path):
+    """Two pieces per lane only where all workgroups find room at once (32 waves on each of 256 compute units, a workgroup's
+    waves on one of them), and rows of one pass in several rounds only for small batches."""
+    shapes = [(ob, nb, k) for ob in (5003, 8192, 16_384, 20_000, 24_000, 28_224, 28_688, 30_720, 32_768)
+              for nb, k in ((1, 256), (1, 512), (1, 640), (1, 768), (1, 896), (1, 1024), (2, 600), (3, 512), (12, 100))]
+    at_once = lambda waves: 256 * (32 // waves)
+    for (ob, nb, k), found in zip(shapes, recorded_hip.run(tmp_path, SAMPLES % (shapes,))):
+        pieces = -(-ob // 16)
+        waves = {n: min(16, 1 + -(-pieces // (64 * n))) for n in (2, 4)}
+        by_rows = [x for x in found if "sample_rows_kernel" in x["kernel"]]
+        assert bool(by_rows) == (nb * k <= at_once(waves[4]) or k <= 384), (ob, nb, k)
+        for x in by_rows:
+            n = 2 if nb * k <= at_once(waves[2]) else 4
+            assert "sample_rows_kernelILi%d" % n in x["kernel"] and x["block"] == 64 * waves[n], (ob, nb, k)

@@ -1344,9 +1344,12 @@ def test_steps_of_large_and_of_many_batches(P, ob, nb, k, depth):
     test_steps_of_several_batches_in_one_launch_each(P, ob, nb, k, depth, 24)
 
 
-# replay.Sample on both sides of the lines beyond which long rows are two launches.
+# replay.Sample on both sides of the lines beyond which long rows, and large batches of rows that do not all find room on the
+# chip at once, are two launches; two and four pieces per lane on both sides of a full chip.
 @pytest.mark.parametrize("ob,nb,k", [
-    (98_304, 1, 40), (98_305, 1, 40), (98_320, 1, 33), (53_248, 1, 513), (53_249, 1, 513),
+    (98_304, 1, 40), (98_305, 1, 40), (98_320, 1, 33), (53_248, 1, 513), (53_249, 1, 513), (32_768, 1, 769), (32_769, 1, 769),
+    (28_688, 1, 768), (28_688, 1, 769), (28_688, 3, 384), (28_688, 2, 385), (16_384, 1, 768), (16_384, 1, 769), (20_000, 1, 512),
+    (20_001, 1, 513),
 ])
 def test_samples_of_long_rows_at_the_edges_of_their_rule(ob, nb, k):
     rng = np.random.default_rng(ob + k)
