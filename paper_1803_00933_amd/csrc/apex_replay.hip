@@ -1190,7 +1190,8 @@ int apex_replay_sample(apex_replay_t *r, uint32_t num_batches, uint32_t k, float
                        float *ret_out, float *gacc_out, void *hip_stream)
 {
   if (!r || !(beta >= 0.0f) || !(beta <= 1.0f)) return APEX_ERR_INVALID_ARG;
-  const bool apart = obs_out && num_batches == 1 && k > kGatherApartAboveK && r->cfg.obs_bytes <= kGatherApartBytes;
+  const bool apart = obs_out && weight_out && num_batches == 1 && k > kGatherApartAboveK && k <= kWeightsInDrawMaxK &&
+                     r->cfg.obs_bytes <= kGatherApartBytes;
   if (!obs_out || (gather_in_draw(r) && !apart) || sample_by_rows(r->cfg.obs_bytes, num_batches, k))
     return sample_in_one(r, num_batches, k, beta, rnd, key_out, slot_out, r->mass(), weight_out, obs_out, act_out, ret_out,
                          gacc_out, /*claim=*/false, static_cast<hipStream_t>(hip_stream));

@@ -1668,14 +1668,17 @@ constexpr uint32_t kGatherInDrawBytes = 4096;
 // took that launch 21.6 us instead of 8.2 without, where a launch of its own takes 5).
 constexpr uint32_t kWeightsInDrawMaxK = 4096;
 
-// One batch of more samples than this of rows up to this length is gathered by a launch of its own after all, which writes the
-// weights as well: with the draw, the last workgroup's weights are the tail of the launch (us with / apart):
-//    rows of   32 B   2048  8.5 /  7.6   3000  9.2 / 8.1   4096  9.9 /  8.5
-//             268 B         9.0 /  8.4         9.7 / 9.5        10.8 / 10.2
-//            1024 B         9.1 /  8.4        10.1 / 9.8        11.1 / 11.1
-//            2048 B        10.1 / 10.3        11.3 / 11.4       12.4 / 13.0
-// (up to 2048 samples the update that follows is one launch, and the host would be slower than the device with one more).
-constexpr uint32_t kGatherApartAboveK = 2048;
+// One batch of more samples than kGatherApartAboveK of rows up to kGatherApartBytes is gathered by a launch of its own after all,
+// which writes the weights as well: with the draw, the last workgroup's weights are the tail of the launch.  (Above
+// kWeightsInDrawMaxK they have a launch of their own either way.)  us per call, host included, with / apart, from 2^18 slots:
+//                    2049          2560          3300          4096          8192         32,768
+//    rows of   32 B   8.6 /  8.7    8.9 /  8.8    9.4 /  9.0   10.0 /  9.1   11.2 / 11.3  24.3 / 24.1
+//             268 B   8.7 /  8.9    9.0 /  8.9    9.5 /  9.2   10.2 /  9.4   11.6 / 11.9  25.7 / 28.2
+//            1024 B   9.1 /  9.3    9.4 /  9.5   10.0 /  9.9   10.7 / 10.3   12.6 / 14.2  32.9 / 34.4
+// with the update behind it (one launch up to kUpdateOneLaunchMax pairs)
+//              32 B  14.8 / 14.9   15.1 / 15.0   15.5 / 15.4   16.2 / 15.5
+//            1024 B  15.1 / 15.4   15.6 / 15.7   16.2 / 16.2   16.9 / 16.7
+constexpr uint32_t kGatherApartAboveK = 2560;
 constexpr uint64_t kGatherApartBytes = 1024;
 
 // Threads per workgroup.  16 samples (256 threads) spread the draws best over the chip; a batch of at most 32 goes into

@@ -170,3 +170,23 @@ def test_samples_by_rows_fill_the_chip_once(tmp_path):
         for x in by_rows:
             n = 2 if nb * k <= at_once(waves[2]) else 4
             assert "sample_rows_kernelILi%d" % n in x["kernel"] and x["block"] == 64 * waves[n], (ob, nb, k)
+
+
+def test_large_batches_are_gathered_apart_only_where_their_weights_are_the_tail(tmp_path):
+    """One batch of 2561 to 4096 short rows is drawn by one launch, gathered and weighted by another; without weights there is
+    no tail to take away, and those of more samples have a launch of their own behind draw and gather."""
+    shapes = [(ob, k, w) for ob in (32, 1024, 1025) for k in (2049, 2560, 2561, 4096, 4097, 32_768) for w in (True, False)]
+    out = recorded_hip.run(tmp_path, """
+result = []
+for obs_bytes, k, weights in %r:
+    r = replay(50_000, obs_bytes)
+    assert call("apex_replay_sample", r, 1, k, 0.4, memory(), memory(), memory(), memory() if weights else None, memory(),
+                memory(), memory(), memory(), None) == 0
+    result.append([x["kernel"] for x in launches()])
+    assert call("apex_replay_destroy", r) == 0
+""" % shapes)
+    for (ob, k, weights), names in zip(shapes, out):
+        apart = weights and 2560 < k <= 4096 and ob <= 1024
+        assert "sample_kernel" in names[0] and len(names) == (2 if apart or weights and k > 4096 else 1), (ob, k, weights)
+        assert any("finish_short" in n for n in names) == apart
+        assert any("batch_weights" in n for n in names) == (weights and k > 4096)
