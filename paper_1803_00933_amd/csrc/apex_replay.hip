@@ -645,7 +645,7 @@ int apex_replay_add(apex_replay_t *r, uint64_t count, const void *obs, const voi
   if (obs && r->cfg.obs_bytes <= kAddRowsInOneBytes && r->cfg.act_bytes <= kColumnsInAddBytes) {
     const RowPieces rp = row_pieces((uintptr_t)obs | (uintptr_t)r->obs(), r->cfg.obs_bytes);
     const uint32_t vpr = (uint32_t)pieces_per_row(rp, r->cfg.obs_bytes), lanes_log2 = ceil_log2(vpr);
-    const uint32_t threads = std::min(leaves_threads(count), add_rows_threads(count));
+    const uint32_t threads = std::min(leaves_threads(count), add_rows_threads(count, r->cfg.obs_bytes));
     return publish_with(r, count, prio, first_key_out, [&](const AddLeavesArgs &a) {
       with_pieces(rp, [&](auto p) {
         add_rows_kernel<decltype(p)><<<dim3(blocks_for(count, threads)), dim3(threads), 0, static_cast<hipStream_t>(hip_stream)>>>(

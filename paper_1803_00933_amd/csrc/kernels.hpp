@@ -1109,9 +1109,15 @@ __global__ __launch_bounds__(kLeavesThreads) void add_leaves_kernel(AddLeavesArg
 //    3000 rows of 256 B of 2^20 slots  10.0 /  9.1 /  9.6 / 12.2      51,200   14.5 / 12.8 / 12.6 / 14.9
 //    3000 rows of 128 B of 2^24 slots  10.4 /  8.8 /  8.9 / 10.7      51,200   12.3 / 12.0 / 11.1 / 12.1
 //     400 rows of 500 B of 2^20 slots   8.7 /  9.2 /  9.7 /  9.8      18,000   13.6 / 12.2 / 13.1 / 17.6
+// and with 512 / 1024, whole calls, of 2^22 slots:
+//    300,000 rows of 16 B  18.9 / 18.7 / 16.5    64 B  24.2 / 22.9 / 20.3    256 B  43.2 / 33.3 / 37.1
+//    400,000               22.2 / 23.4 / 18.2          29.3 / 28.7 / 22.4           53.6 / 42.1 / 46.7
 constexpr uint32_t kAddRowsInOneBytes = 256;
 
-constexpr uint32_t add_rows_threads(uint64_t count) { return count > 16384 ? 512 : 256; }
+constexpr uint32_t add_rows_threads(uint64_t count, uint64_t obs_bytes)
+{
+  return count > 16384 ? (count > 200000 && obs_bytes <= 64 ? 1024 : 512) : 256;
+}
 
 template <typename P>
 __global__ __launch_bounds__(kLeavesThreads) void add_rows_kernel(AddLeavesArgs a, AddColumns c, const uint8_t *__restrict__ obs,

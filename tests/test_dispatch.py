@@ -190,3 +190,19 @@ for obs_bytes, k, weights in %r:
         assert "sample_kernel" in names[0] and len(names) == (2 if apart or weights and k > 4096 else 1), (ob, k, weights)
         assert any("finish_short" in n for n in names) == apart
         assert any("batch_weights" in n for n in names) == (weights and k > 4096)
+
+
+def test_large_adds_of_the_shortest_rows_take_large_workgroups(tmp_path):
+    """Adds of short rows in one launch: small workgroups for the rows' sake, large ones where the atomics of many
+    transitions on the upper levels outweigh short rows."""
+    shapes = [(16, 300), (16, 16_384), (16, 16_385), (16, 200_000), (16, 200_001), (64, 200_001), (65, 200_001), (256, 400_000)]
+    out = recorded_hip.run(tmp_path, """
+result = []
+for obs_bytes, count in %r:
+    r = replay(1 << 20, obs_bytes, filled=100)
+    assert call("apex_replay_add", r, count, *[memory() for _ in range(5)], None, None) == 0
+    result.append([[x["kernel"], x["grid"], x["block"]] for x in launches()])
+""" % shapes)
+    for (ob, count), found, threads in zip(shapes, out, (256, 256, 512, 512, 1024, 1024, 512, 512)):
+        (kernel, grid, block), = found
+        assert "add_rows_kernel" in kernel and (grid, block) == (-(-count // threads), threads), (ob, count)

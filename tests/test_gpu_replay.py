@@ -1357,3 +1357,24 @@ def test_samples_of_long_rows_at_the_edges_of_their_rule(ob, nb, k):
     assert add_both(g, o, rng, 700) == 0
     for _ in range(2):
         sample_both(g, o, rng, nb, k)
+
+
+@pytest.mark.parametrize("obs_bytes", [16, 7])
+def test_the_largest_adds_of_short_rows(obs_bytes):
+    """Adds of so many short rows that they go in the largest workgroups, over the end of the ring."""
+    rng = np.random.default_rng(obs_bytes)
+    P = 450_000
+    g, o = make_pair(1000, P, obs_bytes, 4)
+    for cnt in (200_000, 200_001, 300_333):
+        obs, act = (rng.integers(0, 256, (cnt, n), dtype=np.uint8) for n in (obs_bytes, 4))
+        ret, gacc, prio = rng.standard_normal(cnt).astype(F32), rng.random(cnt).astype(F32), rng.lognormal(0, 1, cnt).astype(F32)
+        rc, first = g.add(dev(prio), dev(obs), dev(act), dev(ret), dev(gacc))
+        assert (rc, first) == o.add(prio, obs, act, ret, gacc) and rc == 0
+        rows = (first + np.arange(cnt)) % P
+        torch.cuda.synchronize()
+        assert np.array_equal(host(g.obs_view()).reshape(P, obs_bytes)[rows], obs)
+        assert np.array_equal(host(g.act_view()).reshape(P, 4)[rows], act)
+        assert np.array_equal(host(g.ret_view())[rows], ret) and np.array_equal(host(g.gacc_view())[rows], gacc)
+        check_gpu_tree(g, o)
+        assert g.evict() == o.evict()
+    check_gpu_tree(g, o)
