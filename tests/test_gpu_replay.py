@@ -159,8 +159,8 @@ def test_sample_with_a_workgroup_per_sample(P, ob, ab, nb, k):
 @pytest.mark.parametrize("P", [1025, 4608, 70_000, 294_912])
 @pytest.mark.parametrize("m", [512, 513, 1024])
 def test_updates_on_trees_with_a_summit(P, m):
-    """Batches on both sides of the line above which what they add to the summit is collected on the way: random keys,
-    the keys of a batch, one key again and again, stale ones; given priorities and those of the learner's Q-values."""
+    """Batches of half to the whole of a workgroup on trees with a summit and without one: random keys, the keys of a batch,
+    one key again and again, stale ones; given priorities and those of the learner's Q-values."""
     rng = np.random.default_rng(P + m)
     g, o = make_pair(P - 200, P, 16, 4)
     assert add_both(g, o, rng, P - 200) == 0 and add_both(g, o, rng, 150) == 0
@@ -1378,3 +1378,69 @@ def test_the_largest_adds_of_short_rows(obs_bytes):
         check_gpu_tree(g, o)
         assert g.evict() == o.evict()
     check_gpu_tree(g, o)
+
+
+# Steps of several batches of short rows, and of one large one, take one launch each, which leaves both copies of the tree
+# behind: add rounds in between, as one launch or from the copy stream, have to keep them alike.
+SEVERAL_BATCH_SHAPES = [(3, 100, 64), (1, 1100, 256), (20, 33, 7)]
+
+
+@pytest.mark.parametrize("depth", [3, 2])
+@pytest.mark.parametrize("nb,k,ob", SEVERAL_BATCH_SHAPES)
+def test_steps_of_several_batches_beside_add_rounds(nb, k, ob, depth):
+    test_pipeline_matches_the_plain_call_order(nb, k, ob, depth)
+
+
+@pytest.mark.parametrize("nb,k,ob", SEVERAL_BATCH_SHAPES)
+def test_steps_of_several_batches_beside_add_rounds_replayed(nb, k, ob):
+    test_pipeline_graph_replays(nb, k, ob)
+
+
+@pytest.mark.parametrize("nb,k", [(3, 100), (1, 1100)])
+def test_steps_of_several_batches_beside_small_and_large_add_rounds(nb, k):
+    """Rounds below and above 4 MB of observations, the latter from the copy stream, with steps of several batches in
+    between that read what the rounds have left in either copy of the tree."""
+    from paper_1803_00933_amd import apex, synth
+    small = synth.WORKLOADS["tiny"].scaled(obs_bytes=4096, capacity=9000, max_slots=12288, streams=4, chunk=25, k=k)
+    large = small.scaled(streams=44)              # 1100 rows of 4096 B
+    rng = np.random.default_rng(k)
+    g, o = make_pair(small.capacity, small.max_slots, small.obs_bytes, small.act_bytes)
+    add_both(g, o, rng, 8000)
+    depth = 4
+    pipe = apex.Pipeline(g, depth, nb, k)
+    assert pipe.fork() == 0
+    for i, w in enumerate([small, large, large, small, large, small]):
+        d = synth.actor_round(w, i)
+        n_rows = w.streams * w.chunk
+        d["obs"] = rng.integers(0, 256, (n_rows, w.obs_bytes), dtype=np.uint8)
+        dd = {k2: dev(v) for k2, v in d.items()}
+        scratch = [torch.empty(n_rows, dtype=torch.float32, device="cuda:0") for _ in range(3)]
+        rnd = rng.integers(0, U64, (4, nb * k), dtype=np.uint64)
+        newp = rng.lognormal(0, 1, (4, nb * k)).astype(F32)
+        d_rnd, d_newp = dev(rnd), dev(newp)
+        torch.cuda.synchronize()
+        assert pipe.add_begin(dd["q_online"], dd["q_target"], dd["action"], dd["reward"], dd["discount"], w.n,
+                              dd["obs"], dd["act"], *scratch) == 0
+        rc, first = pipe.steps(3, 0.4, d_rnd, d_newp)
+        assert rc == 0
+        rc, first_key, ev = pipe.add_end(i % 2 == 0)
+        assert pipe.steps(1, 0.4, d_rnd[3], d_newp[3])[0] == 0
+        refs = []
+        for s in range(4):
+            if s == 3:
+                ref = oracle.nstep_priorities(d["q_online"], d["q_target"], d["action"], d["reward"], d["discount"],
+                                              w.n, w.alpha, w.eps, w.frac_bits, w.max_slots)
+                rco, fo = o.add(ref[0].reshape(-1), d["obs"], d["act"], ref[1].reshape(-1), ref[2].reshape(-1))
+                assert (rc, first_key) == (rco, fo)
+                if i % 2 == 0:
+                    assert o.evict() == (0, ev)
+            refs.append(o.sample(nb, k, 0.4, rnd[s])[1])
+            o.update_priorities(refs[-1]["key"], newp[s])
+        assert pipe.join() == 0
+        torch.cuda.synchronize()
+        for s in range(4):
+            assert_sample_equal(pipe.sets[(first + s) % depth], refs[s])
+        check_gpu_tree(g, o)
+        assert pipe.fork() == 0
+    assert pipe.join() == 0
+    pipe.close()
