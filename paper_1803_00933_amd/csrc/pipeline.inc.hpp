@@ -128,6 +128,18 @@ int use_stream(apex_pipeline *p, int i)
   return rc;
 }
 
+// Whether the event is complete.  Asked in the relaxed capture mode: in the global one, a capture that any thread of the
+// program has open forbids the question, and one of this thread's own is lost by it.
+bool event_complete(hipEvent_t e)
+{
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  const bool exchanged = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+  const bool complete = exchanged && hipEventQuery(e) == hipSuccess;
+  if (exchanged) (void)hipThreadExchangeStreamCaptureMode(&mode);
+  if (!complete) (void)hipGetLastError();  // not an error: nothing to report later
+  return complete;
+}
+
 // Makes the event of the next fork free: that of kForks forks ago, which a copy stream that has not been used since may
 // still have to wait for.  It does so now, unless the event is long complete, as it mostly is.
 int free_fork_event(apex_pipeline *p)
@@ -138,8 +150,7 @@ int free_fork_event(apex_pipeline *p)
   for (int i = 1; i < apex_pipeline::kStreams; ++i) {
     if (!p->streams(i) || p->forks_seen[i] > oldest) continue;
     if (!asked) {
-      complete = hipEventQuery(p->fork_ev[oldest % apex_pipeline::kForks]) == hipSuccess;
-      if (!complete) (void)hipGetLastError();  // not an error: nothing to report later
+      complete = event_complete(p->fork_ev[oldest % apex_pipeline::kForks]);
       asked = true;
     }
     if (complete) p->forks_seen[i] = oldest + 1;

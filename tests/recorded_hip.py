@@ -47,7 +47,9 @@ int hipStreamCreateWithFlags(P *s, unsigned f) { *s = (P)(next_handle += 16); li
 int hipEventCreateWithFlags(P *e, unsigned f) { *e = (P)(next_handle += 16); return 0; }
 int hipEventRecord(P e, P s) { line("record %lu %lu\n", (unsigned long)e, (unsigned long)s); return 0; }
 int hipStreamWaitEvent(P s, P e, unsigned f) { line("wait %lu %lu\n", (unsigned long)s, (unsigned long)e); return 0; }
-int hipEventQuery(P e) { return complete ? 0 : 600; }
+int capture_mode = 0;  /* the thread's: global, as every thread begins */
+int hipThreadExchangeStreamCaptureMode(int *m) { int had = capture_mode; capture_mode = *m; *m = had; return 0; }
+int hipEventQuery(P e) { line("query %lu %d\n", (unsigned long)e, capture_mode); return complete ? 0 : 600; }
 int hipStreamIsCapturing(P s, int *status) { *status = capturing; return 0; }
 int hipHostMalloc(P *p, size_t n, unsigned f) { *p = calloc(1, n); return 0; }
 int hipHostFree(P p) { free(p); return 0; }

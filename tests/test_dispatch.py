@@ -64,6 +64,20 @@ result = [c for c in take() if c[0] == "wait" and c[1] == add]
         assert len(out) <= (0 if complete else 50)
 
 
+def test_forks_ask_for_events_in_a_way_that_no_capture_forbids(tmp_path):
+    """While any thread of the program captures in the global mode, asking whether an event is complete is refused to every
+    other thread, and to the capturing one at the price of its capture, unless the asking thread is in the relaxed mode (2)."""
+    queries, mode = recorded_hip.run(tmp_path, """
+r = replay(4000, 64)
+p, (tree, add) = pipeline(r, 3, 1, 64)
+for i in range(50):
+    C.c_int.in_dll(hip, "complete").value = i & 1
+    assert call("apex_pipeline_fork", p, 0x1000) == 0
+result = [[c for c in take() if c[0] == "query"], C.c_int.in_dll(hip, "capture_mode").value]
+""")
+    assert all(c[2] == 2 for c in queries) and mode == 0, (queries, mode)
+
+
 def test_a_fork_in_the_callers_own_capture_takes_the_copy_streams_along(tmp_path):
     """All streams of the pipeline enter a capture of the caller's and are joined back, and what is waited for after it
     has nothing of it."""
