@@ -1061,7 +1061,13 @@ int fused_steps(apex_replay *r, uint32_t n, uint32_t k, float beta, const uint64
 // us per step, so 7.2; 16 x 512 on 512 nodes 8.4 and 7.7; 2 x 512 on 512 6.2, and 6.6 with it.
 constexpr uint32_t kMultiStepMaxBatches = 160, kMultiStepMaxPerTopNode = 64, kMergePerTopNode = 8;
 
-// The second copy of the tree may have to be brought up to date first, at some 5 TB/s; a step gains 7 us.
+// The second copy of the tree may have to be brought up to date first, at some 5 TB/s.  A call that finds it behind does so
+// where its steps win that back.  n steps, join, update_priorities of 64, fork, two launches per step / refresh and one launch,
+// us (2 x 512): 2^20 slots n = 1 46 / 51; 2^21 n = 4 75 / 65; 2^22 n = 4 76 / 70; 2^23 n = 8 134 / 110; 2^24 n = 8 134 / 134.
+// By ratios the line stands where calls of four steps (2^22 - 2^23) and of eight (2^24) break even.  Calls of one or two
+// steps that alternate with plain updates break even at 2^18 and 2^21 already and lose up to 10 % between there and the line
+// (2^21, 2^22): they are let through because declining would last.  Two launches per step leave the copy behind, so a learner
+// that makes one plain update and then single steps only would never come back; let through, it refreshes the copy once.
 constexpr uint64_t kTreeWordsPerStep = 2u << 20;
 
 bool multi_steps_fit(const apex_replay *r, uint32_t n, uint32_t num_batches, uint32_t k, uint32_t depth)
