@@ -8,6 +8,7 @@
 #include <algorithm>
 #include <mutex>
 #include <new>
+#include <type_traits>
 #include <vector>
 
 #include "kernels.hpp"
@@ -79,6 +80,7 @@ FastDiv make_fast_div(uint32_t d)
 uint64_t qmax_for(uint64_t max_slots) { return max_slots ? 1ull << (62 - ceil_log2(max_slots)) : 1ull << 62; }
 
 constexpr uint64_t kTicketBytes = (uint64_t)APEX_MAX_BATCHES_PER_CALL * kTicketStride * 4;
+constexpr uint64_t kBoardSetWords = board_place(kBoardWordsMax), kBoardBytes = 4 * kTicketSets * kBoardSetWords;
 constexpr uint32_t kStepSets = 64;  // buffer sets a sequence of fused steps can cycle through
 
 struct Geometry {
@@ -87,8 +89,8 @@ struct Geometry {
   uint32_t exported_nlev;   // ... of which apex_replay_layout shows these (a summit is not shown)
   uint32_t top_log2;        // fan-out of the last level over the one below it
   uint64_t level_off[kMaxLevels], level_size[kMaxLevels], tree_words;
-  // scratch: DeviceState | tickets of sample calls | mass | claim | new masses of the batches of fused steps
-  uint64_t state_off, ticket_off, mass_off, claim_off, stepq_off, scratch_bytes;
+  // scratch: DeviceState | tickets of sample calls | mass | claim | new masses of the batches of fused steps | board of sample calls
+  uint64_t state_off, ticket_off, mass_off, claim_off, stepq_off, board_off, scratch_bytes;
 };
 
 int validate(const apex_replay_config_t *c)
@@ -137,13 +139,15 @@ int geometry(const apex_replay_config_t *c, Geometry *g)
   g->mass_off = g->ticket_off + kTicketBytes;
   g->claim_off = g->mass_off + (uint64_t)APEX_MAX_SAMPLES_PER_CALL * 8;
   g->stepq_off = g->claim_off + round_up(P * 4, 256);
-  g->scratch_bytes = g->stepq_off + (uint64_t)kStepSets * kStepMaxK * 8;
+  g->board_off = g->stepq_off + (uint64_t)kStepSets * kStepMaxK * 8;
+  g->scratch_bytes = g->board_off + kBoardBytes;
   return APEX_OK;
 }
 
-// The sample launches on one memory that have taken tickets (see sample_kernel), and the most words one of them used.
+// The sample launches on one memory that have used tickets or a board (see sample_kernel, sample_rows_kernel), and the most
+// words one of them used.
 struct TicketUse {
-  uint32_t launches = 0, lines = 0;
+  uint32_t launches = 0, lines = 0, board_words = 0;
 };
 
 }  // namespace
@@ -177,6 +181,7 @@ struct apex_replay {
   uint32_t *tickets() const { return reinterpret_cast<uint32_t *>(scratch + geo.ticket_off); }
   uint64_t *mass() const { return reinterpret_cast<uint64_t *>(scratch + geo.mass_off); }
   uint32_t *claim() const { return reinterpret_cast<uint32_t *>(scratch + geo.claim_off); }
+  uint32_t *board() const { return reinterpret_cast<uint32_t *>(scratch + geo.board_off); }
   uint64_t *stepq(uint32_t set) const { return reinterpret_cast<uint64_t *>(scratch + geo.stepq_off) + (uint64_t)set * kStepMaxK; }
   uint8_t *obs() const { return storage + geo.obs_off; }
   uint8_t *act() const { return storage + geo.act_off; }
@@ -670,14 +675,18 @@ int launch_weights(const WeightArgs &wa, uint32_t num_batches, hipStream_t strea
   return hip_failed(hipGetLastError()) ? APEX_ERR_HIP : APEX_OK;
 }
 
-// Gives a launch that takes tickets its set of words.
-void take_tickets(SampleArgs &a, uint32_t lines, TicketUse *tickets)
+// Gives a launch that takes tickets, or uses a board (a.board then names its region), its set of words.
+void take_tickets(SampleArgs &a, uint32_t lines, uint32_t board_words, TicketUse *tickets)
 {
-  const uint32_t set = tickets->launches++ & (kTicketSets - 1);
-  a.ticket_ahead = a.ticket + ((set + 2) & (kTicketSets - 1));
-  a.ticket += set;
+  const uint32_t set = tickets->launches++ & (kTicketSets - 1), ahead = (set + 2) & (kTicketSets - 1);
   tickets->lines = std::max(tickets->lines, lines);
+  tickets->board_words = std::max(tickets->board_words, board_words);
+  a.ticket_ahead = a.ticket + ahead;
+  a.ticket += set;
   a.ticket_lines = tickets->lines;
+  a.board_ahead = a.board + ahead * kBoardSetWords;
+  a.board = board_words ? a.board + set * kBoardSetWords : nullptr;
+  a.board_words = tickets->board_words;
 }
 
 // Waves of a workgroup of sample_rows_kernel whose lanes hold `pieces` pieces of a row of vpr (a row that it does not hold
@@ -685,13 +694,27 @@ void take_tickets(SampleArgs &a, uint32_t lines, TicketUse *tickets)
 uint32_t sample_rows_waves(uint32_t vpr, uint32_t pieces) { return std::min(1 + blocks_for(vpr, pieces * kWave), 1024u / kWave); }
 uint32_t sample_rows_at_once(uint32_t waves) { return kChipCus * (kChipWaves / kChipCus / waves); }
 
+// Whether such a launch finds its batches' smallest masses by the board.
+bool sample_uses_board(uint32_t num_batches, uint32_t k) { return num_batches * k <= kBoardSamplesMax || k <= kBoardSmallK; }
+
 // Whether num_batches x k samples with rows of obs_bytes go into sample_rows_kernel rather than sample_kernel (rows of up to
-// kGatherInDrawBytes) or two launches.  (The times on both sides of the lines are at the kernel.)
+// kGatherInDrawBytes) or two launches.  (The times on both sides of the lines of long rows are at the kernel.)  Short rows, us,
+// sample_kernel / sample_rows_kernel:
+//                1 x 512     1 x 700     1 x 1024    2 x 512     12 x 100    40 x 32     3 x 500
+//     32 bytes   6.1 / 5.2   6.3 / 6.0   6.7 / 6.9   6.1 / 5.9   6.2 / 6.4   6.2 / 5.6   6.2 / 8.3
+//    268         6.1 / 5.2   6.4 / 6.0   7.1 / 7.0   6.6 / 6.0   7.0 / 6.4   7.0 / 5.6   7.1 / 8.8
+//   1024         6.6 / 5.3   7.1 / 6.2   7.7 / 7.6   7.3 / 6.7   7.3 / 6.6   7.3 / 6.0   7.4 / 9.1
+//   2048         6.5 / 5.3   7.7 / 6.1   8.1 / 7.1   6.8 / 6.0   6.6 / 6.5   6.1 / 5.8   (by tickets 7.6)
+//   4096         6.5 / 5.4   7.6 / 6.3   8.7 / 7.6   7.2 / 6.3   7.4 / 6.7   7.1 / 6.5   (by tickets 8.9)
 bool sample_by_rows(uint64_t obs_bytes, uint32_t num_batches, uint32_t k)
 {
   const uint64_t samples = (uint64_t)num_batches * k;
   if (obs_bytes < 16 || k > kSampleRowsMaxK || samples > kSampleRowsMax) return false;
-  if (obs_bytes <= kGatherInDrawBytes) return obs_bytes >= 2048 ? k <= obs_bytes / 4 : samples <= 384;
+  if (obs_bytes <= kGatherInDrawBytes) {
+    if (obs_bytes < 1024 && k > 768) return false;
+    if (samples <= kBoardSamplesMax) return true;
+    return k <= kBoardSmallK ? obs_bytes >= 256 : obs_bytes >= 2048 && k <= obs_bytes / 4;
+  }
   if (obs_bytes > (samples <= 512 ? kSampleRowsMaxBytes : kSampleRowsMaxBytesOfMany)) return false;
   // not where workgroups that copy a row in one pass come in more than one round, their batches' weights in the last one
   return obs_bytes > kCopyRowBytes || k <= 384 ||
@@ -704,15 +727,28 @@ bool sample_by_rows(uint64_t obs_bytes, uint32_t num_batches, uint32_t k)
 int launch_sample_rows(SampleArgs &a, uint32_t num_batches, hipStream_t stream, TicketUse *tickets)
 {
   a.k_div = make_fast_div(a.k);
-  const uint32_t groups = blocks_for(a.k, kTicketGroup);
-  if (a.weight_out) take_tickets(a, num_batches * (groups > 1 ? 1 + groups : 1), tickets);
+  a.top = a.tv.level[a.tv.nlev - 1];
+  uint32_t weight_waves = 0;
+  if (a.weight_out) {
+    const uint32_t groups = blocks_for(a.k, kTicketGroup);
+    if (sample_uses_board(num_batches, a.k)) take_tickets(a, 0, num_batches * board_stride(a.k), tickets);
+    else take_tickets(a, num_batches * (groups > 1 ? 1 + groups : 1), 0, tickets);
+    weight_waves = std::min(kWeightWaves, 1 + a.k / kWave);
+  } else {
+    a.board = nullptr;
+  }
   const uint32_t vpr = (uint32_t)((a.g.obs_bytes + 15) / 16);
   const bool two = num_batches * a.k <= sample_rows_at_once(sample_rows_waves(vpr, 2)), wide = a.tv.n_top > 512;
-  const dim3 grid(a.k, num_batches), block(sample_rows_waves(vpr, two ? 2 : 4) * kWave);
-  if (two && wide) sample_rows_kernel<2, true><<<grid, block, 0, stream>>>(a, vpr);
-  else if (two) sample_rows_kernel<2, false><<<grid, block, 0, stream>>>(a, vpr);
-  else if (wide) sample_rows_kernel<4, true><<<grid, block, 0, stream>>>(a, vpr);
-  else sample_rows_kernel<4, false><<<grid, block, 0, stream>>>(a, vpr);
+  const dim3 grid(a.k, num_batches), block(std::max(weight_waves, sample_rows_waves(vpr, two ? 2 : 4)) * kWave);
+  const auto launch = [&](auto unroll, auto streaming) {
+    if (wide) sample_rows_kernel<unroll.value, true, streaming.value><<<grid, block, 0, stream>>>(a, vpr);
+    else sample_rows_kernel<unroll.value, false, streaming.value><<<grid, block, 0, stream>>>(a, vpr);
+  };
+  typedef std::integral_constant<int, 2> Two;
+  typedef std::integral_constant<int, 4> Four;
+  if (a.g.obs_bytes < kStreamingBytes) launch(Two{}, std::false_type{});
+  else if (two) launch(Two{}, std::true_type{});
+  else launch(Four{}, std::true_type{});
   return hip_failed(hipGetLastError()) ? APEX_ERR_HIP : APEX_OK;
 }
 
@@ -720,8 +756,9 @@ int launch_sample_rows(SampleArgs &a, uint32_t num_batches, hipStream_t stream, 
 int launch_sample(SampleArgs &a, uint32_t num_batches, hipStream_t stream, TicketUse *tickets = nullptr)
 {
   a.k_div = make_fast_div(a.k);
+  a.top = a.tv.level[a.tv.nlev - 1];
   const uint32_t threads = sample_threads(a.k, a.weight_out != nullptr), wgs = blocks_for(a.k, threads / 16);
-  if (a.weight_out && wgs > 1) take_tickets(a, num_batches, tickets);
+  if (a.weight_out && wgs > 1) take_tickets(a, num_batches, 0, tickets);
   const dim3 grid(wgs, num_batches), block(threads);
   if (a.tv.n_top > 512)
     sample_kernel<true><<<grid, block, 0, stream>>>(a);
@@ -793,6 +830,7 @@ int sample_in_one(apex_replay *r, uint32_t num_batches, uint32_t k, float beta, 
   a.weight_out = k <= kWeightsInDrawMaxK ? weight_out : nullptr;
   a.beta = beta;
   a.ticket = r->tickets();
+  a.board = r->board();
   a.claim = claim ? r->claim() : nullptr;
   const int rl = !claim && obs_out && sample_by_rows(a.g.obs_bytes, num_batches, k)
                      ? launch_sample_rows(a, num_batches, stream, &r->ticket_use)

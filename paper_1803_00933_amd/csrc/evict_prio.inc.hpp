@@ -426,7 +426,7 @@ struct PeGeometry {
   uint64_t obs_off, act_off, ret_off, gacc_off, storage_bytes;
   uint32_t nlev, exported_nlev, top_log2;  // as in Geometry
   uint64_t level_off[kMaxLevels], level_size[kMaxLevels], tree_words;  // of one tree; the second follows it
-  uint64_t state_off, ticket_off, mass_off, cand_off, sums_off, gen_off, ring_off, claim_off, scratch_bytes;
+  uint64_t state_off, ticket_off, mass_off, cand_off, sums_off, gen_off, ring_off, claim_off, board_off, scratch_bytes;
 };
 
 int pe_validate(const apex_pe_config_t *c)
@@ -472,7 +472,8 @@ int pe_geometry(const apex_pe_config_t *c, PeGeometry *g)
   g->gen_off = g->sums_off + round_up(kPeScanThreads * 4, 256);
   g->ring_off = g->gen_off + round_up(P * 4, 256);
   g->claim_off = g->ring_off + round_up(P * 4, 256);
-  g->scratch_bytes = g->claim_off + round_up(P * 4, 256);
+  g->board_off = g->claim_off + round_up(P * 4, 256);
+  g->scratch_bytes = g->board_off + kBoardBytes;
   return APEX_OK;
 }
 
@@ -502,6 +503,7 @@ struct apex_pe_replay {
   uint32_t *cand() const { return reinterpret_cast<uint32_t *>(scratch + geo.cand_off); }
   uint32_t *sums() const { return reinterpret_cast<uint32_t *>(scratch + geo.sums_off); }
   uint32_t *claim() const { return reinterpret_cast<uint32_t *>(scratch + geo.claim_off); }
+  uint32_t *board() const { return reinterpret_cast<uint32_t *>(scratch + geo.board_off); }
   uint8_t *obs() const { return storage + geo.obs_off; }
   uint8_t *act() const { return storage + geo.act_off; }
   float *ret() const { return reinterpret_cast<float *>(storage + geo.ret_off); }
@@ -596,6 +598,7 @@ SampleArgs pe_sample_args(apex_pe_replay *r, uint32_t k, const uint64_t *rnd, ui
   a.g.obs = r->obs();
   a.g.obs_bytes = r->cfg.obs_bytes;
   a.ticket = r->tickets();
+  a.board = r->board();
   return a;
 }
 

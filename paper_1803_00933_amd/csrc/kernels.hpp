@@ -22,6 +22,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "apex_replay.h"
 #include "quantise.hpp"
 #include "wave.hpp"
 
@@ -769,9 +770,13 @@ struct WeightArgs {
 
 // fp32 with the library's own power routine (relative error below 1e-6 here): a double-precision pow would cost 70
 // registers per lane.
+__device__ __forceinline__ float batch_weight(float mass_min, float mass, float beta)
+{
+  return pow_fixed_sequence(mass_min / mass, beta);
+}
 __device__ __forceinline__ float batch_weight(uint64_t mass_min, uint64_t mass, float beta)
 {
-  return pow_fixed_sequence((float)mass_min / (float)mass, beta);
+  return batch_weight((float)mass_min, (float)mass, beta);
 }
 
 // part, nparts: the workgroup writes the weights of samples [part * k / nparts ...) of batch b only
@@ -1353,6 +1358,7 @@ struct GatherArgs {
 };
 
 struct SampleArgs : DrawArgs {
+  const uint64_t *top;       // the level that the walks start from (its address at a fixed place of the arguments)
   const uint64_t *k_dev;     // not null: the number of samples is read here, on the device (waves beyond it idle)
   FastDiv k_div;             // division by k (unused with k_dev)
   const uint32_t *gen;       // not null: keys are (generation of the slot << 32) | slot instead of ring keys
@@ -1362,16 +1368,51 @@ struct SampleArgs : DrawArgs {
   uint32_t *ticket;          // with weight_out: words that lie kTicketStride apart, 0 before and after: one per batch ...
   uint32_t *ticket_ahead;    // the words that a launch to come will use, at most this many: cleared by this launch
   uint32_t ticket_lines;
+  uint32_t *board;           // sample_rows_kernel: as `ticket`, a word per sample; null: tickets
+  uint32_t *board_ahead;
+  uint32_t board_words;
   uint32_t *claim;           // not null: the first pass of an update of the drawn keys (update_claim_block) as well
 };
 
 constexpr uint32_t kTicketStride = 16;
 constexpr uint32_t kTicketSets = 4;  // a power of two
 
+// Where word i of the board lies: 64 of every 256 bytes are used, so that the words are spread over more of the memory's
+// channels (64 samples 4.4 -> 4.2 us, 256 5.4 -> 5.2).  A batch's words start at an even one.
+__host__ __device__ constexpr uint32_t board_place(uint32_t i) { return i / 16 * 64 + i % 16; }
+__host__ __device__ constexpr uint32_t board_stride(uint32_t k) { return (k + 1) & ~1u; }
+constexpr uint32_t kBoardWordsMax = 4096;  // of a launch
+
+// The words that launches to come will use are cleared by the n threads that call this.
+__device__ __forceinline__ void clear_ahead(const SampleArgs &a, uint32_t thread, uint32_t n)
+{
+  for (uint32_t i = thread; i < a.ticket_lines; i += n) a.ticket_ahead[i * kTicketStride] = 0;
+  for (uint32_t i = thread; i < a.board_words; i += n) a.board_ahead[board_place(i)] = 0;
+}
+
 // Waits until every load (and store) that this wave has issued is through.
 __device__ __forceinline__ void wait_for_all_loads()
 {
   __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0); the other counters at their maxima (not waited for)
+}
+
+// Keeps wave-uniform values in scalar registers from here on: the compiler would otherwise fetch a kernel argument only
+// where it is first used, behind a wait of its own.  Values named in one call are waited for together.
+template <typename T>
+__device__ __forceinline__ void fetch_now(T p)
+{
+  asm volatile("" ::"s"(p));
+}
+template <typename A, typename B, typename C, typename D>
+__device__ __forceinline__ void fetch_now(A a, B b, C c, D d)
+{
+  asm volatile("" ::"s"(a), "s"(b), "s"(c), "s"(d));
+}
+
+// A barrier for what the workgroup exchanges through LDS: stores to memory that are under way are not waited for.
+__device__ __forceinline__ void lds_barrier()
+{
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
 struct Drawn {
@@ -1396,26 +1437,26 @@ __device__ __forceinline__ uint64_t read_lane_u64(uint64_t v, uint32_t l)
 
 typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
 
-// The top level in the registers of one wave: lane l holds the masses v[0..8) of nodes 8l .. 8l+7 (zero beyond
-// the level), and, of a level of more than 512 nodes, w[0..8) of nodes 512 + 8l .. 512 + 8l+7.  load() only issues
-// the loads (16 bytes wide), scan() waits for them.
+// The top level in the registers of one wave: lane l holds the masses v[0..8) of nodes 8l .. 8l+7, and, of a level of
+// more than 512 nodes, w[0..8) of nodes 512 + 8l .. 512 + 8l+7.  Lanes beyond the level hold its first nodes again, count
+// as empty in the sums and are never found: their prefix sum is the level's.  (No load sits in a branch: what other loads
+// the wave has in flight would be waited for behind it.)  load() only issues the loads (16 bytes wide), scan() waits for
+// them.
 // kMayBeWide: levels of more than 512 nodes are provided for.
 template <bool kMayBeWide>
 struct TopLevel {
   uint64_t v[8], w[8];
   uint64_t before, before_w;  // sum of all nodes before this lane's (before_w: of the whole level if there are none)
   bool wide;                  // the same for all lanes
+  bool in, in_w;              // this lane's nodes v, w belong to the level
 
   static __device__ __forceinline__ void load_8(uint64_t (&r)[8], const uint64_t *top, uint32_t i0, uint32_t n_pad)
   {
+    const uint64_t *const at = top + (i0 < n_pad ? i0 : 0);
 #pragma unroll
-    for (int t = 0; t < 8; ++t) r[t] = 0;
-    if (i0 < n_pad) {
-#pragma unroll
-      for (int t = 0; t < 8; t += 2) {
-        const u64x2 v2 = *reinterpret_cast<const u64x2 *>(top + i0 + t);
-        r[t] = v2.x, r[t + 1] = v2.y;
-      }
+    for (int t = 0; t < 8; t += 2) {
+      const u64x2 v2 = *reinterpret_cast<const u64x2 *>(at + t);
+      r[t] = v2.x, r[t + 1] = v2.y;
     }
   }
 
@@ -1424,6 +1465,7 @@ struct TopLevel {
     const uint32_t i0 = 8 * (uint32_t)lane_id();
     const uint32_t n_pad = (n_top + kFanout - 1) & ~(kFanout - 1);  // the level is zero-padded to this in memory
     wide = kMayBeWide && n_top > 512;
+    in = i0 < n_pad, in_w = 512 + i0 < n_pad;
     load_8(v, top, i0, n_pad);
     if (wide) load_8(w, top, 512 + i0, n_pad);
   }
@@ -1439,12 +1481,12 @@ struct TopLevel {
   // Returns the sum of the whole level.
   __device__ __forceinline__ uint64_t scan()
   {
-    const uint64_t mine = sum_8(v), incl = wave_inclusive_scan(mine);
+    const uint64_t mine = in ? sum_8(v) : 0, incl = wave_inclusive_scan(mine);
     before = incl - mine;
     uint64_t total = read_lane_u64(incl, kWave - 1);
     before_w = total;
     if (wide) {
-      const uint64_t mine_w = sum_8(w), incl_w = wave_inclusive_scan(mine_w);
+      const uint64_t mine_w = in_w ? sum_8(w) : 0, incl_w = wave_inclusive_scan(mine_w);
       before_w = total + incl_w - mine_w;
       total += read_lane_u64(incl_w, kWave - 1);
     }
@@ -1492,7 +1534,7 @@ template <typename Between>
 __device__ __forceinline__ Drawn walk_down(const TreeView &tv, const TopHit &top, Between between)
 {
   const uint32_t lane = lane_id();
-  // the two lowest levels' addresses are at fixed places of the arguments: fetched with them, not on the way down
+  // the lowest levels' addresses are at fixed places of the arguments: fetched with them, not on the way down
   const uint64_t *const low0 = tv.level[0], *const low1 = tv.level[1];
   uint64_t x = top.x, idx = top.idx, mass = top.mass;
   // up to 64 children per step, prefix sum across the wave, first child whose running sum exceeds the remainder
@@ -1794,8 +1836,7 @@ __global__ __launch_bounds__(kSampleMaxThreads) void sample_kernel(SampleArgs a)
   uint32_t *const ticket = a.ticket + (uint64_t)b * kTicketStride;
   if (threadIdx.x == 0) sh_ticket = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   __syncthreads();
-  if (blockIdx.x == 0 && b == 0)
-    for (uint32_t i = threadIdx.x; i < a.ticket_lines; i += nthr) a.ticket_ahead[i * kTicketStride] = 0;
+  if (blockIdx.x == 0 && b == 0) clear_ahead(a, threadIdx.x, nthr);
   if (sh_ticket != gridDim.x - 1) return;
   if (threadIdx.x == 0) *ticket = 0;
   const uint64_t *const bm = a.mass + (uint64_t)b * k;
@@ -1818,106 +1859,82 @@ __global__ __launch_bounds__(kSampleMaxThreads) void sample_kernel(SampleArgs a)
   }
 }
 
-// replay.Sample in one launch with a workgroup per sample: its first wave draws the sample and, in the batch's last
-// workgroup, writes the weights; the others wait for the slot and copy the row, the last of them the small columns.
-// For rows too long for 16 lanes, and for few samples, where it spreads the draws over more of the chip and the weights'
-// chain (mass, tickets, masses) runs beside the copies.  Against the draw and a copying launch with the weights (rows above
-// 4 KB) or sample_kernel, us:
-//                     1 x 16        1 x 64       1 x 256      1 x 512      1 x 1024      2 x 512       5 x 400
-//   rows of   32 B   5.5 -> 5.0   6.5 -> 5.5   6.6 -> 6.1   6.8    6.8   7.4    8.4    6.8    7.0    6.9    7.5
-//           1028 B   5.7 -> 5.1   6.6 -> 5.6   6.7 -> 6.2   6.9    6.9   7.5    8.6    7.0    7.2    7.9    7.8
-//           2048 B   5.8 -> 4.9   6.7 -> 5.5   6.8 -> 6.1   7.1 -> 6.8   7.9    8.4    7.7 -> 7.1    8.8 -> 8.0
-//           4096 B   6.3 -> 4.9   7.3 -> 5.4   7.4 -> 6.1   8.3 -> 6.9   9.5 -> 8.6    9.4 -> 7.2   10.4 -> 9.3
-//           8192 B   7.9 -> 4.9   8.2 -> 5.5   8.1 -> 6.2   8.4 -> 7.0   9.8    9.9    9.9 -> 8.3   12.6 -> 11.8
-//         28,224 B   8.8 -> 5.1   9.3 -> 5.8   9.5 -> 7.3  11.7 -> 10.1 17.0 -> 15.1  16.9 -> 13.9  26.6    26.4
-//         40,000 B   9.2 -> 5.5  10.1 -> 6.5  12.2 -> 8.5  16.1 -> 11.9 24.3 -> 22.2  24.2 -> 20.8
-//         53,000 B                                                    28.2 -> 28.1  28.1 -> 26.6
-//         65,536 B   9.5 -> 7.5  10.2 -> 8.4  12.7 -> 11.7 18.8 -> 18.0 29.9   32.1  29.9   31.0
-//         98,304 B   9.6 -> 9.2  10.5 -> 10.4 16.3 -> 15.0 24.5 -> 23.9 40.7   43.7  41.0   43.6
-//        131,072 B   9.2   10.8  10.3   12.5  18.7   18.3  29.6   30.4  51.4   57.6  52.0   57.2
-//        400,000 B   9.9   26.7  16.0   31.6  40.9   48.9  73.8   84.5 141.7  164.6 141.9  161.3
+// replay.Sample in one launch with a workgroup per sample: its first wave draws the sample, the others wait for the slot
+// and copy the row, the last of them the small columns.  For rows too long for 16 lanes, and for few samples, where it spreads
+// the draws over more of the chip and the weights' chain runs beside the copies.
+//
+// The weights need the smallest mass of the batch.  Every workgroup puts its sample's mass, as the float that the weights
+// are made of, on a board (a word per sample, 0 before the launch), waits until it is there, and reads the whole batch's
+// words: the one that does so last, if not others before it, finds all of them and writes the weights.  (Word written
+// through at agent scope, wait for it, words read at agent scope: the order that sequential consistency asks for.)  Several
+// may find them all; they write the same weights, and clear the words.  That is two round trips; a ticket to be the last
+// workgroup by, in two steps because atomics on one address take turns of some 14 ns, was four: of the 4.3 us of 32 samples
+// 1.2 were spent behind the draw, of the 5.8 of 256 2.0.  Weights by all waves of the workgroup, four at least: one took 0.6 us
+// for 512 and 1.3 for 1024.  Launches of more than kBoardSamplesMax samples in batches of more than kBoardSmallK keep the
+// tickets: words written through wait behind too many reads of the same board (3 x 500 rows of 2 KB 7.6 us by tickets, 8.9).
+//
+// Within a wave everything that does not depend on the slot is fetched before it, all loads of a pass are on their way
+// before the first is waited for (as first written a lane's second piece waited for its first, and the small columns one by
+// one for the row), and a wave has one streaming store in flight at a time (512 frame stacks 8.7 us with both at once, 8.5
+// so).  Rows below kStreamingBytes are stored through the cache: streaming, the partial lines at their ends cost 268-byte
+// rows 0.3 us.  The barrier in between does not wait for stores.
+//
+// us by tickets, one wave for the weights -> so (device time, replayed graphs):
+//                     1 x 32       1 x 64       1 x 256      1 x 512      3 x 333      1 x 1000     2 x 200
+//      32 B, 268 B   4.4 -> 3.9   4.9 -> 3.9   5.9 -> 4.5
+//      1 KB, 4 KB                 5.2 -> 4.2 (128)           6.5 -> 5.3
+//      5003 B                                                             7.8 -> 6.7
+//      8 KB                                                                            9.4 -> 8.1
+//      16 KB                                                 7.7 -> 6.6
+//      28,224 B                                7.0 -> 6.2    9.5 -> 8.6
+//      40,000 B                                                                                     10.0 -> 10.0
 // A workgroup holds 30 KB of a row with two pieces per lane and 60 with four; what is longer takes passes that wait for one
-// another, where two launches give every 32 KB a workgroup.  Rows of up to 32 KB stay with two launches where the chip does not
+// another, where two launches give every 32 KB a workgroup (65,536 bytes, 512 samples 18.0 us and 18.8 in two launches, 1024
+// 32.1 and 29.9; 131,072 bytes, 16 samples 10.8 and 9.2).  Rows of up to 32 KB stay with two launches where the chip does not
 // hold all their workgroups at once, unless the batches are small (28,688 bytes, 768 at once: 1024 samples 17.7 us apart and
 // 19.2, 2 x 700 21.8 and 23.6, 12 x 100 20.1 and 18.7; 20,000 bytes, 1280 at once: 3 x 512 18.0 and 18.9).
-// Beyond 1024 samples in a batch one wave is too few for the weights (2048 samples 13 us, 9.2 apart).
-// The tickets of a batch in two steps, a word per kTicketGroup samples and then the batch's own: an atomic that returns to
-// one address takes its turn of some 14 ns (512 samples of 1028 bytes on one word 11.5 us).
-// The weights in a short loop over masses in LDS: unrolled over masses in registers they are kilobytes of code that every
-// launch has to fetch (0.5 us at 16 samples, 0.7 at 512).
 constexpr uint32_t kTicketGroup = 32;
 constexpr uint32_t kSampleRowsMaxK = 1024;
 constexpr uint32_t kSampleRowsMax = 1536;   // samples of a call: beyond, long rows are bound by memory either way
+constexpr uint32_t kBoardSamplesMax = 1024, kBoardSmallK = 128;
+constexpr uint32_t kWeightWaves = 4;
+constexpr uint64_t kStreamingBytes = 2048;
 constexpr uint32_t kChipCus = 256, kChipWaves = 8192;  // compute units of the chip, waves that it holds at once
 constexpr uint64_t kSampleRowsMaxBytes = 96 << 10, kSampleRowsMaxBytesOfMany = 52 << 10;  // longest rows: up to 512 samples, beyond
 constexpr uint64_t kCopyRowBytes = 32 << 10;  // what a workgroup of copy_rows_long_kernel moves
+static_assert(kSampleRowsMax + APEX_MAX_BATCHES_PER_CALL <= kBoardWordsMax);
 
-template <int kUnroll, bool kWide>
-__global__ __launch_bounds__(1024) void sample_rows_kernel(SampleArgs a, uint32_t vecs_per_row)
+// Whether all words of a batch of k samples are on the board, from word `first` on; the masses go to sh_mass, the smallest to
+// *smallest.  By one wave.
+__device__ __forceinline__ bool board_complete(const uint32_t *board, uint32_t first, uint32_t k, float *sh_mass, float *smallest)
 {
-  __shared__ uint32_t sh_slot;
-  __shared__ uint64_t sh_mass[kSampleRowsMaxK];  // of one wave
-  const TreeView &tv = a.tv;
-  const uint32_t tid = threadIdx.x, lane = lane_id(), j = blockIdx.x, b = blockIdx.y, k = a.k;
-  const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid / kWave));
-  const uint64_t o = (uint64_t)b * k + j;
-  if (wave == 0) {
-    __builtin_amdgcn_s_setprio(2);
-    TopLevel<kWide> top;
-    top.load(tv.level[tv.nlev - 1], tv.n_top);
-    const uint64_t u = a.rnd[o], head = a.st->head;
-    const uint64_t w = fast_div(top.scan(), a.k_div);  // stratum width
-    uint64_t head_slot = 0;
-    const Drawn drawn = walk_down(tv, top.find((uint64_t)j * w + __umul64hi(u, w)), [&] { head_slot = ring_slot(tv, head); });
-    if (lane == 0) {
-      sh_slot = (uint32_t)drawn.slot;
-      __hip_atomic_store(a.mass + o, drawn.mass, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      a.slot_out[o] = (uint32_t)drawn.slot;
-      if (a.key_out) a.key_out[o] = a.gen ? ((uint64_t)a.gen[drawn.slot] << 32) | drawn.slot : ring_key(drawn.slot, head, head_slot, tv.P);
-    }
-    __builtin_amdgcn_s_setprio(0);
-  }
-  __syncthreads();
-  if (wave != 0) {
-    const uint64_t slot = sh_slot;
-    const uint32_t copiers = blockDim.x - kWave, c0 = tid - kWave;
-    const uint8_t *const s = a.g.obs + slot * a.g.obs_bytes;
-    uint8_t *const d = a.g.obs_out + o * a.g.obs_bytes;
-    for (uint32_t v0 = 0; v0 < vecs_per_row; v0 += copiers * kUnroll) {
-      PieceAny::Reg t[kUnroll];
+  constexpr uint32_t kPairs = kSampleRowsMaxK / (2 * kWave);
+  const uint32_t lane = lane_id();
+  uint64_t m[kPairs];
 #pragma unroll
-      for (int u = 0; u < kUnroll; ++u) {
-        const uint32_t v = v0 + u * copiers + c0;
-        if (v < vecs_per_row) t[u] = load_piece_streaming<PieceAny>(s, v, a.g.obs_bytes);
-      }
+  for (uint32_t t = 0; t < kPairs; ++t)
+    if (t * 2 * kWave < k)
+      m[t] = __hip_atomic_load(reinterpret_cast<const uint64_t *>(board + board_place(first + min(2 * (t * kWave + lane), (k - 1) & ~1u))),
+                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  bool all = true;
+  float mn = __builtin_inff();
 #pragma unroll
-      for (int u = 0; u < kUnroll; ++u) {
-        const uint32_t v = v0 + u * copiers + c0;
-        if (v < vecs_per_row) store_piece_streaming<PieceAny>(d, v, a.g.obs_bytes, t[u]);
-      }
-    }
-    if (wave == blockDim.x / kWave - 1) {
-      if (a.g.ret_out && lane == 0) a.g.ret_out[o] = a.g.ret[slot];
-      if (a.g.gacc_out && lane == 1) a.g.gacc_out[o] = a.g.gacc[slot];
-      if (a.g.act_out) {
-        const uint8_t *const act = a.g.act + slot * a.g.act_bytes;
-        uint8_t *const act_out = a.g.act_out + o * a.g.act_bytes;
-        if (a.g.act_bytes < 4) {
-          if (lane < a.g.act_bytes) act_out[lane] = act[lane];
-        } else {
-          for (uint32_t at = 4 * lane; at < a.g.act_bytes; at += 4 * kWave) {  // the last piece overlaps the one before it
-            const uint32_t p = min(at, a.g.act_bytes - 4);
-            *reinterpret_cast<u32_any *>(act_out + p) = *reinterpret_cast<const u32_any *>(act + p);
-          }
-        }
-      }
-    }
-    return;
+  for (uint32_t t = 0; t < kPairs; ++t) {
+    if (t * 2 * kWave >= k) break;
+    const uint32_t i = min(2 * (t * kWave + lane), (k - 1) & ~1u);
+    const uint32_t m0 = (uint32_t)m[t], m1 = i + 1 < k ? (uint32_t)(m[t] >> 32) : m0;
+    all &= m0 != 0 && m1 != 0;
+    mn = fminf(mn, fminf(__uint_as_float(m0), __uint_as_float(m1)));
+    sh_mass[i] = __uint_as_float(m0), sh_mass[i + 1] = __uint_as_float(m1);
   }
-  if (!a.weight_out) return;
-  wait_for_all_loads();  // this sample's mass is in memory from here on
-  if (j == 0 && b == 0)
-    for (uint32_t i = lane; i < a.ticket_lines; i += kWave) a.ticket_ahead[i * kTicketStride] = 0;
+  *smallest = wave_min(mn);
+  return __ballot(!all) == 0;
+}
+
+// The same by tickets, a word per kTicketGroup samples and then the batch's own, from the masses as the draws left them.
+__device__ __forceinline__ bool last_by_tickets(const SampleArgs &a, uint32_t b, uint32_t j, uint32_t k, float *sh_mass, float *smallest)
+{
+  const uint32_t lane = lane_id();
   auto last_of = [&](uint32_t line, uint32_t n) {
     uint32_t *const t = a.ticket + (uint64_t)line * kTicketStride;
     uint32_t taken = 0;
@@ -1927,26 +1944,154 @@ __global__ __launch_bounds__(1024) void sample_rows_kernel(SampleArgs a, uint32_
     return last;
   };
   const uint32_t groups = (k + kTicketGroup - 1) / kTicketGroup, g = j / kTicketGroup;
-  if (groups > 1 && !last_of(gridDim.y + b * groups + g, min(kTicketGroup, k - g * kTicketGroup))) return;
-  if (!last_of(b, groups > 1 ? groups : k)) return;
+  if (groups > 1 && !last_of(gridDim.y + b * groups + g, min(kTicketGroup, k - g * kTicketGroup))) return false;
+  if (!last_of(b, groups > 1 ? groups : k)) return false;
   const uint64_t *const bm = a.mass + (uint64_t)b * k;
-  float *const bw = a.weight_out + (uint64_t)b * k;
-  uint64_t mn = ~0ull;
+  float mn = __builtin_inff();
 #pragma unroll 1
-  for (uint32_t i0 = lane; i0 < k + lane; i0 += 8 * kWave) {  // eight loads in flight
+  for (uint32_t i0 = 0; i0 < k; i0 += 8 * kWave) {  // eight loads in flight
     uint64_t m[8];
 #pragma unroll
     for (int t = 0; t < 8; ++t)
-      m[t] = __hip_atomic_load(bm + min(i0 + t * kWave, k - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      m[t] = __hip_atomic_load(bm + min(i0 + t * kWave + lane, k - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
     for (int t = 0; t < 8; ++t) {
-      mn = m[t] < mn ? m[t] : mn;
-      sh_mass[i0 + t * kWave] = m[t];
+      const float mass = (float)m[t];
+      mn = fminf(mn, mass);
+      sh_mass[min(i0 + t * kWave + lane, k - 1)] = mass;
     }
   }
-  mn = wave_min(mn);
-#pragma unroll 2
-  for (uint32_t i = lane; i < k; i += kWave) bw[i] = batch_weight(mn, sh_mass[i], a.beta);
+  *smallest = wave_min(mn);
+  return true;
+}
+
+template <int kUnroll, bool kWide, bool kStreaming>
+__global__ __launch_bounds__(1024) void sample_rows_kernel(SampleArgs a, uint32_t vecs_per_row)
+{
+  __shared__ uint32_t sh_slot;
+  __shared__ float sh_min;                         // smallest mass of the batch; 0: the weights are not written here
+  __shared__ float sh_mass[kSampleRowsMaxK + 1];
+  const TreeView &tv = a.tv;
+  const uint32_t tid = threadIdx.x, lane = lane_id(), j = blockIdx.x, b = blockIdx.y, k = a.k;
+  const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid / kWave));
+  const uint64_t o = (uint64_t)b * k + j;
+  float *const weight_out = a.weight_out;
+
+  if (wave == 0) {
+    __builtin_amdgcn_s_setprio(2);
+    uint64_t *const mass_out = a.mass, *const key_out = a.key_out;
+    uint32_t *const slot_out = a.slot_out, *const board = a.board;
+    const uint32_t *const gen = a.gen;
+    fetch_now(a.top, tv.n_top, a.rnd, a.st);
+    fetch_now(a.k_div.mul, a.k_div.sh1, a.k_div.sh2, tv.nlev);
+    fetch_now(tv.level[0], tv.level[1], tv.top_log2, tv.P);
+    fetch_now(tv.p_div.mul, tv.p_div.sh1, tv.p_div.sh2, gen);
+    fetch_now(mass_out, slot_out, key_out, board);
+    fetch_now(weight_out);
+    const uint64_t u = a.rnd[o], head = a.st->head;
+    TopLevel<kWide> top;
+    top.load(a.top, tv.n_top);
+    const uint64_t w = fast_div(top.scan(), a.k_div);  // stratum width
+    uint64_t head_slot = 0;
+    const Drawn drawn = walk_down(tv, top.find((uint64_t)j * w + __umul64hi(u, w)), [&] { head_slot = ring_slot(tv, head); });
+    if (lane == 0) sh_slot = (uint32_t)drawn.slot;
+    lds_barrier();
+    const uint32_t first = b * board_stride(k);
+    if (lane == 0) {
+      if (board) {  // (a mass is at least 1; one drawn from an empty tree counts as there, too)
+        __hip_atomic_store(board + board_place(first + j), max(__float_as_uint((float)drawn.mass), 1u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        mass_out[o] = drawn.mass;
+      } else {
+        __hip_atomic_store(mass_out + o, drawn.mass, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+      slot_out[o] = (uint32_t)drawn.slot;
+      if (key_out) key_out[o] = gen ? ((uint64_t)gen[drawn.slot] << 32) | drawn.slot : ring_key(drawn.slot, head, head_slot, tv.P);
+    }
+    __builtin_amdgcn_s_setprio(0);
+    if (weight_out) {
+      wait_for_all_loads();  // this sample's mass is in memory from here on
+      asm volatile("" ::: "memory");
+      if (j == 0 && b == 0) clear_ahead(a, lane, kWave);
+      float smallest = 0.f;
+      const bool writes = board ? board_complete(board, first, k, sh_mass, &smallest) : last_by_tickets(a, b, j, k, sh_mass, &smallest);
+      if (lane == 0) sh_min = writes ? smallest : 0.f;
+      if (writes && board)
+        for (uint32_t i = lane; i < k; i += kWave) board[board_place(first + i)] = 0;
+    }
+  } else {
+    const uint8_t *const obs = a.g.obs, *const act = a.g.act;
+    const float *const ret = a.g.ret, *const gacc = a.g.gacc;
+    uint8_t *const obs_out = a.g.obs_out, *const act_out = a.g.act_out;
+    float *const ret_out = a.g.ret_out, *const gacc_out = a.g.gacc_out;
+    const uint64_t row_bytes = a.g.obs_bytes;
+    const uint32_t act_bytes = a.g.act_bytes;
+    fetch_now(obs, obs_out, row_bytes, vecs_per_row);
+    fetch_now(act, act_out, act_bytes, ret);
+    fetch_now(gacc, ret_out, gacc_out, weight_out);
+    const uint32_t copiers = blockDim.x - kWave, c0 = tid - kWave, c_wave = (wave - 1) * kWave, v_last = vecs_per_row - 1;
+    uint8_t *const d = obs_out + o * row_bytes;
+    const bool columns = wave == blockDim.x / kWave - 1, words = act_bytes >= 4;
+    const uint32_t act_last = act_bytes - (words ? 4 : 1), act_at = min(words ? 4 * lane : lane, act_last);
+    lds_barrier();
+    const uint32_t slot = read_lane_u32(sh_slot, 0);
+    const uint8_t *const s = obs + slot * row_bytes;
+    const auto store = [&](uint32_t v, PieceAny::Reg x) {
+      if (kStreaming) store_piece_streaming<PieceAny>(d, v, row_bytes, x);
+      else store_piece<PieceAny>(d, v, row_bytes, x);
+    };
+    // no load sits in a branch that the lanes of a wave take apart: indices are clamped
+    PieceAny::Reg t[kUnroll];
+    float col_r = 0.f, col_g = 0.f;
+    uint32_t act_piece = 0;
+#pragma unroll
+    for (int u = 0; u < kUnroll; ++u) {
+      if (c_wave + u * copiers >= vecs_per_row) break;
+      t[u] = load_piece_streaming<PieceAny>(s, min(u * copiers + c0, v_last), row_bytes);
+    }
+    if (columns) {
+      col_r = ret[slot], col_g = gacc[slot];
+      const uint8_t *const act_row = act + (uint64_t)slot * act_bytes + act_at;
+      if (words) act_piece = *reinterpret_cast<const u32_any *>(act_row);
+      else act_piece = *act_row;
+    }
+    wait_for_all_loads();
+#pragma unroll
+    for (int u = 0; u < kUnroll; ++u) {
+      const uint32_t v = u * copiers + c0;
+      if (u > 0) wait_for_all_loads();
+      if (v < vecs_per_row) store(v, t[u]);
+    }
+    if (columns) {
+      if (ret_out && lane == 0) ret_out[o] = col_r;
+      if (gacc_out && lane == 0) gacc_out[o] = col_g;
+      if (act_out) {
+        uint8_t *const act_to = act_out + o * act_bytes;
+        if (words) *reinterpret_cast<u32_any *>(act_to + act_at) = act_piece;
+        else act_to[act_at] = (uint8_t)act_piece;
+        for (uint32_t at = 4 * (kWave + lane); at < act_bytes; at += 4 * kWave) {  // the last piece overlaps the one before it
+          const uint32_t p = min(at, act_last);
+          *reinterpret_cast<u32_any *>(act_to + p) = *reinterpret_cast<const u32_any *>(act + (uint64_t)slot * act_bytes + p);
+        }
+      }
+    }
+    for (uint32_t v0 = copiers * kUnroll; v0 < vecs_per_row; v0 += copiers * kUnroll) {
+#pragma unroll
+      for (int u = 0; u < kUnroll; ++u) t[u] = load_piece_streaming<PieceAny>(s, min(v0 + u * copiers + c0, v_last), row_bytes);
+#pragma unroll
+      for (int u = 0; u < kUnroll; ++u) {
+        const uint32_t v = v0 + u * copiers + c0;
+        if (v < vecs_per_row) store(v, t[u]);
+      }
+    }
+  }
+
+  if (!weight_out) return;
+  lds_barrier();
+  const float smallest = sh_min;
+  if (smallest == 0.f) return;
+  float *const bw = weight_out + (uint64_t)b * k;
+#pragma unroll 1
+  for (uint32_t i = tid; i < k; i += blockDim.x) bw[i] = batch_weight(smallest, sh_mass[i], a.beta);
 }
 
 // --------------------------------------------------------------------------------------------
@@ -2019,14 +2164,6 @@ struct StepArgs {
 };
 
 enum StepRider { kNoRider = 0, kRoundRides = 1, kLeavesRide = 2 };
-
-// Keeps a wave-uniform value in scalar registers from here on: the compiler would otherwise fetch a
-// kernel argument only where it is first used, behind a wait of its own.
-template <typename T>
-__device__ __forceinline__ void fetch_now(T *p)
-{
-  asm volatile("" ::"s"(p));
-}
 
 // The draw of sample `row` of the next batch by the first wave of a workgroup, with no barrier and no LDS: the
 // top level in registers, the walk down, outputs, and the change that the sample's new priority brings.

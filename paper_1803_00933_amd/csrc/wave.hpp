@@ -51,6 +51,26 @@ __device__ __forceinline__ uint64_t wave_min(uint64_t v)
   return v;
 }
 
+// One step of a minimum with data-parallel primitives: lanes to which the DPP control word routes no value keep theirs.
+template <int kCtrl, int kRowMask>
+__device__ __forceinline__ float dpp_min_step(float v)
+{
+  const int x = (int)__float_as_uint(v);
+  return fminf(v, __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(x, x, kCtrl, kRowMask, 0xf, false)));
+}
+
+// Minimum over the wave, the same in every lane.  The minimum of no NaN.
+__device__ __forceinline__ float wave_min(float v)
+{
+  v = dpp_min_step<0x111, 0xf>(v);  // the rows and masks of wave_inclusive_scan
+  v = dpp_min_step<0x112, 0xf>(v);
+  v = dpp_min_step<0x114, 0xf>(v);
+  v = dpp_min_step<0x118, 0xf>(v);
+  v = dpp_min_step<0x142, 0xa>(v);
+  v = dpp_min_step<0x143, 0xc>(v);
+  return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(v), kWave - 1));
+}
+
 // Device-scope atomics on the tree.  The eight XCDs of the chip have separate L2 caches, so
 // these must be (and are) performed at agent scope.
 __device__ __forceinline__ void atomic_add_u64(uint64_t *p, uint64_t v)

@@ -1444,3 +1444,42 @@ def test_steps_of_several_batches_beside_small_and_large_add_rounds(nb, k):
         assert pipe.fork() == 0
     assert pipe.join() == 0
     pipe.close()
+
+
+# Batches around the edges of what a wave reads of the board together, of the odd word at a batch's end, of the lines between
+# board and tickets (1024 samples, 128 per batch) and between the kernels; rows on both sides of the streaming stores.
+@pytest.mark.parametrize("ob,ab,nb,k", [
+    (16, 1, 1, 1), (16, 3, 1024, 1), (20, 4, 3, 2), (31, 5, 16, 63), (268, 84, 2, 65), (255, 4, 12, 100), (256, 4, 12, 100),
+    (256, 255, 11, 128), (256, 256, 7, 129), (2047, 257, 8, 128), (2048, 300, 3, 500), (2048, 2, 2, 512), (1023, 4, 1, 768),
+    (1023, 4, 1, 769), (1024, 4, 1, 1024), (4096, 4, 3, 341), (28224, 4, 3, 333), (33000, 4, 1, 129),
+])
+def test_weights_by_the_board(ob, ab, nb, k):
+    """replay.Sample with a workgroup per sample: every weight, again and again and in replays of one captured call, with calls
+    of other sizes and of the kernels that take tickets in between; the words of the board are 0 again afterwards, and words
+    that overlapping calls have left there (planted) are gone two calls later."""
+    rng = np.random.default_rng(ob + k)
+    g, o = make_pair(1100, 1200, ob, ab)
+    assert add_both(g, o, rng, 1100, lambda r, n: r.pareto(1.1, n)) == 0
+    for n, m in ((nb, k), (1, 40), (nb, k), (nb, k), (2, 700), (nb, k)):
+        sample_both(g, o, rng, n, m)
+    rnd = rng.integers(0, U64, nb * k, dtype=np.uint64)
+    out, d_rnd = g.alloc_sample_outputs(nb, k), dev(rnd)
+    ref = o.sample(nb, k, 0.4, rnd)[1]
+    s, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=s):
+        assert g.sample(nb, k, 0.4, d_rnd, out=out)[0] == 0
+    for _ in range(3):
+        out["weight"].fill_(-1.0)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert_sample_equal(out, ref)
+        sample_both(g, o, rng, 2, 33)
+    board = g.scratch[-4 * 4 * 16384:].view(torch.int32)       # the last region: four sets of 4096 words, 16 of every 64
+    torch.cuda.synchronize()
+    assert int(board.abs().max()) == 0
+    board.view(-1, 64)[:, :16] = 0x3f800000
+    for _ in range(2):
+        assert g.sample(nb, k, 0.4, d_rnd, out=out)[0] == 0
+    for _ in range(4):
+        sample_both(g, o, rng, nb, k)
