@@ -573,7 +573,7 @@ int apex_nstep_priorities(uint32_t S, uint32_t T, uint32_t n, uint32_t A, const 
   const uint64_t total = (uint64_t)S * T;
   if (total > 0x7fffffffull * 256 || (uint64_t)T + n > 0xffffffffull) return APEX_ERR_TOO_LARGE;
   const QuantParams qp{alpha, eps, frac_bits, qmax_for(max_slots)};
-  const NstepArgs ns{S, T, n, A, q_online, q_target, action, reward, discount};
+  const NstepArgs ns{S, T, n, A, make_fast_div(T), q_online, q_target, action, reward, discount};
   nstep_kernel<<<dim3(blocks_for(total, 256)), dim3(256), 0, static_cast<hipStream_t>(hip_stream)>>>(ns, qp, prio, ret,
                                                                                                  gacc, prio_fx);
   APEX_HIP(hipGetLastError());

@@ -38,38 +38,43 @@ __device__ __forceinline__ bool pe_key_valid(const PeView &v, uint64_t key, uint
 __device__ __forceinline__ void pe_add_runs(const PeView &v, bool active, uint32_t slot, uint64_t d1, uint64_t d2)
 {
   const uint64_t incl1 = wave_inclusive_scan(active ? d1 : 0), incl2 = wave_inclusive_scan(active ? d2 : 0);
-  uint64_t idx = slot;
-  for (uint32_t l = 1; l < v.ts.nlev; ++l) {
+  uint32_t idx = slot;
+  for_levels<1>(v.ts, [&](uint32_t l) {
     idx >>= fanout_log2(v.ts, l);
-    const LaneRuns run = lane_runs(active ? idx : ~0ull);
+    const LaneRuns run = lane_runs(active ? idx : ~0u);
     const int lane_before = run.first > 0 ? run.first - 1 : 0;
     const uint64_t before1 = __shfl(incl1, lane_before, kWave), before2 = __shfl(incl2, lane_before, kWave);
     if (active && run.ends) {
       atomic_add_u64(v.ts.level[l] + idx, incl1 - (run.first > 0 ? before1 : 0));
       atomic_add_u64(v.te.level[l] + idx, incl2 - (run.first > 0 ? before2 : 0));
     }
-  }
+  });
+}
+
+// Counts the masses that had to be clamped, c1 and c2 one of a lane's each.  By the whole wave.
+__device__ __forceinline__ void pe_count_clamped(PeState *st, bool c1, bool c2)
+{
+  const uint64_t nc = __popcll(__ballot(c1)) + __popcll(__ballot(c2));
+  if (nc && lane_id() == 0) atomic_add_u64(&st->base.n_clamped, nc);
 }
 
 __global__ __launch_bounds__(256) void pe_add_kernel(PeView v, PeState *__restrict__ st, uint64_t count,
                                                      const float *__restrict__ prio)
 {
   const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  uint32_t nclamp = 0, slot = 0;
+  uint32_t slot = 0;
   uint64_t q1 = 0, q2 = 0;
+  bool c1 = false, c2 = false;
   if (i < count) {
     slot = v.free_ring[ring_slot(v.ts, st->free_head + i)];
     v.gen[slot] += 1;
-    bool c1, c2;
     const float p = prio[i];
     q1 = quantise_priority(p, v.qs, &c1), q2 = quantise_priority(p, v.qe, &c2);
     v.ts.level[0][slot] = q1;  // a free slot weighs nothing in either tree
     v.te.level[0][slot] = q2;
-    nclamp = (uint32_t)c1 + (uint32_t)c2;
   }
   pe_add_runs(v, i < count, slot, q1, q2);
-  const uint64_t nc = wave_sum(nclamp);
-  if (nc && lane_id() == 0) atomic_add_u64(&st->base.n_clamped, nc);
+  pe_count_clamped(st, c1, c2);
   // the last workgroup to finish moves the free ring's head and the insertion count on
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -82,12 +87,14 @@ __global__ __launch_bounds__(256) void pe_add_kernel(PeView v, PeState *__restri
   }
 }
 
-// The same with the payload of short observation rows in the same launch, in workgroups of kPeAddThreads lanes.
-// First 2^lanes_log2 lanes per transition copy its observation and action bytes into the next free slot; the
-// first of them finds the priority - given (prio), or the n-step priority of an actor round (ns.S != 0:
-// Algorithm 1, ComputePriorities; the partial return and accumulated discount are then the computed ones) - and
-// leaves slot and priority in LDS.  Then one lane per transition enters the masses, whole waves of neighbouring
-// transitions together (add_runs_to_ancestors).  act, ret, gacc may be null.
+// The same with the payload of short observation rows in the same launch, in workgroups of kPeAddThreads lanes:
+// 2^lanes_log2 lanes per transition copy its observation and action bytes into the next free slot; the first waves, a lane per
+// transition, find its priority as well - given (prio), or the n-step priority of an actor round (ns.S != 0: Algorithm 1,
+// ComputePriorities; the partial return and accumulated discount are then the computed ones) - and enter the masses, whole
+// waves of neighbouring transitions together (add_runs_to_ancestors).  act, ret, gacc may be null.
+// Bound by its chain: arguments, the free ring's head, the free slot, generation and atomics.  Rows, action bytes and n-step
+// inputs do not depend on the slot and are fetched beside it; a lane that enters a mass looks its slot up by itself, so nothing
+// goes through LDS.  Rounds of 3200 rows of 256 bytes, five steps: 5.9 us in the trace when rows came first, 5.0 so.
 // The workgroups are as large as they can be, for the sake of the atomics on the top levels: rounds of 3200 rows of 256
 // bytes 5.5 us with 1024 threads and 7 with 256, of 7680 rows of 1000 bytes 13 and 32.  (64 transitions per workgroup
 // whatever the rows, in several passes: 6.2 and 18.)
@@ -107,38 +114,64 @@ __global__ __launch_bounds__(kPeAddThreads) void pe_add_rows_kernel(PeView v, Pe
                                                                     uint32_t lanes_log2, uint64_t obs_bytes,
                                                                     uint32_t act_bytes)
 {
-  __shared__ uint32_t sh_slot[kPeAddThreads];
-  __shared__ float sh_prio[kPeAddThreads];
   const uint32_t rows_per_block = blockDim.x >> lanes_log2, lanes = 1u << lanes_log2;
-  const uint32_t r = threadIdx.x >> lanes_log2;
-  const uint64_t i = (uint64_t)blockIdx.x * rows_per_block + r;
+  fetch_now(st, v.free_ring, v.ts.P, v.ts.p_div.mul);
+  fetch_now(v.ts.p_div.sh1, v.ts.p_div.sh2, obs, act);
+  fetch_now(obs_bytes, act_bytes, vecs_per_row, count);
+  fetch_now(ns.q_online, ns.q_target, ns.action, ns.reward);
+  fetch_now(ns.discount, ns.t_div.mul, ns.t_div.sh1, ns.t_div.sh2);
+  fetch_now(ns.S, ns.T, ns.n, ns.A);
+  const uint64_t free_head = st->free_head, tail = st->base.tail, last = count - 1;
+  // what this thread copies: piece vv of transition i, and its action bytes from the one numbered vv on, four at a time
+  const uint64_t i = (uint64_t)blockIdx.x * rows_per_block + (threadIdx.x >> lanes_log2), i_at = min(i, last);
   const uint32_t vv = threadIdx.x & (lanes - 1);
-  const uint64_t free_head = st->free_head, tail = st->base.tail;
-  if (i < count) {
-    const uint64_t slot = v.free_ring[ring_slot(v.ts, free_head + i)];
-    if (vv < vecs_per_row)
-      store_piece<P>(obs_ring + slot * obs_bytes, vv, obs_bytes, load_piece<P>(obs + i * obs_bytes, vv, obs_bytes));
-    if (act)
-      for (uint32_t by = vv; by < act_bytes; by += lanes) act_ring[slot * act_bytes + by] = act[i * act_bytes + by];
-    if (vv == 0) {
-      float p;
-      if (ns.S) {
-        const NstepOut o = nstep_one(ns, i);
-        ret_ring[slot] = o.R;
-        gacc_ring[slot] = o.G;
-        p = o.p;
-      } else {
-        if (ret) ret_ring[slot] = ret[i];
-        if (gacc) gacc_ring[slot] = gacc[i];
-        p = prio[i];
-      }
-      sh_slot[r] = (uint32_t)slot;
-      sh_prio[r] = p;
+  const uint32_t unit = act_bytes >= 4 ? 4 : 1, act_last = act_bytes - unit;
+  // the transition whose masses it enters, if it is one of the first rows_per_block
+  const uint64_t e = (uint64_t)blockIdx.x * rows_per_block + threadIdx.x, e_at = min(e, last);
+  const bool mass_wave = threadIdx.x < ((rows_per_block + kWave - 1) & ~(uint32_t)(kWave - 1));  // the same for a whole wave
+  const bool active = threadIdx.x < rows_per_block && e < count;
+  const uint32_t slot = v.free_ring[ring_slot(v.ts, free_head + i_at)];
+  uint32_t slot_e = 0, act_piece = 0;
+  if (mass_wave) slot_e = v.free_ring[ring_slot(v.ts, free_head + e_at)];
+  const typename P::Reg piece = load_piece<P>(obs + i_at * obs_bytes, min(vv, vecs_per_row - 1), obs_bytes);
+  if (act) {
+    const uint8_t *const from = act + i_at * act_bytes + min(unit * vv, act_last);
+    if (unit == 4) act_piece = *reinterpret_cast<const u32_any *>(from);
+    else act_piece = *from;
+  }
+  float p = 0.f, r_in = 0.f, g_in = 0.f;
+  if (mass_wave) {
+    if (ns.S) {
+      const NstepOut o = nstep_one(ns, e_at);
+      r_in = o.R, g_in = o.G, p = o.p;
+    } else {
+      p = prio[e_at];
+      if (ret) r_in = ret[e_at];
+      if (gacc) g_in = gacc[e_at];
     }
   }
-  __syncthreads();
+  if (i < count) {
+    if (vv < vecs_per_row) store_piece<P>(obs_ring + (uint64_t)slot * obs_bytes, vv, obs_bytes, piece);
+    if (act) {
+      uint8_t *const to = act_ring + (uint64_t)slot * act_bytes;
+      const uint32_t at = min(unit * vv, act_last);
+      if (unit == 4) *reinterpret_cast<u32_any *>(to + at) = act_piece;
+      else to[at] = (uint8_t)act_piece;
+      for (uint32_t by = unit * (vv + lanes); by < act_bytes; by += unit * lanes) {  // the last piece overlaps the one before it
+        const uint32_t q = min(by, act_last);
+        if (unit == 4) *reinterpret_cast<u32_any *>(to + q) = *reinterpret_cast<const u32_any *>(act + i * act_bytes + q);
+        else to[q] = act[i * act_bytes + q];
+      }
+    }
+  }
+  uint64_t *const leaf1 = v.ts.level[0], *const leaf2 = v.te.level[0];
+  fetch_now(leaf1, leaf2, v.ts.nlev, v.ts.top_log2);
+  fetch_now(v.ts.level[1], v.te.level[1], v.ts.level[2], v.te.level[2]);
+  fetch_now(v.qs.alpha, v.qs.eps, v.qs.frac_bits, v.qs.qmax);
+  fetch_now(v.qe.alpha, v.qe.eps, v.qe.frac_bits, v.qe.qmax);
   // the last workgroup to have read the free ring's head moves it and the insertion count on (by its last lane: the
   // ticket's round trip then runs beside those of the first wave; at the end of the launch it took 0.5 us more)
+  lds_barrier();
   if (threadIdx.x == blockDim.x - 1) {
     const uint32_t t = __hip_atomic_fetch_add(&st->base.ticket_add, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (t == gridDim.x - 1) {
@@ -147,25 +180,20 @@ __global__ __launch_bounds__(kPeAddThreads) void pe_add_rows_kernel(PeView v, Pe
       st->base.tail = tail + count;
     }
   }
-  if (threadIdx.x < ((rows_per_block + kWave - 1) & ~(uint32_t)(kWave - 1))) {  // whole waves
-    const uint32_t e = threadIdx.x;
-    const bool active = e < rows_per_block && (uint64_t)blockIdx.x * rows_per_block + e < count;
-    uint32_t slot = 0, nclamp = 0;
-    uint64_t q1 = 0, q2 = 0;
-    if (active) {
-      slot = sh_slot[e];
-      v.gen[slot] += 1;
-      bool c1, c2;
-      q1 = quantise_priority(sh_prio[e], v.qs, &c1);
-      q2 = quantise_priority(sh_prio[e], v.qe, &c2);
-      v.ts.level[0][slot] = q1;  // a free slot weighs nothing in either tree
-      v.te.level[0][slot] = q2;
-      nclamp = (uint32_t)c1 + (uint32_t)c2;
-    }
-    pe_add_runs(v, active, slot, q1, q2);
-    const uint64_t nc = wave_sum(nclamp);
-    if (nc && lane_id() == 0) atomic_add_u64(&st->base.n_clamped, nc);
+  if (!mass_wave) return;
+  bool c1 = false, c2 = false;
+  uint64_t q1 = 0, q2 = 0;
+  if (active) {
+    v.gen[slot_e] += 1;
+    if (ns.S || ret) ret_ring[slot_e] = r_in;
+    if (ns.S || gacc) gacc_ring[slot_e] = g_in;
+    q1 = quantise_priority(p, v.qs, &c1);
+    q2 = quantise_priority(p, v.qe, &c2);
+    leaf1[slot_e] = q1;  // a free slot weighs nothing in either tree
+    leaf2[slot_e] = q2;
   }
+  pe_add_runs(v, active, slot_e, q1, q2);
+  pe_count_clamped(st, c1, c2);
 }
 
 // A learner batch of at most 1024 pairs in one workgroup of at least that many lanes: pairs naming one slot are
@@ -181,8 +209,9 @@ __device__ __forceinline__ void pe_update_small_block(const PeView &v, PeState *
     h_pos[t] = 0;
   }
   __syncthreads();
-  uint32_t slot = 0, h = 0, nclamp = 0;
+  uint32_t slot = 0, h = 0;
   uint64_t q1 = 0, q2 = 0;
+  bool c1 = false, c2 = false;
   const bool valid = i < m && pe_key_valid(v, key[i], &slot);
   const bool stale = i < m && !valid;
   if (valid) {
@@ -193,11 +222,9 @@ __device__ __forceinline__ void pe_update_small_block(const PeView &v, PeState *
       h = (h + 1) & (kDedupeSlots - 1);
     }
     atomicMax(&h_pos[h], i + 1);
-    bool c1, c2;
     const float p = prio[i];
     q1 = quantise_priority(p, v.qs, &c1);
     q2 = quantise_priority(p, v.qe, &c2);
-    nclamp = (uint32_t)c1 + (uint32_t)c2;
   }
   __syncthreads();
   const bool wins = valid && h_pos[h] == i + 1;
@@ -208,11 +235,9 @@ __device__ __forceinline__ void pe_update_small_block(const PeView &v, PeState *
     v.te.level[0][slot] = q2;
   }
   pe_add_runs(v, wins, slot, d1, d2);  // the keys of a drawn batch ascend: neighbours share their ancestors
-  const uint64_t ns = __popcll(__ballot(stale)), nc = wave_sum(nclamp);
-  if (lane_id() == 0) {
-    if (ns) atomic_add_u64(&st->base.n_stale, ns);
-    if (nc) atomic_add_u64(&st->base.n_clamped, nc);
-  }
+  const uint64_t ns = __popcll(__ballot(stale));
+  if (ns && lane_id() == 0) atomic_add_u64(&st->base.n_stale, ns);
+  pe_count_clamped(st, c1, c2);
 }
 
 __global__ __launch_bounds__(1024) void pe_update_small_kernel(PeView v, PeState *__restrict__ st, uint32_t m,
@@ -232,29 +257,36 @@ __device__ __forceinline__ void pe_writeback_wave(const PeView &v, PeState *__re
                                                   const uint32_t *__restrict__ slot, const uint64_t *__restrict__ mass,
                                                   const float *__restrict__ prio)
 {
+  uint64_t *const leaf1 = v.ts.level[0], *const leaf2 = v.te.level[0];
+  fetch_now(leaf1, leaf2, v.ts.nlev, v.ts.top_log2);
+  fetch_now(v.ts.level[1], v.te.level[1], v.ts.level[2], v.te.level[2]);
+  fetch_now(v.qs.alpha, v.qs.eps, v.qs.frac_bits, v.qs.qmax);
+  fetch_now(v.qe.alpha, v.qe.eps, v.qe.frac_bits, v.qe.qmax);
   const bool in = i < m;
-  const uint32_t at = min(i, m - 1), s = slot[at], s_next = slot[min(i + 1, m - 1)];
-  const uint64_t drawn = mass[at];
-  const float p = prio[at];
+  const uint32_t at = min(i, m - 1);
+  uint32_t s = slot[at], s_next = slot[min(i + 1, m - 1)];
+  uint64_t drawn = mass[at];
+  float p = prio[at];
+  arrived(s), arrived(s_next), arrived(drawn), arrived(p);
   const bool wins = in && (i + 1 == m || s != s_next);
-  uint64_t d1 = 0, d2 = 0;
-  const uint64_t old2 = v.te.level[0][s];
+  uint64_t old2 = leaf2[s];  // on its way during the arithmetic
   bool c1, c2;
   const uint64_t q1 = quantise_priority(p, v.qs, &c1), q2 = quantise_priority(p, v.qe, &c2);
+  arrived(old2);
+  const uint64_t d1 = wins ? q1 - drawn : 0, d2 = wins ? q2 - old2 : 0;
   if (wins) {
-    d1 = q1 - drawn, d2 = q2 - old2;
-    v.ts.level[0][s] = q1;
-    v.te.level[0][s] = q2;
+    leaf1[s] = q1;
+    leaf2[s] = q2;
   }
   pe_add_runs(v, wins, s, d1, d2);
-  const uint64_t nc = wave_sum(in ? (uint32_t)c1 + (uint32_t)c2 : 0);  // of pairs that lose too, as when they are applied one by one
-  if (nc && lane_id() == 0) atomic_add_u64(&st->base.n_clamped, nc);
+  pe_count_clamped(st, in && c1, in && c2);  // of pairs that lose too, as when they are applied one by one
 }
 
 // What follows the draw and gather of one batch whose new priorities are known: the first half of the workgroups (one wave
 // each) write the new priorities of 64 pairs back (m = k <= 1024 pairs in all), the others the weights of as many samples.
 // One workgroup for all pairs is one compute unit that reads the scattered eviction masses and sends every atomic: draw
-// and this, 512 pairs of 1,114,112 slots 11.0 us, 8.9 so; 1024 pairs 14.1 and 8.9.
+// and this, 512 pairs of 1,114,112 slots 11.0 us, 8.9 so; 1024 pairs 14.1 and 8.9.  Bound by the chain arguments, slot, eviction
+// mass, atomics; with the arguments fetched together and the eviction mass ahead of the arithmetic 0.2 us less.
 __global__ __launch_bounds__(kWave) void pe_finish_update_kernel(WeightArgs wa, PeView v, PeState *__restrict__ st,
                                                                  uint32_t m, const uint32_t *__restrict__ slot,
                                                                  const float *__restrict__ prio)
@@ -290,14 +322,12 @@ __global__ __launch_bounds__(256) void pe_update_apply_kernel(PeView v, PeState 
                                                               uint32_t *__restrict__ claim)
 {
   const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-  uint32_t nclamp = 0, slot = 0;
-  bool wins = false;
+  uint32_t slot = 0;
+  bool wins = false, c1 = false, c2 = false;
   uint64_t d1 = 0, d2 = 0;
   if (i < m && pe_key_valid(v, key[i], &slot)) {  // a winner only ever writes non-zero masses, so this cannot flip
-    bool c1, c2;
     const float p = prio[i];
     const uint64_t q1 = quantise_priority(p, v.qs, &c1), q2 = quantise_priority(p, v.qe, &c2);
-    nclamp = (uint32_t)c1 + (uint32_t)c2;
     if (claim[slot] == i + 1) {
       wins = true;
       d1 = q1 - v.ts.level[0][slot], d2 = q2 - v.te.level[0][slot];
@@ -307,8 +337,7 @@ __global__ __launch_bounds__(256) void pe_update_apply_kernel(PeView v, PeState 
     }
   }
   pe_add_runs(v, wins, slot, d1, d2);  // the keys of a drawn batch ascend: neighbours share their ancestors
-  const uint64_t nc = wave_sum(nclamp);
-  if (nc && lane_id() == 0) atomic_add_u64(&st->base.n_clamped, nc);
+  pe_count_clamped(st, c1, c2);
 }
 
 constexpr uint32_t kPeScanThreads = 1024;
@@ -855,7 +884,7 @@ int apex_pe_add_round(apex_pe_replay_t *r, uint32_t S, uint32_t T, uint32_t n, u
   const uint64_t blocks = (count + rows_per_block - 1) / rows_per_block;
   if (blocks > 0x7fffffffull) return APEX_ERR_TOO_LARGE;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-  const NstepArgs ns{S, T, n, A, q_online, q_target, action, reward, discount};
+  const NstepArgs ns{S, T, n, A, make_fast_div(T), q_online, q_target, action, reward, discount};
   const dim3 grid((uint32_t)blocks), block(kPeAddThreads);
   const uint8_t *o8 = static_cast<const uint8_t *>(obs), *a8 = static_cast<const uint8_t *>(act);
   with_pieces(rp, [&](auto p) {
@@ -880,7 +909,11 @@ int apex_pe_sample_update(apex_pe_replay_t *r, uint32_t k, float beta, const uin
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   SampleArgs a = pe_sample_args(r, k, rnd, key_out, slot_out, act_out, ret_out, gacc_out);
   a.g.obs_out = static_cast<uint8_t *>(obs_out);
-  APEX_TRY(launch_sample(a, 1, stream));
+  // The draw and the rows by a workgroup per sample, whatever the size: without weights nothing is settled between workgroups
+  // (with 16 lanes per sample, this launch and the next, 512 of 256 bytes 8.3 us, so 7.5; 128 of 64 bytes 7.7 and 6.9; 1000 of
+  // 1000 bytes 9.3 and 8.3).
+  if (obs_out && r->cfg.obs_bytes >= 16) APEX_TRY(launch_sample_rows(a, 1, stream, nullptr));
+  else APEX_TRY(launch_sample(a, 1, stream));
   // weights and the write-back of the batch just drawn: one launch
   const WeightArgs wa{r->mass(), weight_out, k, beta};
   const dim3 grid(blocks_for(k, kWave) * (weight_out ? 2 : 1));

@@ -92,19 +92,28 @@ __device__ __forceinline__ uint32_t fanout_log2(const TreeView &tv, uint32_t l)
   return l + 1 == tv.nlev ? tv.top_log2 : kFanoutLog2;
 }
 
-// Adds delta (mod 2^64) to every ancestor of `slot` above level 0 (below level `levels`).
-__device__ __forceinline__ void add_to_ancestors(const TreeView &tv, uint64_t slot, uint64_t delta, uint32_t levels)
+// Calls f(l) for the levels from kFrom up.  The lowest ones one by one: their addresses are at fixed places of a kernel's
+// arguments then and are fetched together, where a loop fetched each behind a wait of its own.
+template <uint32_t kFrom, typename F>
+__device__ __forceinline__ void for_levels(const TreeView &tv, F f)
 {
-  uint64_t idx = slot;
-  for (uint32_t l = 1; l < levels; ++l) {
-    idx >>= fanout_log2(tv, l);
-    atomic_add_u64(tv.level[l] + idx, delta);
+  constexpr uint32_t kApart = 4;
+#pragma unroll
+  for (uint32_t l = kFrom; l < kApart; ++l) {
+    if (l >= tv.nlev) return;
+    f(l);
   }
+  for (uint32_t l = kApart; l < tv.nlev; ++l) f(l);
 }
 
+// Adds delta (mod 2^64) to every ancestor of `slot` above level 0.
 __device__ __forceinline__ void add_to_ancestors(const TreeView &tv, uint64_t slot, uint64_t delta)
 {
-  add_to_ancestors(tv, slot, delta, tv.nlev);
+  uint64_t idx = slot;
+  for_levels<1>(tv, [&](uint32_t l) {
+    idx >>= fanout_log2(tv, l);
+    atomic_add_u64(tv.level[l] + idx, delta);
+  });
 }
 
 // Where the runs of neighbouring lanes with equal `node` lie that a prefix sum of the lanes' values is cut into.
@@ -113,10 +122,10 @@ struct LaneRuns {
   int first;        // the first lane of this lane's run
 };
 
-__device__ __forceinline__ LaneRuns lane_runs(uint64_t node)
+__device__ __forceinline__ LaneRuns lane_runs(uint32_t node)
 {
   const int lane = lane_id();
-  const uint64_t prev = __shfl_up(node, 1, kWave);
+  const uint32_t prev = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)node, 0x138, 0xf, 0xf, false);  // wave_shr:1
   const uint64_t starts = __ballot(lane == 0 || prev != node);
   LaneRuns r;
   r.ends = lane == kWave - 1 || ((starts >> (lane + 1)) & 1);
@@ -136,17 +145,18 @@ __device__ __forceinline__ void atomic_add_both(uint64_t *p, uint64_t second, ui
 // is summed with one prefix sum over the wave and sends one atomic instead of one per lane.  A node that appears
 // in several runs receives several atomics.  Sums are modulo 2^64, so a removal passes 0 - mass.  Must be called
 // by all 64 lanes; `active` marks the lanes that carry a delta.
-// idx: the node of level `from` - 1 that the delta belongs to (a slot, from = 1).
-__device__ __forceinline__ void add_runs_to_ancestors(const TreeView &tv, bool active, uint64_t idx, uint64_t delta,
-                                                      uint64_t second = 0, uint32_t from = 1)
+// idx: the node of level kFrom - 1 that the delta belongs to (a slot, kFrom = 1).
+template <uint32_t kFrom = 1>
+__device__ __forceinline__ void add_runs_to_ancestors(const TreeView &tv, bool active, uint32_t idx, uint64_t delta,
+                                                      uint64_t second = 0)
 {
   const uint64_t incl = wave_inclusive_scan(active ? delta : 0);
-  for (uint32_t l = from; l < tv.nlev; ++l) {
+  for_levels<kFrom>(tv, [&](uint32_t l) {
     idx >>= fanout_log2(tv, l);
-    const LaneRuns run = lane_runs(active ? idx : ~0ull);  // lanes without a delta form runs of their own, which send nothing
+    const LaneRuns run = lane_runs(active ? idx : ~0u);  // lanes without a delta form runs of their own, which send nothing
     const uint64_t before = __shfl(incl, run.first > 0 ? run.first - 1 : 0, kWave);
     if (active && run.ends) atomic_add_both(tv.level[l] + idx, second, incl - (run.first > 0 ? before : 0));
-  }
+  });
 }
 
 // Same, for a workgroup of at most 1024 threads that holds consecutive slots of the ring, one per thread: the waves'
@@ -169,8 +179,8 @@ __device__ __forceinline__ void add_dense_to_ancestors(const TreeView &tv, bool 
   }
   const uint32_t lane = lane_id(), wave = threadIdx.x / kWave;
   const uint64_t incl = wave_inclusive_scan(active ? delta : 0);
-  const uint64_t node = slot >> fanout_log2(tv, 1);
-  const LaneRuns run = lane_runs(active ? node : ~0ull);
+  const uint32_t node = (uint32_t)slot >> fanout_log2(tv, 1);
+  const LaneRuns run = lane_runs(active ? node : ~0u);
   const uint64_t before = __shfl(incl, run.first > 0 ? run.first - 1 : 0, kWave);
   const uint64_t sum = incl - (run.first > 0 ? before : 0);
   const bool sends = active && run.ends;
@@ -180,7 +190,7 @@ __device__ __forceinline__ void add_dense_to_ancestors(const TreeView &tv, bool 
   const uint32_t e = 4 * wave + (more ? __popcll(senders & ((1ull << lane) - 1)) : 0);
   if (sends && more) {
     sh.sum[e] = sum;
-    sh.node[e] = (uint32_t)node;
+    sh.node[e] = node;
   }
   // places a wave does not use: zero on its last node (a gap would cut the runs of the second stage), none if idle
   const uint32_t n_sent = __popcll(senders);
@@ -192,7 +202,7 @@ __device__ __forceinline__ void add_dense_to_ancestors(const TreeView &tv, bool 
   __syncthreads();
   if (wave == 0 && more) {
     const uint32_t nd = lane < 4 * (blockDim.x / kWave) ? sh.node[lane] : ~0u;
-    add_runs_to_ancestors(tv, nd != ~0u, nd, sh.sum[lane], second, 2);
+    add_runs_to_ancestors<2>(tv, nd != ~0u, nd, sh.sum[lane], second);
   }
 }
 
@@ -201,6 +211,7 @@ __device__ __forceinline__ void add_dense_to_ancestors(const TreeView &tv, bool 
 // --------------------------------------------------------------------------------------------
 struct NstepArgs {
   uint32_t S, T, n, A;
+  FastDiv t_div;                     // division by T
   const float *q_online, *q_target;  // [S, T+n, A]
   const int32_t *action;             // [S, T+n]
   const float *reward, *discount;    // [S, T+n]
@@ -243,18 +254,26 @@ constexpr int kNstepHeld = 8;
 __device__ __forceinline__ NstepOut nstep_one(const NstepArgs &a, uint64_t gid)
 {
   const uint32_t T = a.T, n = a.n, A = a.A;
-  const uint32_t s = (uint32_t)(gid / T), t = (uint32_t)(gid - (uint64_t)s * T);
+  const uint32_t s = (uint32_t)fast_div(gid, a.t_div), t = (uint32_t)(gid - (uint64_t)s * T);
   const uint64_t row0 = (uint64_t)s * (T + n);  // first row of this stream
   const float *rw = a.reward + row0 + t;
   const float *dc = a.discount + row0 + t;
 
-  const uint32_t best = greedy_action(a.q_online + (row0 + t + n) * A, A);
-  float R = 0.0f, G = 1.0f;
-  if (n <= kNstepHeld) {
-    float r[kNstepHeld], d[kNstepHeld];
+  // rewards, discounts and the action go out ahead of the Q-values that the greedy action is looked for in: all is on its way
+  // before the first wait
+  uint32_t at = (uint32_t)a.action[row0 + t];
+  float r[kNstepHeld], d[kNstepHeld];
+  const bool held = n <= kNstepHeld;
+  if (held) {
 #pragma unroll
     for (int j = 0; j < kNstepHeld; ++j)
       if ((uint32_t)j < n) r[j] = rw[j], d[j] = dc[j];
+  }
+  const uint32_t best = greedy_action(a.q_online + (row0 + t + n) * A, A);
+  if (at >= A) at = A - 1;  // keeps a corrupt action index inside the row
+  const float boot = a.q_target[(row0 + t + n) * A + best], q_at = a.q_online[(row0 + t) * A + at];
+  float R = 0.0f, G = 1.0f;
+  if (held) {
 #pragma unroll
     for (int j = kNstepHeld - 1; j >= 0; --j) R = (uint32_t)j < n ? __builtin_fmaf(d[j], R, r[j]) : R;  // Horner, one rounding per step
 #pragma unroll
@@ -263,11 +282,8 @@ __device__ __forceinline__ NstepOut nstep_one(const NstepArgs &a, uint64_t gid)
     for (int j = (int)n - 1; j >= 0; --j) R = __builtin_fmaf(dc[j], R, rw[j]);
     for (uint32_t j = 0; j < n; ++j) G = G * dc[j];
   }
-  const float boot = a.q_target[(row0 + t + n) * A + best];
-  uint32_t at = (uint32_t)a.action[row0 + t];
-  if (at >= A) at = A - 1;  // keeps a corrupt action index inside the row
   const float target = __builtin_fmaf(G, boot, R);
-  const float delta = target - a.q_online[(row0 + t) * A + at];
+  const float delta = target - q_at;
   return NstepOut{__builtin_fabsf(delta), R, G};
 }
 

@@ -395,7 +395,7 @@ int apex_pipeline_add_begin(apex_pipeline_t *p, uint32_t S, uint32_t T, uint32_t
   p->add_deferred = p->add_on_tree && obs && r->cfg.obs_bytes <= 1024 && !p->codec_raw_bytes;
   if (p->add_deferred) {
     // a small round of short rows is one launch, issued by add_end (the inputs stay untouched until then)
-    p->add_ns = NstepArgs{S, T, n, A, q_online, q_target, action, reward, discount};
+    p->add_ns = NstepArgs{S, T, n, A, make_fast_div(T), q_online, q_target, action, reward, discount};
     p->add_obs = obs;
     p->add_act = act;
   } else {

@@ -336,3 +336,35 @@ def test_write_back_at_the_edges_of_its_waves(k, weights):
             out["weight"] = torch.from_numpy(oo["weight"].astype(F32))
         assert_sample_equal(out, oo)
         check(g, o)
+
+
+@pytest.mark.parametrize("ob,ab", [(15, 1), (16, 3), (17, 4), (28, 5), (272, 32), (256, 33), (1040, 64), (4096, 67), (12, 1100)])
+def test_adds_and_steps_around_the_pieces_of_a_row(ob, ab):
+    """apex_pe_add with and without its columns and apex_pe_sample_update, for rows and action bytes around the units they
+    are moved in, and numbers of transitions around a wave's and a workgroup's share."""
+    from paper_1803_00933_amd import apex
+    rng = np.random.default_rng(ob * 3 + ab)
+    P = 3100
+    g, o = apex.PeReplay(P, P, ob, ab), oracle.PrioritizedEvictionReplay(P, P, ob, ab)
+    for n, columns in ((300, True), (1, True), (63, False), (64, True), (65, False), (257, True), (1000, True), (1025, False)):
+        prio = rng.lognormal(0, 1, n).astype(F32)
+        obs, act = (rng.integers(0, 256, (n, m), dtype=np.uint8) for m in (ob, ab))
+        ret, gacc = rng.standard_normal(n).astype(F32), rng.random(n).astype(F32)
+        assert o.add(prio, obs, act, ret, gacc)[0] == 0
+        if not columns:       # written in place by their producer
+            first = o.inserted - n
+            at = torch.arange(first, first + n, device="cuda:0")
+            lay = g.layout
+            for off, size, x in ((lay.act_offset, ab, act), (lay.ret_offset, 4, ret), (lay.gacc_offset, 4, gacc)):
+                g.storage[off:off + P * size].view(P, size)[at] = dev(x.view(np.uint8).reshape(n, size))
+            act = ret = gacc = None
+        assert g.add(*(None if x is None else dev(x) for x in (prio, obs, act, ret, gacc))) == 0
+        k = int(rng.integers(1, 200))
+        rnd, newp = rng.integers(0, U64, k, dtype=np.uint64), rng.lognormal(0, 1, k).astype(F32)
+        rco, oo = o.sample(1, k, 0.4, rnd)
+        assert rco == 0 and o.update_priorities(oo["key"], newp) == 0
+        out = g.alloc_sample_outputs(1, k)
+        assert g.sample_update(k, 0.4, dev(rnd), dev(newp), out) == 0
+        torch.cuda.synchronize()
+        assert_sample_equal(out, oo)
+        check(g, o)
