@@ -671,7 +671,8 @@ namespace {
 // Importance weights in a launch of their own.
 int launch_weights(const WeightArgs &wa, uint32_t num_batches, hipStream_t stream)
 {
-  batch_weights_kernel<<<dim3(num_batches, blocks_for(wa.k, 512)), dim3(256), 0, stream>>>(wa);
+  const uint32_t threads = (uint32_t)std::clamp<uint64_t>(round_up(wa.k, kWave), kWave, kWeightThreads);
+  batch_weights_kernel<<<dim3(num_batches, blocks_for(wa.k, threads)), dim3(threads), 0, stream>>>(wa);
   return hip_failed(hipGetLastError()) ? APEX_ERR_HIP : APEX_OK;
 }
 
@@ -1234,9 +1235,7 @@ int apex_replay_sample(apex_replay_t *r, uint32_t num_batches, uint32_t k, float
                        float *ret_out, float *gacc_out, void *hip_stream)
 {
   if (!r || !(beta >= 0.0f) || !(beta <= 1.0f)) return APEX_ERR_INVALID_ARG;
-  const bool apart = obs_out && weight_out && num_batches == 1 && k > kGatherApartAboveK && k <= kWeightsInDrawMaxK &&
-                     r->cfg.obs_bytes <= kGatherApartBytes;
-  if (!obs_out || (gather_in_draw(r) && !apart) || sample_by_rows(r->cfg.obs_bytes, num_batches, k))
+  if (!obs_out || gather_in_draw(r) || sample_by_rows(r->cfg.obs_bytes, num_batches, k))
     return sample_in_one(r, num_batches, k, beta, rnd, key_out, slot_out, r->mass(), weight_out, obs_out, act_out, ret_out,
                          gacc_out, /*claim=*/false, static_cast<hipStream_t>(hip_stream));
   const int rc = apex_replay_sample_begin(r, num_batches, k, rnd, key_out, slot_out, r->mass(), act_out, ret_out,

@@ -291,7 +291,7 @@ __global__ __launch_bounds__(kWave) void pe_finish_update_kernel(WeightArgs wa, 
                                                                  uint32_t m, const uint32_t *__restrict__ slot,
                                                                  const float *__restrict__ prio)
 {
-  __shared__ uint64_t red[1];
+  __shared__ float red[1];
   const uint32_t shares = (m + kWave - 1) / kWave;
   if (blockIdx.x < shares)
     pe_writeback_wave(v, st, m, blockIdx.x * kWave + threadIdx.x, slot, wa.mass, prio);

@@ -86,6 +86,25 @@ struct TreeView {
 // key mod P
 __device__ __forceinline__ uint64_t ring_slot(const TreeView &tv, uint64_t key) { return key - fast_div(key, tv.p_div) * tv.P; }
 
+// Keeps wave-uniform values in scalar registers from here on: the compiler would otherwise fetch a kernel argument only
+// where it is first used, behind a wait of its own.  Values named in one call are waited for together.
+template <typename T>
+__device__ __forceinline__ void fetch_now(T p)
+{
+  asm volatile("" ::"s"(p));
+}
+template <typename A, typename B, typename C, typename D>
+__device__ __forceinline__ void fetch_now(A a, B b, C c, D d)
+{
+  asm volatile("" ::"s"(a), "s"(b), "s"(c), "s"(d));
+}
+
+// A barrier for what the workgroup exchanges through LDS: stores to memory that are under way are not waited for.
+__device__ __forceinline__ void lds_barrier()
+{
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
 // log2 of the fan-out of level l (l >= 1) over the level below it.
 __device__ __forceinline__ uint32_t fanout_log2(const TreeView &tv, uint32_t l)
 {
@@ -790,19 +809,21 @@ __device__ __forceinline__ float batch_weight(float mass_min, float mass, float 
 {
   return pow_fixed_sequence(mass_min / mass, beta);
 }
-__device__ __forceinline__ float batch_weight(uint64_t mass_min, uint64_t mass, float beta)
-{
-  return batch_weight((float)mass_min, (float)mass, beta);
-}
 
 // part, nparts: the workgroup writes the weights of samples [part * k / nparts ...) of batch b only
-// (every part still finds the minimum over the whole batch).
-__device__ __forceinline__ void batch_weights(const WeightArgs &wa, uint32_t b, uint64_t *red, uint32_t part = 0,
-                                              uint32_t nparts = 1)
+// (every part still finds the minimum over the whole batch).  The masses that a thread writes weights of go out with those it
+// looks for the minimum in, the first two of them; the minimum is a float's from the lanes on, by data-parallel primitives
+// (the rounding of a smaller mass is no larger, so it is the rounding of the smallest).
+__device__ __forceinline__ void batch_weights(const WeightArgs &wa, uint32_t b, float *red, uint32_t part = 0, uint32_t nparts = 1)
 {
+  constexpr uint32_t kOwn = 2;
   const uint32_t tid = threadIdx.x, nthr = blockDim.x, nwave = nthr / kWave;
   const uint64_t *bm = wa.mass + (uint64_t)b * wa.k;
-  uint64_t mn = ~0ull;
+  const uint32_t per = (wa.k + nparts - 1) / nparts;
+  const uint32_t lo = min(part * per, wa.k), hi = min(lo + per, wa.k);
+  uint64_t own[kOwn], mn = ~0ull;
+#pragma unroll
+  for (uint32_t t = 0; t < kOwn; ++t) own[t] = bm[min(lo + t * nthr + tid, wa.k - 1)];
   for (uint32_t i0 = 0; i0 < wa.k; i0 += 8 * nthr) {  // eight loads in flight (one by one, 16,384 masses took 20 us)
     uint64_t m[8];
 #pragma unroll
@@ -812,23 +833,32 @@ __device__ __forceinline__ void batch_weights(const WeightArgs &wa, uint32_t b, 
     for (int t = 0; t < 8; ++t)
       if (i0 + t * nthr < wa.k) mn = m[t] < mn ? m[t] : mn;
   }
-  mn = wave_min(mn);
-  if (lane_id() == 0) red[tid / kWave] = mn;
-  __syncthreads();
-  for (uint32_t w = 0; w < nwave; ++w) mn = red[w] < mn ? red[w] : mn;
-  const uint32_t per = (wa.k + nparts - 1) / nparts;
-  const uint32_t lo = min(part * per, wa.k), hi = min(lo + per, wa.k);
-  for (uint32_t i = lo + tid; i < hi; i += nthr)
-    wa.weight_out[(uint64_t)b * wa.k + i] = batch_weight(mn, bm[i], wa.beta);
+  float smallest = wave_min((float)mn);
+  if (nwave > 1) {
+    if (lane_id() == 0) red[tid / kWave] = smallest;
+    lds_barrier();
+    smallest = wave_min(red[lane_id() < (int)nwave ? lane_id() : 0]);
+  }
+  float *const out = wa.weight_out + (uint64_t)b * wa.k;
+#pragma unroll
+  for (uint32_t t = 0; t < kOwn; ++t) {
+    const uint32_t i = lo + t * nthr + tid;
+    if (i < hi) out[i] = batch_weight(smallest, (float)own[t], wa.beta);
+  }
+  for (uint32_t i = lo + kOwn * nthr + tid; i < hi; i += nthr) out[i] = batch_weight(smallest, (float)bm[i], wa.beta);
 }
 
 constexpr int kLongCopyThreads = 1024;  // one workgroup of 16 waves per 28 KB frame stack
 constexpr int kLongCopyUnroll = 2;      // 1024 lanes * 2 * 16 B = 32 KB per workgroup
 
-// grid: (batches, parts of a batch)
-__global__ __launch_bounds__(256) void batch_weights_kernel(WeightArgs wa)
+// grid: (batches, parts of a batch).  Bound by its chain: masses, minimum over the workgroup, arithmetic.  A weight per thread:
+// behind a draw with its rows, one batch of 4096 / 8192 / 30,000 9.6 / 11.7 / 24.3 us with 256 threads for 512 weights and the
+// masses fetched anew behind the minimum, 8.6 / 10.0 / 19.5 so.
+constexpr uint32_t kWeightThreads = 512;
+
+__global__ __launch_bounds__(kWeightThreads) void batch_weights_kernel(WeightArgs wa)
 {
-  __shared__ uint64_t red[256 / kWave];
+  __shared__ float red[kWeightThreads / kWave];
   batch_weights(wa, blockIdx.x, red, blockIdx.y, gridDim.y);
 }
 
@@ -901,7 +931,7 @@ __global__ __launch_bounds__(kLongCopyThreads) void copy_rows_long_kernel(const 
     }
   }
   if (kWeights) {
-    __shared__ uint64_t red[kLongCopyThreads / kWave];
+    __shared__ float red[kLongCopyThreads / kWave];
     const uint32_t first = kUpdate == 1 ? 1 : 0;
     if (blk >= first && blk < first + weight_blocks) batch_weights(wa, blk - first, red);
   }
@@ -954,7 +984,7 @@ __global__ __launch_bounds__(kLongCopyThreads) void copy_rows_packed_kernel(cons
                                                                             WeightArgs wa, uint32_t weight_blocks)
 {
   if (kWeights && blockIdx.x < weight_blocks) {
-    __shared__ uint64_t red[kLongCopyThreads / kWave];
+    __shared__ float red[kLongCopyThreads / kWave];
     batch_weights(wa, blockIdx.x, red);
     return;
   }
@@ -1300,7 +1330,7 @@ template <typename P>
 __global__ __launch_bounds__(256) void finish_short_kernel(ShortCopyArgs c, uint32_t copy_blocks, WeightArgs wa,
                                                            uint32_t batches, uint32_t weight_parts, ClaimArgs cl)
 {
-  __shared__ uint64_t red[256 / kWave];
+  __shared__ float red[256 / kWave];
   const uint32_t blk = blockIdx.x, weight_blocks = batches * weight_parts;
   if (blk < copy_blocks) {
     copy_rows_short_block<P>(c, blk);
@@ -1412,25 +1442,6 @@ __device__ __forceinline__ void wait_for_all_loads()
   __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0); the other counters at their maxima (not waited for)
 }
 
-// Keeps wave-uniform values in scalar registers from here on: the compiler would otherwise fetch a kernel argument only
-// where it is first used, behind a wait of its own.  Values named in one call are waited for together.
-template <typename T>
-__device__ __forceinline__ void fetch_now(T p)
-{
-  asm volatile("" ::"s"(p));
-}
-template <typename A, typename B, typename C, typename D>
-__device__ __forceinline__ void fetch_now(A a, B b, C c, D d)
-{
-  asm volatile("" ::"s"(a), "s"(b), "s"(c), "s"(d));
-}
-
-// A barrier for what the workgroup exchanges through LDS: stores to memory that are under way are not waited for.
-__device__ __forceinline__ void lds_barrier()
-{
-  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
-
 struct Drawn {
   uint64_t slot, mass;
   uint64_t x;  // where in the slot's interval of cumulative mass the point fell: 0 <= x < mass
@@ -1494,9 +1505,11 @@ struct TopLevel {
     return sum;
   }
 
-  // Returns the sum of the whole level.
+  // Returns the sum of the whole level.  (All loads of the wave that come before in the source are on their way by then: the
+  // statement in assembly, which names the values, keeps them from being moved behind it, or into a branch on `in`.)
   __device__ __forceinline__ uint64_t scan()
   {
+    asm volatile("" : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]), "+v"(v[6]), "+v"(v[7]));
     const uint64_t mine = in ? sum_8(v) : 0, incl = wave_inclusive_scan(mine);
     before = incl - mine;
     uint64_t total = read_lane_u64(incl, kWave - 1);
@@ -1583,16 +1596,6 @@ __device__ __forceinline__ uint64_t ring_key(uint64_t slot, uint64_t head, uint6
   return head + (slot >= head_slot ? slot - head_slot : slot + P - head_slot);
 }
 
-// One of the four 16-lane rows of a wave: inclusive prefix sum.
-__device__ __forceinline__ uint64_t row_inclusive_scan(uint64_t v)
-{
-  v = dpp_add_step<0x111, 0xf>(v);  // row_shr:1
-  v = dpp_add_step<0x112, 0xf>(v);  // row_shr:2
-  v = dpp_add_step<0x114, 0xf>(v);  // row_shr:4
-  v = dpp_add_step<0x118, 0xf>(v);  // row_shr:8
-  return v;
-}
-
 // The walk of four samples at once, one per 16-lane row of the wave (every lane of a row holds its sample's values):
 // a lane takes four neighbouring children, so that a level costs four steps of a prefix sum for four samples
 // instead of six for one.  With a whole wave per sample the arithmetic of the scans, not memory, was what a call
@@ -1602,7 +1605,16 @@ struct RowWalk {
   uint64_t idx, x, mass;
 };
 
+// c ? a : b without a branch (which the compiler makes of a choice between 64-bit values, and moves loads into).
+__device__ __forceinline__ uint64_t pick(bool c, uint64_t a, uint64_t b)
+{
+  const uint32_t lo = c ? (uint32_t)a : (uint32_t)b, hi = c ? (uint32_t)(a >> 32) : (uint32_t)(b >> 32);
+  return ((uint64_t)hi << 32) | lo;
+}
+
 // The lane of the row that holds the first running sum above x has found the child: its values go to the whole row.
+// kMass: the child's mass is wanted.
+template <bool kMass>
 __device__ __forceinline__ void row_descend(RowWalk &w, const uint64_t *lv, uint32_t fl)
 {
   const uint32_t lane = lane_id(), gl = lane & 15, child0 = 4 * gl;
@@ -1619,12 +1631,12 @@ __device__ __forceinline__ void row_descend(RowWalk &w, const uint64_t *lv, uint
   const uint32_t hits = (uint32_t)(__ballot(incl > w.x) >> (lane & 48)) & 0xffffu;
   const uint32_t src = (lane & 48) + (hits ? __ffs(hits) - 1 : 15);
   const uint64_t r = w.x - (incl - sum);  // of use in the lane that has the hit
-  const uint32_t t = (r >= c0) + (r >= p1) + (r >= p2);
-  const uint64_t below = t == 0 ? 0 : t == 1 ? c0 : t == 2 ? p1 : p2;
-  const uint64_t m = t == 0 ? c0 : t == 1 ? c1 : t == 2 ? c2 : c3;
+  const bool ge0 = r >= c0, ge1 = r >= p1, ge2 = r >= p2;
+  const uint32_t t = (uint32_t)ge0 + (uint32_t)ge1 + (uint32_t)ge2;
+  const uint64_t below = pick(ge2, p2, pick(ge1, p1, pick(ge0, c0, 0)));
   w.idx = base + __shfl(child0 + t, src, kWave);
   w.x = __shfl(r - below, src, kWave);
-  w.mass = __shfl(m, src, kWave);
+  if (kMass) w.mass = __shfl(pick(ge2, c3, pick(ge1, c2, pick(ge0, c1, c0))), src, kWave);
 }
 
 // Tells the compiler that a loaded value has arrived, where a wait for all loads has just been made: it would wait for the
@@ -1688,13 +1700,22 @@ __device__ __forceinline__ RowWalk walk_four(const TreeView &tv, const TopLevel<
   RowWalk walk;
   walk.x = point - before;
   walk.idx = l;
-  row_descend(walk, top_level, 3);
-  between();
+  const uint64_t *const low0 = tv.level[0], *const low1 = tv.level[1], *const low2 = tv.level[2];
+  const uint32_t nlev = tv.nlev;
   uint32_t fl = tv.top_log2;
-  for (int lv = (int)tv.nlev - 2; lv >= 0; --lv) {
-    row_descend(walk, tv.level[lv], fl);
+  fetch_now(low0, low1, low2, fl);
+  if (nlev == 1) {
+    row_descend<true>(walk, top_level, 3);
+    between();
+    return walk;
+  }
+  row_descend<false>(walk, top_level, 3);
+  between();
+  for (int lv = (int)nlev - 2; lv > 0; --lv) {
+    row_descend<false>(walk, lv == 1 ? low1 : lv == 2 ? low2 : tv.level[lv], fl);
     fl = kFanoutLog2;
   }
+  row_descend<true>(walk, low0, fl);
   return walk;
 }
 
@@ -1751,38 +1772,29 @@ __device__ __forceinline__ void gather_by_16(const GatherArgs &a, uint64_t slot,
 //           5003 B 12.9 / 8.2   11.8 / 8.9   21.9 / 17.5  24.9 / 25.5
 constexpr uint32_t kGatherInDrawBytes = 4096;
 
-// Most samples of a batch whose weights the draw's launch can write: its last workgroup writes them all (16,384 of them
-// took that launch 21.6 us instead of 8.2 without, where a launch of its own takes 5).
-constexpr uint32_t kWeightsInDrawMaxK = 4096;
-
-// One batch of more samples than kGatherApartAboveK of rows up to kGatherApartBytes is gathered by a launch of its own after all,
-// which writes the weights as well: with the draw, the last workgroup's weights are the tail of the launch.  (Above
-// kWeightsInDrawMaxK they have a launch of their own either way.)  us per call, host included, with / apart, from 2^18 slots:
-//                    2049          2560          3300          4096          8192         32,768
-//    rows of   32 B   8.6 /  8.7    8.9 /  8.8    9.4 /  9.0   10.0 /  9.1   11.2 / 11.3  24.3 / 24.1
-//             268 B   8.7 /  8.9    9.0 /  8.9    9.5 /  9.2   10.2 /  9.4   11.6 / 11.9  25.7 / 28.2
-//            1024 B   9.1 /  9.3    9.4 /  9.5   10.0 /  9.9   10.7 / 10.3   12.6 / 14.2  32.9 / 34.4
-// with the update behind it (one launch up to kUpdateOneLaunchMax pairs)
-//              32 B  14.8 / 14.9   15.1 / 15.0   15.5 / 15.4   16.2 / 15.5
-//            1024 B  15.1 / 15.4   15.6 / 15.7   16.2 / 16.2   16.9 / 16.7
-constexpr uint32_t kGatherApartAboveK = 2560;
-constexpr uint64_t kGatherApartBytes = 1024;
+// Most samples of a batch whose weights the draw's launch writes: its last workgroup writes them all, and what that takes is
+// the tail of the launch.  Beyond, a launch of their own (batch_weights_kernel); the rows ride in the draw either way.  Us of
+// device time, in the draw / apart:
+//                        1200          1500          2048          2049          2561          4096
+//    rows of   32 B    6.6 / 6.5     7.0 / 6.7     7.8 / 7.4     8.1 / 7.5     7.8 / 7.3     8.3 / 7.8
+//             268 B    7.0 / 7.1     7.4 / 7.4     8.2 / 7.8     8.7 / 7.9     8.6 / 8.3     9.1 / 8.7
+//            1024 B    7.6 / 8.0     8.0 / 8.1     8.8 / 8.4     9.3 / 8.4     9.0 / 8.9    10.0 / 9.3
+// Up to 2048 the 0.4 us are less than the launch more costs the host (2.4); beyond, a call with its update is 14 us on the device
+// and 12 on the host.  (Rows and weights of one batch together in a launch behind the draw: 4096 of 128 bytes from 2^24 slots
+// 9.7, so 8.6.)
+constexpr uint32_t kWeightsInDrawMaxK = 2048;
 
 // Threads per workgroup.  16 samples (256 threads) spread the draws best over the chip; a batch of at most 32 goes into
 // one workgroup, whose waves agree on the smallest mass through LDS (32 samples: 5.7 instead of 6.5 us through tickets
-// and memory; with 64 the sixteen waves of the workgroup slow one another down, 8.8 us); a large one has fewer tickets to
-// take and more threads for its weights with 32 samples than with 16 (4096 samples 9.9 and 12.1 us, 3000 9.1 and 10.7,
-// 2048 8.5 and 8.6, 1500 8.2 and 7.9, 512 7.7 and 6.8).
+// and memory; with 64 the sixteen waves of the workgroup slow one another down, 8.8 us).
 constexpr uint32_t kSampleMaxThreads = 512;
 constexpr int kHeldMasses = 8;  // masses per thread of the workgroup that writes a batch's weights
 
 __host__ __device__ constexpr uint32_t sample_threads(uint32_t k, bool weights)
 {
-  if (!weights) return 256;
-  return k <= 32 ? (k + 3) / 4 * kWave : k > 2048 ? kSampleMaxThreads : 256;
+  return weights && k <= 32 ? (k + 3) / 4 * kWave : 256;
 }
-static_assert(kHeldMasses * sample_threads(2048, true) >= 2048 && sample_threads(32, true) <= kSampleMaxThreads &&
-              kHeldMasses * sample_threads(kWeightsInDrawMaxK, true) >= kWeightsInDrawMaxK);
+static_assert(sample_threads(32, true) <= kSampleMaxThreads && kHeldMasses * sample_threads(kWeightsInDrawMaxK, true) >= kWeightsInDrawMaxK);
 
 // Four consecutive samples of a batch per wave: the walks, and with them whatever of replay.Sample the caller wants in
 // the same launch: the gather of short observation rows, the importance weights, the first pass of an update.
@@ -1801,7 +1813,7 @@ static_assert(kHeldMasses * sample_threads(2048, true) >= 2048 && sample_threads
 template <bool kWide>
 __global__ __launch_bounds__(kSampleMaxThreads) void sample_kernel(SampleArgs a)
 {
-  __shared__ uint64_t red[kSampleMaxThreads / kWave];
+  __shared__ float red[kSampleMaxThreads / kWave];
   __shared__ uint32_t sh_ticket;
   const TreeView &tv = a.tv;
   const uint32_t lane = lane_id(), gl = lane & 15, b = blockIdx.y;
@@ -1812,11 +1824,11 @@ __global__ __launch_bounds__(kSampleMaxThreads) void sample_kernel(SampleArgs a)
   uint64_t my_mass = ~0ull;
   if (j0 < k) {
     const uint64_t o = (uint64_t)b * k + min(j, k - 1);  // a row without a sample repeats the last one and writes nothing
+    const uint64_t *const top_level = a.top;
+    fetch_now(top_level, tv.n_top, a.rnd, a.st);
     TopLevel<kWide> top;
-    const uint64_t *const top_level = tv.level[tv.nlev - 1];
     top.load(top_level, tv.n_top);
-    const uint64_t u = a.rnd[o];
-    const uint64_t head = a.st->head;
+    const uint64_t u = a.rnd[o], head = a.st->head;
     const uint64_t total = top.scan();
     const uint64_t w = a.k_dev ? total / k : fast_div(total, a.k_div);  // stratum width
     const uint64_t point = (uint64_t)min(j, k - 1) * w + __umul64hi(u, w);  // inside stratum j
@@ -1839,13 +1851,17 @@ __global__ __launch_bounds__(kSampleMaxThreads) void sample_kernel(SampleArgs a)
   }
   if (!a.weight_out) return;
 
+  const uint32_t wave = threadIdx.x / kWave, nwave = nthr / kWave;
+  // The smallest of the waves' masses; as floats, which round alike.  Called by every thread.
+  const auto smallest_of = [&](float mine) {
+    const float of_wave = wave_min(mine);
+    if (lane == 0) red[wave] = of_wave;
+    lds_barrier();
+    return wave_min(red[lane < nwave ? lane : 0]);
+  };
   if (gridDim.x == 1) {  // the whole batch is here
-    const uint64_t wave_mn = wave_min(my_mass);
-    if (lane == 0) red[threadIdx.x / kWave] = wave_mn;
-    __syncthreads();
-    uint64_t mn = red[0];
-    for (uint32_t v = 1; v < nthr / kWave; ++v) mn = red[v] < mn ? red[v] : mn;
-    if (gl == 0 && j < k) a.weight_out[(uint64_t)b * k + j] = batch_weight(mn, my_mass, a.beta);
+    const float mass = (float)my_mass, smallest = smallest_of(mass);
+    if (gl == 0 && j < k) a.weight_out[(uint64_t)b * k + j] = batch_weight(smallest, mass, a.beta);
     return;
   }
   __syncthreads();
@@ -1858,20 +1874,18 @@ __global__ __launch_bounds__(kSampleMaxThreads) void sample_kernel(SampleArgs a)
   const uint64_t *const bm = a.mass + (uint64_t)b * k;
   float *const bw = a.weight_out + (uint64_t)b * k;
   // every mass of the batch in a register of this workgroup: all loads on their way together
-  uint64_t m[kHeldMasses], mn = ~0ull;
+  uint64_t held[kHeldMasses];
 #pragma unroll
   for (int t = 0; t < kHeldMasses; ++t)
-    m[t] = __hip_atomic_load(bm + min(threadIdx.x + t * nthr, k - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    held[t] = __hip_atomic_load(bm + min(threadIdx.x + t * nthr, k - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  float m[kHeldMasses], mn = __builtin_inff();
 #pragma unroll
-  for (int t = 0; t < kHeldMasses; ++t) mn = m[t] < mn ? m[t] : mn;
-  mn = wave_min(mn);
-  if (lane == 0) red[threadIdx.x / kWave] = mn;
-  __syncthreads();
-  for (uint32_t v = 0; v < nthr / kWave; ++v) mn = red[v] < mn ? red[v] : mn;
+  for (int t = 0; t < kHeldMasses; ++t) m[t] = (float)held[t], mn = fminf(mn, m[t]);
+  const float smallest = smallest_of(mn);
 #pragma unroll
   for (int t = 0; t < kHeldMasses; ++t) {
     const uint32_t i = threadIdx.x + t * nthr;
-    if (i < k) bw[i] = batch_weight(mn, m[t], a.beta);
+    if (i < k) bw[i] = batch_weight(smallest, m[t], a.beta);
   }
 }
 
@@ -2004,9 +2018,9 @@ __global__ __launch_bounds__(1024) void sample_rows_kernel(SampleArgs a, uint32_
     fetch_now(tv.p_div.mul, tv.p_div.sh1, tv.p_div.sh2, gen);
     fetch_now(mass_out, slot_out, key_out, board);
     fetch_now(weight_out);
-    const uint64_t u = a.rnd[o], head = a.st->head;
     TopLevel<kWide> top;
     top.load(a.top, tv.n_top);
+    const uint64_t u = a.rnd[o], head = a.st->head;
     const uint64_t w = fast_div(top.scan(), a.k_div);  // stratum width
     uint64_t head_slot = 0;
     const Drawn drawn = walk_down(tv, top.find((uint64_t)j * w + __umul64hi(u, w)), [&] { head_slot = ring_slot(tv, head); });
@@ -2429,7 +2443,7 @@ __global__ __launch_bounds__(kThreads) void learner_step_kernel(StepArgs a)
     }
   }
   if (weigher) {
-    const float weight = batch_weight(wave_min(mass_min), mass_mine, a.wa.beta);
+    const float weight = batch_weight(wave_min((float)mass_min), (float)mass_mine, a.wa.beta);
     if (row * kWave + lane < a.k) a.wa.weight_out[row * kWave + lane] = weight;
   }
 
@@ -2533,7 +2547,7 @@ constexpr uint32_t kMultiStepRows = kMultiStepThreads / 16;  // samples per work
 template <bool kWide, bool kMerge>
 __global__ __launch_bounds__(kMultiStepThreads) void multi_step_kernel(MultiStepArgs a)
 {
-  __shared__ uint64_t red[kMultiStepThreads / kWave];
+  __shared__ float red[kMultiStepThreads / kWave];
   const uint32_t lane = lane_id(), gl = lane & 15, blk = blockIdx.x;
   if (blk >= a.weight_first && blk - a.weight_first < a.weight_wgs) {
     const uint32_t b = (blk - a.weight_first) / a.weight_wgs_per_batch, part = blk - a.weight_first - b * a.weight_wgs_per_batch;

@@ -10,44 +10,56 @@ constexpr int kWave = 64;
 
 __device__ __forceinline__ int lane_id() { return threadIdx.x & (kWave - 1); }
 
-// One step of a prefix sum with data-parallel primitives (no LDS traffic): every lane adds the
-// value that the DPP control word routes to it, and 0 where it routes none.
-template <int kCtrl, int kRowMask>
-__device__ __forceinline__ uint64_t dpp_add_step(uint64_t v)
+// Prefix sums with data-parallel primitives (no LDS traffic): in every step a lane adds the value that the DPP control routes to
+// it, or 0 where it routes none.  In assembly because the two halves of a 64-bit sum can take their operand through the control
+// themselves, with the carry between them: two instructions a step and a wait state (a DPP operand must have been written two
+// instructions before at least), where the compiler moves both halves through the control first, into registers that it has
+// cleared, and adds twice (six).  The waits at both ends are for what the compiler puts before and behind.
+#define APEX_SCAN_STEP(ctrl)                             \
+  "v_add_co_u32_dpp %0, vcc, %0, %0 " ctrl "\n\t"        \
+  "v_addc_co_u32_dpp %1, vcc, %1, %1, vcc " ctrl "\n\t"
+#define APEX_SCAN_ROW                                                       \
+  "s_nop 1\n\t"                                                             \
+  APEX_SCAN_STEP("row_shr:1 row_mask:0xf bank_mask:0xf bound_ctrl:0")       \
+  "s_nop 0\n\t"                                                             \
+  APEX_SCAN_STEP("row_shr:2 row_mask:0xf bank_mask:0xf bound_ctrl:0")       \
+  "s_nop 0\n\t"                                                             \
+  APEX_SCAN_STEP("row_shr:4 row_mask:0xf bank_mask:0xf bound_ctrl:0")       \
+  "s_nop 0\n\t"                                                             \
+  APEX_SCAN_STEP("row_shr:8 row_mask:0xf bank_mask:0xf bound_ctrl:0")
+
+// Inclusive prefix sum inside each 16-lane row of the wave, modulo 2^64.  Called by all 64 lanes.
+__device__ __forceinline__ uint64_t row_inclusive_scan(uint64_t v)
 {
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, kCtrl, kRowMask, 0xf, false);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(v >> 32), kCtrl, kRowMask, 0xf, false);
-  return v + (((uint64_t)hi << 32) | lo);
+  uint32_t lo = (uint32_t)v, hi = (uint32_t)(v >> 32);
+  asm volatile(APEX_SCAN_ROW "s_nop 1" : "+v"(lo), "+v"(hi) : : "vcc");
+  return ((uint64_t)hi << 32) | lo;
 }
 
-// Inclusive prefix sum of one uint64 per lane: shifts by 1, 2, 4, 8 lanes inside each row of 16
-// lanes, then the last lane of row 0 (2) is added to row 1 (3), then lane 31 to rows 2 and 3.
+// Inclusive prefix sum of one uint64 per lane over the wave: inside the rows, then the last lane of row 0 (2) is added to row 1
+// (3), then lane 31 to rows 2 and 3.  Called by all 64 lanes.
 __device__ __forceinline__ uint64_t wave_inclusive_scan(uint64_t v)
 {
-  v = dpp_add_step<0x111, 0xf>(v);  // row_shr:1
-  v = dpp_add_step<0x112, 0xf>(v);  // row_shr:2
-  v = dpp_add_step<0x114, 0xf>(v);  // row_shr:4
-  v = dpp_add_step<0x118, 0xf>(v);  // row_shr:8
-  v = dpp_add_step<0x142, 0xa>(v);  // row_bcast:15 into rows 1 and 3
-  v = dpp_add_step<0x143, 0xc>(v);  // row_bcast:31 into rows 2 and 3
-  return v;
+  uint32_t lo = (uint32_t)v, hi = (uint32_t)(v >> 32);
+  asm volatile(APEX_SCAN_ROW
+               "s_nop 0\n\t"
+               APEX_SCAN_STEP("row_bcast:15 row_mask:0xa bank_mask:0xf")
+               "s_nop 0\n\t"
+               APEX_SCAN_STEP("row_bcast:31 row_mask:0xc bank_mask:0xf")
+               "s_nop 1"
+               : "+v"(lo), "+v"(hi)
+               :
+               : "vcc");
+  return ((uint64_t)hi << 32) | lo;
 }
+#undef APEX_SCAN_ROW
+#undef APEX_SCAN_STEP
 
 // Sum over the wave, result in every lane.
 __device__ __forceinline__ uint64_t wave_sum(uint64_t v)
 {
 #pragma unroll
   for (int d = kWave / 2; d >= 1; d >>= 1) v += __shfl_xor(v, d, kWave);
-  return v;
-}
-
-__device__ __forceinline__ uint64_t wave_min(uint64_t v)
-{
-#pragma unroll
-  for (int d = kWave / 2; d >= 1; d >>= 1) {
-    uint64_t t = __shfl_xor(v, d, kWave);
-    v = t < v ? t : v;
-  }
   return v;
 }
 
@@ -62,7 +74,7 @@ __device__ __forceinline__ float dpp_min_step(float v)
 // Minimum over the wave, the same in every lane.  The minimum of no NaN.
 __device__ __forceinline__ float wave_min(float v)
 {
-  v = dpp_min_step<0x111, 0xf>(v);  // the rows and masks of wave_inclusive_scan
+  v = dpp_min_step<0x111, 0xf>(v);  // row_shr:1, the steps of wave_inclusive_scan
   v = dpp_min_step<0x112, 0xf>(v);
   v = dpp_min_step<0x114, 0xf>(v);
   v = dpp_min_step<0x118, 0xf>(v);
