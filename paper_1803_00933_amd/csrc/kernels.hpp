@@ -511,10 +511,9 @@ __device__ __forceinline__ TdInputs td_inputs(const QSource &qs, uint32_t i)
   return TdInputs{qs.q_target_next[(uint64_t)i * qs.A + best], taken};
 }
 
-__device__ __forceinline__ float td_priority(const QSource &qs, const TdInputs &in, uint64_t slot)
+__device__ __forceinline__ float td_priority(float ret, float gacc, const TdInputs &in)
 {
-  const float target = __builtin_fmaf(qs.gacc[slot], in.boot, qs.ret[slot]);
-  return __builtin_fabsf(target - in.taken);
+  return __builtin_fabsf(__builtin_fmaf(gacc, in.boot, ret) - in.taken);
 }
 
 struct UpdateArgs {
@@ -615,6 +614,9 @@ __device__ __forceinline__ void update_batch_apply(const UpdateArgs &ua, UpdateL
 //   512 / 1024 pairs from the learner's Q-values, 18 actions, 2^21 slots  7.4 / 15.2 -> 4.3 / 4.5
 // With twice instead of four times as many places as pairs 1024 take 4.4 us and 2048 take 6.0 - 7.2 (probing); 4096 pairs
 // with four per thread take 8 - 10 us.
+// A pair's mass, and from Q-values its columns, are asked for as soon as its key is there, ahead of the table (device time,
+// replayed graphs, behind the table / ahead): 32 pairs of 2^24 slots 2.67 / 2.55, from Q-values 3.35 / 3.06, 512 pairs
+// 3.01 / 2.93 and 3.71 / 3.47, 2048 4.56 / 4.49 and 5.38 / 4.98; 4096, the kernel below, 5.54 / 5.09 and 6.88 / 5.81.
 constexpr uint32_t kUpdateThreads = 1024;       // most threads per workgroup ...
 constexpr uint32_t kUpdateMinThreads = 256;     // ... and fewest: one wave alone is slow to clear the table (32 pairs 3.8 us)
 
@@ -626,35 +628,50 @@ __global__ __launch_bounds__(kUpdateThreads) void update_small_kernel(UpdateArgs
   __shared__ __align__(16) uint32_t h_pos[kPlaces];
   const TreeView &tv = ua.tv;
   const uint32_t tid = threadIdx.x, nthr = blockDim.x, per = nthr / kWave;
+  uint64_t *const leaves = tv.level[0];
   // the pairs that are written back here: number own_t of those that the lanes of wave own_wave hold
   const uint32_t own_t = kHeld == 1 ? 0 : blockIdx.x / per, own_wave = kHeld == 1 ? blockIdx.x : blockIdx.x - own_t * per;
-  const bool own = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid / kWave)) == own_wave;
+  const bool own = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid / kWave)) == own_wave, from_q = ua.qs.q_taken != nullptr;
   uint64_t key[kHeld];
 #pragma unroll
   for (int t = 0; t < kHeld; ++t) key[t] = ua.key[min(t * nthr + tid, ua.m - 1)];
   const uint32_t i = own_t * nthr + tid;
   const uint64_t head = ua.st->head, tail = ua.st->tail;
-  float prio = 0.f;
-  TdInputs td{};
-  if (own && !ua.qs.q_taken) prio = ua.prio[min(i, ua.m - 1)];
   for (uint32_t t = tid; t < kPlaces / 4; t += nthr) {
     reinterpret_cast<u32x4 *>(h_slot)[t] = u32x4{~0u, ~0u, ~0u, ~0u};  // no slot has this number: max_slots <= 2^31
     reinterpret_cast<u32x4 *>(h_pos)[t] = u32x4{0, 0, 0, 0};
   }
-  if (own && ua.qs.q_taken) td = td_inputs(ua.qs, min(i, ua.m - 1));
-  __syncthreads();
+  // Everything that a pair's mass and priority are made of is on its way before the workgroup first waits for one another:
+  // Q-values beside the keys, the transition's mass and columns as soon as the key is there.  (Those of a key that is not valid
+  // any more are those of the slot it would have: read, and not used.)
+  float prio = 0.f, ret = 0.f, gacc = 0.f;
+  TdInputs td{};
+  uint64_t old = 0;
   uint32_t slot[kHeld], h[kHeld], prev[kHeld];
   bool valid[kHeld], valid_own = false;
   uint32_t slot_own = 0, h_own = 0;
-  uint64_t old = 0;
+  if (own) {
+    if (from_q) td = td_inputs(ua.qs, min(i, ua.m - 1));
+    else prio = ua.prio[min(i, ua.m - 1)];
+  }
+#pragma unroll
+  for (int t = 0; t < kHeld; ++t) {
+    slot[t] = (uint32_t)ring_slot(tv, key[t]);
+    if (t == (int)own_t) slot_own = slot[t];
+  }
+  if (own) {
+    old = leaves[slot_own];
+    if (from_q) ret = ua.qs.ret[slot_own], gacc = ua.qs.gacc[slot_own];
+  }
 #pragma unroll
   for (int t = 0; t < kHeld; ++t) {
     valid[t] = t * nthr + tid < ua.m && key[t] >= head && key[t] < tail;
-    slot[t] = (uint32_t)ring_slot(tv, key[t]);
     h[t] = (slot[t] * 2654435761u) / (0xffffffffu / kPlaces + 1);
-    if (own && t == (int)own_t && valid[t]) old = tv.level[0][slot[t]];
-    if (valid[t]) prev[t] = atomicCAS(&h_slot[h[t]], 0xffffffffu, slot[t]);
   }
+  __syncthreads();
+#pragma unroll
+  for (int t = 0; t < kHeld; ++t)
+    if (valid[t]) prev[t] = atomicCAS(&h_slot[h[t]], 0xffffffffu, slot[t]);
 #pragma unroll
   for (int t = 0; t < kHeld; ++t) {
     if (valid[t]) {
@@ -664,21 +681,22 @@ __global__ __launch_bounds__(kUpdateThreads) void update_small_kernel(UpdateArgs
       }
       atomicMax(&h_pos[h[t]], t * nthr + tid + 1);
     }
-    if (t == (int)own_t) valid_own = valid[t], slot_own = slot[t], h_own = h[t];
+    if (t == (int)own_t) valid_own = valid[t], h_own = h[t];
   }
   bool clamped = false;
   uint64_t q = 0;
-  if (own && valid_own) {
-    const float p = ua.qs.q_taken ? td_priority(ua.qs, td, slot_own) : prio;
+  float p = prio;
+  if (own) {
+    if (from_q) p = td_priority(ret, gacc, td);
     q = quantise_priority(p, ua.qp, &clamped);
-    if (ua.qs.q_taken && ua.qs.prio_out) ua.qs.prio_out[i] = p;
+    clamped &= valid_own;
   }
   __syncthreads();
   if (!own) return;
   const bool stale = i < ua.m && !valid_own;
-  if (stale && ua.qs.q_taken && ua.qs.prio_out) ua.qs.prio_out[i] = 0.0f;
+  if (from_q && ua.qs.prio_out && i < ua.m) ua.qs.prio_out[i] = valid_own ? p : 0.0f;
   if (valid_own && h_pos[h_own] == i + 1) {
-    tv.level[0][slot_own] = q;
+    leaves[slot_own] = q;
     add_to_ancestors(tv, slot_own, q - old);
   }
   const uint64_t ns = __popcll(__ballot(stale)), nc = __popcll(__ballot(clamped));
@@ -709,7 +727,8 @@ __global__ __launch_bounds__(kUpdateManyThreads) void update_many_kernel(UpdateA
   __shared__ uint32_t seen[kSeenWords];
   const TreeView &tv = ua.tv;
   const uint32_t tid = threadIdx.x;
-  const bool first_wave = __builtin_amdgcn_readfirstlane((int)tid) == 0;
+  const bool first_wave = __builtin_amdgcn_readfirstlane((int)tid) == 0, from_q = ua.qs.q_taken != nullptr;
+  uint64_t *const leaves = tv.level[0];
   const uint32_t i = blockIdx.x * kWave + (tid & (kWave - 1)), mine = min(i, ua.m - 1);
   const uint32_t later = min((blockIdx.x + 1) * kWave, ua.m);
   const uint64_t key = ua.key[mine];
@@ -726,27 +745,29 @@ __global__ __launch_bounds__(kUpdateManyThreads) void update_many_kernel(UpdateA
     own_last[tid] = 0;
   }
   auto hash = [](uint64_t k) { return (uint32_t)k * 2654435761u; };
-  float prio = 0.f;
+  // as in the kernel above: what the pair's mass and priority are made of goes out before the first wait for one another
+  float prio = 0.f, ret = 0.f, gacc = 0.f;
   TdInputs td{};
-  uint64_t old = 0;
-  uint32_t slot = 0, h = hash(key) >> 24;
+  uint64_t old = 0, slot = 0;
+  uint32_t h = hash(key) >> 24;
   const bool valid = first_wave && i < ua.m && key >= head && key < tail;
-  __syncthreads();
   if (first_wave) {
-    if (valid) {
-      slot = (uint32_t)ring_slot(tv, key);
-      old = tv.level[0][slot];  // on its way during the look-ups
-      for (;;) {
-        const uint64_t prev = atomicCAS(&own_key[h], ~0ull, key);
-        if (prev == ~0ull || prev == key) break;
-        h = (h + 1) & (kOwnPlaces - 1);
-      }
-      atomicMax(&own_last[h], tid + 1);
-      const uint32_t bit = hash(key) >> 18;
-      atomicOr(&seen[bit >> 5], 1u << (bit & 31));
-    }
-    if (ua.qs.q_taken) td = td_inputs(ua.qs, mine);
+    if (from_q) td = td_inputs(ua.qs, mine);
     else prio = ua.prio[mine];
+    slot = ring_slot(tv, key);
+    old = leaves[slot];
+    if (from_q) ret = ua.qs.ret[slot], gacc = ua.qs.gacc[slot];
+  }
+  __syncthreads();
+  if (valid) {
+    for (;;) {
+      const uint64_t prev = atomicCAS(&own_key[h], ~0ull, key);
+      if (prev == ~0ull || prev == key) break;
+      h = (h + 1) & (kOwnPlaces - 1);
+    }
+    atomicMax(&own_last[h], tid + 1);
+    const uint32_t bit = hash(key) >> 18;
+    atomicOr(&seen[bit >> 5], 1u << (bit & 31));
   }
   __syncthreads();
   for (uint32_t j0 = later; j0 < ua.m; j0 += kUpdateManyAhead * kUpdateManyThreads) {
@@ -771,20 +792,21 @@ __global__ __launch_bounds__(kUpdateManyThreads) void update_many_kernel(UpdateA
       }
     }
   }
-  __syncthreads();
-  if (!first_wave) return;
   bool clamped = false;
   uint64_t q = 0;
-  if (valid) {
-    const float p = ua.qs.q_taken ? td_priority(ua.qs, td, slot) : prio;
+  float p = prio;
+  if (first_wave) {
+    if (from_q) p = td_priority(ret, gacc, td);
     q = quantise_priority(p, ua.qp, &clamped);
-    if (ua.qs.q_taken && ua.qs.prio_out) ua.qs.prio_out[i] = p;
+    clamped &= valid;
   }
+  __syncthreads();
+  if (!first_wave) return;
   const bool stale = i < ua.m && !valid;
-  if (stale && ua.qs.q_taken && ua.qs.prio_out) ua.qs.prio_out[i] = 0.0f;
+  if (from_q && ua.qs.prio_out && i < ua.m) ua.qs.prio_out[i] = valid ? p : 0.0f;
   const bool wins = valid && own_last[h] == tid + 1;
-  if (wins) tv.level[0][slot] = q;
-  add_runs_to_ancestors(tv, wins, slot, q - old);  // the keys of a drawn batch ascend: neighbours share their upper nodes
+  if (wins) leaves[slot] = q;
+  add_runs_to_ancestors(tv, wins, (uint32_t)slot, q - old);  // the keys of a drawn batch ascend: neighbours share their upper nodes
   const uint64_t ns = __popcll(__ballot(stale)), nc = __popcll(__ballot(clamped));
   if (tid == 0) {
     if (ns) atomic_add_u64(&ua.st->n_stale, ns);
@@ -1355,7 +1377,7 @@ __global__ __launch_bounds__(256) void update_apply_kernel(TreeView tv, DeviceSt
     const TdInputs td = qs.q_taken ? td_inputs(qs, i) : TdInputs{};
     if (k >= st->head && k < st->tail) {
       slot = ring_slot(tv, k);
-      const float p = qs.q_taken ? td_priority(qs, td, slot) : prio[i];
+      const float p = qs.q_taken ? td_priority(qs.ret[slot], qs.gacc[slot], td) : prio[i];
       if (qs.q_taken && qs.prio_out) qs.prio_out[i] = p;
       const uint64_t q = quantise_priority(p, qp, &clamped);
       if (claim[slot] == i + 1) {
