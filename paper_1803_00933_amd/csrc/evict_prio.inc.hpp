@@ -342,8 +342,15 @@ __global__ __launch_bounds__(256) void pe_update_apply_kernel(PeView v, PeState 
 
 constexpr uint32_t kPeScanThreads = 1024;
 
-// Candidates of a round up to which pe_remove_kernel counts for itself (see there).  Eviction of 32,000 in three rounds 45.8 us
-// so, 48.6 with the launch that counts; of 65,536 55.4 and 55.9, of 98,304 64.0 and 62.8, of 262,144 113.8 and 102.6.
+// Threads of a workgroup of pe_remove_kernel that counts for itself: smaller ones start and end sooner and spread over more
+// compute units, but there are more of them to read what lies before.  An add and an eviction of 1000 in three rounds, with
+// workgroups of 1024 / 512 / 256: 39.1 / 34.9 / 33.3 us; of 8000 40.1 / 36.3 / 36.5; of 32,000 50.6 / 47.3 / 49.2; of 65,000
+// 60.1 / 58.3 / 64.1.
+constexpr uint32_t kPeRecountThreads = 512;
+
+// Candidates of a round up to which pe_remove_kernel counts for itself (see there).  An add and an eviction of 32,000 in three
+// rounds 47.2 us so, 53.8 with the launch that counts; of 50,000 52.7 and 58.0, of 65,000 58.1 and 60.8, of 98,000 69.0 and 68.2,
+// of 131,000 81.2 and 76.2.
 constexpr uint64_t kPeRecountMax = 65536;
 
 // A drawn candidate counts if it is the first of its run of equal slots.
@@ -372,9 +379,10 @@ __global__ __launch_bounds__(kPeScanThreads) void pe_count_kernel(const uint32_t
 // Removes the candidates that count, in the order of their points.  first_rem: evictions asked for in the first round
 // of a call, 0 in the later ones (what the round before has left to do is in st).
 // A workgroup's place in the free ring is the number of candidates before it that count.  Up to kPeRecountMax
-// candidates every workgroup counts them itself (block_sums null): four candidates per lane and load, all of them in
-// the second cache, all loads independent; above, a launch of its own has counted them (block_sums), because the
-// repeated reading grows with the square of the round.
+// candidates every workgroup counts them itself (block_sums null): four candidates per lane and load, four loads ahead of the
+// first wait, all of them in the second cache; above, a launch of its own has counted them (block_sums), because the repeated
+// reading grows with the square of the round.  What bounds it is its chain of memory trips: counters, candidate and masses are
+// asked for before the count, so that they arrive beside it, and nothing is loaded behind the barrier.
 // An eviction of 32,000 in three rounds is six launches instead of ten (count and removal apart, a launch ahead of them
 // that set the number): ten add rounds, ten learner steps and the eviction 243.5 -> 238.6 us.
 __global__ __launch_bounds__(kPeScanThreads) void pe_remove_kernel(PeView v, PeState *__restrict__ st,
@@ -383,39 +391,58 @@ __global__ __launch_bounds__(kPeScanThreads) void pe_remove_kernel(PeView v, PeS
                                                                    const uint32_t *__restrict__ block_sums)
 {
   __shared__ uint32_t wave_before[kPeScanThreads / kWave], wave_own[kPeScanThreads / kWave];
-  const uint32_t t = threadIdx.x, wave = t / kWave;
-  const uint64_t rem = first_rem ? first_rem : st->remaining, head = st->base.head;
-  uint64_t free_tail = st->free_tail;
-  asm volatile("" : "+s"(free_tail));  // read here, ahead of this workgroup's ticket, and not where it is used
-  const uint64_t j0 = (uint64_t)blockIdx.x * kPeScanThreads, j = j0 + t;
+  const uint32_t t = threadIdx.x, wave = t / kWave, nthr = blockDim.x, lane = lane_id();
+  uint64_t *const leaf1 = v.ts.level[0], *const leaf2 = v.te.level[0];
+  fetch_now(st, cand, leaf1, leaf2);
+  fetch_now(v.ts.P, v.ts.p_div.mul, v.ts.p_div.sh1, v.ts.p_div.sh2);
+  fetch_now(v.ts.level[1], v.te.level[1], v.ts.level[2], v.te.level[2]);
+  // (read here, ahead of the barrier and of this workgroup's ticket, not where they are used)
+  const uint64_t rem = first_rem ? first_rem : st->remaining, head = st->base.head, free_tail = st->free_tail;
+  const uint64_t j0 = (uint64_t)blockIdx.x * nthr, j = j0 + t;
+  // this thread's candidate and its masses: on their way during the count (one beyond the round's reads the round's last)
+  const uint64_t at = min(j, max(rem, (uint64_t)1) - 1);
+  const uint32_t slot = cand[at], slot_prev = cand[max(at, (uint64_t)1) - 1];
+  const bool counts = j < rem && (j == 0 || slot != slot_prev);
+  const uint64_t o1 = leaf1[slot], o2 = leaf2[slot];
   uint32_t before = 0;
   if (block_sums) {
-    if (t < blockIdx.x) before = block_sums[t];  // at most kPeScanThreads workgroups: one per lane
+    if (t < blockIdx.x) before = block_sums[t];  // at most kPeScanThreads workgroups of as many threads: one per lane
   } else if (j0 < rem) {  // (then every candidate before j0 belongs to the round)
     const u32x4 *const cand4 = reinterpret_cast<const u32x4 *>(cand);
-#pragma unroll 4
-    for (uint32_t i = t; i < (uint32_t)j0 / 4; i += kPeScanThreads) {
-      const u32x4 c = cand4[i];
-      const uint32_t prev = i ? cand[4 * i - 1] : ~c.x;
-      before += (uint32_t)(c.x != prev) + (uint32_t)(c.y != c.x) + (uint32_t)(c.z != c.y) + (uint32_t)(c.w != c.z);
+    const uint32_t n4 = (uint32_t)j0 / 4;
+    constexpr uint32_t kAhead = 4;
+    for (uint32_t i0 = t; i0 < n4 + t; i0 += kAhead * nthr) {  // the same number of turns for all threads
+      u32x4 c[kAhead];
+      uint32_t prev[kAhead];
+#pragma unroll
+      for (uint32_t u = 0; u < kAhead; ++u) {
+        const uint32_t i = min(i0 + u * nthr, n4 - 1);
+        c[u] = cand4[i], prev[u] = cand[max(4 * i, 1u) - 1];
+      }
+#pragma unroll
+      for (uint32_t u = 0; u < kAhead; ++u) {
+        const uint32_t i = i0 + u * nthr;
+        const uint32_t n = (uint32_t)(i == 0 || c[u].x != prev[u]) + (uint32_t)(c[u].y != c[u].x) + (uint32_t)(c[u].z != c[u].y) +
+                           (uint32_t)(c[u].w != c[u].z);
+        before += i < n4 ? n : 0;
+      }
     }
   }
-  const bool counts = pe_counts(cand, j, rem);
   const uint64_t mask = __ballot(counts);
-  before = (uint32_t)wave_sum(before);
-  if (lane_id() == 0) {
-    wave_before[wave] = before;
+  const uint32_t wave_total = read_lane_u32((uint32_t)wave_inclusive_scan(before), kWave - 1);
+  if (lane == 0) {
+    wave_before[wave] = wave_total;
     wave_own[wave] = __popcll(mask);
   }
-  __syncthreads();
-  uint32_t place = __popcll(mask & ((1ull << lane_id()) - 1)), own = 0;
-  for (uint32_t w = 0; w < kPeScanThreads / kWave; ++w) {
+  lds_barrier();
+  uint32_t place = __popcll(mask & ((1ull << lane) - 1)), own = 0;
+  for (uint32_t w = 0; w < nthr / kWave; ++w) {
     place += wave_before[w] + (w < wave ? wave_own[w] : 0);
     own += wave_own[w];
   }
   // the last workgroup to have read the round's counters closes the round: its ticket comes with what the others
   // remove (ticket in the low word, removals in the high one); the round trip runs beside those of the other lanes
-  if (t == kPeScanThreads - 1) {
+  if (t == nthr - 1) {
     const uint64_t tk = __hip_atomic_fetch_add(&st->round_done, ((uint64_t)own << 32) | 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if ((uint32_t)tk == gridDim.x - 1) {
       const uint64_t removed = (tk >> 32) + own;
@@ -425,13 +452,9 @@ __global__ __launch_bounds__(kPeScanThreads) void pe_remove_kernel(PeView v, PeS
       st->remaining = rem - removed;
     }
   }
-  uint32_t slot = 0;
-  uint64_t o1 = 0, o2 = 0;
   if (counts) {
-    slot = cand[j];
-    o1 = v.ts.level[0][slot], o2 = v.te.level[0][slot];
-    v.ts.level[0][slot] = 0;
-    v.te.level[0][slot] = 0;
+    leaf1[slot] = 0;
+    leaf2[slot] = 0;
     v.free_ring[ring_slot(v.ts, free_tail + place)] = slot;
   }
   pe_add_runs(v, counts, slot, 0 - o1, 0 - o2);  // the candidates ascend: neighbours share their ancestors
@@ -590,8 +613,9 @@ int pe_enqueue_eviction(apex_pe_replay *r, uint64_t e, uint32_t rounds, const ui
   a.g.ret = a.g.gacc = nullptr;
   a.g.act_out = nullptr;
   a.g.ret_out = a.g.gacc_out = nullptr;
-  const dim3 grid(blocks_for(e, kPeScanThreads)), block(kPeScanThreads);  // <= 1024 workgroups since e <= 2^20
   uint32_t *const sums = e > kPeRecountMax ? r->sums() : nullptr;
+  const uint32_t threads = sums ? kPeScanThreads : kPeRecountThreads;
+  const dim3 grid(blocks_for(e, threads)), block(threads);  // <= 1024 workgroups with sums since e <= 2^20
   for (uint32_t rd = 0; rd < rounds; ++rd) {
     const uint64_t first_rem = rd == 0 ? e : 0;
     a.k_dev = rd == 0 ? nullptr : &st->remaining;

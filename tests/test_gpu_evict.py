@@ -368,3 +368,10 @@ def test_adds_and_steps_around_the_pieces_of_a_row(ob, ab):
         torch.cuda.synchronize()
         assert_sample_equal(out, oo)
         check(g, o)
+
+
+@pytest.mark.parametrize("e", [63, 64, 65, 511, 512, 513, 2559, 2561])
+def test_removals_around_a_workgroup_that_counts_for_itself(e):
+    """Workgroups of 512 candidates, each counting what lies before it four words at a time and four loads ahead: rounds that
+    end a wave, a workgroup and a turn of those loads, with half of the candidates equal to their neighbours."""
+    test_rounds_at_the_edges_of_the_removal(e)
