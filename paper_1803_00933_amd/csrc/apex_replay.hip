@@ -290,16 +290,17 @@ int launch_copy_t(const uint8_t *src, const RowMap &smap, uint8_t *dst, const Ro
   } else {
     uint32_t lanes_log2 = 0;
     while ((1u << lanes_log2) < vpr) ++lanes_log2;
-    const uint64_t rows_per_block = 256u >> lanes_log2;
+    const bool w = jobs && jobs->wa.weight_out, cl = jobs && jobs->claim.m;
+    const uint32_t threads = w && jobs->wa.k > 256 ? kWeightThreads : 256;  // powers of two: whole rows
+    const uint64_t rows_per_block = threads >> lanes_log2;
     const uint64_t blocks = (nrows + rows_per_block - 1) / rows_per_block;
     if (blocks > 0x7ffffff0ull) return APEX_ERR_TOO_LARGE;
     const ShortCopyArgs c{src, smap, dst, dmap, nrows, vpr, lanes_log2, row_bytes};
-    const bool w = jobs && jobs->wa.weight_out, cl = jobs && jobs->claim.m;
     if (w || cl) {
       // the importance weights and the claim pass of a large update ride along
-      const uint32_t batches = w ? (uint32_t)(nrows / jobs->wa.k) : 0, parts = w ? blocks_for(jobs->wa.k, 512) : 0;
-      const uint32_t claim_blocks = cl ? blocks_for(jobs->claim.m, 256) : 0;
-      finish_short_kernel<Vec><<<dim3((uint32_t)blocks + batches * parts + claim_blocks), dim3(256), 0, stream>>>(
+      const uint32_t batches = w ? (uint32_t)(nrows / jobs->wa.k) : 0, parts = w ? blocks_for(jobs->wa.k, kWeightThreads) : 0;
+      const uint32_t claim_blocks = cl ? blocks_for(jobs->claim.m, threads) : 0;
+      finish_short_kernel<Vec><<<dim3((uint32_t)blocks + batches * parts + claim_blocks), dim3(threads), 0, stream>>>(
           c, (uint32_t)blocks, w ? jobs->wa : WeightArgs{nullptr, nullptr, 1, 0.f}, batches, parts,
           cl ? jobs->claim : ClaimArgs{});
       if (w) jobs->wa.weight_out = nullptr;
@@ -1235,7 +1236,9 @@ int apex_replay_sample(apex_replay_t *r, uint32_t num_batches, uint32_t k, float
                        float *ret_out, float *gacc_out, void *hip_stream)
 {
   if (!r || !(beta >= 0.0f) || !(beta <= 1.0f)) return APEX_ERR_INVALID_ARG;
-  if (!obs_out || gather_in_draw(r) || sample_by_rows(r->cfg.obs_bytes, num_batches, k))
+  const bool apart = obs_out && weight_out && num_batches == 1 && k > kGatherApartAboveK && k <= kWeightsInDrawMaxK &&
+                     r->cfg.obs_bytes <= kGatherApartBytes;
+  if (!obs_out || (gather_in_draw(r) && !apart) || sample_by_rows(r->cfg.obs_bytes, num_batches, k))
     return sample_in_one(r, num_batches, k, beta, rnd, key_out, slot_out, r->mass(), weight_out, obs_out, act_out, ret_out,
                          gacc_out, /*claim=*/false, static_cast<hipStream_t>(hip_stream));
   const int rc = apex_replay_sample_begin(r, num_batches, k, rnd, key_out, slot_out, r->mass(), act_out, ret_out,

@@ -1349,10 +1349,10 @@ __global__ __launch_bounds__(256) void update_claim_kernel(ClaimArgs c) { update
 // the importance weights, and the first pass of a priority update of the drawn keys.  Workgroups
 // [0, copy_blocks) copy, the next batches * weight_parts write weights, the rest claim.
 template <typename P>
-__global__ __launch_bounds__(256) void finish_short_kernel(ShortCopyArgs c, uint32_t copy_blocks, WeightArgs wa,
+__global__ __launch_bounds__(kWeightThreads) void finish_short_kernel(ShortCopyArgs c, uint32_t copy_blocks, WeightArgs wa,
                                                            uint32_t batches, uint32_t weight_parts, ClaimArgs cl)
 {
-  __shared__ float red[256 / kWave];
+  __shared__ float red[kWeightThreads / kWave];
   const uint32_t blk = blockIdx.x, weight_blocks = batches * weight_parts;
   if (blk < copy_blocks) {
     copy_rows_short_block<P>(c, blk);
@@ -1785,38 +1785,48 @@ __device__ __forceinline__ void gather_by_16(const GatherArgs &a, uint64_t slot,
   if (gacc_lane) a.gacc_out[o] = col;
 }
 
-// Observation rows up to here ride in the draw's launch.  Together / apart, us of device time for one batch of 32, one of 512,
-// one of 4096 and 16 of 512 from 2^18 slots (a launch less on the host, some 3 us, not counted):
-//   rows of  268 B  6.0 / 6.5    6.8 / 7.3   10.0 / 9.3    8.8 / 9.6
-//           1024 B  6.2 / 6.9    6.9 / 7.4   10.9 / 10.7   9.9 / 12.3
-//           2048 B  6.5 / 6.7    7.5 / 7.6   12.0 / 12.7  12.9 / 14.9
-//           4096 B  7.9 / 6.9    9.1 / 8.6   16.1 / 15.3  20.4 / 20.1
-//           5003 B 12.9 / 8.2   11.8 / 8.9   21.9 / 17.5  24.9 / 25.5
+// Observation rows up to here ride in the draw's launch.  Together / apart, us of device time for one batch of 1500, 4 of 512,
+// 16 of 512 and one of 4096 from 2^18 slots (a launch less on the host, 2.4 us, not counted; fewer: sample_by_rows, and one batch
+// of more with shorter rows: kGatherApartAboveK):
+//   rows of  268 B   7.0 /  6.7    6.3 /  6.9    7.7 /  9.2
+//           1024 B   8.0 /  8.0    7.5 /  8.2    9.2 / 11.4
+//           2048 B   8.6 /  8.5    8.2 /  8.9   11.9 / 14.2   10.8 / 11.7
+//           4096 B   9.8 /  9.5   10.0 / 10.7   19.3 / 19.5   16.0 / 14.7
+//           5003 B  12.5 / 10.0   12.8 / 12.1   23.8 / 24.5   17.5 / 16.8
 constexpr uint32_t kGatherInDrawBytes = 4096;
 
-// Most samples of a batch whose weights the draw's launch writes: its last workgroup writes them all, and what that takes is
-// the tail of the launch.  Beyond, a launch of their own (batch_weights_kernel); the rows ride in the draw either way.  Us of
-// device time, in the draw / apart:
-//                        1200          1500          2048          2049          2561          4096
-//    rows of   32 B    6.6 / 6.5     7.0 / 6.7     7.8 / 7.4     8.1 / 7.5     7.8 / 7.3     8.3 / 7.8
-//             268 B    7.0 / 7.1     7.4 / 7.4     8.2 / 7.8     8.7 / 7.9     8.6 / 8.3     9.1 / 8.7
-//            1024 B    7.6 / 8.0     8.0 / 8.1     8.8 / 8.4     9.3 / 8.4     9.0 / 8.9    10.0 / 9.3
-// Up to 2048 the 0.4 us are less than the launch more costs the host (2.4); beyond, a call with its update is 14 us on the device
-// and 12 on the host.  (Rows and weights of one batch together in a launch behind the draw: 4096 of 128 bytes from 2^24 slots
-// 9.7, so 8.6.)
-constexpr uint32_t kWeightsInDrawMaxK = 2048;
+// Most samples of a batch whose weights the draw's launch can write: its last workgroup writes them all (16,384 of them
+// took that launch 21.6 us instead of 8.2 without, where a launch of its own takes 5).
+constexpr uint32_t kWeightsInDrawMaxK = 4096;
+
+// One batch of more samples than kGatherApartAboveK of rows up to kGatherApartBytes is gathered by a launch of its own after all,
+// which writes the weights as well (a weight per thread, finish_short_kernel): with the draw, the last workgroup's weights are the
+// tail of the launch.  (Above kWeightsInDrawMaxK they have a launch of their own either way.)  Us of device time, with / apart,
+// from 2^18 slots:
+//                    2561          3300          4096
+//    rows of   32 B   7.6 / 6.8     8.0 / 7.0     8.6 / 7.0
+//             268 B   7.9 / 7.4     8.3 / 7.8     9.0 / 8.3
+//            1024 B   8.7 / 8.5     9.1 / 8.8     9.8 / 9.4
+// (With 256 threads for 512 weights, apart, 4096: 7.6, 8.8 and 9.9.)  Up to 2560 the 0.2 to 0.7 us are less than the launch more
+// costs the host (2.4); beyond, a call with its update is 13 us on the device and 12 on the host.
+constexpr uint32_t kGatherApartAboveK = 2560;
+constexpr uint64_t kGatherApartBytes = 1024;
 
 // Threads per workgroup.  16 samples (256 threads) spread the draws best over the chip; a batch of at most 32 goes into
 // one workgroup, whose waves agree on the smallest mass through LDS (32 samples: 5.7 instead of 6.5 us through tickets
-// and memory; with 64 the sixteen waves of the workgroup slow one another down, 8.8 us).
+// and memory; with 64 the sixteen waves of the workgroup slow one another down, 8.8 us); a large one has fewer tickets to
+// take and more threads for its weights with 32 samples than with 16 (4096 samples 9.9 and 12.1 us, 3000 9.1 and 10.7,
+// 2048 8.5 and 8.6, 1500 8.2 and 7.9, 512 7.7 and 6.8).
 constexpr uint32_t kSampleMaxThreads = 512;
 constexpr int kHeldMasses = 8;  // masses per thread of the workgroup that writes a batch's weights
 
 __host__ __device__ constexpr uint32_t sample_threads(uint32_t k, bool weights)
 {
-  return weights && k <= 32 ? (k + 3) / 4 * kWave : 256;
+  if (!weights) return 256;
+  return k <= 32 ? (k + 3) / 4 * kWave : k > 2048 ? kSampleMaxThreads : 256;
 }
-static_assert(sample_threads(32, true) <= kSampleMaxThreads && kHeldMasses * sample_threads(kWeightsInDrawMaxK, true) >= kWeightsInDrawMaxK);
+static_assert(kHeldMasses * sample_threads(2048, true) >= 2048 && sample_threads(32, true) <= kSampleMaxThreads &&
+              kHeldMasses * sample_threads(kWeightsInDrawMaxK, true) >= kWeightsInDrawMaxK);
 
 // Four consecutive samples of a batch per wave: the walks, and with them whatever of replay.Sample the caller wants in
 // the same launch: the gather of short observation rows, the importance weights, the first pass of an update.
