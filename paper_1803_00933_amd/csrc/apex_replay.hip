@@ -1098,7 +1098,8 @@ int fused_steps(apex_replay *r, uint32_t n, uint32_t k, float beta, const uint64
 //     neighbours together, where two launches add up whole waves of 64.  8192 samples (16 x 512) on 74 nodes 13.7 / 14.8,
 //     on 128 13.3 / 11.0, 16,384 (32 x 512) on 128 16.3 / 19.3, on 256 14.9 / 12.6, on 512 16.3 / 12.2.
 // Neighbours are added up (add_four) from kMergePerTopNode samples per top node on: without it 4 x 512 on 74 nodes take 12.4
-// us per step, so 7.2; 16 x 512 on 512 nodes 8.4 and 7.7; 2 x 512 on 512 6.2, and 6.6 with it.
+// us per step, so 7.2; 16 x 512 on 512 nodes 8.4 and 7.7; 2 x 512 on 512 6.2, and 6.6 with it.  (All of them before prefix sums
+// took two instructions a step: one launch is 0.4 to 0.8 us shorter since, 16 x 512 on 512 nodes 7.1, 2 x 512 5.4.)
 constexpr uint32_t kMultiStepMaxBatches = 160, kMultiStepMaxPerTopNode = 64, kMergePerTopNode = 8;
 
 // The second copy of the tree may have to be brought up to date first, at some 5 TB/s.  A call that finds it behind does so

@@ -1275,6 +1275,13 @@ def test_finish_with_update_riding_along(ob, k, extra):
         check_gpu_tree(g, o)
 
 
+@pytest.mark.parametrize("ob,k,extra", [(16, 256, 900), (16, 257, 900), (33, 511, 700), (1024, 512, 600), (1000, 513, 600),
+                                        (4096, 256, 800), (4096, 300, 800), (2049, 1025, 0)])
+def test_finish_around_a_workgroup_of_weights(ob, k, extra):
+    """Rows, weights and the first pass of an update in one launch: workgroups of 512 from 257 weights on, at their edges."""
+    test_finish_with_update_riding_along(ob, k, extra)
+
+
 @pytest.mark.parametrize("m,A", [(512, 18), (96, 1), (3000, 4)])
 def test_update_from_learner_q_values(m, A):
     """apex_replay_update_from_q: priorities recomputed from the stored (ret, gacc) and fresh Q-values, in the
