@@ -12,20 +12,21 @@ __device__ __forceinline__ int lane_id() { return threadIdx.x & (kWave - 1); }
 
 // Prefix sums with data-parallel primitives (no LDS traffic): in every step a lane adds the value that the DPP control routes to
 // it, or 0 where it routes none.  In assembly because the two halves of a 64-bit sum can take their operand through the control
-// themselves, with the carry between them: two instructions a step and a wait state (a DPP operand must have been written two
-// instructions before at least), where the compiler moves both halves through the control first, into registers that it has
-// cleared, and adds twice (six).  The waits at both ends are for what the compiler puts before and behind.
+// themselves, with the carry between them: two instructions a step and a wait, where the compiler moves both halves through the
+// control first, into registers that it has cleared, and adds twice (six and a wait).
+// The waits, which nobody adds to assembly, are the compiler's own on this target: two wait states between an instruction that
+// writes vcc and one that reads it, the carry included, and two between the write of a register and its read through a DPP
+// control.  The first keeps a step's halves apart and brings the second with it; those at both ends are for what the compiler
+// puts before and behind.
 #define APEX_SCAN_STEP(ctrl)                             \
   "v_add_co_u32_dpp %0, vcc, %0, %0 " ctrl "\n\t"        \
+  "s_nop 1\n\t"                                          \
   "v_addc_co_u32_dpp %1, vcc, %1, %1, vcc " ctrl "\n\t"
 #define APEX_SCAN_ROW                                                       \
   "s_nop 1\n\t"                                                             \
   APEX_SCAN_STEP("row_shr:1 row_mask:0xf bank_mask:0xf bound_ctrl:0")       \
-  "s_nop 0\n\t"                                                             \
   APEX_SCAN_STEP("row_shr:2 row_mask:0xf bank_mask:0xf bound_ctrl:0")       \
-  "s_nop 0\n\t"                                                             \
   APEX_SCAN_STEP("row_shr:4 row_mask:0xf bank_mask:0xf bound_ctrl:0")       \
-  "s_nop 0\n\t"                                                             \
   APEX_SCAN_STEP("row_shr:8 row_mask:0xf bank_mask:0xf bound_ctrl:0")
 
 // Inclusive prefix sum inside each 16-lane row of the wave, modulo 2^64.  Called by all 64 lanes.
@@ -42,9 +43,7 @@ __device__ __forceinline__ uint64_t wave_inclusive_scan(uint64_t v)
 {
   uint32_t lo = (uint32_t)v, hi = (uint32_t)(v >> 32);
   asm volatile(APEX_SCAN_ROW
-               "s_nop 0\n\t"
                APEX_SCAN_STEP("row_bcast:15 row_mask:0xa bank_mask:0xf")
-               "s_nop 0\n\t"
                APEX_SCAN_STEP("row_bcast:31 row_mask:0xc bank_mask:0xf")
                "s_nop 1"
                : "+v"(lo), "+v"(hi)

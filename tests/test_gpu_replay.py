@@ -1490,3 +1490,27 @@ def test_weights_by_the_board(ob, ab, nb, k):
         assert g.sample(nb, k, 0.4, d_rnd, out=out)[0] == 0
     for _ in range(4):
         sample_both(g, o, rng, nb, k)
+
+
+@pytest.mark.parametrize("P", [512, 1024, 30_000, 300_000])
+def test_carries_in_prefix_sums(P):
+    """Masses whose low words carry in every step of a 64-bit prefix sum and in every lane, and masses of which only some do:
+    draws by one wave alone, by a workgroup per sample and by 16 lanes, updates and add rounds, bit for bit."""
+    rng = np.random.default_rng(P)
+    carrying = F32(1 - 2.0 ** -20)                # a mass of 2^32 - 2^12, give or take some hundred
+    some = lambda r, n: np.where(r.random(n) < 0.5, carrying, F32(2.0 ** -28))
+    for dist in (lambda r, n: np.full(n, carrying), some):
+        g, o = make_pair(P - 300, P, 16, 4, alpha=1.0, eps=0.0, frac_bits=32)
+        assert add_both(g, o, rng, P - 300, dist) == 0
+        assert int((o.leaves() & 0x80000000).max()) != 0
+        check_gpu_tree(g, o)
+        for nb, k in ((1, 1), (1, 300), (1, 1500), (3, 600), (1, 4096)):
+            oo = sample_both(g, o, rng, nb, k)
+            pr = some(rng, len(oo["key"])).astype(F32)
+            assert g.update_priorities(dev(oo["key"]), dev(pr)) == o.update_priorities(oo["key"], pr) == 0
+            check_gpu_tree(g, o)
+        assert add_both(g, o, rng, 257, dist) == 0
+        check_gpu_tree(g, o)
+        sample_both(g, o, rng, 2, 64)
+        assert g.evict() == o.evict()
+        check_gpu_tree(g, o)
