@@ -17,6 +17,9 @@ struct PeState {
   uint64_t free_head, free_tail;   // the free ring holds slots free_ring[free_head .. free_tail) mod P
   uint64_t remaining;              // evictions still to go in the current call
   uint64_t round_done;             // workgroups of the running removal that are done, and what they removed
+  // Workgroups of the running pe_add_rows_kernel that have the counters.  On a line of its own: every wave of such a launch reads
+  // the counters, and every ticket takes their line out of the caches.
+  alignas(128) uint32_t ticket_rows;
 };
 
 struct PeView {
@@ -94,14 +97,19 @@ __global__ __launch_bounds__(256) void pe_add_kernel(PeView v, PeState *__restri
 // waves of neighbouring transitions together (add_runs_to_ancestors).  act, ret, gacc may be null.
 // Bound by its chain: arguments, the free ring's head, the free slot, generation and atomics.  Rows, action bytes and n-step
 // inputs do not depend on the slot and are fetched beside it; a lane that enters a mass looks its slot up by itself, so nothing
-// goes through LDS.  Rounds of 3200 rows of 256 bytes, five steps: 5.9 us in the trace when rows came first, 5.0 so.
+// goes through LDS.  Rounds of 3200 rows of 256 bytes, five steps: 5.4 us in the trace when rows came first, 4.8 so.
 // The workgroups are as large as they can be, for the sake of the atomics on the top levels: rounds of 3200 rows of 256
-// bytes 5.5 us with 1024 threads and 7 with 256, of 7680 rows of 1000 bytes 13 and 32.  (64 transitions per workgroup
-// whatever the rows, in several passes: 6.2 and 18.)
+// bytes 4.7 us with 1024 threads, 5.1 with 512 and 6.4 with 256, of 7700 rows of 1000 bytes 11.7, 18.3 and 34.1.  (64
+// transitions per workgroup whatever the rows, in several passes, when rows came first: 6.2 and 18, where these were 5.5 and 13.)
+// Rounds of more workgroups than the chip holds go by what a workgroup costs.  Two are resident per compute unit (64 registers);
+// the ticket is away from the counters' line, which 16 waves a workgroup read; n-step inputs, two trips one behind the other,
+// are ahead of the row, and the first waves read those of their workgroup's transitions only.  Rounds of 15,000 rows of 1000
+// bytes 26.2 us with 66 registers, the ticket beside the counters and rows ahead, 17.8 so (19.8 when rows came first), of
+// 18,000 of 4096 bytes 163, 62 and 66, of 7700 of 1000 13.4, 11.8 and 12.6.
 constexpr uint32_t kPeAddThreads = 1024;
 
 template <typename P>
-__global__ __launch_bounds__(kPeAddThreads) void pe_add_rows_kernel(PeView v, PeState *__restrict__ st, uint64_t count,
+__global__ __launch_bounds__(kPeAddThreads, 8) void pe_add_rows_kernel(PeView v, PeState *__restrict__ st, uint64_t count,
                                                                     NstepArgs ns, const float *__restrict__ prio,
                                                                     const uint8_t *__restrict__ obs,
                                                                     const uint8_t *__restrict__ act,
@@ -127,28 +135,27 @@ __global__ __launch_bounds__(kPeAddThreads) void pe_add_rows_kernel(PeView v, Pe
   const uint32_t vv = threadIdx.x & (lanes - 1);
   const uint32_t unit = act_bytes >= 4 ? 4 : 1, act_last = act_bytes - unit;
   // the transition whose masses it enters, if it is one of the first rows_per_block
-  const uint64_t e = (uint64_t)blockIdx.x * rows_per_block + threadIdx.x, e_at = min(e, last);
+  const uint64_t e = (uint64_t)blockIdx.x * rows_per_block + min(threadIdx.x, rows_per_block - 1), e_at = min(e, last);
   const bool mass_wave = threadIdx.x < ((rows_per_block + kWave - 1) & ~(uint32_t)(kWave - 1));  // the same for a whole wave
   const bool active = threadIdx.x < rows_per_block && e < count;
   const uint32_t slot = v.free_ring[ring_slot(v.ts, free_head + i_at)];
   uint32_t slot_e = 0, act_piece = 0;
   if (mass_wave) slot_e = v.free_ring[ring_slot(v.ts, free_head + e_at)];
+  float p = 0.f, r_in = 0.f, g_in = 0.f;
+  if (mass_wave && ns.S) {
+    const NstepOut o = nstep_one(ns, e_at);
+    r_in = o.R, g_in = o.G, p = o.p;
+  }
   const typename P::Reg piece = load_piece<P>(obs + i_at * obs_bytes, min(vv, vecs_per_row - 1), obs_bytes);
   if (act) {
     const uint8_t *const from = act + i_at * act_bytes + min(unit * vv, act_last);
     if (unit == 4) act_piece = *reinterpret_cast<const u32_any *>(from);
     else act_piece = *from;
   }
-  float p = 0.f, r_in = 0.f, g_in = 0.f;
-  if (mass_wave) {
-    if (ns.S) {
-      const NstepOut o = nstep_one(ns, e_at);
-      r_in = o.R, g_in = o.G, p = o.p;
-    } else {
-      p = prio[e_at];
-      if (ret) r_in = ret[e_at];
-      if (gacc) g_in = gacc[e_at];
-    }
+  if (mass_wave && !ns.S) {
+    p = prio[e_at];
+    if (ret) r_in = ret[e_at];
+    if (gacc) g_in = gacc[e_at];
   }
   if (i < count) {
     if (vv < vecs_per_row) store_piece<P>(obs_ring + (uint64_t)slot * obs_bytes, vv, obs_bytes, piece);
@@ -173,9 +180,9 @@ __global__ __launch_bounds__(kPeAddThreads) void pe_add_rows_kernel(PeView v, Pe
   // ticket's round trip then runs beside those of the first wave; at the end of the launch it took 0.5 us more)
   lds_barrier();
   if (threadIdx.x == blockDim.x - 1) {
-    const uint32_t t = __hip_atomic_fetch_add(&st->base.ticket_add, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const uint32_t t = __hip_atomic_fetch_add(&st->ticket_rows, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (t == gridDim.x - 1) {
-      st->base.ticket_add = 0;
+      st->ticket_rows = 0;
       st->free_head = free_head + count;
       st->base.tail = tail + count;
     }
@@ -517,6 +524,7 @@ int pe_geometry(const apex_pe_config_t *c, PeGeometry *g)
   g->tree_words = base.tree_words;
   const uint64_t P = c->max_slots;
   g->state_off = 0;
+  static_assert(sizeof(PeState) <= 256);
   g->ticket_off = 256;
   g->mass_off = g->ticket_off + kTicketBytes;
   g->cand_off = g->mass_off + (uint64_t)APEX_PE_MAX_EVICT_PER_CALL * 8;  // also holds the masses of a sample call

@@ -63,3 +63,17 @@ def test_wait_states_between_vector_instructions(assembly):
                 written[r] = states
     assert carries > 1000 and dpps > 1000, (carries, dpps)   # the parsing finds them
     assert not too_soon, (len(too_soon), too_soon[:5])
+
+
+def test_two_workgroups_of_a_prioritized_add_fit_a_compute_unit(assembly):
+    """Workgroups of 1024 threads: 8 waves per SIMD for two of them, which have 64 of its 512 vector registers each."""
+    held = {}
+    for line in assembly:
+        if line.strip().startswith("- .a"):      # the next kernel's entry in the metadata
+            name = None
+        m = re.match(r"\s+\.(name|vgpr_count):\s+(\S+)", line)
+        if m and m.group(1) == "name" and m.group(2).startswith("_Z"):
+            name = m.group(2)
+        elif m and m.group(1) == "vgpr_count" and "pe_add_rows_kernel" in (name or ""):
+            held[name] = int(m.group(2))
+    assert len(held) == 4 and max(held.values()) <= 64, held

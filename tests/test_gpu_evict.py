@@ -221,6 +221,8 @@ def test_enqueued_eviction_that_falls_short_is_noticed():
     (600, 400, 12, 4, 3, 7, 3, 4, 33),          # rows of three words, one tree level, ragged everything
     (5000, 4000, 7, 3, 5, 11, 2, 1, 100),       # rows of single bytes, critic values
     (70_000, 60_000, 4096, 8, 4, 50, 5, 18, 512),  # the longest rows the fused calls take, three levels
+    (9000, 6001, 4096, 4, 61, 41, 3, 4, 64),    # rounds of more workgroups than the chip holds, four transitions each
+    (9000, 6001, 1000, 4, 149, 10, 9, 2, 64),   # a last workgroup of 2 of 16 transitions; more steps than are held
 ])
 def test_fused_calls_on_small_and_ragged_shapes(P, C, ob, ab, S, T, n, A, k):
     """apex_pe_add_round / apex_pe_sample_update / apex_pe_evict_enqueue against the oracle's n-step priorities,
