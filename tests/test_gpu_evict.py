@@ -377,3 +377,29 @@ def test_removals_around_a_workgroup_that_counts_for_itself(e):
     """Workgroups of 512 candidates, each counting what lies before it four words at a time and four loads ahead: rounds that
     end a wave, a workgroup and a turn of those loads, with half of the candidates equal to their neighbours."""
     test_rounds_at_the_edges_of_the_removal(e)
+
+
+@pytest.mark.parametrize("m", [1, 63, 65, 512, 1000, 1024])
+def test_updates_of_one_workgroup(m):
+    """apex_pe_update_priorities of up to 1024 pairs: slots named again and again (the last pair stands), keys of earlier
+    generations and keys of no slot."""
+    from paper_1803_00933_amd import apex
+    rng = np.random.default_rng(m)
+    C, P = 500, 900
+    g, o = apex.PeReplay(C, P, 4, 4), oracle.PrioritizedEvictionReplay(C, P, 4, 4)
+    stale = np.empty(0, np.uint64)
+    for it in range(3):
+        prio = rng.lognormal(0, 2.0, P - o.size).astype(F32)
+        assert o.add(prio)[0] == 0 and g.add(dev(prio)) == 0
+        drawn = o.sample(1, m, 0.4, rng.integers(0, U64, m, dtype=np.uint64))[1]["key"]
+        keys = np.where(rng.random(m) < 0.1, np.uint64(P + 3), drawn)
+        if len(stale):
+            keys = np.where(rng.random(m) < 0.2, rng.choice(stale, m), keys)
+        newp = (rng.pareto(0.5, m) + 1e-3).astype(F32)
+        newp[rng.random(m) < 0.1] = np.inf
+        assert o.update_priorities(keys, newp) == 0 and g.update_priorities(dev(keys), dev(newp)) == 0
+        check(g, o)
+        stale = drawn
+        rnd = rng.integers(0, U64, (3, o.size - C), dtype=np.uint64)
+        assert g.evict(3, dev(rnd)) == o.evict(3, rnd)
+        check(g, o)
