@@ -701,19 +701,22 @@ bool sample_uses_board(uint32_t num_batches, uint32_t k) { return num_batches * 
 
 // Whether num_batches x k samples with rows of obs_bytes go into sample_rows_kernel rather than sample_kernel (rows of up to
 // kGatherInDrawBytes) or two launches.  (The times on both sides of the lines of long rows are at the kernel.)  Short rows, us,
-// sample_kernel / sample_rows_kernel:
-//                1 x 512     1 x 700     1 x 1024    2 x 512     12 x 100    40 x 32     3 x 500
-//     32 bytes   6.1 / 5.2   6.3 / 6.0   6.7 / 6.9   6.1 / 5.9   6.2 / 6.4   6.2 / 5.6   6.2 / 8.3
-//    268         6.1 / 5.2   6.4 / 6.0   7.1 / 7.0   6.6 / 6.0   7.0 / 6.4   7.0 / 5.6   7.1 / 8.8
-//   1024         6.6 / 5.3   7.1 / 6.2   7.7 / 7.6   7.3 / 6.7   7.3 / 6.6   7.3 / 6.0   7.4 / 9.1
-//   2048         6.5 / 5.3   7.7 / 6.1   8.1 / 7.1   6.8 / 6.0   6.6 / 6.5   6.1 / 5.8   (by tickets 7.6)
-//   4096         6.5 / 5.4   7.6 / 6.3   8.7 / 7.6   7.2 / 6.3   7.4 / 6.7   7.1 / 6.5   (by tickets 8.9)
+// sample_kernel / sample_rows_kernel, device time from 2^18 to 2^20 slots:
+//               1 x 512    1 x 700    1 x 800    1 x 900    1 x 1024   2 x 512    12 x 100   40 x 32    3 x 500    2 x 768
+//     32 bytes  5.7 / 5.1  5.9 / 5.8  6.1 / 6.3  6.1 / 6.7  6.3 / 6.8  5.7 / 5.6  5.8 / 6.4  5.4 / 5.6  5.8 / 6.3  6.0 / 6.8
+//    128        5.7 / 5.1  6.0 / 5.8  6.2 / 6.2  6.2 / 6.7  6.4 / 6.7  5.8 / 5.6  6.2 / 6.3  5.7 / 5.6  5.9 / 6.4  6.1 / 6.9
+//    268        5.8 / 5.1  6.1 / 5.9  6.3 / 6.3  6.4 / 6.7  6.7 / 6.9  6.2 / 5.7  6.5 / 6.3  6.1 / 5.6  6.6 / 6.5  6.7 / 7.1
+//   1024        6.1 / 5.1  6.8 / 6.1  7.0 / 6.6  7.2 / 7.3  7.4 / 7.8  7.0 / 6.5  6.9 / 6.6  6.5 / 6.0  7.2 / 6.8  7.3 / 7.4
+//   1500        7.0 / 5.3  7.2 / 6.3  7.4 / 7.0  7.5 / 7.7  7.7 / 7.9  7.3 / 6.7  7.2 / 6.5  6.8 / 6.1  7.5 / 7.0  7.7 / 7.5
+//   2048        6.9 / 5.2  7.4 / 5.9  7.7 / 6.4  7.7 / 6.9  7.9 / 7.1  7.6 / 5.8  7.4 / 6.6  7.1 / 5.7  7.7 / 6.8  7.9 / 7.5
+//   4096        8.3 / 5.3  8.5 / 6.2  8.7 / 6.7  8.8 / 7.3  8.9 / 7.4  8.6 / 6.1  8.5 / 6.8  8.9 / 6.2  9.0 / 7.6  9.3 / 8.3
+// (3 x 500 and 2 x 768 by tickets.  From 256 to 2047 bytes the two are too close there, and on either side, for a line.)
 bool sample_by_rows(uint64_t obs_bytes, uint32_t num_batches, uint32_t k)
 {
   const uint64_t samples = (uint64_t)num_batches * k;
   if (obs_bytes < 16 || k > kSampleRowsMaxK || samples > kSampleRowsMax) return false;
   if (obs_bytes <= kGatherInDrawBytes) {
-    if (obs_bytes < 1024 && k > 768) return false;
+    if (obs_bytes < 2048 && k > (obs_bytes < 1024 ? 768u : 832u)) return false;
     if (samples <= kBoardSamplesMax) return true;
     return k <= kBoardSmallK ? obs_bytes >= 256 : obs_bytes >= 2048 && k <= obs_bytes / 4;
   }

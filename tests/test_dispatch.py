@@ -186,6 +186,15 @@ def test_samples_by_rows_fill_the_chip_once(tmp_path):
             assert "sample_rows_kernelILi%d" % n in x["kernel"] and x["block"] == 64 * waves[n], (ob, nb, k)
 
 
+def test_large_batches_of_rows_below_the_streaming_size_take_16_lanes_a_sample(tmp_path):
+    """One batch of more than 768 samples of rows below 1 KB, of more than 832 below 2 KB: draws by 16 lanes; a workgroup per
+    sample otherwise."""
+    shapes = [(ob, 1, k) for ob in (16, 1023, 1024, 2047, 2048, 4096) for k in (768, 769, 832, 833, 1024)]
+    for (ob, nb, k), found in zip(shapes, recorded_hip.run(tmp_path, SAMPLES % (shapes,))):
+        limit = 768 if ob < 1024 else 832 if ob < 2048 else 1024
+        assert ("sample_rows_kernel" in found[0]["kernel"]) == (k <= limit), (ob, k)
+
+
 def test_large_batches_are_gathered_apart_only_where_their_weights_are_the_tail(tmp_path):
     """One batch of 2561 to 4096 short rows is drawn by one launch, gathered and weighted by another; without weights there is
     no tail to take away, and those of more samples have a launch of their own behind draw and gather."""

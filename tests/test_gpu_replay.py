@@ -1459,6 +1459,7 @@ def test_steps_of_several_batches_beside_small_and_large_add_rounds(nb, k):
     (16, 1, 1, 1), (16, 3, 1024, 1), (20, 4, 3, 2), (31, 5, 16, 63), (268, 84, 2, 65), (255, 4, 12, 100), (256, 4, 12, 100),
     (256, 255, 11, 128), (256, 256, 7, 129), (2047, 257, 8, 128), (2048, 300, 3, 500), (2048, 2, 2, 512), (1023, 4, 1, 768),
     (1023, 4, 1, 769), (1024, 4, 1, 1024), (4096, 4, 3, 341), (28224, 4, 3, 333), (33000, 4, 1, 129),
+    (1024, 4, 1, 832), (2047, 4, 1, 833), (2048, 4, 1, 1024),
 ])
 def test_weights_by_the_board(ob, ab, nb, k):
     """replay.Sample with a workgroup per sample: every weight, again and again and in replays of one captured call, with calls
