@@ -389,8 +389,13 @@ __global__ __launch_bounds__(kPeScanThreads) void pe_count_kernel(const uint32_t
 // A workgroup's place in the free ring is the number of candidates before it that count.  Up to kPeRecountMax
 // candidates every workgroup counts them itself (block_sums null): four candidates per lane and load, four loads ahead of the
 // first wait, all of them in the second cache; above, a launch of its own has counted them (block_sums), because the repeated
-// reading grows with the square of the round.  What bounds it is its chain of memory trips: counters, candidate and masses are
-// asked for before the count, so that they arrive beside it, and nothing is loaded behind the barrier.
+// reading grows with the square of the round.  What bounds it is its chain of memory trips: counters, candidate, masses, the
+// candidates before, atomics.  The masses are asked for ahead of the count so that nothing is loaded behind the barrier (as
+// compiled they are in before the count's first load goes out).
+// Waves beyond the round's candidates, most of them in the rounds after the first, load none, and the counters come as scalars:
+// vector loads of every wave queue for a line that every ticket takes out of the caches.  Rounds 1 / 2 / 3 of an eviction of
+// 32,000 8.6 / 3.4 / 3.4 us in the trace, where lanes beyond the round loaded its last candidate and counters came as vectors
+// 9.0 / 4.1 / 4.0; of 98,000 9.4 / 4.5 / 4.3 and 9.5 / 4.9 / 5.0.
 // An eviction of 32,000 in three rounds is six launches instead of ten (count and removal apart, a launch ahead of them
 // that set the number): ten add rounds, ten learner steps and the eviction 243.5 -> 238.6 us.
 __global__ __launch_bounds__(kPeScanThreads) void pe_remove_kernel(PeView v, PeState *__restrict__ st,
@@ -401,17 +406,22 @@ __global__ __launch_bounds__(kPeScanThreads) void pe_remove_kernel(PeView v, PeS
   __shared__ uint32_t wave_before[kPeScanThreads / kWave], wave_own[kPeScanThreads / kWave];
   const uint32_t t = threadIdx.x, wave = t / kWave, nthr = blockDim.x, lane = lane_id();
   uint64_t *const leaf1 = v.ts.level[0], *const leaf2 = v.te.level[0];
-  fetch_now(st, cand, leaf1, leaf2);
+  const uint64_t rem_before = st->remaining, head = st->base.head, free_tail = st->free_tail;
+  fetch_now(cand, leaf1, leaf2, rem_before);
   fetch_now(v.ts.P, v.ts.p_div.mul, v.ts.p_div.sh1, v.ts.p_div.sh2);
   fetch_now(v.ts.level[1], v.te.level[1], v.ts.level[2], v.te.level[2]);
-  // (read here, ahead of the barrier and of this workgroup's ticket, not where they are used)
-  const uint64_t rem = first_rem ? first_rem : st->remaining, head = st->base.head, free_tail = st->free_tail;
+  const uint64_t rem = first_rem ? first_rem : rem_before;  // at most 2^20
   const uint64_t j0 = (uint64_t)blockIdx.x * nthr, j = j0 + t;
-  // this thread's candidate and its masses: on their way during the count (one beyond the round's reads the round's last)
-  const uint64_t at = min(j, max(rem, (uint64_t)1) - 1);
-  const uint32_t slot = cand[at], slot_prev = cand[max(at, (uint64_t)1) - 1];
+  // this thread's candidate and its masses (a lane beyond the round's reads the round's last)
+  uint32_t slot = 0, slot_prev = 0;
+  uint64_t o1 = 0, o2 = 0;
+  const uint32_t n = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)rem);
+  if ((uint32_t)j0 + (uint32_t)__builtin_amdgcn_readfirstlane((int)wave) * kWave < n) {
+    const uint32_t at = min((uint32_t)j, n - 1);
+    slot = cand[at], slot_prev = cand[max(at, 1u) - 1];
+    o1 = leaf1[slot], o2 = leaf2[slot];
+  }
   const bool counts = j < rem && (j == 0 || slot != slot_prev);
-  const uint64_t o1 = leaf1[slot], o2 = leaf2[slot];
   uint32_t before = 0;
   if (block_sums) {
     if (t < blockIdx.x) before = block_sums[t];  // at most kPeScanThreads workgroups of as many threads: one per lane
@@ -430,9 +440,9 @@ __global__ __launch_bounds__(kPeScanThreads) void pe_remove_kernel(PeView v, PeS
 #pragma unroll
       for (uint32_t u = 0; u < kAhead; ++u) {
         const uint32_t i = i0 + u * nthr;
-        const uint32_t n = (uint32_t)(i == 0 || c[u].x != prev[u]) + (uint32_t)(c[u].y != c[u].x) + (uint32_t)(c[u].z != c[u].y) +
-                           (uint32_t)(c[u].w != c[u].z);
-        before += i < n4 ? n : 0;
+        const uint32_t runs = (uint32_t)(i == 0 || c[u].x != prev[u]) + (uint32_t)(c[u].y != c[u].x) + (uint32_t)(c[u].z != c[u].y) +
+                              (uint32_t)(c[u].w != c[u].z);
+        before += i < n4 ? runs : 0;
       }
     }
   }
