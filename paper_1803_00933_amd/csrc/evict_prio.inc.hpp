@@ -177,7 +177,8 @@ __global__ __launch_bounds__(kPeAddThreads, 8) void pe_add_rows_kernel(PeView v,
   fetch_now(v.qs.alpha, v.qs.eps, v.qs.frac_bits, v.qs.qmax);
   fetch_now(v.qe.alpha, v.qe.eps, v.qe.frac_bits, v.qe.qmax);
   // the last workgroup to have read the free ring's head moves it and the insertion count on (by its last lane: the
-  // ticket's round trip then runs beside those of the first wave; at the end of the launch it took 0.5 us more)
+  // ticket's round trip then runs beside those of the first wave; at the end of the launch it took 0.5 us more; every wave has
+  // looked its slots up by the head, so it has the head)
   lds_barrier();
   if (threadIdx.x == blockDim.x - 1) {
     const uint32_t t = __hip_atomic_fetch_add(&st->ticket_rows, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -452,6 +453,7 @@ __global__ __launch_bounds__(kPeScanThreads) void pe_remove_kernel(PeView v, PeS
     wave_before[wave] = wave_total;
     wave_own[wave] = __popcll(mask);
   }
+  fetch_now(head), fetch_now(free_tail);  // every wave has them before its workgroup's ticket lets another one overwrite them
   lds_barrier();
   uint32_t place = __popcll(mask & ((1ull << lane) - 1)), own = 0;
   for (uint32_t w = 0; w < nthr / kWave; ++w) {

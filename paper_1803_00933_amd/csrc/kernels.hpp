@@ -99,7 +99,9 @@ __device__ __forceinline__ void fetch_now(A a, B b, C c, D d)
   asm volatile("" ::"s"(a), "s"(b), "s"(c), "s"(d));
 }
 
-// A barrier for what the workgroup exchanges through LDS: stores to memory that are under way are not waited for.
+// A barrier for what the workgroup exchanges through LDS (and for scalar loads): vector loads and stores that are under way are
+// not waited for.  Whoever lets go of a word behind it, by a ticket, has to see to it that every wave has the word by then:
+// fetch_now for a scalar, arrived for a vector.
 __device__ __forceinline__ void lds_barrier()
 {
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
