@@ -292,8 +292,8 @@ def test_eviction_with_uniforms_for_fewer_than_are_due(enqueue):
 
 @pytest.mark.parametrize("e", [1, 1023, 1025, 4097, 65_535, 65_536, 65_537, 70_000])
 def test_rounds_at_the_edges_of_the_removal(e):
-    """Rounds of whole and ragged workgroups (1024 candidates), on both sides of the line (65,536) above which a launch
-    of its own counts the candidates; heavy-tailed priorities, so that rounds have long runs of equal candidates.
+    """Rounds of whole and ragged workgroups (512 candidates, 1024 above the line), on both sides of the line (65,536) above
+    which a launch of its own counts the candidates; heavy-tailed priorities, so that rounds have long runs of equal candidates.
     Two evictions in a row: the second starts from the counters that the first has left."""
     from paper_1803_00933_amd import apex
     rng = np.random.default_rng(e)
@@ -372,10 +372,11 @@ def test_adds_and_steps_around_the_pieces_of_a_row(ob, ab):
         check(g, o)
 
 
-@pytest.mark.parametrize("e", [63, 64, 65, 511, 512, 513, 2559, 2561])
+@pytest.mark.parametrize("e", [63, 64, 65, 511, 512, 513, 2559, 2561, 8191, 8192, 8193, 8704, 8705, 16_384, 16_385, 16_897])
 def test_removals_around_a_workgroup_that_counts_for_itself(e):
     """Workgroups of 512 candidates, each counting what lies before it four words at a time and four loads ahead: rounds that
-    end a wave, a workgroup and a turn of those loads, with half of the candidates equal to their neighbours."""
+    end a wave and a workgroup, and whose last workgroup has just under, exactly and just over one and two turns of those loads
+    (8192 candidates each) before it, with half of the candidates equal to their neighbours."""
     test_rounds_at_the_edges_of_the_removal(e)
 
 
