@@ -954,9 +954,13 @@ int apex_pe_sample_update(apex_pe_replay_t *r, uint32_t k, float beta, const uin
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   SampleArgs a = pe_sample_args(r, k, rnd, key_out, slot_out, act_out, ret_out, gacc_out);
   a.g.obs_out = static_cast<uint8_t *>(obs_out);
-  // The draw and the rows by a workgroup per sample, whatever the size: without weights nothing is settled between workgroups
-  // (with 16 lanes per sample, this launch and the next, 512 of 256 bytes 8.3 us, so 7.5; 128 of 64 bytes 7.7 and 6.9; 1000 of
-  // 1000 bytes 9.3 and 8.3).
+  // The draw and the rows by a workgroup per sample, whatever the size: without weights nothing is settled between workgroups.
+  // Both launches, us, with 16 lanes per sample / so, k of 1, 32, 128, 512 and 1000:
+  //     16 bytes  5.9 / 5.4   7.0 / 6.5   7.6 / 6.8    7.8 / 7.3    7.9 / 7.6
+  //     64        5.8 / 5.3   7.2 / 6.1   7.4 / 6.4    7.4 / 6.7    7.6 / 7.3
+  //    256        5.9 / 5.4   7.1 / 6.4   7.6 / 6.8    7.9 / 7.3    8.4 / 7.7
+  //   1000        5.8 / 5.2   7.3 / 6.5   7.8 / 6.8    8.0 / 7.3    8.9 / 7.9
+  //   4096        6.6 / 5.6   9.1 / 6.8   9.4 / 7.1   11.0 / 7.5   11.2 / 8.3
   if (obs_out && r->cfg.obs_bytes >= 16) APEX_TRY(launch_sample_rows(a, 1, stream, nullptr));
   else APEX_TRY(launch_sample(a, 1, stream));
   // weights and the write-back of the batch just drawn: one launch

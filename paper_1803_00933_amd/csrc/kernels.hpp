@@ -1788,8 +1788,10 @@ __device__ __forceinline__ void gather_by_16(const GatherArgs &a, uint64_t slot,
 }
 
 // Observation rows up to here ride in the draw's launch.  Together / apart, us of device time for one batch of 1500, 4 of 512,
-// 16 of 512 and one of 4096 from 2^18 slots (a launch less on the host, 2.4 us, not counted; fewer: sample_by_rows, and one batch
-// of more with shorter rows: kGatherApartAboveK):
+// 16 of 512 and one of 4096 from 2^18 slots (fewer: sample_by_rows, and one batch of more with shorter rows:
+// kGatherApartAboveK).  A launch less is 2.4 us on the host, not counted, which decides where a call with its update is bound by
+// the host, at some 12 us; one batch of 4096 rows of 4096 bytes is not, and would be 1.3 us shorter apart: the line goes by the
+// row alone.
 //   rows of  268 B   7.0 /  6.7    6.3 /  6.9    7.7 /  9.2
 //           1024 B   8.0 /  8.0    7.5 /  8.2    9.2 / 11.4
 //           2048 B   8.6 /  8.5    8.2 /  8.9   11.9 / 14.2   10.8 / 11.7
@@ -1931,9 +1933,11 @@ __global__ __launch_bounds__(kSampleMaxThreads) void sample_kernel(SampleArgs a)
 // are made of, on a board (a word per sample, 0 before the launch), waits until it is there, and reads the whole batch's
 // words: the one that does so last, if not others before it, finds all of them and writes the weights.  (Word written
 // through at agent scope, wait for it, words read at agent scope: the order that sequential consistency asks for.)  Several
-// may find them all; they write the same weights, and clear the words.  That is two round trips; a ticket to be the last
+// may find them all; they write the same weights, and clear the words.  That is two round trips (where keys hold the slot's
+// generation three: its load is waited for with the word, the key's store behind it); a ticket to be the last
 // workgroup by, in two steps because atomics on one address take turns of some 14 ns, was four: of the 4.3 us of 32 samples
-// 1.2 were spent behind the draw, of the 5.8 of 256 2.0.  Weights by all waves of the workgroup, four at least: one took 0.6 us
+// 1.2 were spent behind the draw, of the 5.8 of 256 2.0.  Weights by all waves of the workgroup, which are as many as the rows
+// want, and at least a wave more than there are whole waves of samples, up to four: one took 0.6 us
 // for 512 and 1.3 for 1024.  Launches of more than kBoardSamplesMax samples in batches of more than kBoardSmallK keep the
 // tickets: words written through wait behind too many reads of the same board (3 x 500 rows of 2 KB 7.6 us by tickets, 8.9).
 //

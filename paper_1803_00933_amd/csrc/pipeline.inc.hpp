@@ -36,7 +36,8 @@ struct apex_pipeline {
   // Work issued on each stream, and how much of it the tree stream has waited for (indices as in streams(); the tree
   // stream's are not used): join asks the caller's stream to wait for a copy stream only if something on it is left.
   // fork makes a copy stream wait when it is next used.  An event's record and the wait of another stream for it are some
-  // 10 us of host time each (fork, four launches, join: 27 us with one stream, 42 with two, 55 with three, the launches 10).
+  // 10 us of host time.  With one stream, call by call and over six processes: fork 9 to 17 us, four steps of several batches 15
+  // to 19, join with the launch that it issues 15 to 18; the five launches take the device 32.
   hipEvent_t join_ev = nullptr;
   uint64_t issued[3] = {}, covered[3] = {};
   uint64_t payload_at = 0;                // issued[1] when payload_done was recorded

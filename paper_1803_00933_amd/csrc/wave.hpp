@@ -54,14 +54,6 @@ __device__ __forceinline__ uint64_t wave_inclusive_scan(uint64_t v)
 #undef APEX_SCAN_ROW
 #undef APEX_SCAN_STEP
 
-// Sum over the wave, result in every lane.
-__device__ __forceinline__ uint64_t wave_sum(uint64_t v)
-{
-#pragma unroll
-  for (int d = kWave / 2; d >= 1; d >>= 1) v += __shfl_xor(v, d, kWave);
-  return v;
-}
-
 // One step of a minimum with data-parallel primitives: lanes to which the DPP control word routes no value keep theirs.
 template <int kCtrl, int kRowMask>
 __device__ __forceinline__ float dpp_min_step(float v)
